@@ -50,13 +50,13 @@
 // largest term at 1, while the weights proper are P'_t / scale_t in fp32.
 //
 // The fp16 residual tail (Sec. IV-B) is shared out evenly over the workgroups of a
-// (sequence, KV head): each takes a slice of the <= 127 residual tokens, scores them with
-// plain dot products and folds them into its partial in the final merge, so no workgroup
-// does the tail alone.
+// (sequence, KV head): each takes a slice of the <= 128 residual tokens (bd_residual.h) and joins
+// it to its partial in the final merge, so no workgroup does the tail alone.
 #include "bd_common.h"
 #include "bd_device.h"
 #include "bd_fmt.h"
 #include "bd_quant_block.h"
+#include "bd_residual.h"
 
 namespace bd {
 namespace {
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   constexpr int HP = GQP / 4;                // passes over the heads where 16 lanes work on one head
 
   __shared__ __attribute__((aligned(16))) unsigned char smem_raw[cmax(sizeof(ML), kWaves * sizeof(WL))];
-  __shared__ float res_s[kBlock][GQP];       // scores of this workgroup's residual tokens, per head
+  __shared__ float res_o[GQP][kD], res_m[GQP], res_l[GQP];   // result of the residual slice
   __shared__ __attribute__((aligned(16))) float q_s[HP > 1 ? GQP : 1][kD];   // larger groups: queries, normalised; padding heads zero
   __shared__ int kq_s[HP > 1 ? GQP : 1];                                     // larger groups: each head's normalising exponent
 
@@ -338,29 +338,13 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       qld[p] = h < gq ? *reinterpret_cast<const uint32_t*>(qbase + h * kD + 2 * lane) : 0u;
     }
   }
-  const uint16_t* kres = a.k_res + unit * kBlock * kD;
-  // row t of the residual keys: the newest token of a fused step is read from where the caller left it
-  auto kres_row = [&](int t) { return t == new_slot ? a.k_new + unit * kD : kres + (size_t)t * kD; };
-  // The residual tokens are scored 16 at a time on the matrix unit: S[token, head] with the fp16
-  // key rows as A and the fp16 queries as B, four k-steps of 32 channels.  Wave w takes token
-  // groups w, w + 4, ...; the operands of its first group are requested here.
-  const int nres = rt1 - rt0, nres_groups = (nres + 15) >> 4;
-  const bool has_res = wave < nres_groups;
-  h8_t res_a[4], res_q[4];
-  auto load_res_keys = [&](int grp) {
-    const int t = min(rt0 + 16 * grp + col, rt1 - 1);   // rows past the slice repeat its last token
-    const uint16_t* row = kres_row(t) + 8 * g;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) res_a[j] = *reinterpret_cast<const h8_t*>(row + 32 * j);
-  };
-  if (has_res) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const h8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
-      res_q[j] = col < gq ? *reinterpret_cast<const h8_t*>(qbase + col * kD + 32 * j + 8 * g) : zero;
-    }
-    load_res_keys(wave);
-  }
+  const uint16_t *kres = a.k_res + unit * kBlock * kD, *vres = a.v_res + unit * kBlock * kD;
+  // rows of the residual slice: the newest token of a fused step is read from where the caller left it
+  const int nres = rt1 - rt0;
+  auto kres_row = [&](int t) { return rt0 + t == new_slot ? a.k_new + unit * kD : kres + (size_t)(rt0 + t) * kD; };
+  auto vres_row = [&](int t) { return rt0 + t == new_slot ? a.v_new + unit * kD : vres + (size_t)(rt0 + t) * kD; };
+  ResidualSlice res;
+  if (nres > 0) res.start(qbase, gq, nres, kres_row, vres_row, wave, lane);
   if (new_slot >= 0 && split == 0 && head0 == 0 && tid < 32 && res_len < kBlock && (PAGED || a.flush_mode == kFlushNone)) {   // fused step: file the new token for later steps
     const bool is_v = tid >= 16;
     const uint16_t* src = (is_v ? a.v_new : a.k_new) + unit * kD + 8 * (tid & 15);
@@ -389,23 +373,17 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   int blk = blk0 + wave;
   size_t bi = unit * a.nbcap + blk;
   if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
+  // (the residual slice inside both branches: the loads behind its own are then known to the compiler, which
+  // otherwise waits for all of them)
   if (blk < blk1) {   // parameters first: they are the block's first consumers
     issue_kpar(bi);
     issue_vpar(bi);
 #pragma unroll
     for (int T = 0; T < 8; ++T) issue_ktile(bi, T);
+    if (nres > 0) res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
+  } else if (nres > 0) {
+    res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
   }
-
-  // The first residual value rows this workgroup folds in at the very end: requested now, so
-  // that the final merge does not wait on memory (thread tid: channels 2*(tid%64), +1).
-  constexpr int kResPre = 2;
-  auto vres_row = [&](int t) {
-    return t == new_slot ? a.v_new + unit * kD : a.v_res + (unit * kBlock + t) * kD;
-  };
-  uint32_t vres_pre[kResPre];
-#pragma unroll
-  for (int i = 0; i < kResPre; ++i)
-    vres_pre[i] = i < nres ? *reinterpret_cast<const uint32_t*>(vres_row(rt0 + i) + 2 * lane) : 0u;
 
   // ---- larger groups: the queries, scaled, for everybody in the workgroup
   if constexpr (HP > 1) {
@@ -422,21 +400,6 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       if (lane == 0) kq_s[h] = kqh;
     }
     __syncthreads();
-  }
-
-  // ---- residual slice, part 1: scores s[t][h] = q_h . k_t * softmax_scale * log2(e)
-  if (has_res) {
-    for (int grp = wave; grp < nres_groups; grp += kWaves) {
-      if (grp != wave) load_res_keys(grp);
-      f4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(res_a[j], res_q[j], acc, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int t = 16 * grp + 4 * g + r;   // row 4g + r of the tile
-        if (t < nres && col < GQP) res_s[t][col] = acc[r] * a.scale_log2;
-      }
-    }
   }
 
   // tokens whose softmax this lane runs: for its o-th owned k-step j = cg * OWN + o, the low
@@ -830,7 +793,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       float M = ml.m[0][h];
 #pragma unroll
       for (int w = 1; w < kWaves; ++w) M = fmaxf(M, ml.m[w][h]);
-      for (int t = 0; t < nres; ++t) M = fmaxf(M, res_s[t][h]);
+      if (nres > 0) M = fmaxf(M, res_m[h]);
       float L = 0.f, Z = 0.f, o0 = 0.f, o1 = 0.f;
       if (M > -INFINITY) {
 #pragma unroll
@@ -841,18 +804,12 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
           o0 += f * ml.o[w][h][c0];
           o1 += f * ml.o[w][h][c0 + 1];
         }
-        // residual slice, part 2: fold the fp16 tokens in (the first rows were requested at the
-        // start of the kernel, any further ones are read here)
-        auto fold = [&](int t, uint32_t raw) {
-          const float p = __builtin_amdgcn_exp2f(res_s[t][h] - M);
-          L += p;
-          o0 = __builtin_fmaf(p, h2f((uint16_t)(raw & 0xFFFFu)), o0);
-          o1 = __builtin_fmaf(p, h2f((uint16_t)(raw >> 16)), o1);
-        };
-#pragma unroll
-        for (int t = 0; t < kResPre; ++t)
-          if (t < nres) fold(t, vres_pre[t]);
-        for (int t = kResPre; t < nres; ++t) fold(t, *reinterpret_cast<const uint32_t*>(vres_row(rt0 + t) + c0));
+        if (nres > 0) {
+          const float f = __builtin_amdgcn_exp2f(res_m[h] - M);
+          L += f * res_l[h];
+          o0 += f * res_o[h][c0];
+          o1 += f * res_o[h][c0 + 1];
+        }
       }
       const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * a.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};

@@ -24,6 +24,7 @@
 #include "bd_device.h"
 #include "bd_fmt.h"
 #include "bd_quant_block.h"
+#include "bd_residual.h"
 
 namespace bd {
 namespace {
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   using ML = GrpMergeLds<GQP, NV>;
 
   __shared__ __attribute__((aligned(16))) unsigned char smem_raw[gmax(sizeof(ML), kWaves * sizeof(WL))];
-  __shared__ float res_s[kBlock][GQP];
+  __shared__ float res_o[GQP][kD], res_m[GQP], res_l[GQP];   // result of the residual slice
   // queries * softmax_scale * log2(e), each head brought below 2^kQTop by a power of two whose inverse is
   // qinv_s[head]; padding heads zero
   __shared__ __attribute__((aligned(16))) float q_s[GQP][kD];
@@ -255,6 +256,14 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   const int rt0 = (res_len * split) / a.num_splits, rt1 = (res_len * (split + 1)) / a.num_splits;
   const uint16_t* qbase = a.q + ((size_t)b * a.n_q_heads + hkv * a.gq + head0) * kD;
 
+  // rows of the residual slice: the newest token of a fused step is read from where the caller left it
+  const int nres = rt1 - rt0;
+  const uint16_t *kres = a.k_res + unit * kBlock * kD, *vres = a.v_res + unit * kBlock * kD;
+  auto kres_row = [&](int t) { return rt0 + t == new_slot ? a.k_new + unit * kD : kres + (size_t)(rt0 + t) * kD; };
+  auto vres_row = [&](int t) { return rt0 + t == new_slot ? a.v_new + unit * kD : vres + (size_t)(rt0 + t) * kD; };
+  ResidualSlice res;
+  if (nres > 0) res.start(qbase, gq, nres, kres_row, vres_row, wave, lane);
+
   // ---- queries, scaled, for everybody in the workgroup
 #pragma unroll
   for (int p = 0; p < HP; ++p) {
@@ -270,37 +279,13 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
     if (lane == 0) qinv_s[h] = pow2i(-kq);
   }
 
-  // ---- residual slice, part 1: scores of this workgroup's fp16 tokens, 16 per MFMA chain
-  const int nres = rt1 - rt0, nres_groups = (nres + 15) >> 4;
-  if (wave < nres_groups) {
-    h8_t res_q[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const h8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
-      res_q[j] = col < gq ? *reinterpret_cast<const h8_t*>(qbase + col * kD + 32 * j + 8 * g) : zero;
-    }
-    for (int grp = wave; grp < nres_groups; grp += kWaves) {
-      const int t = min(rt0 + 16 * grp + col, rt1 - 1);   // rows past the slice repeat its last token
-      // (the newest token of a fused step is read from where the caller left it)
-      const uint16_t* row = (t == new_slot ? a.k_new + unit * kD : a.k_res + (unit * kBlock + t) * kD) + 8 * g;
-      f4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const h8_t*>(row + 32 * j), res_q[j], acc, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int tt = 16 * grp + 4 * g + r;
-        if (tt < nres && col < GQP) res_s[tt][col] = acc[r] * a.scale_log2;
-      }
-    }
-  }
   if (new_slot >= 0 && split == 0 && head0 == 0 && tid < 32 && res_len < kBlock && (PAGED || a.flush_mode == kFlushNone)) {   // fused step: file the new token for later steps
     const bool is_v = tid >= 16;
     const uint16_t* src = (is_v ? a.v_new : a.k_new) + unit * kD + 8 * (tid & 15);
     uint16_t* dst = const_cast<uint16_t*>(is_v ? a.v_res : a.k_res) + (unit * kBlock + new_slot) * kD + 8 * (tid & 15);
     *reinterpret_cast<u4_t*>(dst) = *reinterpret_cast<const u4_t*>(src);
   }
-  __syncthreads();   // q_s and res_s are complete
+  __syncthreads();   // q_s is complete
 
   float m_run = -INFINITY, l_run = 0.0f;
   float z_run[NV];
@@ -505,9 +490,12 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   int blk = blk0 + wave;
   size_t bi = unit * a.nbcap + blk;
   if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
-  if (blk < blk1) {
+  if (blk < blk1) {   // (the residual slice as in the group-128 kernel)
     issue_params(bi);
     issue_keys(bi);
+    if (nres > 0) res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
+  } else if (nres > 0) {
+    res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
   }
   // this lane's 8 tokens of chunk c are block tokens tok0 + 32*c + {run_base offsets}: slot group 4*c + g
   while (blk < blk1) {
@@ -750,7 +738,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
       float M = ml.m[0][h];
 #pragma unroll
       for (int w = 1; w < kWaves; ++w) M = fmaxf(M, ml.m[w][h]);
-      for (int t = 0; t < nres; ++t) M = fmaxf(M, res_s[t][h]);
+      if (nres > 0) M = fmaxf(M, res_m[h]);
       float L = 0.f, Z = 0.f, o0 = 0.f, o1 = 0.f;
       if (M > -INFINITY) {
 #pragma unroll
@@ -761,14 +749,11 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
           o0 += f * ml.o[w][h][c0];
           o1 += f * ml.o[w][h][c0 + 1];
         }
-        // residual slice, part 2: fold the fp16 tokens in
-        for (int t = 0; t < nres; ++t) {
-          const float pr = __builtin_amdgcn_exp2f(res_s[t][h] - M);
-          const uint16_t* vrow = rt0 + t == new_slot ? a.v_new + unit * kD : a.v_res + (unit * kBlock + rt0 + t) * kD;
-          const uint32_t raw = *reinterpret_cast<const uint32_t*>(vrow + c0);
-          L += pr;
-          o0 = __builtin_fmaf(pr, h2f((uint16_t)(raw & 0xFFFFu)), o0);
-          o1 = __builtin_fmaf(pr, h2f((uint16_t)(raw >> 16)), o1);
+        if (nres > 0) {
+          const float f = __builtin_amdgcn_exp2f(res_m[h] - M);
+          L += f * res_l[h];
+          o0 += f * res_o[h][c0];
+          o1 += f * res_o[h][c0 + 1];
         }
       }
       const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * a.gq + head0 + h;

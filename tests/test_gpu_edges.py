@@ -1,0 +1,38 @@
+"""GPU parity at the sizes where the kernels' tiles and dispatch rules change: remainders, the smallest and
+the largest of a range, against the CPU oracle on the same seeded inputs."""
+import numpy as np
+import pytest
+
+from oracle import bitdecode_oracle as O
+from paper_2503_18773_amd import binding as B
+from paper_2503_18773_amd import workloads as W
+from tests.test_gpu_parity import BITS, GROUP, _int_cache_pair
+from tests.util import assert_attn_close, attn_errors, out_to_f64, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _attend_f32(gc, w, q, num_splits):
+    import torch
+    gc.desc.out_type = B.BD_OUT_F32
+    out = torch.full((w.batch, w.n_q_heads, 128), 7.0, dtype=torch.float32, device="cuda:0")
+    gc.decode_attn(to_dev(q, w.in_dtype), W.softmax_scale(w), out, num_splits=num_splits)
+    torch.cuda.synchronize()
+    return out_to_f64(out)
+
+
+@pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int4", 16), ("int2_kt", 7), ("int4_g32", 3), ("int2_kt_g64", 8)])
+def test_residual_slices_of_every_remainder(fmt, gq):
+    """Nothing but residual tokens, 1 .. 127 of them, in one slice and in several: the slice ends on and beside
+    the steps of the second product (4 tokens a load, 32 a k-step).  Scores and weights are fp32 (weights enter
+    the product with 22 bits), so the bar is fp32's: a score is a sum of 128 products whose magnitudes add up to
+    about 1e2, which the matrix unit rounds (truncating) at 2^-23 of its size, i.e. 1e-5 in the exponent; the
+    result's relative L2 error is at most that."""
+    for L in (1, 3, 4, 5, 31, 32, 33, 64, 97, 127):
+        w = W.scaled(W.CONFIGS["cfg1"], batch=2, n_q_heads=2 * gq, n_kv_heads=2, context=L, fmt=fmt, seed=300 + L)
+        K, V, oc, gc = _int_cache_pair(w, 128)
+        q = W.make_q(w)
+        ref = O.decode_attn(oc, q, W.softmax_scale(w))
+        for ns in (1, 3):
+            ma, rl = attn_errors(_attend_f32(gc, w, q, ns), ref)
+            assert rl <= 1e-5, f"{fmt} gq={gq} L={L} splits={ns}: rel-L2 {rl:.2e} max-abs {ma:.2e}"
