@@ -158,7 +158,7 @@ bd_status bd_quant_pack_kv(const bd_cache* c, const void* k, const void* v, int3
   const long stride = (long)L * kD;
   if (c->format == BD_FMT_MXFP4) {
     if (L > c->capacity) return BD_ERR_CAPACITY;
-    if ((s = hip_status(launch_mx_quant(k, v, stride, L, units, c, 0, st))) != BD_OK) return s;
+    if ((s = hip_status(launch_mx_quant(k, v, L, units, c, st))) != BD_OK) return s;
     *packed_len = L;
     *res_len = 0;
     return BD_OK;
@@ -187,7 +187,7 @@ bd_status bd_append_kv(const bd_cache* c, const void* k_new, const void* v_new, 
   if (c->format == BD_FMT_MXFP4) {
     if (*packed_len < 0 || *res_len != 0) return BD_ERR_INVALID_ARG;
     if (*packed_len + 1 > c->capacity) return BD_ERR_CAPACITY;
-    if ((s = hip_status(launch_mx_quant(k_new, v_new, (long)kD, 1, units, c, *packed_len, st))) != BD_OK) return s;
+    if ((s = hip_status(launch_mx_append(k_new, v_new, units, c, *packed_len, st))) != BD_OK) return s;
     *packed_len += 1;
     return BD_OK;
   }

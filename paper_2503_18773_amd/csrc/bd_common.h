@@ -45,8 +45,9 @@ hipError_t launch_copy_rows(const void* ksrc, const void* vsrc, long src_unit_st
                             int units, hipStream_t st);
 // measurement aid: streams the packed K and V codes of the first packed_len tokens and nothing else
 hipError_t launch_stream_probe(const bd_cache* c, int packed_len, void* sink, hipStream_t st);
-hipError_t launch_mx_quant(const void* k, const void* v, long src_unit_stride, int ntok, int units,
-                           const bd_cache* c, int dst_tok0, hipStream_t st);
+// MXFP4: tokens [0, L) of every unit from [unit][L][128] arrays; one token of every unit to position t
+hipError_t launch_mx_quant(const void* k, const void* v, int L, int units, const bd_cache* c, hipStream_t st);
+hipError_t launch_mx_append(const void* k_new, const void* v_new, int units, const bd_cache* c, int t, hipStream_t st);
 
 hipError_t launch_paged_prefill(const bd_paged_cache* c, int seq, const void* k, const void* v, int L,
                                 hipStream_t st);

@@ -169,95 +169,7 @@ __device__ __forceinline__ long mx_block_index(const MxDst& d, int u, int blk) {
   return (long)page * d.n_kv_heads + u;
 }
 
-// One workgroup quantizes up to 128 tokens (one V block) of one (batch, kv_head).
-// Thread t handles token t: 4 MX groups of K and of V.  K codes go out token-major;
-// V codes pass through an LDS tile to be written channel-major, two tokens per byte.
-// When `single` (decode append of one token) the V bytes are updated nibble-wise.
-__global__ __launch_bounds__(128) void mx_quant_kernel(const uint16_t* __restrict__ ksrc,
-                                                        const uint16_t* __restrict__ vsrc,
-                                                        long src_unit_stride, int ntok, MxDst d,
-                                                        int dst_tok0) {
-  constexpr int PITCH = kD + 4;
-  __shared__ uint8_t tile[kBlock * PITCH];
-  uint8_t *k_codes = d.k_codes, *k_scales = d.k_scales, *v_codes = d.v_codes, *v_scales = d.v_scales;
-  const int unit = blockIdx.y;
-  // this workgroup covers destination tokens [t_lo, t_hi) of block `dblk`
-  const int first_blk = dst_tok0 / kBlock;
-  const int dblk = first_blk + blockIdx.x;
-  const int t_lo = max(dblk * kBlock, dst_tok0);
-  const int t_hi = min((dblk + 1) * kBlock, dst_tok0 + ntok);
-  const int t = dblk * kBlock + threadIdx.x;  // destination token of this thread
-  const bool live = t >= t_lo && t < t_hi;
-  const long bi = mx_block_index(d, unit, dblk);
-  if (bi < 0) return;
-
-  if (live) {
-    const size_t so = (size_t)unit * src_unit_stride + (size_t)(t - dst_tok0) * kD;
-    const size_t tok = (size_t)bi * kBlock + threadIdx.x;
-#pragma unroll 1
-    for (int which = 0; which < 2; ++which) {
-      const uint16_t* src = (which == 0 ? ksrc : vsrc) + so;
-      uint32_t scale_word = 0;
-#pragma unroll 1
-      for (int g = 0; g < kD / kMxGroup; ++g) {
-        float xv[kMxGroup];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          u4_t raw = *reinterpret_cast<const u4_t*>(src + g * kMxGroup + 8 * v);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            xv[8 * v + 2 * e] = bf16_bits_to_float((uint16_t)(raw[e] & 0xFFFFu));
-            xv[8 * v + 2 * e + 1] = bf16_bits_to_float((uint16_t)(raw[e] >> 16));
-          }
-        }
-        float amax = 0.0f;
-#pragma unroll
-        for (int i = 0; i < kMxGroup; ++i) amax = fmaxf(amax, fabsf(xv[i]));
-        int e = 0;
-        if (amax > 0.0f) e = mx_shared_exp(amax);
-        scale_word |= (uint32_t)(e + 127) << (8 * g);
-        if (which == 0) {
-          u4_t out;
-#pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            uint32_t word = 0;
-#pragma unroll
-            for (int n = 0; n < 8; ++n)
-              word |= (amax > 0.0f ? e2m1_code(xv[8 * w + n], e) : 0u) << (4 * n);
-            out[w] = word;
-          }
-          *reinterpret_cast<u4_t*>(k_codes + tok * (kD / 2) + g * 16) = out;
-        } else {
-#pragma unroll
-          for (int i = 0; i < kMxGroup; ++i)
-            tile[threadIdx.x * PITCH + g * kMxGroup + i] =
-                (uint8_t)(amax > 0.0f ? e2m1_code(xv[i], e) : 0u);
-        }
-      }
-      *reinterpret_cast<uint32_t*>((which == 0 ? k_scales : v_scales) + tok * 4) = scale_word;
-    }
-  }
-  __syncthreads();
-  // V codes, channel-major: byte j of channel c holds block tokens 2j (low), 2j+1 (high).
-  uint8_t* vrow = v_codes + (size_t)bi * (size_t)(kD * 64);
-  const int j_lo = (t_lo - dblk * kBlock) / 2, j_hi = (t_hi - dblk * kBlock + 1) / 2;
-  const int nj = j_hi - j_lo;
-  for (int k = threadIdx.x; k < kD * nj; k += 128) {
-    const int ch = k / nj, j = j_lo + k % nj;
-    const int id = ch * 64 + j;
-    const int ta = dblk * kBlock + 2 * j, tb = ta + 1;
-    uint8_t old = 0;
-    const bool a_new = ta >= t_lo && ta < t_hi, b_new = tb >= t_lo && tb < t_hi;
-    if (!(a_new && b_new)) old = vrow[id];       // keep the nibble of a token not in this call
-    uint8_t lo = a_new ? tile[(2 * j) * PITCH + ch] : (uint8_t)(old & 0x0F);
-    uint8_t hi = b_new ? tile[(2 * j + 1) * PITCH + ch] : (uint8_t)(old >> 4);
-    // a token beyond the current end of the cache has never been written: store 0 for it
-    if (!b_new && tb >= t_hi) hi = 0;
-    vrow[id] = (uint8_t)(lo | (hi << 4));
-  }
-}
-
-// Whole 128-token blocks of an MXFP4 cache (the bulk of a prefill), in the tiling of the integer block
+// Prefill of an MXFP4 cache, one workgroup per 128-token block, in the tiling of the integer block
 // quantizer: 256 threads, a thread holds 8 token rows x 8 consecutive channels of each tensor (one 16-byte
 // load per row; 16 lanes per token row, so every load of a wave covers 1 KB of contiguous source and the
 // four lanes of a DPP quad hold one MX group).  K rows are four apart inside the wave's 32 tokens, so that
@@ -269,25 +181,33 @@ __global__ __launch_bounds__(128) void mx_quant_kernel(const uint16_t* __restric
 // identical to the definition) except that it keeps the sign of values that round to zero, which is
 // cleared afterwards; groups with a very small maximum (shared exponent below -120, where elements can be
 // fp32 subnormals) take the explicit path.  Source rows and codes are streaming (non-temporal) accesses.
-__global__ __launch_bounds__(256, 4) void mx_quant_block_kernel(const uint16_t* __restrict__ ksrc,
-                                                                 const uint16_t* __restrict__ vsrc,
-                                                                 long src_unit_stride, MxDst d, int dst_blk0) {
+// TAIL: the block holds only `ntok` < 128 tokens (the end of a prompt).  Rows past them are neither read nor
+// written, and V's bytes past them stay as they are (an odd last token's byte gets a zero high nibble).  (A
+// kernel of its own with a thread per token -- 128 values in turn, 47 us for 31 tokens -- served this block
+// before, whatever the prompt's length: 57.5 us for 4 prompts of 2079 tokens.)
+template <bool TAIL>
+__device__ __forceinline__ void mx_quant_block(const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc,
+                                               size_t src_blk, const MxDst& d, long bi, int ntok,
+                                               uint32_t (*vw)[kBlock / 8 + 1]) {
   constexpr int C = 8, T = 8, NCG = kD / C, WPC = kBlock / 8;   // 16 lanes per row; 16 words per channel
-  __shared__ uint32_t vw[kD][WPC + 1];
-  const int unit = blockIdx.y, blk = dst_blk0 + blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const long bi = mx_block_index(d, unit, blk);
-  if (bi < 0) return;
-  const size_t src_blk = (size_t)unit * src_unit_stride + (size_t)blockIdx.x * kBlock * kD;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cg = tid % NCG, tg = tid / NCG;
   auto krow = [&](int t) { return 32 * wave + (lane >> 4) + 4 * t; };
   auto vrow = [&](int t) { return T * tg + t; };
+  auto live = [&](int row) { return !TAIL || row < ntok; };
   u4_t kraw[T], vraw[T];
 #pragma unroll
-  for (int t = 0; t < T; ++t)
-    kraw[t] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(ksrc + src_blk + (size_t)krow(t) * kD + C * cg));
+  for (int t = 0; t < T; ++t) {
+    kraw[t] = (u4_t){0u, 0u, 0u, 0u};
+    if (live(krow(t)))
+      kraw[t] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(ksrc + src_blk + (size_t)krow(t) * kD + C * cg));
+  }
 #pragma unroll
-  for (int t = 0; t < T; ++t)
-    vraw[t] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(vsrc + src_blk + (size_t)vrow(t) * kD + C * cg));
+  for (int t = 0; t < T; ++t) {
+    vraw[t] = (u4_t){0u, 0u, 0u, 0u};
+    if (live(vrow(t)))
+      vraw[t] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(vsrc + src_blk + (size_t)vrow(t) * kD + C * cg));
+  }
 
   // the 8 codes of one row of this lane (channel C*cg + n at nibble n) and the group's scale byte
   auto row_codes = [&](const u4_t& raw, uint32_t& word, uint32_t& ebyte) {
@@ -341,9 +261,11 @@ __global__ __launch_bounds__(256, 4) void mx_quant_block_kernel(const uint16_t* 
     uint32_t word, ebyte;
     row_codes(kraw[t], word, ebyte);
     const size_t tok = (size_t)bi * kBlock + krow(t);
-    __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(d.k_codes + tok * (kD / 2)) + cg);
     const uint32_t sc4 = row_scales(ebyte);
-    if (cg == 0) *reinterpret_cast<uint32_t*>(d.k_scales + tok * 4) = sc4;
+    if (live(krow(t))) {
+      __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(d.k_codes + tok * (kD / 2)) + cg);
+      if (cg == 0) *reinterpret_cast<uint32_t*>(d.k_scales + tok * 4) = sc4;
+    }
   }
   // ---- V: channel-major codes
   uint32_t lo[T], hi[T];   // per token: the codes of channels 0..3 / 4..7 of this lane, one per byte
@@ -353,7 +275,7 @@ __global__ __launch_bounds__(256, 4) void mx_quant_block_kernel(const uint16_t* 
     row_codes(vraw[t], word, ebyte);
     const size_t tok = (size_t)bi * kBlock + vrow(t);
     const uint32_t sc4 = row_scales(ebyte);
-    if (cg == 0) *reinterpret_cast<uint32_t*>(d.v_scales + tok * 4) = sc4;
+    if (cg == 0 && live(vrow(t))) *reinterpret_cast<uint32_t*>(d.v_scales + tok * 4) = sc4;
     const uint32_t x = word & 0x0F0F0F0Fu, y = (word >> 4) & 0x0F0F0F0Fu;   // even / odd channels, one per byte
     lo[t] = __builtin_amdgcn_perm(y, x, 0x05010400u);   // x.b0 y.b0 x.b1 y.b1
     hi[t] = __builtin_amdgcn_perm(y, x, 0x07030602u);   // x.b2 y.b2 x.b3 y.b3
@@ -370,10 +292,32 @@ __global__ __launch_bounds__(256, 4) void mx_quant_block_kernel(const uint16_t* 
     const int idx = 4 * (tid + 256 * k);
     const uint32_t* row = &vw[idx / WPC][idx % WPC];
     const u4_t w4 = {row[0], row[1], row[2], row[3]};
-    __builtin_nontemporal_store(w4, reinterpret_cast<u4_t*>(vdst + idx));
+    const int t0 = 8 * (idx % WPC);   // the 32 tokens t0 .. of channel idx / WPC
+    if (live(t0 + 31)) {
+      __builtin_nontemporal_store(w4, reinterpret_cast<u4_t*>(vdst + idx));
+    } else {
+      uint8_t* bytes = reinterpret_cast<uint8_t*>(vdst + idx);
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (t0 + 2 * j < ntok) bytes[j] = (uint8_t)(w4[j / 4] >> (8 * (j % 4)));
+    }
   }
 }
 
+// Tokens [0, L) of every unit; with `seq_len` (one sequence of a paged cache) the length is recorded too.
+__global__ __launch_bounds__(256, 4) void mx_quant_block_kernel(const uint16_t* __restrict__ ksrc,
+                                                                 const uint16_t* __restrict__ vsrc,
+                                                                 long src_unit_stride, MxDst d, int L, int32_t* seq_len) {
+  const int unit = blockIdx.y, blk = blockIdx.x;
+  if (seq_len && unit == 0 && blk == 0 && threadIdx.x == 0) *seq_len = L;
+  const long bi = mx_block_index(d, unit, blk);
+  if (bi < 0) return;
+  const size_t src_blk = (size_t)unit * src_unit_stride + (size_t)blk * kBlock * kD;
+  const int ntok = L - blk * kBlock;
+  __shared__ uint32_t vw[kD][kBlock / 8 + 1];
+  if (ntok >= kBlock) mx_quant_block<false>(ksrc, vsrc, src_blk, d, bi, kBlock, vw);
+  else mx_quant_block<true>(ksrc, vsrc, src_blk, d, bi, ntok, vw);
+}
 
 // Decode-step append for MXFP4: one token of one (sequence, KV head) goes to position i of block bi
 // (mx_quantize_token, 128 threads).
@@ -413,27 +357,12 @@ __global__ void set_len_kernel(int32_t* seq_lens, int seq, int L) {
 
 }  // namespace
 
-// Tokens [dst_tok0, dst_tok0 + ntok) of every unit: whole blocks through the block kernel, the
-// rest through the general one.
-static hipError_t launch_mx_range(const uint16_t* kk, const uint16_t* vv, long src_unit_stride, int ntok, int units,
-                           const MxDst& d, int dst_tok0, hipStream_t st) {
-  // tokens [t0, t1) of the range that do not fill a block go through the general kernel
-  auto partial = [&](int t0, int t1) -> hipError_t {
-    if (t1 <= t0) return hipSuccess;
-    const size_t off = (size_t)(t0 - dst_tok0) * kD;
-    dim3 grid((t1 - 1) / kBlock - t0 / kBlock + 1, units), block(128);
-    mx_quant_kernel<<<grid, block, 0, st>>>(kk + off, vv + off, src_unit_stride, t1 - t0, d, t0);
-    return hipGetLastError();
-  };
-  const int end = dst_tok0 + ntok;
-  const int full0 = (dst_tok0 + kBlock - 1) / kBlock, full1 = end / kBlock;   // whole blocks [full0, full1)
-  if (full1 <= full0) return partial(dst_tok0, end);
-  hipError_t e = partial(dst_tok0, full0 * kBlock);
-  if (e != hipSuccess) return e;
-  const size_t off = (size_t)(full0 * kBlock - dst_tok0) * kD;
-  mx_quant_block_kernel<<<dim3(full1 - full0, units), dim3(256), 0, st>>>(kk + off, vv + off, src_unit_stride, d, full0);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  return partial(full1 * kBlock, end);
+// Tokens [0, L) of every unit, L > 0.
+static hipError_t launch_mx_prefill(const void* k, const void* v, int L, int units, const MxDst& d, int32_t* seq_len,
+                                    hipStream_t st) {
+  mx_quant_block_kernel<<<dim3((L + kBlock - 1) / kBlock, units), dim3(256), 0, st>>>(
+      (const uint16_t*)k, (const uint16_t*)v, (long)L * kD, d, L, seq_len);
+  return hipGetLastError();
 }
 
 hipError_t launch_quant_blocks(const void* k, const void* v, long src_unit_stride, int src_tok0, int nblocks,
@@ -505,10 +434,7 @@ hipError_t launch_paged_prefill(const bd_paged_cache* c, int seq, const void* k,
     // every token is quantized on arrival: the last, partly filled block lives in a page as well
     MxDst d = paged_mx_dst(c);
     d.table_row = c->block_table + (size_t)seq * c->max_pages_per_seq;
-    if (L > 0) {
-      hipError_t e = launch_mx_range((const uint16_t*)k, (const uint16_t*)v, (long)L * kD, L, c->n_kv_heads, d, 0, st);
-      if (e != hipSuccess) return e;
-    }
+    if (L > 0) return launch_mx_prefill(k, v, L, c->n_kv_heads, d, c->seq_lens + seq, st);
     set_len_kernel<<<dim3(1), dim3(64), 0, st>>>(c->seq_lens, seq, L);
     return hipGetLastError();
   }
@@ -625,21 +551,23 @@ hipError_t launch_copy_rows(const void* ksrc, const void* vsrc, long src_unit_st
   return hipGetLastError();
 }
 
-hipError_t launch_mx_quant(const void* k, const void* v, long src_unit_stride, int ntok, int units,
-                           const bd_cache* c, int dst_tok0, hipStream_t st) {
-  if (ntok <= 0) return hipSuccess;
+static MxDst mx_dst(const bd_cache* c) {
   MxDst d{};
   d.k_codes = (uint8_t*)c->k_codes;
   d.k_scales = (uint8_t*)c->k_params;
   d.v_codes = (uint8_t*)c->v_codes;
   d.v_scales = (uint8_t*)c->v_params;
   d.nbcap = c->capacity / kBlock;
-  const uint16_t *kk = (const uint16_t*)k, *vv = (const uint16_t*)v;
-  if (ntok == 1 && src_unit_stride == kD) {
-    mx_append_kernel<<<dim3(units), dim3(128), 0, st>>>(kk, vv, d, dst_tok0);
-    return hipGetLastError();
-  }
-  return launch_mx_range(kk, vv, src_unit_stride, ntok, units, d, dst_tok0, st);
+  return d;
+}
+
+hipError_t launch_mx_quant(const void* k, const void* v, int L, int units, const bd_cache* c, hipStream_t st) {
+  return L > 0 ? launch_mx_prefill(k, v, L, units, mx_dst(c), nullptr, st) : hipSuccess;
+}
+
+hipError_t launch_mx_append(const void* k_new, const void* v_new, int units, const bd_cache* c, int t, hipStream_t st) {
+  mx_append_kernel<<<dim3(units), dim3(128), 0, st>>>((const uint16_t*)k_new, (const uint16_t*)v_new, mx_dst(c), t);
+  return hipGetLastError();
 }
 
 }  // namespace bd

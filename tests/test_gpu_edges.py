@@ -36,3 +36,27 @@ def test_residual_slices_of_every_remainder(fmt, gq):
         for ns in (1, 3):
             ma, rl = attn_errors(_attend_f32(gc, w, q, ns), ref)
             assert rl <= 1e-5, f"{fmt} gq={gq} L={L} splits={ns}: rel-L2 {rl:.2e} max-abs {ma:.2e}"
+
+
+@pytest.mark.parametrize("L", [1, 2, 7, 8, 31, 32, 33, 63, 65, 96, 126, 127, 129])
+def test_mx_prompt_ends_inside_a_block(L):
+    """The block at the end of an MXFP4 prompt: the tokens' codes and scales bit for bit, and the bytes past them
+    left as they were (pre-set to a pattern; an odd last token's byte gets a zero high nibble)."""
+    import torch
+    w = W.scaled(W.CONFIGS["cfg4"], batch=2, n_q_heads=4, n_kv_heads=2, context=L, seed=500 + L)
+    K, V = W.make_kv(w)
+    oc = O.MxCache(2, 2, 256); oc.quant_pack_kv(K, V)
+    gc = B.KVCache(2, 4, 2, "mxfp4", 256)
+    for buf in gc.buffers[:4]:
+        buf.fill_(0xA5)
+    gc.quant_pack_kv(to_dev(K, "bf16"), to_dev(V, "bf16"))
+    torch.cuda.synchronize()
+    assert gc.packed_len == L
+    for i, name in enumerate(["k_codes", "v_codes", "k_scales", "v_scales"]):
+        ref = getattr(oc, name).copy()
+        if name == "v_codes":   # [.., block, channel, byte of two tokens]
+            tok = 128 * np.arange(2)[:, None, None] + 2 * np.arange(64)[None, None, :] + np.zeros((2, 128, 64), int)
+            ref[:, :, tok >= L] = 0xA5
+        else:
+            ref[:, :, L:] = 0xA5
+        assert np.array_equal(gc.host_buffer(i).reshape(ref.shape), ref), name
