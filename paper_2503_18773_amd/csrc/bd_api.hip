@@ -165,11 +165,7 @@ bd_status bd_quant_pack_kv(const bd_cache* c, const void* k, const void* v, int3
   }
   const int nb = L / kBlock, r = L % kBlock;
   if (nb * kBlock > c->capacity) return BD_ERR_CAPACITY;
-  if ((s = hip_status(launch_quant_blocks(k, v, stride, 0, nb, units, c, 0, st))) != BD_OK)
-    return s;
-  if ((s = hip_status(launch_copy_rows(k, v, stride, nb * kBlock, c->k_res, c->v_res, (long)kBlock * kD, 0, r,
-                                       units, st))) != BD_OK)
-    return s;
+  if ((s = hip_status(launch_quant_blocks(k, v, stride, 0, nb, units, c, 0, r, st))) != BD_OK) return s;
   *packed_len = nb * kBlock;
   *res_len = r;
   return BD_OK;
@@ -201,7 +197,7 @@ bd_status bd_append_kv(const bd_cache* c, const void* k_new, const void* v_new, 
   if (flush) {
     // The residual block is full: quantize and pack it as packed block pl/128 (Sec. IV-B(1)).
     if ((s = hip_status(launch_quant_blocks(c->k_res, c->v_res, (long)kBlock * kD, 0, 1, units, c,
-                                            pl / kBlock, st))) != BD_OK)
+                                            pl / kBlock, 0, st))) != BD_OK)
       return s;
     *packed_len = pl + kBlock;
     *res_len = 0;

@@ -24,8 +24,9 @@ void note_hip_error(hipError_t e);
 
 // Kernel launchers (host side, defined next to their kernels).  All return hipError_t of
 // the launch.  `units` = batch * n_kv_heads.
+// `tail` > 0: the tail < 128 token rows that follow the blocks go to the residual buffers in the same launch.
 hipError_t launch_quant_blocks(const void* k, const void* v, long src_unit_stride, int src_tok0,
-                               int nblocks, int units, const bd_cache* c, int dst_blk0,
+                               int nblocks, int units, const bd_cache* c, int dst_blk0, int tail,
                                hipStream_t st);
 
 static inline bool fmt_is_int(int f) { return f != BD_FMT_MXFP4 && f >= BD_FMT_INT4 && f <= BD_FMT_INT2_KT_G32; }

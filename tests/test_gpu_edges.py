@@ -60,3 +60,36 @@ def test_mx_prompt_ends_inside_a_block(L):
         else:
             ref[:, :, L:] = 0xA5
         assert np.array_equal(gc.host_buffer(i).reshape(ref.shape), ref), name
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int2_kt", "int4_g32"])
+@pytest.mark.parametrize("L", [1, 15, 63, 64, 65, 127, 128, 129, 255])
+def test_prompt_tails_go_to_the_residual(fmt, L):
+    """One launch quantizes a prompt's whole blocks and copies its L mod 128 last tokens (four rounds of 64
+    rows' pieces): contiguous against the oracle, rows past the tail untouched, and a paged sequence the same
+    bytes."""
+    import torch
+    from tests.test_gpu_parity import _assert_int_cache_equal
+    w = W.scaled(W.CONFIGS["cfg1"], batch=2, n_q_heads=6, n_kv_heads=3, context=L, fmt=fmt, seed=600 + L)
+    K, V = W.make_kv(w)
+    oc = O.IntCache(2, 3, BITS[fmt], 256, k_per_token="_kt" in fmt, group=GROUP.get(fmt, 128))
+    oc.quant_pack_kv(K, V)
+    gc = B.KVCache(2, 6, 3, fmt, 256)
+    pc = B.PagedKVCache(2, 6, 3, fmt, 4, np.array([[2, 0], [3, 1]], np.int32))
+    for c in (gc, pc):
+        for buf in c.buffers[4:]:
+            buf.fill_(0x3C)
+    k, v = to_dev(K, "fp16"), to_dev(V, "fp16")
+    gc.quant_pack_kv(k, v)
+    for s in range(2):
+        pc.quant_pack_kv(s, k[s], v[s])
+    _assert_int_cache_equal(oc, gc)
+    assert pc.seq_lens.tolist() == [L, L] and pc.status.item() == 0
+    for i in (4, 5):
+        res = gc.host_buffer(i).view(np.uint16).reshape(2, 3, 128, 128)
+        assert np.all(res[:, :, L % 128:] == 0x3C3C)
+        assert np.array_equal(pc.host_buffer(i), gc.host_buffer(i))
+    for i in range(4):
+        pages = pc.host_buffer(i).reshape(4, 3, -1)[[[2, 0], [3, 1]]]   # [sequence][block][head]
+        blocks = gc.host_buffer(i).reshape(2, 3, 2, -1).transpose(0, 2, 1, 3)
+        assert np.array_equal(pages[:, :L // 128], blocks[:, :L // 128])
