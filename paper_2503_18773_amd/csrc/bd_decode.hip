@@ -18,10 +18,20 @@
 // inside a word are chosen so that this holds (the analogue, for MFMA, of inducing the packed
 // layout from the consumer instruction, Sec. III-A(1)).
 //
-// The 16 columns carry the <= 4 heads of the group four times over (column c holds head c%4).
-// Column group c/4 then keeps only every fourth S^T tile, so the softmax arithmetic runs on
-// 8 values per lane per 128-token block instead of 32, with every lane doing useful work; the
-// packed probabilities are moved back to columns 0..3 with DPP row shifts.
+// Query groups of up to 4 heads run both products on v_mfma_scale_f32_16x16x128_f8f6f4 instead: one instruction
+// contracts all 128 channels (tokens) of a 16-row tile, with the codes as e4m3 / e2m1 numbers (masking again, bd_fmt.h)
+// and Q' and P' as sums of e4m3 pieces, 2^-5 apart: piece k of head h in column 4k + h.  So the 16 columns hold four
+// pieces of four heads, a tile costs one matrix instruction of 32 cycles instead of four of 16, and 3 instead of
+// 5 (8) mask instructions per word of 4-bit (2-bit) codes.  The pieces' partial scores are added over the column
+// groups with DPP moves, column group c keeping tiles c and 4 + c (8 values per lane per block, every lane doing
+// useful work); the pieces of the weights are exchanged between the column groups likewise, and the column groups'
+// partial O^T are added once, after the loop.  Every product of codes and pieces is exact, and the pieces hold more
+// than the fp16 operands they replace: relative L2 of fp32 outputs 1.7e-4 .. 2.4e-4 before, 1e-6 .. 3e-6 (4 bits) and
+// 1.0e-5 .. 1.6e-5 (2 bits) now, at 128 .. 5120 tokens.  What bounds these instances after that is memory, the 2-bit
+// one's 33.5 -> 29.3 us at 8 x 32K tokens (152 MB), the 4-bit one's 26.2 -> 25.7 us at 128K (143 MB).  Groups of 5 .. 16
+// heads have no columns to spare for the pieces and stay on fp16.
+//
+// Groups of 5 .. 16 heads carry the heads twice or once over the 16 columns (column c holds head c % GQP).
 //
 // Dequantization is reduced to masking (Sec. III-A(3) uses lop3 to the same end):
 //   * a masked code sitting in the low bits of an fp16 lane IS the fp16 subnormal code * 2^-24
@@ -116,6 +126,16 @@ struct WaveLds {
   uint16_t c16[kBlock];    // per V token: centre code * position factor, in the A-operand order of P'
   float zq[GQP];           // per head: sum_c Q_c z_c * 2^-24 (Q as normalised below)
 };
+// Groups of up to 4 heads: Q' as four e4m3 pieces, the B operand of one f8f6f4 instruction per tile, as its lanes
+// read it: [register half][lane group][column = 4 * piece + head][register].
+template <>
+struct WaveLds<4> {
+  uint32_t qp[2][4][16][4];
+  float4 vpar[kParSlots];
+  float2 kpar[kParSlots];  // per-token K only: (scale, zero)
+  uint32_t c8[4][8];       // per V token: centre code as e4m3, in B-operand order ([lane group][register])
+  float zq[4];
+};
 template <int GQP>
 struct MergeLds {
   float o[kWaves][GQP][kD];
@@ -127,9 +147,7 @@ constexpr size_t cmax(size_t x, size_t y) { return x > y ? x : y; }
 // GQP: the query group padded to 4, 8 or 16 heads; the 16 MFMA columns carry it 16/GQP times
 //      (column c holds head c % GQP, "column group" c / GQP) and the softmax work of a block
 //      is shared out over the column groups.
-//      GQP = 4: column group cg keeps S^T tiles cg and 4 + cg (8 values per lane) and the
-//      packed probabilities are moved to columns 0..3 with DPP row shifts, so O^T accumulates
-//      in those columns only.
+//      GQP = 4: see the top of the file; column group cg keeps S^T tiles cg and 4 + cg.
 //      GQP = 8, 16: each column group owns 4 / COPIES of the block's four 32-token k-steps of
 //      the second product: it keeps the S^T tiles of those tokens, runs their softmax, and
 //      presents their P' as its part of the B operand (zero in the k-steps it does not own);
@@ -151,6 +169,8 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   constexpr int COPIES = 16 / GQP;           // column groups
   constexpr int OWN = 4 / COPIES;            // k-steps owned by a column group
   constexpr int HP = GQP / 4;                // passes over the heads where 16 lanes work on one head
+  constexpr bool kF8 = GQP == 4;             // both products on f8f6f4 instructions (see the top of the file)
+  using E = FmtF8<BITS>;
 
   __shared__ __attribute__((aligned(16))) unsigned char smem_raw[cmax(sizeof(ML), kWaves * sizeof(WL))];
   __shared__ float res_o[GQP][kD], res_m[GQP], res_l[GQP];   // result of the residual slice
@@ -292,8 +312,10 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   // early only delays what the others are waiting for: 8 KB per wave (16 MB over the chip) keeps
   // HBM busy, and a shorter queue shortens the ramp at both ends of the kernel.
   const int prep_sg = lane & 15;
-  const int run0 = F::run_base(prep_sg, 0), run1 = F::run_base(prep_sg, 1);
-  const int tok_base = 32 * (col >> 2) + (col & 3);   // row `col` of tile T holds token tok_base + 4T
+  const int run0 = kF8 ? 8 * prep_sg : F::run_base(prep_sg, 0), run1 = kF8 ? run0 + 4 : F::run_base(prep_sg, 1);
+  // block token in row `col` of tile T
+  auto row_token = [&](int T) { return (kF8 ? E::token(col >> 2, T) : 32 * (col >> 2) + 4 * T) + (col & 3); };
+  auto slot = [&](int t) { return kF8 ? E::par_slot(t) : par_slot(t); };
   RawTile<WORDS> kraw[8], vraw[8];
   u4_t kp0, kp1;   // K parameters (half2) of this lane's two channel runs
   u2_t kp2;        // per-token K: parameters of tokens 2*lane, 2*lane+1
@@ -314,7 +336,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   };
   auto issue_ktile = [&](size_t bi, int T) {
     const uint32_t* kp = a.k_codes + bi * (size_t)(kBlock * KROW) + WORDS * g;
-    kraw[T] = load_raw<WORDS>(kp + (size_t)(tok_base + 4 * T) * KROW);
+    kraw[T] = load_raw<WORDS>(kp + (size_t)row_token(T) * KROW);
   };
   auto issue_vtile = [&](size_t bi, int mt) {
     const uint32_t* vp = a.v_codes + bi * (size_t)(kD * VROW) + WORDS * g;
@@ -407,6 +429,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   // of half j / 2; token = 32 g + 4 tile + row
   // Every head's queries times the power of two that brings the largest below 1 (kq); the factor comes
   // back out of the scores, together with softmax_scale * log2(e) and the 2^24 of the subnormal codes (kS).
+  constexpr int kQTop8 = KT ? E::kTop : E::kTop - kSTop;   // f8f6f4: with the K scales below 2^kSTop, |Q'| < 2^kTop
   float qv[2][4];
   int kq_head = 0;   // of the head this lane's column carries
   if constexpr (HP == 1) {
@@ -415,17 +438,17 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     for (int i = 0; i < 2; ++i)
       qb = max(max(qb, max(qraw0[i] & 0x7FFFu, (qraw0[i] >> 16) & 0x7FFFu)), max(qraw1[i] & 0x7FFFu, (qraw1[i] >> 16) & 0x7FFFu));
     qb = row_max16_u(qb);   // largest |q| of head lane / 16
-    const float f = pow2i(norm_exponent(qb, kQTop));
+    const float f = pow2i(norm_exponent(qb, kQTop8));
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       qv[0][i] = h2f((uint16_t)((qraw0[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
       qv[1][i] = h2f((uint16_t)((qraw1[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
     }
-    kq_head = norm_exponent((uint32_t)__shfl((int)qb, 16 * head), kQTop);   // (head h's queries sit in lanes 16h ..)
+    kq_head = norm_exponent((uint32_t)__shfl((int)qb, 16 * head), kQTop8);   // (head h's queries sit in lanes 16h ..)
   } else {
     kq_head = kq_s[head];
   }
-  const float kS = a.scale_log2 * pow2i((KT ? 0 : 24) - kq_head);   // what the kept scores still have to be multiplied by
+  const float kS = a.scale_log2 * pow2i((KT || kF8 ? 0 : 24) - kq_head);   // what the kept scores still have to be multiplied by
   const float kZ = a.scale_log2 * pow2i(-kq_head);                  // ... and the zero term sum_c Q_c z_c
   int tb[OWN][2];
 #pragma unroll
@@ -434,9 +457,9 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     tb[o][0] = 32 * g + 4 * (4 * (j >> 1) + ((j & 1) ? F::tile_lo(1) : F::tile_lo(0)));
     tb[o][1] = 32 * g + 4 * (4 * (j >> 1) + ((j & 1) ? F::tile_hi(1) : F::tile_hi(0)));
   }
-  if (COPIES == 4) {   // tiles cg and 4 + cg
-    tb[0][0] = 32 * g + 4 * cg;
-    tb[0][1] = 32 * g + 16 + 4 * cg;
+  if constexpr (kF8) {   // tiles cg and 4 + cg
+    tb[0][0] = E::token(g, cg);
+    tb[0][1] = E::token(g, 4 + cg);
   }
 
   // Q' = Q * s_c as an fp16 high + low pair in B-operand order, and the zero term sum_c Q_c z_c, per
@@ -459,6 +482,41 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) nrm[i] = f * F::un(i);
     }
+    if constexpr (kF8) {   // four e4m3 pieces of Q' in units of 2^ek, 2^(ek - 5), ..: 20 bits and more
+      float t[8], zsum = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float qc = qv[i >> 2][i & 3];
+        if constexpr (KT) {
+          t[i] = qc;
+          zsum += qc;
+        } else {
+          const h2_t pr = __builtin_bit_cast(h2_t, i < 4 ? kp0[i] : kp1[i - 4]);   // (scale, zero)
+          t[i] = qc * (float)pr[0];   // exact: 11 bits times 11 bits
+          zsum = __builtin_fmaf(qc, (float)pr[1], zsum);
+        }
+      }
+      zsum = row_sum16(zsum);
+      const int h = lane >> 4;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float unit = pow2i(ek - 5 * k);
+        uint32_t ev = 0, od = 0;   // channels 0, 2, 4, 6 / 1, 3, 5, 7 of the lane's eight
+        if (k < 3) {
+          ev = e4m3_piece<true>(e4m3_piece<false>(ev, t[0], t[2], unit), t[4], t[6], unit);
+          od = e4m3_piece<true>(e4m3_piece<false>(od, t[1], t[3], unit), t[5], t[7], unit);
+        } else {
+          ev = e4m3_last<true>(e4m3_last<false>(ev, t[0], t[2], unit), t[4], t[6], unit);
+          od = e4m3_last<true>(e4m3_last<false>(od, t[1], t[3], unit), t[5], t[7], unit);
+        }
+        uint32_t* dst = wl.qp[E::b_half(run0)][E::b_group(run0)][4 * k + h];
+        dst[E::b_reg(run0)] = ev;
+        dst[E::b_reg(run0 + 1)] = od;
+      }
+      if (prep_sg == 0) wl.zq[h] = zsum;
+      return ek;
+    }
+    if constexpr (!kF8) {
 #pragma unroll
     for (int p = 0; p < HP; ++p) {
       const int ph = 4 * p + (lane >> 4);
@@ -501,6 +559,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       *reinterpret_cast<u4_t*>(&wl.qlo[ph][8 * prep_sg]) = plo;
       if (prep_sg == 0) wl.zq[ph] = zsum;
     }
+    }
     return ek;
   };
   // Groups of up to 8 heads: the high piece of Q' goes to the even column groups and the low piece to
@@ -508,8 +567,17 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   // groups afterwards); groups of 9..16 have no columns to spare and run two MFMAs per k-step.
   constexpr bool kSplitCols = COPIES >= 2;
   h8_t bqh[4], bql[4];
+  i8_t bq8;   // groups of up to 4 heads: piece cg of Q'
+  const int sb_q = 127 - 5 * cg;              // its block scale
+  const int sb_p = 127 - E::kTop - 5 * cg;    // that of piece cg of P'
   auto load_bq = [&](int j) {
-    if constexpr (kSplitCols) {
+    if constexpr (kF8) {
+      if (j < 2) {
+        const u4_t x = *reinterpret_cast<const u4_t*>(wl.qp[j][g][col]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bq8[4 * j + i] = (int)x[i];
+      }
+    } else if constexpr (kSplitCols) {
       bqh[j] = *reinterpret_cast<const h8_t*>(cg & 1 ? &wl.qlo[head][8 * (4 * g + j)] : &wl.qhi[head][8 * (4 * g + j)]);
     } else {
       bqh[j] = *reinterpret_cast<const h8_t*>(&wl.qhi[head][8 * (4 * g + j)]);
@@ -551,10 +619,11 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const float sk = h2f((uint16_t)(kp2[u] & 0xFFFFu)), zk = h2f((uint16_t)(kp2[u] >> 16));
-        wl.kpar[par_slot(2 * lane + u)] = make_float2(sk * kTwo24, zk);
+        wl.kpar[slot(2 * lane + u)] = make_float2(kF8 ? sk : sk * kTwo24, zk);
       }
     }
     // V parameters of the block's 128 tokens
+    float centre[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const float sv = h2f((uint16_t)(vp2[u] & 0xFFFFu)), zv = h2f((uint16_t)(vp2[u] >> 16));
@@ -563,8 +632,17 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       // (a token whose values are all equal has scale 0 and all-zero codes: any scale does, take 1)
       const float se = sv > 0.0f ? sv : 1.0f, rs = __builtin_amdgcn_rcpf(se);
       const float ct = sv > 0.0f ? rintf(fminf(fmaxf(-zv * rs, 0.0f), F::kQmax)) : 0.0f;
-      wl.vpar[par_slot(t)] = make_float4(__builtin_amdgcn_logf(se), rs, __builtin_fmaf(ct, sv, zv) * rs, 0.0f);
-      wl.c16[F::p_slot(t)] = (uint16_t)(ct * F::inv_un(r));
+      wl.vpar[slot(t)] = make_float4(__builtin_amdgcn_logf(se), rs, __builtin_fmaf(ct, sv, zv) * rs, 0.0f);
+      centre[u] = ct;
+      if constexpr (!kF8) wl.c16[F::p_slot(t)] = (uint16_t)(ct * F::inv_un(r));
+    }
+    if constexpr (kF8) {
+      const uint32_t c2 = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(centre[0], centre[1], 0, false);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int t = 2 * lane + u;
+        reinterpret_cast<uint8_t*>(&wl.c8[E::b_group(t)][4 * E::b_half(t) + E::b_reg(t)])[E::b_byte(t)] = (uint8_t)(c2 >> (8 * u));
+      }
     }
     wave_sync();
     if constexpr (!KT) {
@@ -575,7 +653,11 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       zq = wl.zq[head];
     }
     bool has_next = !SINGLE && nblk < blk1;
-    if (!PAGED && has_next) {   // small, and the next block's first consumers: requested a block ahead
+    // The next block's keys are requested as soon as this block's are consumed, not at the block's end, where the
+    // arithmetic is short or the blocks are (8 x 32K tokens, 2 bits: 32.5 -> 29.3 us, with 8 heads 39.0 -> 37.7; 128K
+    // tokens, 4 bits: 26.3 -> 25.8, but with 8 heads 26.8 -> 28.2).
+    constexpr bool kEarly = kF8 || (BITS == 2 && GQP == 8);
+    if (!PAGED && !kEarly && has_next) {   // small, and the next block's first consumers: requested a block ahead
       issue_kpar(nbi);
       issue_vpar(nbi);
     }
@@ -591,11 +673,16 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 #pragma unroll
       for (int tt = 0; tt < 4; ++tt) {
         f4_t acc = {0.f, 0.f, 0.f, 0.f};   // (the zero term, one number per head, joins in the softmax)
+        if constexpr (kF8) {
+          acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(E::a_operand(kraw[4 * half + tt].w), bq8, acc, E::kFormatA, 0,
+                                                                 0, E::kScaleA, 0, sb_q);
+        } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const h8_t ak = F::dequant(kraw[4 * half + tt].w, j);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ak, bqh[j], acc, 0, 0, 0);
-          if constexpr (!kSplitCols) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ak, bql[j], acc, 0, 0, 0);
+          for (int j = 0; j < 4; ++j) {
+            const h8_t ak = F::dequant(kraw[4 * half + tt].w, j);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ak, bqh[j], acc, 0, 0, 0);
+            if constexpr (!kSplitCols) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ak, bql[j], acc, 0, 0, 0);
+          }
         }
         s[tt] = acc;
       }
@@ -624,21 +711,30 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
             sc[jj][0][r] = (half == 0 || cg == 1) ? lo : sc[jj][0][r];
             sc[jj][1][r] = (half == 0 || cg == 1) ? hi : sc[jj][1][r];
           }
-      } else {                              // column group cg keeps tile cg of each half: its own partial
-                                            // product plus that of the neighbouring column group
+      } else {                              // column group cg keeps tile cg of each half: the sum of the four pieces' products
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float v0 = s[0][r] + dpp_f<kRowShl4>(s[0][r]), v1 = s[1][r] + dpp_f<kRowShr4>(s[1][r]);
-          const float v2 = s[2][r] + dpp_f<kRowShl4>(s[2][r]), v3 = s[3][r] + dpp_f<kRowShr4>(s[3][r]);
-          const float lo = cg & 1 ? v1 : v0, hi = cg & 1 ? v3 : v2;
-          sc[0][half][r] = cg & 2 ? hi : lo;
-        }
+        for (int r = 0; r < 4; ++r) sc[0][half][r] = reduce_scatter4(s[0][r], s[1][r], s[2][r], s[3][r], cg);
       }
     }
     if (kValuesAfterQK) {
 #pragma unroll
       for (int mt = 0; mt < 8; ++mt) issue_vtile(bi, mt);
     }
+    // the keys' registers are free: request the next block's
+    auto request_next = [&]() {
+      if (PAGED) {
+        nblk = first_valid(nblk, next_entry, nbi);
+        has_next = nblk < blk1;
+        if (!has_next) return;
+      }
+      if (PAGED || kEarly) {   // parameters first: the next block's first consumers
+        issue_kpar(nbi);
+        issue_vpar(nbi);
+      }
+#pragma unroll
+      for (int T = 0; T < 8; ++T) issue_ktile(nbi, T);
+    };
+    auto attend_block = [&]() {
     if constexpr (KT) {   // per-token scale and zero of K
 #pragma unroll
       for (int o = 0; o < OWN; ++o)
@@ -646,7 +742,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
         for (int lh = 0; lh < 2; ++lh)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const float2 kq = wl.kpar[par_slot(tb[o][lh]) + r];
+            const float2 kq = wl.kpar[slot(tb[o][lh]) + r];
             sc[o][lh][r] = __builtin_fmaf(sc[o][lh][r], kq.x, kq.y * qsum);
           }
     }
@@ -658,7 +754,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       for (int lh = 0; lh < 2; ++lh)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          sc[o][lh][r] = __builtin_fmaf(sc[o][lh][r], kSb, wl.vpar[par_slot(tb[o][lh]) + r].x);
+          sc[o][lh][r] = __builtin_fmaf(sc[o][lh][r], kSb, wl.vpar[slot(tb[o][lh]) + r].x);
     float bmax = sc[0][0][0];
 #pragma unroll
     for (int o = 0; o < OWN; ++o)
@@ -681,21 +777,36 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       xacc *= alpha;
     }
     u4_t pb[4];   // P' as the B operand of the 4 k-steps of O^T += V^T P'
-    if constexpr (COPIES == 4) {   // valid in columns 0..3
+    i8_t pb8;     // groups of up to 4 heads: piece cg of P'
+    if constexpr (kF8) {   // the e4m3 pieces of this lane's 8 weights, to the column groups that take them
 #pragma unroll
-      for (int half = 0; half < 2; ++half)
+      for (int half = 0; half < 2; ++half) {
+        float e[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float e = __builtin_amdgcn_exp2f(sc[0][half][r] + zoff);   // P' = weight * V scale, <= 1
-          const float4& par = wl.vpar[par_slot(tb[0][half]) + r];
-          l_run = __builtin_fmaf(e, par.y, l_run);
-          z_run = __builtin_fmaf(e, par.z, z_run);
-          // gather the column groups' fp16 values into the B-operand register pairs
-          const uint32_t x = (uint32_t)f2h(e * F::un(r));
-          const uint32_t pr = x | dpp_u<F::kPairShift>(x << 16);
-          pb[2 * half][r] = pr;
-          pb[2 * half + 1][r] = dpp_u<F::kStepShift>(pr);
+          e[r] = __builtin_amdgcn_exp2f(sc[0][half][r] + zoff);   // P' = weight * V scale, <= 1
+          const float4& par = wl.vpar[slot(tb[0][half]) + r];
+          l_run = __builtin_fmaf(e[r], par.y, l_run);
+          z_run = __builtin_fmaf(e[r], par.z, z_run);
         }
+        uint32_t u[4] = {0u, 0u, 0u, 0u}, from[4];
+        float unit = 1.0f / (1 << E::kTop);
+#pragma unroll
+        for (int k = 0; k < E::kWeightPieces; ++k) {
+          if (k < E::kWeightPieces - 1)
+            u[k] = e4m3_piece<true>(e4m3_piece<false>(u[k], e[0], e[2], unit), e[1], e[3], unit);
+          else
+            u[k] = e4m3_last<true>(e4m3_last<false>(u[k], e[0], e[2], unit), e[1], e[3], unit);
+          unit *= 1.0f / 32;
+        }
+        exchange_pieces(u, from);
+        // rows 0, 2 (low halves) and 1, 3 (high halves) of two neighbouring tiles make a register each
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          pb8[4 * half + E::b_reg(8 * w)] = (int)__builtin_amdgcn_perm(from[2 * w + 1], from[2 * w], 0x05040100u);
+          pb8[4 * half + E::b_reg(8 * w + 1)] = (int)__builtin_amdgcn_perm(from[2 * w + 1], from[2 * w], 0x07060302u);
+        }
+      }
     } else {                       // zero where another column group owns the k-step
       u4_t pair[OWN];
 #pragma unroll
@@ -706,7 +817,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 #pragma unroll
           for (int lh = 0; lh < 2; ++lh) {
             const float e = __builtin_amdgcn_exp2f(sc[o][lh][r] + zoff);
-            const float4& par = wl.vpar[par_slot(tb[o][lh]) + r];
+            const float4& par = wl.vpar[slot(tb[o][lh]) + r];
             l_run = __builtin_fmaf(e, par.y, l_run);
             z_run = __builtin_fmaf(e, par.z, z_run);
             hv[lh] = (uint32_t)f2h(e * F::un(r));
@@ -721,7 +832,16 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
           else pb[j][r] = cg == (j >> 1) ? pair[j & 1][r] : 0u;
         }
     }
-    // ---- O^T += V^T P' : k-step j contracts 32 tokens (8 per lane group)
+    // ---- O^T += V^T P'
+    if constexpr (kF8) {
+      const u4_t c0 = *reinterpret_cast<const u4_t*>(&wl.c8[g][0]), c1 = *reinterpret_cast<const u4_t*>(&wl.c8[g][4]);
+      const i8_t ac = {(int)c0[0], (int)c0[1], (int)c0[2], (int)c0[3], (int)c1[0], (int)c1[1], (int)c1[2], (int)c1[3]};
+      xacc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ac, pb8, xacc, 0, 0, 0, 127, 0, sb_p);
+#pragma unroll
+      for (int mt = 0; mt < 8; ++mt)
+        oacc[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(E::a_operand(vraw[mt].w), pb8, oacc[mt], E::kFormatA, 0,
+                                                                    0, E::kScaleA, 0, sb_p);
+    } else {   // k-step j contracts 32 tokens (8 per lane group)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const h8_t ac = *reinterpret_cast<const h8_t*>(&wl.c16[8 * (4 * g + j)]);
@@ -734,17 +854,14 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       for (int mt = 0; mt < 8; ++mt)
         oacc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::dequant(vraw[mt].w, j), bp, oacc[mt], 0, 0, 0);
     }
-    if (PAGED && has_next) {
-      nblk = first_valid(nblk, next_entry, nbi);
-      has_next = nblk < blk1;
-      if (has_next) {
-        issue_kpar(nbi);
-        issue_vpar(nbi);
-      }
     }
-    if (has_next) {
-#pragma unroll
-      for (int T = 0; T < 8; ++T) issue_ktile(nbi, T);
+    };
+    if (kEarly && has_next) {   // (both branches whole: the compiler then knows how many loads are behind the values)
+      request_next();
+      attend_block();
+    } else {
+      attend_block();
+      if (!kEarly && has_next) request_next();
     }
     // Both sums grow with the number of tokens, their difference (the signal) with its square root: every
     // 16 blocks the centre sum is taken out of the accumulators and starts again from zero.
@@ -774,11 +891,23 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) oacc[mt][r] += dpp_f<kRowShl8>(oacc[mt][r]);
   }
+  if constexpr (kF8) {   // the column groups hold the pieces' shares: column group cg sums M tiles 2 cg and 2 cg + 1
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      f4_t o;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        o[r] = reduce_scatter4(oacc[i][r], oacc[2 + i][r], oacc[4 + i][r], oacc[6 + i][r], cg);
+      *reinterpret_cast<f4_t*>(&ml.o[wave][head][16 * (2 * cg + i) + 4 * g]) = o;
+    }
+  }
   if (col < GQP) {
+    if constexpr (!kF8) {
 #pragma unroll
-    for (int mt = 0; mt < 8; ++mt)
+      for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) ml.o[wave][col][16 * mt + 4 * g + r] = oacc[mt][r] * kTwo24;
+        for (int r = 0; r < 4; ++r) ml.o[wave][col][16 * mt + 4 * g + r] = oacc[mt][r] * kTwo24;
+    }
     if (g == 0) {
       ml.m[wave][col] = m_run;
       ml.l[wave][col] = l_run;

@@ -93,3 +93,21 @@ def test_prompt_tails_go_to_the_residual(fmt, L):
         pages = pc.host_buffer(i).reshape(4, 3, -1)[[[2, 0], [3, 1]]]   # [sequence][block][head]
         blocks = gc.host_buffer(i).reshape(2, 3, 2, -1).transpose(0, 2, 1, 3)
         assert np.array_equal(pages[:, :L // 128], blocks[:, :L // 128])
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int2", "int4_kt", "int2_kt"])
+@pytest.mark.parametrize("gq", [1, 2, 3, 4])
+def test_small_query_groups_hold_the_precision_of_their_pieces(fmt, gq):
+    """Query groups of up to 4 heads run both products on 8-bit matrix operands, queries and weights as sums of
+    e4m3 pieces whose products add up exactly: one block, fewer blocks than waves, several rounds of blocks, and
+    enough rounds (17 a wave) to fold the centre sum.  Weights hold 14 bits with three pieces (2-bit codes), 19
+    with four, queries 19: a relative error of 2^-15 (2^-20) per weight, independent from token to token like the
+    values themselves, and for the scores 2^-20 of a sum of magnitudes of at most some tens (1e-5 in the
+    exponent)."""
+    bar = 2.0 ** -15 + 1e-5 if fmt.startswith("int2") else 2.0 ** -20 + 1e-5
+    for L, ns in [(128, 1), (128 * 3 + 1, 1), (128 * 5, 2), (128 * 4 * 17 + 130, 1)]:
+        w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=2 * gq, n_kv_heads=2, context=L, fmt=fmt, seed=700 + L + gq)
+        K, V, oc, gc = _int_cache_pair(w, (L // 128 + 1) * 128)
+        q = W.make_q(w)
+        ma, rl = attn_errors(_attend_f32(gc, w, q, ns), O.decode_attn(oc, q, W.softmax_scale(w)))
+        assert rl <= bar, f"{fmt} gq={gq} L={L}: rel-L2 {rl:.2e} max-abs {ma:.2e}"
