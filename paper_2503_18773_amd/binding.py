@@ -98,13 +98,24 @@ EXPORTS = ["bd_cache_bytes", "bd_choose_splits", "bd_workspace_bytes", "bd_quant
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = None   # () -> handle of the current device's current stream
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # without the Stream object around the handle
+        if raw is None:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+        else:
+            _raw_stream = lambda: raw(torch.cuda.current_device())
+    return _raw_stream()
 
 
 def _check(status: int, where: str):
@@ -240,6 +251,7 @@ class KVCache:
         self.res_len = 0
         self.device = device
         self._ws = None
+        self._ws_rows = 0
         self._retired = []
 
     @property
@@ -256,12 +268,16 @@ class KVCache:
     def workspace(self, num_splits: int):
         """A device buffer of at least bd_workspace_bytes(num_splits).  It only grows, and a buffer it
         outgrows is kept alive (kernels queued on any stream may still be writing partials into it)."""
+        rows = num_splits * self.desc.batch * self.desc.n_q_heads   # partial results; what the size is proportional to
+        if 0 < rows <= self._ws_rows:
+            return self._ws
         import torch
         need = bd_workspace_bytes(self.desc, num_splits)
         if self._ws is None or self._ws.numel() < need:
             if self._ws is not None:
                 self._retired.append(self._ws)
             self._ws = torch.empty(need, dtype=torch.uint8, device=self.device)
+            self._ws_rows = rows
         return self._ws
 
     def choose_splits(self) -> int:
@@ -317,6 +333,7 @@ class PagedKVCache:
         self.desc.status = self.status.data_ptr()
         self.device = device
         self._ws = None
+        self._ws_rows = 0
         self._retired = []
 
     def quant_pack_kv(self, seq: int, k, v, stream=None):
@@ -328,12 +345,16 @@ class PagedKVCache:
 
     def workspace(self, num_splits: int):
         """As KVCache.workspace: grows only, outgrown buffers stay alive."""
+        rows = num_splits * self.desc.batch * self.desc.n_q_heads   # partial results; what the size is proportional to
+        if 0 < rows <= self._ws_rows:
+            return self._ws
         import torch
         need = bd_paged_workspace_bytes(self.desc, num_splits)
         if self._ws is None or self._ws.numel() < need:
             if self._ws is not None:
                 self._retired.append(self._ws)
             self._ws = torch.empty(need, dtype=torch.uint8, device=self.device)
+            self._ws_rows = rows
         return self._ws
 
     def decode_attn(self, q, softmax_scale: float, out, num_splits: int, stream=None):
