@@ -171,14 +171,19 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   constexpr int HP = GQP / 4;                // passes over the heads where 16 lanes work on one head
   constexpr bool kF8 = GQP == 4;             // both products on f8f6f4 instructions (see the top of the file)
   using E = FmtF8<BITS>;
+  // The next block's keys are requested as soon as this block's are consumed, not at the block's end, where the
+  // arithmetic is short or the blocks are (8 x 32K tokens, 2 bits: 32.5 -> 29.3 us, with 8 heads 39.0 -> 37.7; 128K
+  // tokens, 4 bits: 26.3 -> 25.8, but with 8 heads 26.8 -> 28.2).
+  constexpr bool kEarly = kF8 || (BITS == 2 && GQP == 8);
 
   __shared__ __attribute__((aligned(16))) unsigned char smem_raw[cmax(sizeof(ML), kWaves * sizeof(WL))];
   __shared__ float res_o[GQP][kD], res_m[GQP], res_l[GQP];   // result of the residual slice
   __shared__ __attribute__((aligned(16))) float q_s[HP > 1 ? GQP : 1][kD];   // larger groups: queries, normalised; padding heads zero
   __shared__ int kq_s[HP > 1 ? GQP : 1];                                     // larger groups: each head's normalising exponent
 
-  const int b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int seq_len = 0;
+  const int b = PAGED ? paged_sequence(a.seq_lens, lane, seq_len, INT32_MAX) : blockIdx.z;
   const bool flush_after = a.flush_mode == kFlushAfter;
   const int split = (int)blockIdx.x - (flush_after ? 1 : 0);
   const int col = lane & 15, g = lane >> 4;            // MFMA column and contraction group
@@ -199,7 +204,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   int new_slot = a.new_slot;   // fused step: residual slot of the token that is still in the caller's buffer, or -1
   int flush_page = -1;         // paged fused step that fills the residual: the page the block goes to
   if (PAGED) {
-    int len = a.seq_lens[b];
+    int len = seq_len;
     new_slot = -1;
     if (a.step && len >= 0) {
       // fused step: this step's token counts (unless it needs a page the table does not name) and
@@ -653,10 +658,6 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       zq = wl.zq[head];
     }
     bool has_next = !SINGLE && nblk < blk1;
-    // The next block's keys are requested as soon as this block's are consumed, not at the block's end, where the
-    // arithmetic is short or the blocks are (8 x 32K tokens, 2 bits: 32.5 -> 29.3 us, with 8 heads 39.0 -> 37.7; 128K
-    // tokens, 4 bits: 26.3 -> 25.8, but with 8 heads 26.8 -> 28.2).
-    constexpr bool kEarly = kF8 || (BITS == 2 && GQP == 8);
     if (!PAGED && !kEarly && has_next) {   // small, and the next block's first consumers: requested a block ahead
       issue_kpar(nbi);
       issue_vpar(nbi);
@@ -722,11 +723,6 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     }
     // the keys' registers are free: request the next block's
     auto request_next = [&]() {
-      if (PAGED) {
-        nblk = first_valid(nblk, next_entry, nbi);
-        has_next = nblk < blk1;
-        if (!has_next) return;
-      }
       if (PAGED || kEarly) {   // parameters first: the next block's first consumers
         issue_kpar(nbi);
         issue_vpar(nbi);
@@ -856,12 +852,24 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     }
     }
     };
-    if (kEarly && has_next) {   // (both branches whole: the compiler then knows how many loads are behind the values)
+    auto next_page = [&]() {
+      if (PAGED && has_next) {
+        nblk = first_valid(nblk, next_entry, nbi);
+        has_next = nblk < blk1;
+      }
+    };
+    if constexpr (kEarly) {
+      next_page();
+      if (!has_next) {   // (a branch of its own: the compiler then knows how many loads are behind the values)
+        attend_block();
+        break;
+      }
       request_next();
       attend_block();
     } else {
       attend_block();
-      if (!kEarly && has_next) request_next();
+      next_page();
+      if (has_next) request_next();
     }
     // Both sums grow with the number of tokens, their difference (the signal) with its square root: every
     // 16 blocks the centre sum is taken out of the accumulators and starts again from zero.

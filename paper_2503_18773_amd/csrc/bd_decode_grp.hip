@@ -141,10 +141,11 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   __shared__ __attribute__((aligned(16))) float q_s[GQP][kD];
   __shared__ float qinv_s[GQP];
 
-  const int b = blockIdx.z;
   const bool flush_after = a.flush_mode == kFlushAfter;
   const int split = (int)blockIdx.x - (flush_after ? 1 : 0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int seq_len = 0;
+  const int b = PAGED ? paged_sequence(a.seq_lens, lane, seq_len, INT32_MAX) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   // Every copy of a head's column receives the same S^T; copy cp keeps the chunks c with
   // c % COPIES == cp, runs their softmax and writes their P', so that work is shared out.
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   int new_slot = a.new_slot;   // fused step: residual slot of the token that is still in the caller's buffer, or -1
   int flush_page = -1;         // paged fused step that fills the residual: the page the block goes to
   if (PAGED) {
-    int len = a.seq_lens[b];
+    int len = seq_len;
     new_slot = -1;
     if (a.step && len >= 0) {
       // fused step: this step's token counts (unless it needs a page the table does not name) and

@@ -166,8 +166,10 @@ __device__ __forceinline__ void mx_query_operand(const uint16_t* qp, i8_t& bhi, 
 template <bool PAGED>
 __global__ __launch_bounds__(256, 2) void decode_mx_kernel(MxArgs a) {
   __shared__ MergeLdsMx ml;
-  const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
+  const int split = blockIdx.x, hkv = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int seq_len = 0;
+  const int b = PAGED ? paged_sequence(a.seq_lens, lane, seq_len, 512) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   const int head = col & 3, cg = col >> 2;
   const int head0 = hkv * a.gq;                  // first query head of this workgroup
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(256, 2) void decode_mx_kernel(MxArgs a) {
   long app_bi = -1;   // fused step without an append launch: array index of the block the token goes to
   int app_pos = 0;
   if (PAGED) {
-    length = a.seq_lens[b];
+    length = seq_len;
     if (a.step && length >= 0) {
       // fused step: this step's token counts if the table names a page for it (a preceding kernel
       // has appended it, or, with a.k_new, this launch does); the length is raised only after this kernel
@@ -435,8 +437,10 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
   constexpr int NT = 8 / COPIES;       // S^T tiles a lane keeps
   __shared__ MergeLdsMxG<GQP> ml;
   const int nwg = (a.gq + GQP - 1) / GQP;        // workgroups per (split, KV head)
-  const int split = blockIdx.x, hkv = blockIdx.y / nwg, sub0 = GQP * (blockIdx.y % nwg), b = blockIdx.z;
+  const int split = blockIdx.x, hkv = blockIdx.y / nwg, sub0 = GQP * (blockIdx.y % nwg);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int seq_len = 0;
+  const int b = PAGED ? paged_sequence(a.seq_lens, lane, seq_len, 512) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   const int head = col % GQP, cg = col / GQP;
   const int head0 = hkv * a.gq + sub0;           // first query head of this workgroup
@@ -446,7 +450,7 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
   long app_bi = -1;   // fused step without an append launch (see decode_mx_kernel)
   int app_pos = 0;
   if (PAGED) {
-    length = a.seq_lens[b];
+    length = seq_len;
     if (a.step && length >= 0) {
       const int n = length / kBlock;
       const int e = n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1;

@@ -136,5 +136,41 @@ __device__ __forceinline__ void workgroup_global_sync() {
 constexpr int kParSlots = 128 + 8;
 __device__ __forceinline__ int par_slot(int t) { return t + 2 * (t >> 5); }
 
+// Paged cache: the sequence of grid row z and its length.  Where the launch's last round of workgroups (one per
+// compute unit a round) would fill at most half of the units, a ragged batch runs longest sequence first (to 1/16 of
+// the length, then by index), so that those units get short ones.  The lengths' load then stands before everything
+// else of the workgroup, which costs 1.2 us: not worth it for fuller rounds (64 sequences of up to 700 tokens, 512
+// workgroups: 18.9 against 20.3 us a step), nor for MXFP4 past two rounds (24 of up to 5K: 29.4 / 30.1).  Gains, a step:
+// 40 sequences of up to 3.1K tokens, one split, 2-bit codes and 8 heads per KV head 34.9 -> 30.9 us, 4 bits 33.9 -> 31.1,
+// MXFP4 34.8 -> 31.5; 24 of up to 5K, three splits, groups of 32 42.4 -> 39.3, groups of 128 28.0 as before.  Every wave
+// selects the z-th longest itself, a bit of the key at a time; batches of more than 64 sequences stay as they are.
+__device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_lens, int lane, int& seq_len, int max_wgs) {
+  const int n = gridDim.z, wgs = gridDim.x * gridDim.y * gridDim.z;
+  if (n < 2 || n > 64 || wgs <= 256 || wgs > max_wgs || (wgs - 1) % 256 >= 128) {
+    seq_len = seq_lens[blockIdx.z];
+    return blockIdx.z;
+  }
+  const int len = seq_lens[min(lane, n - 1)];
+  // exponent and four bits of the length: 0 .. 30 * 16 + 15
+  const uint32_t key = len > 0 ? (__float_as_uint((float)len) >> 19) - (127u << 4) : 0u;
+  uint64_t cand = __ballot(lane < n);   // those that share the key's leading bits
+  int z = blockIdx.z;                   // of which this is the wanted one's place
+#pragma unroll
+  for (int bit = 8; bit >= 0; --bit) {
+    const uint64_t ones = __ballot(((key >> bit) & 1u) != 0) & cand;
+    const int c = __builtin_popcountll(ones);
+    if (z < c) {
+      cand = ones;
+    } else {
+      z -= c;
+      cand &= ~ones;
+    }
+  }
+  const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(cand >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cand, 0u));
+  const int b = __builtin_ctzll(__ballot((cand >> lane & 1u) != 0 && before == z));
+  seq_len = __builtin_amdgcn_readlane(len, b);
+  return b;
+}
+
 }  // namespace
 }  // namespace bd

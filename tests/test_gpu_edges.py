@@ -111,3 +111,40 @@ def test_small_query_groups_hold_the_precision_of_their_pieces(fmt, gq):
         q = W.make_q(w)
         ma, rl = attn_errors(_attend_f32(gc, w, q, ns), O.decode_attn(oc, q, W.softmax_scale(w)))
         assert rl <= bar, f"{fmt} gq={gq} L={L}: rel-L2 {rl:.2e} max-abs {ma:.2e}"
+
+
+@pytest.mark.parametrize("fmt,hq", [("int4", 8), ("int2_kt", 16), ("int4_g32", 8), ("mxfp4", 8), ("mxfp4", 20)])
+@pytest.mark.parametrize("batch", [2, 33, 64, 65])
+def test_ragged_batches_attend_their_own_lengths_in_any_order(fmt, hq, batch):
+    """A paged launch whose last round of workgroups is short (257 .. 384, 513 .. 640, ..) takes up to 64 sequences
+    longest first: equal, empty and one-token lengths among them, every row is that of a batch of one."""
+    import torch
+    mx = fmt == "mxfp4"
+    rng = np.random.default_rng(batch)
+    lens = rng.integers(0, 500, batch)
+    lens[:2] = 300, 300
+    if batch > 8:
+        lens[3:8] = 0, 1, 499, 499, 128
+    maxp = 4
+    dt = torch.bfloat16 if mx else torch.float16
+    table = torch.randperm(batch * maxp).view(batch, maxp).to(torch.int32)
+    gen = torch.Generator(device="cuda:0").manual_seed(batch)
+    pc = B.PagedKVCache(batch, hq, 2, fmt, batch * maxp, table)
+    q = torch.randn((batch, hq, 128), device="cuda:0", generator=gen).to(dt)
+    kv = []
+    for s in range(batch):
+        k, v = (torch.randn((2, int(lens[s]), 128), device="cuda:0", generator=gen).to(dt) for _ in range(2))
+        pc.quant_pack_kv(s, k, v)
+        kv.append((k, v))
+    wgs = 2 * batch
+    for ns in (2, 3, 256 // wgs + 1, 512 // wgs + 1):   # the last two: just above one and two rounds
+        out = torch.full((batch, hq, 128), 7.0, dtype=dt, device="cuda:0")
+        pc.decode_attn(q, 0.088, out, num_splits=ns)
+        for s in range(batch):
+            one = B.PagedKVCache(1, hq, 2, fmt, maxp, torch.arange(maxp, dtype=torch.int32).view(1, maxp))
+            one.quant_pack_kv(0, *kv[s])
+            ref = torch.full((1, hq, 128), 5.0, dtype=dt, device="cuda:0")
+            one.decode_attn(q[s:s + 1].contiguous(), 0.088, ref, num_splits=ns)
+            torch.cuda.synchronize()
+            assert torch.equal(out[s], ref[0]), f"{fmt} batch {batch} splits {ns}: sequence {s} of {lens[s]} tokens"
+    assert pc.status.item() == 0
