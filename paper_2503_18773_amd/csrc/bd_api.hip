@@ -116,11 +116,29 @@ int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len) {
   const long units = (long)c->batch * group_workgroups(c);
   const int nb = (packed_len + kBlock - 1) / kBlock;
   const int quanta = (nb + 3) / 4;
+  const int gq = c->n_q_heads / c->n_kv_heads;
+  // Two rounds of blocks in one workgroup take no longer than one round in two and the merge behind it, and are one
+  // launch less (1K tokens, up to 4 heads per KV head: 8.5 -> 8.4 us with 8 units, 10.1 -> 8.8 with 128, issued one by
+  // one 10.2 -> 8.3; with more heads, or in groups of 64 and 32, the second round costs more than the merge).
+  if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 4 && quanta <= 2) return 1;
+  // Few units, hence many partials per output row: the merge then costs more than a second workgroup per compute
+  // unit gives, if the kernel's arithmetic leaves one the time (4-bit codes with up to 4 heads per KV head: any
+  // context; other integer codes up to 3.5 blocks per wave; MXFP4 around two).  A step, 8 units, 4 bits: 24.6K tokens 13.1 us with 48
+  // splits, 12.1 with 32; 32K 13.2 / 12.6; 48K 17.5 (94 splits) / 14.7; 128K 28.9 / 27.9; 2 bits 32K 12.1 / 11.5
+  // but 128K 20.3 / 21.9; MXFP4 32K 16.3 / 15.6; 4 units, 128K 19.5 (128) / 18.6 (64); one unit, 128K 14.3 (256)
+  // / 13.0 (128).  From 17 units on the two are equal, and the groups of 64 and 32 want the waves.
+  if (fmt_group(c->format) == kBlock && units <= 16) {
+    const int one_round = units == 1 ? 128 : (int)(256 / units);
+    if (quanta <= one_round) return quanta;
+    const bool light = fmt_is_int(c->format) && fmt_bits(c->format) == 4 && gq <= 4;
+    const bool moderate = fmt_is_int(c->format) ? 2 * quanta <= 7 * one_round
+                                                : units <= 8 && 2 * quanta >= 3 * one_round && 2 * quanta <= 5 * one_round;
+    if (light || moderate) return one_round;
+  }
   // Up to three workgroups per compute unit fit when no wave has more than one block (that kernel
   // instance needs half the registers; groups of up to 8 heads, integer formats): then one block
   // per wave beats two blocks for some waves and one for others.  Measured at 40K and 48K tokens.
-  if (c->format != BD_FMT_MXFP4 && fmt_group(c->format) == kBlock && c->n_q_heads / c->n_kv_heads <= 8 &&
-      (long)quanta * units <= 768)
+  if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 8 && (long)quanta * units <= 768)
     return quanta;
   // With one workgroup per compute unit already, a single split needs no merge kernel at all; that beats
   // the better occupancy of two splits until the call is long enough to amortize the merge (measured at
