@@ -123,8 +123,8 @@ int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len) {
   if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 4 && quanta <= 2) return 1;
   // Few units, hence many partials per output row: the merge then costs more than a second workgroup per compute
   // unit gives, if the kernel's arithmetic leaves one the time (4-bit codes with up to 4 heads per KV head: any
-  // context; other integer codes up to 3.5 blocks per wave; MXFP4 around two).  A step, 8 units, 4 bits: 24.6K tokens 13.1 us with 48
-  // splits, 12.1 with 32; 32K 13.2 / 12.6; 48K 17.5 (94 splits) / 14.7; 128K 28.9 / 27.9; 2 bits 32K 12.1 / 11.5
+  // context; other integer codes up to 3.5 blocks per wave; MXFP4 around two).  A step, 8 units, 4 bits: 24.6K tokens
+  // 13.1 us with 48 splits, 12.1 with 32; 32K 13.2 / 12.6; 48K 17.5 (94 splits) / 14.7; 128K 28.9 / 27.9; 2 bits 32K 12.1 / 11.5
   // but 128K 20.3 / 21.9; MXFP4 32K 16.3 / 15.6; 4 units, 128K 19.5 (128) / 18.6 (64); one unit, 128K 14.3 (256)
   // / 13.0 (128).  From 17 units on the two are equal, and the groups of 64 and 32 want the waves.
   if (fmt_group(c->format) == kBlock && units <= 16) {
@@ -135,11 +135,6 @@ int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len) {
                                                 : units <= 8 && 2 * quanta >= 3 * one_round && 2 * quanta <= 5 * one_round;
     if (light || moderate) return one_round;
   }
-  // Up to three workgroups per compute unit fit when no wave has more than one block (that kernel
-  // instance needs half the registers; groups of up to 8 heads, integer formats): then one block
-  // per wave beats two blocks for some waves and one for others.  Measured at 40K and 48K tokens.
-  if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 8 && (long)quanta * units <= 768)
-    return quanta;
   // With one workgroup per compute unit already, a single split needs no merge kernel at all; that beats
   // the better occupancy of two splits until the call is long enough to amortize the merge (measured at
   // 256 and 384 units: 30.0 against 32.4 us and 41.9 against 47.1 us at 4K tokens, 99.5 against 94.2 us at 16K).
@@ -150,12 +145,24 @@ int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len) {
   // per KV head, for 4-bit codes and for per-token K)
   const bool one_wg = fmt_group(c->format) == 32 && (fmt_bits(c->format) == 4 || fmt_kt(c->format)) && c->n_q_heads / c->n_kv_heads > 4;
   const long target = one_wg ? 256 : 512;
-  int want = (int)((target + units - 1) / units);
+  // (not more than one round of workgroups: the few of a second round run with most of the chip idle -- a step, 4 bits,
+  // 160 units at 6K tokens 31.3 us with 640 workgroups, 27.9 with 480, in pages 32.5 / 27.1; 192 units at 8K 46.9 with
+  // 576, 44.2 with 384, in pages 50.7 / 47.4 at up to 9K; 96 units at 3K 17.8 / 16.8 in pages, where one block per wave
+  // took 576)
+  int want = (int)(units < 256 ? target / units : (target + units - 1) / units);
   if (want < 1) want = 1;
   // (no rebalancing: quanta are dealt to the splits round robin, so a count that does not divide them
   // leaves a few workgroups one quantum short, which is faster than fewer workgroups of equal length)
-  const int splits = quanta < want ? quanta : want;
-  return splits < 1 ? 1 : splits;
+  int splits = quanta < want ? quanta : want;
+  // Two workgroups on a compute unit take nearly twice as long as one: one each, with fewer splits, if that leaves a
+  // unit fewer rounds of blocks and few units idle (64 units, 6K tokens: 3 rounds with 4 splits, 2 of 2 workgroups with 8, 15.6 / 17.6 us;
+  // 128 units with 8 heads per KV head, 3K: 18.9 / 20.0; 192 units, 1.5K, no split: 14.6 / 17.4).
+  if (units < 256 && fmt_is_int(c->format) && fmt_group(c->format) == kBlock) {
+    const int single = (int)(256 / units);
+    auto rounds = [&](int ns) { return (quanta + ns - 1) / ns * (int)((units * ns + 255) / 256); };
+    if (single < splits && rounds(single) < rounds(splits) && (single == 1 || units * single >= 224)) splits = single;
+  }
+  return splits;
 }
 
 size_t bd_workspace_bytes(const bd_cache* c, int32_t num_splits) {
