@@ -159,7 +159,9 @@ bd_status bd_append_kv(const bd_cache* c, const void* k_new, const void* v_new,
  * [B][n_q_heads][D], fp16 / bf16) the merge of the partials is enqueued too, so `out`
  * is complete when the stream passes this call; if NULL, call bd_splitk_combine.  (`out` has
  * the element type c->out_type names here and in every other call: fp16 / bf16, or fp32.)
- * num_splits >= 1 (any value; splits beyond the number of 128-token blocks stay empty).
+ * num_splits >= 1 (any value; splits beyond the number of 128-token blocks stay empty).  A call that writes `out`
+ * (this one, the paged one and the decode steps) shares the context out over fewer workgroups where that is
+ * faster; the workspace then still holds num_splits partials, the last ones empty.
  * With no tokens at all the output is zero. */
 bd_status bd_decode_attn(const bd_cache* c, const void* q, int32_t packed_len, int32_t res_len,
                          float softmax_scale, int32_t num_splits, void* workspace, void* out,

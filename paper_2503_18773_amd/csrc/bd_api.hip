@@ -1,4 +1,5 @@
 // C-ABI entry points of libbitdecode.so: argument validation and kernel sequencing only.
+#include <algorithm>
 #include <mutex>
 
 #include "bd_common.h"
@@ -84,6 +85,55 @@ bd_status static_scratch_ptr(void** ptr) {
   return BD_OK;
 }
 
+// Splits a call that writes `out` runs with: as many as asked for, or fewer where fewer are faster, which the merge makes
+// no difference to (the workspace keeps the layout of the count asked for, the rest of its partials being empty).
+// packed_len < 0: the lengths are on the device (paged cache).
+int splits_to_run(const bd_cache* c, int packed_len, int asked) {
+  // (quantum: the 4 blocks that the 4 waves of a workgroup take in a round; 2 workgroups are resident per compute unit)
+  const long units = (long)c->batch * group_workgroups(c);
+  // (some kernel instances run one workgroup per compute unit: groups of 32 with more than 4 query heads
+  // per KV head, for 4-bit codes and for per-token K)
+  const bool one_wg = fmt_group(c->format) == 32 && (fmt_bits(c->format) == 4 || fmt_kt(c->format)) && c->n_q_heads / c->n_kv_heads > 4;
+  const long target = one_wg ? 256 : 512;
+  // (not more than one round of workgroups: the few of a second round run with most of the chip idle -- a step, 4 bits,
+  // 160 units at 6K tokens 31.3 us with 640 workgroups, 27.9 with 480, in pages 32.5 / 27.1; 192 units at 8K 46.9 with
+  // 576, 44.2 with 384, in pages 50.7 / 47.4 at up to 9K; 96 units at 3K 17.8 / 16.8 in pages, where one block per wave
+  // took 576)
+  int want = asked;
+  if (units < 256) want = (int)std::max(1L, std::min((long)asked, target / units));
+  if (packed_len < 0) return want;
+  const int quanta = std::max(1, ((packed_len + kBlock - 1) / kBlock + 3) / 4);
+  const int gq = c->n_q_heads / c->n_kv_heads;
+  // Two rounds of blocks in one workgroup take no longer than one round in two and the merge behind it, and are one
+  // launch less (1K tokens, up to 4 heads per KV head: 8.5 -> 8.4 us with 8 units, 10.1 -> 8.8 with 128, issued one by
+  // one 10.2 -> 8.3; with more heads, or in groups of 64 and 32, the second round costs more than the merge).
+  if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 4 && quanta <= 2) return 1;
+  // Few units, hence many partials per output row: the merge then costs more than a second workgroup per compute
+  // unit gives, if the kernel's arithmetic leaves one the time (4-bit codes with up to 4 heads per KV head: any
+  // context; other integer codes up to 3.5 blocks per wave; MXFP4 around two).  A step, 8 units, 4 bits: 24.6K tokens
+  // 13.1 us with 48 splits, 12.1 with 32; 32K 13.2 / 12.6; 48K 17.5 (94 splits) / 14.7; 128K 28.9 / 27.9; 2 bits 32K 12.1 /
+  // 11.5 but 128K 20.3 / 21.9; MXFP4 32K 16.3 / 15.6; 4 units, 128K 19.5 (128) / 18.6 (64); one unit, 128K 14.3 (256)
+  // / 13.0 (128).  From 17 units on the two are equal, and the groups of 64 and 32 want the waves.
+  if (fmt_group(c->format) == kBlock && units <= 16) {
+    const int one_round = units == 1 ? 128 : (int)(256 / units);
+    if (quanta <= one_round) return std::min(asked, quanta);
+    const bool light = fmt_is_int(c->format) && fmt_bits(c->format) == 4 && gq <= 4;
+    const bool moderate = fmt_is_int(c->format) ? 2 * quanta <= 7 * one_round
+                                                : units <= 8 && 2 * quanta >= 3 * one_round && 2 * quanta <= 5 * one_round;
+    if (light || moderate) return std::min(asked, one_round);
+  }
+  int splits = std::min(quanta, want);
+  // Two workgroups on a compute unit take nearly twice as long as one: one each, with fewer splits, if that leaves a
+  // unit fewer rounds of blocks and few units idle (64 units, 6K tokens: 3 rounds with 4 splits, 2 of 2 workgroups
+  // with 8, 15.6 / 17.6 us; 128 units with 8 heads per KV head, 3K: 18.9 / 20.0; 192 units, 1.5K, no split: 14.6 / 17.4).
+  if (units < 256 && fmt_is_int(c->format) && fmt_group(c->format) == kBlock) {
+    const int single = (int)(256 / units);
+    auto rounds = [&](int ns) { return (quanta + ns - 1) / ns * (int)((units * ns + 255) / 256); };
+    if (single < splits && rounds(single) < rounds(splits) && (single == 1 || units * single >= 224)) splits = single;
+  }
+  return splits;
+}
+
 }  // namespace
 
 extern "C" {
@@ -116,25 +166,12 @@ int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len) {
   const long units = (long)c->batch * group_workgroups(c);
   const int nb = (packed_len + kBlock - 1) / kBlock;
   const int quanta = (nb + 3) / 4;
-  const int gq = c->n_q_heads / c->n_kv_heads;
-  // Two rounds of blocks in one workgroup take no longer than one round in two and the merge behind it, and are one
-  // launch less (1K tokens, up to 4 heads per KV head: 8.5 -> 8.4 us with 8 units, 10.1 -> 8.8 with 128, issued one by
-  // one 10.2 -> 8.3; with more heads, or in groups of 64 and 32, the second round costs more than the merge).
-  if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 4 && quanta <= 2) return 1;
-  // Few units, hence many partials per output row: the merge then costs more than a second workgroup per compute
-  // unit gives, if the kernel's arithmetic leaves one the time (4-bit codes with up to 4 heads per KV head: any
-  // context; other integer codes up to 3.5 blocks per wave; MXFP4 around two).  A step, 8 units, 4 bits: 24.6K tokens
-  // 13.1 us with 48 splits, 12.1 with 32; 32K 13.2 / 12.6; 48K 17.5 (94 splits) / 14.7; 128K 28.9 / 27.9; 2 bits 32K 12.1 / 11.5
-  // but 128K 20.3 / 21.9; MXFP4 32K 16.3 / 15.6; 4 units, 128K 19.5 (128) / 18.6 (64); one unit, 128K 14.3 (256)
-  // / 13.0 (128).  From 17 units on the two are equal, and the groups of 64 and 32 want the waves.
-  if (fmt_group(c->format) == kBlock && units <= 16) {
-    const int one_round = units == 1 ? 128 : (int)(256 / units);
-    if (quanta <= one_round) return quanta;
-    const bool light = fmt_is_int(c->format) && fmt_bits(c->format) == 4 && gq <= 4;
-    const bool moderate = fmt_is_int(c->format) ? 2 * quanta <= 7 * one_round
-                                                : units <= 8 && 2 * quanta >= 3 * one_round && 2 * quanta <= 5 * one_round;
-    if (light || moderate) return one_round;
-  }
+  // Up to three workgroups per compute unit fit when no wave has more than one block (that kernel
+  // instance needs half the registers; groups of up to 8 heads, integer formats): then one block
+  // per wave beats two blocks for some waves and one for others.  Measured at 40K and 48K tokens.
+  if (c->format != BD_FMT_MXFP4 && fmt_group(c->format) == kBlock && c->n_q_heads / c->n_kv_heads <= 8 &&
+      (long)quanta * units <= 768)
+    return quanta;
   // With one workgroup per compute unit already, a single split needs no merge kernel at all; that beats
   // the better occupancy of two splits until the call is long enough to amortize the merge (measured at
   // 256 and 384 units: 30.0 against 32.4 us and 41.9 against 47.1 us at 4K tokens, 99.5 against 94.2 us at 16K).
@@ -145,24 +182,12 @@ int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len) {
   // per KV head, for 4-bit codes and for per-token K)
   const bool one_wg = fmt_group(c->format) == 32 && (fmt_bits(c->format) == 4 || fmt_kt(c->format)) && c->n_q_heads / c->n_kv_heads > 4;
   const long target = one_wg ? 256 : 512;
-  // (not more than one round of workgroups: the few of a second round run with most of the chip idle -- a step, 4 bits,
-  // 160 units at 6K tokens 31.3 us with 640 workgroups, 27.9 with 480, in pages 32.5 / 27.1; 192 units at 8K 46.9 with
-  // 576, 44.2 with 384, in pages 50.7 / 47.4 at up to 9K; 96 units at 3K 17.8 / 16.8 in pages, where one block per wave
-  // took 576)
-  int want = (int)(units < 256 ? target / units : (target + units - 1) / units);
+  int want = (int)((target + units - 1) / units);
   if (want < 1) want = 1;
   // (no rebalancing: quanta are dealt to the splits round robin, so a count that does not divide them
   // leaves a few workgroups one quantum short, which is faster than fewer workgroups of equal length)
-  int splits = quanta < want ? quanta : want;
-  // Two workgroups on a compute unit take nearly twice as long as one: one each, with fewer splits, if that leaves a
-  // unit fewer rounds of blocks and few units idle (64 units, 6K tokens: 3 rounds with 4 splits, 2 of 2 workgroups with 8, 15.6 / 17.6 us;
-  // 128 units with 8 heads per KV head, 3K: 18.9 / 20.0; 192 units, 1.5K, no split: 14.6 / 17.4).
-  if (units < 256 && fmt_is_int(c->format) && fmt_group(c->format) == kBlock) {
-    const int single = (int)(256 / units);
-    auto rounds = [&](int ns) { return (quanta + ns - 1) / ns * (int)((units * ns + 255) / 256); };
-    if (single < splits && rounds(single) < rounds(splits) && (single == 1 || units * single >= 224)) splits = single;
-  }
-  return splits;
+  const int splits = quanta < want ? quanta : want;
+  return splits < 1 ? 1 : splits;
 }
 
 size_t bd_workspace_bytes(const bd_cache* c, int32_t num_splits) {
@@ -243,22 +268,23 @@ bd_status bd_decode_attn(const bd_cache* c, const void* q, int32_t packed_len, i
   hipStream_t st = (hipStream_t)stream;
   float* part_o = ws_part_o(workspace);
   float* part_ml = ws_part_ml(c, workspace, num_splits);
+  const Splits ns = {out ? splits_to_run(c, packed_len, num_splits) : num_splits, num_splits};
   if (c->format == BD_FMT_MXFP4) {
     if (res_len != 0) return BD_ERR_INVALID_ARG;
-    s = hip_status(launch_decode_mx(c, q, packed_len, softmax_scale, num_splits, part_o, part_ml, nullptr, nullptr, out,
+    s = hip_status(launch_decode_mx(c, q, packed_len, softmax_scale, ns, part_o, part_ml, nullptr, nullptr, out,
                                     st));
   } else {
     if (packed_len % kBlock != 0 || res_len < 0 || res_len >= kBlock) return BD_ERR_INVALID_ARG;
     if (fmt_group(c->format) != kBlock)
-      s = hip_status(launch_decode_grp(c, q, packed_len, res_len, softmax_scale, num_splits, part_o, part_ml, nullptr,
+      s = hip_status(launch_decode_grp(c, q, packed_len, res_len, softmax_scale, ns, part_o, part_ml, nullptr,
                                        nullptr, out, st));
     else
-      s = hip_status(launch_decode_int(c, q, packed_len, res_len, softmax_scale, num_splits, part_o, part_ml,
+      s = hip_status(launch_decode_int(c, q, packed_len, res_len, softmax_scale, ns, part_o, part_ml,
                                        nullptr, nullptr, out, st));
   }
   if (s != BD_OK) return s;
   // (one split: the attention kernel has written `out` itself, there is nothing to merge)
-  if (out && num_splits > 1) s = hip_status(launch_combine(c, part_o, part_ml, num_splits, out, st));
+  if (out && ns.run > 1) s = hip_status(launch_combine(c, part_o, part_ml, ns.run, out, st));
   return s;
 }
 
@@ -312,10 +338,10 @@ static bd_status decode_step(const bd_cache* c, const void* k_new, const void* v
     }
     // one workgroup per split and KV head: the attention launch quantizes the token into the cache itself
     // (the workgroup that reads its block does, first thing)
-    if ((s = hip_status(launch_decode_mx(c, q, pl, softmax_scale, num_splits, part_o, part_ml, k_new, v_new, out,
-                                         st))) != BD_OK)
+    const Splits ns = {splits_to_run(c, pl + 1, num_splits), num_splits};
+    if ((s = hip_status(launch_decode_mx(c, q, pl, softmax_scale, ns, part_o, part_ml, k_new, v_new, out, st))) != BD_OK)
       return s;
-    if (num_splits > 1 && (s = hip_status(launch_combine(c, part_o, part_ml, num_splits, out, st))) != BD_OK) return s;
+    if (ns.run > 1 && (s = hip_status(launch_combine(c, part_o, part_ml, ns.run, out, st))) != BD_OK) return s;
     *packed_len = pl + 1;
     return BD_OK;
   }
@@ -334,12 +360,13 @@ static bd_status decode_step(const bd_cache* c, const void* k_new, const void* v
   // the residual block it packs the block as well (before attending it, or, lazy, after)
   const int flush = !fills ? 0 : lazy ? 2 : 1;
   const int att_pl = flush == 1 ? pl + kBlock : pl, att_r = flush == 1 ? 0 : r + 1;
-  s = hip_status(grp ? launch_decode_grp(c, q, att_pl, att_r, softmax_scale, num_splits, part_o, part_ml, k_new, v_new, out, st,
+  const Splits ns = {splits_to_run(c, att_pl, num_splits), num_splits};
+  s = hip_status(grp ? launch_decode_grp(c, q, att_pl, att_r, softmax_scale, ns, part_o, part_ml, k_new, v_new, out, st,
                                          flush)
-                     : launch_decode_int(c, q, att_pl, att_r, softmax_scale, num_splits, part_o, part_ml, k_new, v_new, out, st,
+                     : launch_decode_int(c, q, att_pl, att_r, softmax_scale, ns, part_o, part_ml, k_new, v_new, out, st,
                                          flush));
   if (s != BD_OK) return s;
-  if (num_splits > 1 && (s = hip_status(launch_combine(c, part_o, part_ml, num_splits, out, st))) != BD_OK) return s;
+  if (ns.run > 1 && (s = hip_status(launch_combine(c, part_o, part_ml, ns.run, out, st))) != BD_OK) return s;
   *packed_len = fills ? pl + kBlock : pl;
   *res_len = fills ? 0 : r + 1;
   return BD_OK;
@@ -463,18 +490,19 @@ static bd_status paged_attention(const bd_paged_cache* c, const void* q, float s
   float* part_ml = ws_part_ml(&shape, workspace, num_splits);
   // one split: the attention kernel writes `out` itself and no merge runs (a fused step then raises the
   // lengths with the small kernel of bd_paged_append_kv instead of in the merge)
-  void* direct = num_splits == 1 ? out : nullptr;
+  const Splits ns = {splits_to_run(&shape, -1, num_splits), num_splits};
+  void* direct = ns.run == 1 ? out : nullptr;
   bd_status s = hip_status(c->format == BD_FMT_MXFP4
-                               ? launch_decode_mx_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
+                               ? launch_decode_mx_paged(c, q, softmax_scale, ns, part_o, part_ml, step, k_new, v_new,
                                                         direct, st)
                            : fmt_group(c->format) != kBlock
-                               ? launch_decode_grp_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
+                               ? launch_decode_grp_paged(c, q, softmax_scale, ns, part_o, part_ml, step, k_new, v_new,
                                                          direct, st, lazy)
-                               : launch_decode_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
+                               : launch_decode_paged(c, q, softmax_scale, ns, part_o, part_ml, step, k_new, v_new,
                                                      direct, st, lazy));
   if (s != BD_OK) return s;
   if (direct) return step ? hip_status(launch_paged_bump(c, st)) : BD_OK;
-  return hip_status(launch_combine(&shape, part_o, part_ml, num_splits, out, st, step ? c : nullptr));
+  return hip_status(launch_combine(&shape, part_o, part_ml, ns.run, out, st, step ? c : nullptr));
 }
 
 bd_status bd_paged_decode_attn(const bd_paged_cache* c, const void* q, float softmax_scale, int32_t num_splits,

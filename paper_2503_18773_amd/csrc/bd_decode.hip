@@ -96,6 +96,7 @@ struct DecodeArgs {
   int nbcap;
   int res_len;
   int num_splits;
+  int held_splits;  // partials of the workspace, the ones past num_splits left empty
   float scale_log2; // softmax_scale * log2(e)
   // paged cache: block n of sequence b is page block_table[b][n], pool index page * Hkv + head;
   // nb and res_len then come from seq_lens[b]
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   for (int mt = 0; mt < 8; ++mt) oacc[mt] = (f4_t){0.f, 0.f, 0.f, 0.f};
 
   // A wave keeps little in flight: the keys of its next block are requested when the current
-  // block is done, the values of a block when its keys are about to be consumed.  The eight
+  // block is done (kEarly: when its keys are consumed), the values of a block when its keys are about to be consumed.  The eight
   // waves of a compute unit share one in-order memory pipeline, so whatever one wave requests
   // early only delays what the others are waiting for: 8 KB per wave (16 MB over the chip) keeps
   // HBM busy, and a shorter queue shortens the ramp at both ends of the kernel.
@@ -567,10 +568,10 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     }
     return ek;
   };
-  // Groups of up to 8 heads: the high piece of Q' goes to the even column groups and the low piece to
+  // Groups of 5 .. 8 heads: the high piece of Q' goes to the even column groups and the low piece to
   // the odd ones, so one MFMA per k-step produces both partial products (added across the column
   // groups afterwards); groups of 9..16 have no columns to spare and run two MFMAs per k-step.
-  constexpr bool kSplitCols = COPIES >= 2;
+  constexpr bool kSplitCols = COPIES == 2;
   h8_t bqh[4], bql[4];
   i8_t bq8;   // groups of up to 4 heads: piece cg of Q'
   const int sb_q = 127 - 5 * cg;              // its block scale
@@ -950,13 +951,13 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       }
       const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * a.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
-      if (a.out) {   // one split: row == the output row
-        store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);
-      } else {
+      if (a.out) store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);   // one split: row == the output row
+      if (!a.out || a.held_splits > 1) {
         *reinterpret_cast<float2*>(a.part_o + row * kD + c0) = o;
         if ((tid & 63) == 0) {
           a.part_ml[row * 2] = M;
           a.part_ml[row * 2 + 1] = L;
+          empty_partials(a.part_ml, row, (size_t)gridDim.z * a.n_q_heads, split, a.num_splits, a.held_splits);
         }
       }
     }
@@ -1018,7 +1019,7 @@ __global__ __launch_bounds__(128 * G) void combine_kernel(const float* __restric
       const float fo = live ? __builtin_amdgcn_exp2f(M - Mn) : 1.0f;
       const float fn = live ? __builtin_amdgcn_exp2f(ml[i].x - Mn) : 0.0f;
       L = L * fo + fn * ml[i].y;
-      o = o * fo + fn * ov[i];
+      o = o * fo + fn * (live ? ov[i] : 0.0f);   // (the row of an empty partial may hold anything)
       M = Mn;
     }
   }
@@ -1080,8 +1081,9 @@ void launch_instance(int format, int gq, bool single, bool paged, const DecodeAr
 }  // namespace
 
 hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, int res_len, float softmax_scale,
-                             int num_splits, float* part_o, float* part_ml, const void* k_new, const void* v_new,
+                             Splits ns, float* part_o, float* part_ml, const void* k_new, const void* v_new,
                              void* out, hipStream_t st, int flush) {
+  const int num_splits = ns.run;
   DecodeArgs a;
   a.out = num_splits == 1 ? out : nullptr;
   a.out_kind = out_kind(c->format, c->out_type);
@@ -1108,6 +1110,7 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   a.nbcap = c->capacity / kBlock;
   a.res_len = res_len;
   a.num_splits = num_splits;
+  a.held_splits = ns.held;
   a.scale_log2 = softmax_scale * kLog2e;
   a.block_table = nullptr;
   a.seq_lens = nullptr;
@@ -1120,9 +1123,10 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   return hipGetLastError();
 }
 
-hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
+hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float softmax_scale, Splits ns,
                                float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
                                void* out, hipStream_t st, bool lazy) {
+  const int num_splits = ns.run;
   DecodeArgs a;
   a.step = step ? 1 : 0;
   a.out = num_splits == 1 ? out : nullptr;
@@ -1148,6 +1152,7 @@ hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float sof
   a.gq = c->n_q_heads / c->n_kv_heads;
   a.nb = a.nbcap = a.res_len = 0;   // per sequence, from seq_lens
   a.num_splits = num_splits;
+  a.held_splits = ns.held;
   a.scale_log2 = softmax_scale * kLog2e;
   a.block_table = c->block_table;
   a.seq_lens = c->seq_lens;

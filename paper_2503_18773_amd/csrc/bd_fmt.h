@@ -29,10 +29,6 @@ struct Fmt<4> {
   // half: tile_lo(jj) fills the low fp16 half of the P' registers, tile_hi(jj) the high one
   __device__ static constexpr int tile_lo(int jj) { return 2 * jj; }
   __device__ static constexpr int tile_hi(int jj) { return 2 * jj + 1; }
-  // groups of up to 4 heads (column group c/4 keeps tiles c/4 and 4 + c/4): kPairShift brings the
-  // column group whose tile fills the high half of a P' register next to the one that fills the
-  // low half; kStepShift brings the second k-step of a pair to columns 0..3
-  static constexpr int kPairShift = kRowShl4, kStepShift = kRowShl8;
   // position of block token t in the k-ordered P' / V operand: lane group t/32, then k-step j,
   // register r, half -- tile T = (t%32)/4 feeds k-step T/2, half T%2
   __device__ static int p_slot(int t) {
@@ -62,7 +58,6 @@ struct Fmt<2> {
   __device__ static constexpr float inv_un(int v) { return (float)(1 << (2 * v)); }
   __device__ static constexpr int tile_lo(int jj) { return jj; }
   __device__ static constexpr int tile_hi(int jj) { return jj + 2; }
-  static constexpr int kPairShift = kRowShl8, kStepShift = kRowShl4;
   // tile T = (t%32)/4 feeds k-step 2*(T/4) + T%2, half (T%4)/2
   __device__ static int p_slot(int t) {
     const int T = (t & 31) >> 2, r = t & 3;
