@@ -20,16 +20,22 @@
 //
 // Query groups of up to 4 heads run both products on v_mfma_scale_f32_16x16x128_f8f6f4 instead: one instruction
 // contracts all 128 channels (tokens) of a 16-row tile, with the codes as e4m3 / e2m1 numbers (masking again, bd_fmt.h)
-// and Q' and P' as sums of e4m3 pieces, 2^-5 apart: piece k of head h in column 4k + h.  So the 16 columns hold four
-// pieces of four heads, a tile costs one matrix instruction of 32 cycles instead of four of 16, and 3 instead of
-// 5 (8) mask instructions per word of 4-bit (2-bit) codes.  The pieces' partial scores are added over the column
-// groups with DPP moves, column group c keeping tiles c and 4 + c (8 values per lane per block, every lane doing
-// useful work); the pieces of the weights are exchanged between the column groups likewise, and the column groups'
-// partial O^T are added once, after the loop.  Every product of codes and pieces is exact, and the pieces hold more
-// than the fp16 operands they replace: relative L2 of fp32 outputs 1.7e-4 .. 2.4e-4 before, 1e-6 .. 3e-6 (4 bits) and
-// 1.0e-5 .. 1.6e-5 (2 bits) now, at 128 .. 5120 tokens.  What bounds these instances after that is memory, the 2-bit
-// one's 33.5 -> 29.3 us at 8 x 32K tokens (152 MB), the 4-bit one's 26.2 -> 25.7 us at 128K (143 MB).  Groups of 5 .. 16
-// heads have no columns to spare for the pieces and stay on fp16.
+// and Q' and P' as sums of e4m3 pieces, 2^-5 apart: piece k of head h in column 4 (k % 4) + h.  So the 16 columns hold
+// four pieces of four heads; P' takes one matrix instruction of 32 cycles a tile, Q' two (its pieces 4 .. 6 are the
+// second's), against four of 16, and the codes 3 instead of 5 (8) mask instructions per word of 4-bit (2-bit) codes.
+// The pieces' partial scores are added over the column groups with DPP moves, column group c keeping tiles c and 4 + c (8
+// values per lane per block, every lane doing useful work); the pieces of the weights are exchanged between the column
+// groups likewise, and the column groups' partial O^T are added once, after the loop.  Every product of codes and
+// pieces is exact, and the instruction adds to its accumulator as fp32 does (measured: 1e-7 of the larger of the two).
+//
+// Seven pieces of Q' reach 40 (42, 2 bits) bits below its bound max|q| * max scale, 34 below its own leading bit: they
+// hold the 22-bit product q * scale whole wherever the fp16 high + low pair of the larger groups does (whose low piece
+// ends 39 bits below that bound).  Four, one instruction, end after 25 (27), which costs |Q'| far below the bound their
+// bits: with an outlier channel in q that is not K's, a relative L2 error of 5e-5 (x 30), 2.5e-4 (x 100) and 5e-3
+// (x 1000) against 8e-7, 1.5e-6 and 4e-6 with seven.  The three cost 0.3 .. 2 us a step (4 bits, 32K tokens 12.4 -> 12.7
+// us, 24 ragged sequences of up to 5K 28.4 -> 29.5; 2 bits, 8 x 32K 30.8 -> 32.7).
+// fp32 outputs are 4e-7 .. 5e-7 (4 bits) and 1.3e-5 (2 bits) off at 4096 tokens, with fp16 weights 1.8e-4 .. 2.2e-4.
+// Groups of 5 .. 16 heads have no columns to spare for the pieces and stay on fp16.
 //
 // Groups of 5 .. 16 heads carry the heads twice or once over the 16 columns (column c holds head c % GQP).
 //
@@ -40,8 +46,8 @@
 //     9 per 16 int2 codes; the power-of-two factors are folded into Q' / P'.
 //   * K is quantized per channel, so  S = sum_c (Q_c s_c) code_c + sum_c Q_c z_c : the query is
 //     rescaled once per 128-token block and the zero term is one scalar per head and block.
-//     Q' = Q*s is carried as an fp16 high + low pair (two MFMAs on the same A operand), which
-//     keeps ~22 bits: a single fp16 Q' is not enough when a channel holds outliers.
+//     Q' = Q*s, 22 bits, is carried whole, as an fp16 high + low pair (two MFMAs on the same A
+//     operand) or in e4m3 pieces: a single fp16 Q' is not enough when a channel holds outliers.
 //   * V is quantized per token, so  O = sum_t (P_t s_t) code_t + sum_t P_t z_t.
 //   * Raw codes are offset by the token's zero-point, so sum_t P'_t code_t and sum_t P_t z_t are
 //     two large numbers that nearly cancel; the fp16 rounding of P' and the last bits of two
@@ -127,11 +133,14 @@ struct WaveLds {
   uint16_t c16[kBlock];    // per V token: centre code * position factor, in the A-operand order of P'
   float zq[GQP];           // per head: sum_c Q_c z_c * 2^-24 (Q as normalised below)
 };
-// Groups of up to 4 heads: Q' as four e4m3 pieces, the B operand of one f8f6f4 instruction per tile, as its lanes
-// read it: [register half][lane group][column = 4 * piece + head][register].
+// Groups of up to 4 heads: Q' as seven e4m3 pieces, the B operands of two f8f6f4 instructions per tile (pieces 0 .. 3,
+// pieces 4 .. 6 and zeros), as their lanes read them: [instruction][register half][lane group][column = 4 * (piece % 4) +
+// head][register].  (Four columns of padding: the lanes that prepare eight consecutive channels of a head write to eight
+// (half, lane group) rows at once, which then spread over the banks.)
+constexpr int kQueryPieces = 7;
 template <>
 struct WaveLds<4> {
-  uint32_t qp[2][4][16][4];
+  uint32_t qp[2][2][4][20][4];
   float4 vpar[kParSlots];
   float2 kpar[kParSlots];  // per-token K only: (scale, zero)
   uint32_t c8[4][8];       // per V token: centre code as e4m3, in B-operand order ([lane group][register])
@@ -488,7 +497,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) nrm[i] = f * F::un(i);
     }
-    if constexpr (kF8) {   // four e4m3 pieces of Q' in units of 2^ek, 2^(ek - 5), ..: 20 bits and more
+    if constexpr (kF8) {   // e4m3 pieces of Q' in units of 2^ek, 2^(ek - 5), ..
       float t[8], zsum = 0.0f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -505,17 +514,17 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       zsum = row_sum16(zsum);
       const int h = lane >> 4;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < kQueryPieces; ++k) {
         const float unit = pow2i(ek - 5 * k);
         uint32_t ev = 0, od = 0;   // channels 0, 2, 4, 6 / 1, 3, 5, 7 of the lane's eight
-        if (k < 3) {
+        if (k < kQueryPieces - 1) {
           ev = e4m3_piece<true>(e4m3_piece<false>(ev, t[0], t[2], unit), t[4], t[6], unit);
           od = e4m3_piece<true>(e4m3_piece<false>(od, t[1], t[3], unit), t[5], t[7], unit);
         } else {
           ev = e4m3_last<true>(e4m3_last<false>(ev, t[0], t[2], unit), t[4], t[6], unit);
           od = e4m3_last<true>(e4m3_last<false>(od, t[1], t[3], unit), t[5], t[7], unit);
         }
-        uint32_t* dst = wl.qp[E::b_half(run0)][E::b_group(run0)][4 * k + h];
+        uint32_t* dst = wl.qp[k >> 2][E::b_half(run0)][E::b_group(run0)][4 * (k & 3) + h];
         dst[E::b_reg(run0)] = ev;
         dst[E::b_reg(run0 + 1)] = od;
       }
@@ -524,47 +533,40 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     }
     if constexpr (!kF8) {
 #pragma unroll
-    for (int p = 0; p < HP; ++p) {
-      const int ph = 4 * p + (lane >> 4);
-      f4_t qa, qb;
-      if constexpr (HP == 1) {
-        qa = (f4_t){qv[0][0], qv[0][1], qv[0][2], qv[0][3]};
-        qb = (f4_t){qv[1][0], qv[1][1], qv[1][2], qv[1][3]};
-      } else {
-        qa = *reinterpret_cast<const f4_t*>(&q_s[ph][run0]);
-        qb = *reinterpret_cast<const f4_t*>(&q_s[ph][run1]);
-      }
-      float zsum = 0.0f;
-      h2_t qh[4], ql[4];   // register i: entries 2i (run 0) and 2i + 1 (run 1)
+      for (int p = 0; p < HP; ++p) {
+        const int ph = 4 * p + (lane >> 4);
+        const f4_t qa = *reinterpret_cast<const f4_t*>(&q_s[ph][run0]), qb = *reinterpret_cast<const f4_t*>(&q_s[ph][run1]);
+        float zsum = 0.0f;
+        h2_t qh[4], ql[4];   // register i: entries 2i (run 0) and 2i + 1 (run 1)
 #pragma unroll
-      for (int run = 0; run < 2; ++run)
+        for (int run = 0; run < 2; ++run)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float qc = run ? qb[i] : qa[i];
-          float t = qc;   // per-token K: Q' = Q, and the "zero term" is sum_c Q_c
-          float z = 1.0f;
-          if constexpr (!KT) {
-            const h2_t pr = __builtin_bit_cast(h2_t, run ? kp1[i] : kp0[i]);   // (scale, zero)
-            t = qc * (float)pr[0];   // exact: 11 bits times 11 bits
-            z = (float)pr[1];
+          for (int i = 0; i < 4; ++i) {
+            const float qc = run ? qb[i] : qa[i];
+            float t = qc;   // per-token K: Q' = Q, and the "zero term" is sum_c Q_c
+            float z = 1.0f;
+            if constexpr (!KT) {
+              const h2_t pr = __builtin_bit_cast(h2_t, run ? kp1[i] : kp0[i]);   // (scale, zero)
+              t = qc * (float)pr[0];   // exact: 11 bits times 11 bits
+              z = (float)pr[1];
+            }
+            // high piece, and the rest in one rounding: fma(t, nrm, -high)
+            const _Float16 hi = (_Float16)(t * nrm[i]);
+            qh[i][run] = hi;
+            ql[i][run] = (_Float16)__builtin_fmaf(t, nrm[i], -(float)hi);
+            zsum = __builtin_fmaf(qc, z, zsum);
           }
-          // high piece, and the rest in one rounding: fma(t, nrm, -high)
-          const _Float16 hi = (_Float16)(t * nrm[i]);
-          qh[i][run] = hi;
-          ql[i][run] = (_Float16)__builtin_fmaf(t, nrm[i], -(float)hi);
-          zsum = __builtin_fmaf(qc, z, zsum);
-        }
-      zsum = row_sum16(zsum);
-      u4_t phi, plo;
+        zsum = row_sum16(zsum);
+        u4_t phi, plo;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        phi[v] = __builtin_bit_cast(uint32_t, qh[v]);
-        plo[v] = __builtin_bit_cast(uint32_t, ql[v]);
+        for (int v = 0; v < 4; ++v) {
+          phi[v] = __builtin_bit_cast(uint32_t, qh[v]);
+          plo[v] = __builtin_bit_cast(uint32_t, ql[v]);
+        }
+        *reinterpret_cast<u4_t*>(&wl.qhi[ph][8 * prep_sg]) = phi;
+        *reinterpret_cast<u4_t*>(&wl.qlo[ph][8 * prep_sg]) = plo;
+        if (prep_sg == 0) wl.zq[ph] = zsum;
       }
-      *reinterpret_cast<u4_t*>(&wl.qhi[ph][8 * prep_sg]) = phi;
-      *reinterpret_cast<u4_t*>(&wl.qlo[ph][8 * prep_sg]) = plo;
-      if (prep_sg == 0) wl.zq[ph] = zsum;
-    }
     }
     return ek;
   };
@@ -573,16 +575,14 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   // groups afterwards); groups of 9..16 have no columns to spare and run two MFMAs per k-step.
   constexpr bool kSplitCols = COPIES == 2;
   h8_t bqh[4], bql[4];
-  i8_t bq8;   // groups of up to 4 heads: piece cg of Q'
-  const int sb_q = 127 - 5 * cg;              // its block scale
+  i8_t bq8[2];   // groups of up to 4 heads: pieces cg and 4 + cg of Q'
+  const int sb_q = 127 - 5 * cg;              // block scale of the first, 2^-20 of it that of the second
   const int sb_p = 127 - E::kTop - 5 * cg;    // that of piece cg of P'
   auto load_bq = [&](int j) {
     if constexpr (kF8) {
-      if (j < 2) {
-        const u4_t x = *reinterpret_cast<const u4_t*>(wl.qp[j][g][col]);
+      const u4_t x = *reinterpret_cast<const u4_t*>(wl.qp[j >> 1][j & 1][g][col]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) bq8[4 * j + i] = (int)x[i];
-      }
+      for (int i = 0; i < 4; ++i) bq8[j >> 1][4 * (j & 1) + i] = (int)x[i];
     } else if constexpr (kSplitCols) {
       bqh[j] = *reinterpret_cast<const h8_t*>(cg & 1 ? &wl.qlo[head][8 * (4 * g + j)] : &wl.qhi[head][8 * (4 * g + j)]);
     } else {
@@ -590,6 +590,8 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       bql[j] = *reinterpret_cast<const h8_t*>(&wl.qlo[head][8 * (4 * g + j)]);
     }
   };
+  if constexpr (kF8)   // the columns of the eighth piece stay zero
+    *reinterpret_cast<u2_t*>(&wl.qp[1][lane >> 5][(lane >> 3) & 3][12 + ((lane & 7) >> 1)][2 * (lane & 1)]) = (u2_t){0u, 0u};
   float zq = 0.0f, qsum = 0.0f;
   if constexpr (KT) {
     (void)prep_queries();
@@ -676,8 +678,9 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       for (int tt = 0; tt < 4; ++tt) {
         f4_t acc = {0.f, 0.f, 0.f, 0.f};   // (the zero term, one number per head, joins in the softmax)
         if constexpr (kF8) {
-          acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(E::a_operand(kraw[4 * half + tt].w), bq8, acc, E::kFormatA, 0,
-                                                                 0, E::kScaleA, 0, sb_q);
+          const i8_t ak = E::a_operand(kraw[4 * half + tt].w);
+          acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ak, bq8[1], acc, E::kFormatA, 0, 0, E::kScaleA, 0, sb_q - 20);
+          acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ak, bq8[0], acc, E::kFormatA, 0, 0, E::kScaleA, 0, sb_q);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {

@@ -183,3 +183,42 @@ def test_partials_stay_those_asked_for_when_fewer_splits_run(fmt, gq, L, asked):
     # (fp32 sums in another order; the second comparison also has weights rounded against other running maxima)
     assert torch.allclose(merged, out, rtol=1e-5, atol=1e-6)
     assert (split - out).norm() <= 5e-4 * out.norm().clamp(min=1e-30)
+
+
+def _caches_of(K, V, fmt, gq):
+    """Oracle cache and GPU cache of one sequence, K and V [1, H, L, 128] fp16."""
+    H, cap = K.shape[1], (K.shape[2] // 128 + 1) * 128
+    oc = O.IntCache(1, H, BITS[fmt], cap, k_per_token="_kt" in fmt, group=GROUP.get(fmt, 128))
+    oc.quant_pack_kv(K, V)
+    gc = B.KVCache(1, gq * H, H, fmt, cap)
+    gc.quant_pack_kv(to_dev(K, "fp16"), to_dev(V, "fp16"))
+    return oc, gc
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int2", "int4_kt", "int2_kt"])
+@pytest.mark.parametrize("factor", [30, 100, 1000])
+def test_outlier_queries_keep_their_bits(fmt, factor):
+    """Query groups of up to 4 heads, an outlier channel in q that is not K's: every Q' = q * scale then lies far below
+    max|q| * max scale, and all of it still has to be there.  The bar: a score goes through about eight fp32 roundings
+    (up to 2^-23 each where the matrix unit truncates) of at most M, the largest sum of magnitudes in log2 units,
+    i.e. 8 * 2^-23 * M in the exponent, ln 2 times that in a weight and twice that in numerator and denominator
+    together (12 * 2^-23 * M); and a weight holds 2^-20 (2^-15, 2-bit codes) of itself."""
+    from paper_2503_18773_amd.workloads import softmax_scale
+    scale = softmax_scale(W.CONFIGS["cfg1"])
+    for gq in (1, 4):
+        for seed in range(3):
+            rng = np.random.default_rng(800 + seed)
+            q = rng.standard_normal((1, 2 * gq, 128))
+            K, V = (rng.standard_normal((1, 2, 4096, 128)) for _ in range(2))
+            q[..., 7 + seed] *= factor
+            K[..., 70 + seed] *= factor
+            if factor > 10:
+                q[..., 70 + seed] /= factor   # (both at once would leave one token with all the weight)
+            q, K, V = (x.astype(np.float16) for x in (q, K, V))
+            oc, gc = _caches_of(K, V, fmt, gq)
+            w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=2 * gq, n_kv_heads=2, context=4096, fmt=fmt)
+            qa, ka = np.abs(q.astype(np.float64)).reshape(2, gq, 128), np.abs(K.astype(np.float64))[0]
+            M = scale * 1.4427 * max((qa[h] @ ka[h].T).max() for h in range(2))
+            bar = 12 * 2.0 ** -23 * M + (2.0 ** -15 if fmt.startswith("int2") else 2.0 ** -20)
+            ma, rl = attn_errors(_attend_f32(gc, w, q, 1), O.decode_attn(oc, q, scale))
+            assert rl <= bar, f"{fmt} gq={gq} seed {seed}: rel-L2 {rl:.2e} against {bar:.2e} (M {M:.3g})"
