@@ -34,7 +34,7 @@
 // bits: with an outlier channel in q that is not K's, a relative L2 error of 5e-5 (x 30), 2.5e-4 (x 100) and 5e-3
 // (x 1000) against 8e-7, 1.5e-6 and 4e-6 with seven.  The three cost 0.3 .. 2 us a step (4 bits, 32K tokens 12.4 -> 12.7
 // us, 24 ragged sequences of up to 5K 28.4 -> 29.5; 2 bits, 8 x 32K 30.8 -> 32.7).
-// fp32 outputs are 4e-7 .. 5e-7 (4 bits) and 1.3e-5 (2 bits) off at 4096 tokens, with fp16 weights 1.8e-4 .. 2.2e-4.
+// fp32 outputs are 4e-7 .. 5e-7 off at 4096 tokens, with fp16 weights 1.8e-4 .. 2.2e-4.
 // Groups of 5 .. 16 heads have no columns to spare for the pieces and stay on fp16.
 //
 // Groups of 5 .. 16 heads carry the heads twice or once over the 16 columns (column c holds head c % GQP).
@@ -792,8 +792,8 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
         uint32_t u[4] = {0u, 0u, 0u, 0u}, from[4];
         float unit = 1.0f / (1 << E::kTop);
 #pragma unroll
-        for (int k = 0; k < E::kWeightPieces; ++k) {
-          if (k < E::kWeightPieces - 1)
+        for (int k = 0; k < kWeightPieces; ++k) {
+          if (k < kWeightPieces - 1)
             u[k] = e4m3_piece<true>(e4m3_piece<false>(u[k], e[0], e[2], unit), e[1], e[3], unit);
           else
             u[k] = e4m3_last<true>(e4m3_last<false>(u[k], e[0], e[2], unit), e[1], e[3], unit);

@@ -100,11 +100,10 @@ def test_prompt_tails_go_to_the_residual(fmt, L):
 def test_small_query_groups_hold_the_precision_of_their_pieces(fmt, gq):
     """Query groups of up to 4 heads run both products on 8-bit matrix operands, queries and weights as sums of
     e4m3 pieces whose products add up exactly: one block, fewer blocks than waves, several rounds of blocks, and
-    enough rounds (17 a wave) to fold the centre sum.  Weights hold 14 bits with three pieces (2-bit codes), 19
-    with four, queries 19: a relative error of 2^-15 (2^-20) per weight, independent from token to token like the
-    values themselves, and for the scores 2^-20 of a sum of magnitudes of at most some tens (1e-5 in the
-    exponent)."""
-    bar = 2.0 ** -15 + 1e-5 if fmt.startswith("int2") else 2.0 ** -20 + 1e-5
+    enough rounds (17 a wave) to fold the centre sum.  Weights hold 19 bits, a relative error of 2^-20 each, and
+    queries all of theirs; the scores' fp32 roundings (about eight of 2^-23) are of a sum of magnitudes of at most some
+    tens in log2 units, up to 1e-5 in the exponent."""
+    bar = 2.0 ** -20 + 1e-5
     for L, ns in [(128, 1), (128 * 3 + 1, 1), (128 * 5, 2), (128 * 4 * 17 + 130, 1)]:
         w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=2 * gq, n_kv_heads=2, context=L, fmt=fmt, seed=700 + L + gq)
         K, V, oc, gc = _int_cache_pair(w, (L // 128 + 1) * 128)
@@ -202,9 +201,8 @@ def test_outlier_queries_keep_their_bits(fmt, factor):
     max|q| * max scale, and all of it still has to be there.  The bar: a score goes through about eight fp32 roundings
     (up to 2^-23 each where the matrix unit truncates) of at most M, the largest sum of magnitudes in log2 units,
     i.e. 8 * 2^-23 * M in the exponent, ln 2 times that in a weight and twice that in numerator and denominator
-    together (12 * 2^-23 * M); and a weight holds 2^-20 (2^-15, 2-bit codes) of itself."""
-    from paper_2503_18773_amd.workloads import softmax_scale
-    scale = softmax_scale(W.CONFIGS["cfg1"])
+    together (12 * 2^-23 * M); and a weight is held to 2^-20 of itself."""
+    scale = W.softmax_scale(W.CONFIGS["cfg1"])
     for gq in (1, 4):
         for seed in range(3):
             rng = np.random.default_rng(800 + seed)
@@ -212,13 +210,36 @@ def test_outlier_queries_keep_their_bits(fmt, factor):
             K, V = (rng.standard_normal((1, 2, 4096, 128)) for _ in range(2))
             q[..., 7 + seed] *= factor
             K[..., 70 + seed] *= factor
-            if factor > 10:
-                q[..., 70 + seed] /= factor   # (both at once would leave one token with all the weight)
+            q[..., 70 + seed] /= factor   # (both at once would leave one token with all the weight)
             q, K, V = (x.astype(np.float16) for x in (q, K, V))
             oc, gc = _caches_of(K, V, fmt, gq)
             w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=2 * gq, n_kv_heads=2, context=4096, fmt=fmt)
             qa, ka = np.abs(q.astype(np.float64)).reshape(2, gq, 128), np.abs(K.astype(np.float64))[0]
             M = scale * 1.4427 * max((qa[h] @ ka[h].T).max() for h in range(2))
-            bar = 12 * 2.0 ** -23 * M + (2.0 ** -15 if fmt.startswith("int2") else 2.0 ** -20)
+            bar = 12 * 2.0 ** -23 * M + 2.0 ** -20
             ma, rl = attn_errors(_attend_f32(gc, w, q, 1), O.decode_attn(oc, q, scale))
             assert rl <= bar, f"{fmt} gq={gq} seed {seed}: rel-L2 {rl:.2e} against {bar:.2e} (M {M:.3g})"
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int2", "int4_kt", "int2_kt"])
+@pytest.mark.parametrize("x", [8, 13, 18, 23.5])
+def test_a_long_tail_behind_one_dominating_token_is_kept(fmt, x):
+    """6144 tokens that weigh about 2^-x of one other, their values alike: what rounding takes from each weight adds up.
+    Up to 4 heads per KV head hold 19 bits of a weight, or 2^-25 of the largest where that is more: at most
+    2^-20 + 6144 * 2^-26 * 2^-x' of the result, x' = 0 where the step is the limit (no more than the tail itself, 6144 *
+    2^-x); and the scores' fp32 roundings (about eight, 2^-23 of up to x + 1 in log2 units, as above)."""
+    scale = W.softmax_scale(W.CONFIGS["cfg1"])
+    rng = np.random.default_rng(900)
+    L, gq = 6144, 4
+    d = rng.standard_normal(128)
+    d /= np.linalg.norm(d)
+    q = np.broadcast_to(16 * d, (1, 2 * gq, 128)).astype(np.float16)
+    K = 0.02 * rng.standard_normal((1, 2, L, 128))
+    K[:, :, 0] += d * (x * np.log(2) / (16 * scale))
+    V = 0.3 * rng.standard_normal((1, 2, L, 128)) + np.where(np.arange(128) % 2, 1.5, -1.5)
+    V[:, :, 0] = rng.standard_normal((2, 128))
+    oc, gc = _caches_of(K.astype(np.float16), V.astype(np.float16), fmt, gq)
+    w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=2 * gq, n_kv_heads=2, context=L, fmt=fmt)
+    ma, rl = attn_errors(_attend_f32(gc, w, q, 1), O.decode_attn(oc, q, scale))
+    bar = 12 * 2.0 ** -23 * (x + 1) + 2.0 ** -20 + min(L * 2.0 ** -26, 2.0 ** -3 * L * 2.0 ** -x)
+    assert rl <= bar, f"{fmt} 2^-{x}: rel-L2 {rl:.2e} against {bar:.2e}"
