@@ -6,8 +6,8 @@
 // scores (tokens 4g .. 4g + 3 of a tile in lane group g) is the B-operand layout of the second product, so nothing
 // passes between lanes or waves.  Wave w takes channels 32w .. 32w + 31; a lane loads the channel pair
 // 32w + 2 (lane % 16) of a token, and the halves of the loaded words are two A tiles (row i of tile u: channel
-// 32w + 2i + u).  Weights are fp32 up to the product, which takes them as an fp16 high + low pair (22 bits) of
-// p * 2^14: the low piece is clear of the subnormals for every weight above 2^-27.
+// 32w + 2i + u).  Weights are fp32 up to the product, which takes all 24 bits of p * 2^14 as three fp16 pieces: the last
+// is clear of the subnormals' step for every weight above 2^-15, and what a smaller one loses is below 2^-39.
 //
 // The rows are requested when the kernel starts, ahead of the first packed block, and attended while that block is
 // on its way: an idle wave's time.  What bounds a slice is latency: folding its tokens in one by one at the end of
@@ -96,7 +96,7 @@ struct ResidualSlice {
         o[1] *= alpha;
       }
       m = mx;
-      h8_t ph = {}, pl = {};
+      h8_t ph = {}, pm = {}, pl = {};
       u4_t a0 = {0u, 0u, 0u, 0u}, a1 = a0;
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -106,7 +106,9 @@ struct ResidualSlice {
           const float p = __builtin_amdgcn_exp2f(s[u][r] - m);
           l += p;
           ph[4 * u + r] = (_Float16)(p * kResTop);
-          pl[4 * u + r] = (_Float16)__builtin_fmaf(p, kResTop, -(float)ph[4 * u + r]);
+          const float rest = __builtin_fmaf(p, kResTop, -(float)ph[4 * u + r]);
+          pm[4 * u + r] = (_Float16)rest;
+          pl[4 * u + r] = (_Float16)(rest - (float)pm[4 * u + r]);
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -115,10 +117,11 @@ struct ResidualSlice {
         }
       }
       const h8_t v0 = __builtin_bit_cast(h8_t, a0), v1 = __builtin_bit_cast(h8_t, a1);
-      o[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v0, ph, o[0], 0, 0, 0);
-      o[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v1, ph, o[1], 0, 0, 0);
-      o[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v0, pl, o[0], 0, 0, 0);
-      o[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v1, pl, o[1], 0, 0, 0);
+#pragma unroll
+      for (const h8_t& piece : {pl, pm, ph}) {
+        o[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v0, piece, o[0], 0, 0, 0);
+        o[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v1, piece, o[1], 0, 0, 0);
+      }
     }
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);

@@ -25,7 +25,7 @@ def _attend_f32(gc, w, q, num_splits):
 def test_residual_slices_of_every_remainder(fmt, gq):
     """Nothing but residual tokens, 1 .. 127 of them, in one slice and in several: the slice ends on and beside
     the steps of the second product (4 tokens a load, 32 a k-step).  Scores and weights are fp32 (weights enter
-    the product with 22 bits), so the bar is fp32's: a score is a sum of 128 products whose magnitudes add up to
+    the product whole), so the bar is fp32's: a score is a sum of 128 products whose magnitudes add up to
     about 1e2, which the matrix unit rounds (truncating) at 2^-23 of its size, i.e. 1e-5 in the exponent; the
     result's relative L2 error is at most that."""
     for L in (1, 3, 4, 5, 31, 32, 33, 64, 97, 127):
@@ -243,3 +243,33 @@ def test_a_long_tail_behind_one_dominating_token_is_kept(fmt, x):
     ma, rl = attn_errors(_attend_f32(gc, w, q, 1), O.decode_attn(oc, q, scale))
     bar = 12 * 2.0 ** -23 * (x + 1) + 2.0 ** -20 + min(L * 2.0 ** -26, 2.0 ** -3 * L * 2.0 ** -x)
     assert rl <= bar, f"{fmt} 2^-{x}: rel-L2 {rl:.2e} against {bar:.2e}"
+
+
+@pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int2", 16), ("int4_g32", 8)])
+@pytest.mark.parametrize("L", [2, 33, 127])
+def test_residual_weights_enter_the_product_whole(fmt, gq, L):
+    """Token t's value row is one in channel t only, so the unnormalised output row holds the weights as the product
+    takes them: all 24 bits of the fp32 exp2(s_t - m), for scores that fp32 gives exactly (one channel in q)."""
+    import torch
+    rng = np.random.default_rng(L)
+    q = np.zeros((1, 2 * gq, 128), np.float16)
+    q[..., 5] = 1.0
+    K, V = np.zeros((1, 2, L, 128), np.float16), np.zeros((1, 2, L, 128), np.float16)
+    K[..., 5] = rng.uniform(-40, 40, (1, 2, L)).astype(np.float16)
+    K[:, :, 0, 5] = 41   # (the largest in the first round: no running maximum is raised, which would round what is summed)
+    V[:, :, np.arange(L), np.arange(L)] = 1.0
+    _, gc = _caches_of(K, V, fmt, gq)
+    ws = gc.workspace(1)
+    scale = np.float32(0.088)
+    B.bd_decode_attn(gc.desc, to_dev(q, "fp16"), 0, L, float(scale), 1, ws, None)
+    torch.cuda.synchronize()
+    rows = ws[:2 * gq * 128 * 4].view(torch.float32).view(2, gq, 128)
+    s = torch.from_numpy(K[0, :, :, 5].astype(np.float32) * (scale * np.float32(1.4426950408889634))).cuda()
+    p = torch.exp2(s - s.amax(-1, keepdim=True))
+    whole = p > 2.0 ** -13
+    assert whole.sum() > 2
+    for h in range(2):
+        for i in range(gq):
+            got = rows[h, i, :L]
+            assert torch.equal(got[whole[h]], p[h][whole[h]]), (fmt, gq, L, (got - p[h]).abs().max().item())
+            assert (got - p[h]).abs().max() <= 2.0 ** -38
