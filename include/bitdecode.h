@@ -160,7 +160,7 @@ bd_status bd_append_kv(const bd_cache* c, const void* k_new, const void* v_new,
  * is complete when the stream passes this call; if NULL, call bd_splitk_combine.  (`out` has
  * the element type c->out_type names here and in every other call: fp16 / bf16, or fp32.)
  * num_splits >= 1 (any value; splits beyond the number of 128-token blocks stay empty).  A call that writes `out`
- * (this one, the paged one and the decode steps) shares the context out over fewer workgroups where that is
+ * (this one and the decode steps of a bd_cache) shares the context out over fewer workgroups where that is
  * faster; the workspace then still holds num_splits partials, the last ones empty.
  * With no tokens at all the output is zero. */
 bd_status bd_decode_attn(const bd_cache* c, const void* q, int32_t packed_len, int32_t res_len,
@@ -285,8 +285,8 @@ bd_status bd_paged_quant_pack_kv(const bd_paged_cache* c, int32_t seq, const voi
 bd_status bd_paged_append_kv(const bd_paged_cache* c, const void* k_new, const void* v_new, void* stream);
 
 /* bd_decode_attn over the paged cache: sequence b attends its own seq_lens[b] tokens; a
- * sequence with no tokens gets a zero output row.  Every sequence is split num_splits ways
- * (pick it for the longest sequence, e.g. with bd_choose_splits on a bd_cache of the same
+ * sequence with no tokens gets a zero output row.  Every sequence is split num_splits ways, as
+ * given (pick it for the longest sequence, e.g. with bd_choose_splits on a bd_cache of the same
  * shape); workspace at least bd_paged_workspace_bytes(c, num_splits); `out` (device,
  * [B][n_q_heads][D] fp16; bf16 for MXFP4) must be non-NULL.  With num_splits == 1 the attention
  * kernel writes `out` itself and no merge runs. */

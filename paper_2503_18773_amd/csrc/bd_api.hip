@@ -87,7 +87,8 @@ bd_status static_scratch_ptr(void** ptr) {
 
 // Splits a call that writes `out` runs with: as many as asked for, or fewer where fewer are faster, which the merge makes
 // no difference to (the workspace keeps the layout of the count asked for, the rest of its partials being empty).
-// packed_len < 0: the lengths are on the device (paged cache).
+// Paged calls run the count asked for: the lengths are on the device, and a batch of one long sequence among short
+// ones needs every split of the long one (64K tokens among 23 of 500: 109 us with 3 splits, 147 with 2).
 int splits_to_run(const bd_cache* c, int packed_len, int asked) {
   // (quantum: the 4 blocks that the 4 waves of a workgroup take in a round; 2 workgroups are resident per compute unit)
   const long units = (long)c->batch * group_workgroups(c);
@@ -96,12 +97,9 @@ int splits_to_run(const bd_cache* c, int packed_len, int asked) {
   const bool one_wg = fmt_group(c->format) == 32 && (fmt_bits(c->format) == 4 || fmt_kt(c->format)) && c->n_q_heads / c->n_kv_heads > 4;
   const long target = one_wg ? 256 : 512;
   // (not more than one round of workgroups: the few of a second round run with most of the chip idle -- a step, 4 bits,
-  // 160 units at 6K tokens 31.3 us with 640 workgroups, 27.9 with 480, in pages 32.5 / 27.1; 192 units at 8K 46.9 with
-  // 576, 44.2 with 384, in pages 50.7 / 47.4 at up to 9K; 96 units at 3K 17.8 / 16.8 in pages, where one block per wave
-  // took 576)
+  // 160 units at 6K tokens 31.3 us with 640 workgroups, 27.9 with 480; 192 units at 8K 46.9 with 576, 44.2 with 384)
   int want = asked;
   if (units < 256) want = (int)std::max(1L, std::min((long)asked, target / units));
-  if (packed_len < 0) return want;
   const int quanta = std::max(1, ((packed_len + kBlock - 1) / kBlock + 3) / 4);
   const int gq = c->n_q_heads / c->n_kv_heads;
   // Two rounds of blocks in one workgroup take no longer than one round in two and the merge behind it, and are one
@@ -490,8 +488,8 @@ static bd_status paged_attention(const bd_paged_cache* c, const void* q, float s
   float* part_ml = ws_part_ml(&shape, workspace, num_splits);
   // one split: the attention kernel writes `out` itself and no merge runs (a fused step then raises the
   // lengths with the small kernel of bd_paged_append_kv instead of in the merge)
-  const Splits ns = {splits_to_run(&shape, -1, num_splits), num_splits};
-  void* direct = ns.run == 1 ? out : nullptr;
+  const Splits ns = {num_splits, num_splits};
+  void* direct = num_splits == 1 ? out : nullptr;
   bd_status s = hip_status(c->format == BD_FMT_MXFP4
                                ? launch_decode_mx_paged(c, q, softmax_scale, ns, part_o, part_ml, step, k_new, v_new,
                                                         direct, st)
@@ -502,7 +500,7 @@ static bd_status paged_attention(const bd_paged_cache* c, const void* q, float s
                                                      direct, st, lazy));
   if (s != BD_OK) return s;
   if (direct) return step ? hip_status(launch_paged_bump(c, st)) : BD_OK;
-  return hip_status(launch_combine(&shape, part_o, part_ml, ns.run, out, st, step ? c : nullptr));
+  return hip_status(launch_combine(&shape, part_o, part_ml, num_splits, out, st, step ? c : nullptr));
 }
 
 bd_status bd_paged_decode_attn(const bd_paged_cache* c, const void* q, float softmax_scale, int32_t num_splits,
