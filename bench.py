@@ -116,6 +116,17 @@ def oracle_baseline(w, K, V, cap, seconds, sm_scale):
                       f"single-threaded process per unit (numpy float64)"}
 
 
+def compute_dtype(w):
+    """Operand types of the two products as the kernel of this workload runs them."""
+    if w.fmt == "mxfp4":
+        return "e2m1 mfma, f32 accumulate"
+    codes = "u4" if w.fmt.startswith("int4") else "u2"
+    if w.n_q_heads // w.n_kv_heads > 4 or "_g" in w.fmt:
+        return codes + "->f16 mfma, f32 accumulate"
+    # queries and weights are sums of e4m3 numbers that hold more bits than fp16 (all 22 of q * scale, 19 of a weight)
+    return codes + "->" + ("e4m3" if codes == "u4" else "e2m1") + " x (q * scale 22 bits, weights 19 bits, in e4m3 pieces) mfma, f32 accumulate"
+
+
 def kernel_roofline(B, W, torch, w, caches, qs_last, outs, splits, paged, sm_scale, variant, total_steps):
     """Roofline of the dominant kernel (decode attention), measured live with HIP events on the stream the
     kernels run on: one event pair around the bd_decode_attn launches (partials only, no combine) of all
@@ -297,7 +308,7 @@ def run(args, workload: str, steps: int, warmup: int, with_cpu: bool) -> dict:
     sm_scale = W.softmax_scale(w)
     shape = B.bd_cache(w.batch, w.n_q_heads, w.n_kv_heads, 128, B.FORMATS[w.fmt], cap, None, None, None, None, None,
                        None)
-    splits = args.splits or B.bd_choose_splits(shape, w.context)
+    splits = args.splits or (B.bd_choose_splits if paged else B.bd_step_splits)(shape, w.context)
     for c in caches:
         c.workspace(splits)
     setup_s = time.time() - t_setup
@@ -402,8 +413,7 @@ def run(args, workload: str, steps: int, warmup: int, with_cpu: bool) -> dict:
                   "over the packed cache)",
         "value": round(value, 1), "unit": "GB/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": {"int4": "u4->f16 mfma, f32 accumulate", "int2": "u2->f16 mfma, f32 accumulate",
-                  "mxfp4": "e2m1 mfma, f32 accumulate"}[w.fmt.split("_")[0]],
+        "dtype": compute_dtype(w),
         "data": "synthetic",
         "config": {"workload": f"{w.name}: batch {w.batch}, {w.n_q_heads}/{w.n_kv_heads} heads, head_dim 128, "
                                f"context {w.context}, {w.fmt} KV" + (f", variant {args.variant}" if args.variant else ""),

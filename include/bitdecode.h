@@ -125,6 +125,11 @@ size_t bd_cache_bytes(const bd_cache* c, int which);
  * over the context (the "split-partitioned" scheme named in Sec. V-A). */
 int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len);
 
+/* The same for a call that merges its partials itself (bd_decode_attn with `out`, bd_decode_attn_static, the
+ * decode steps of a bd_cache): at most bd_choose_splits, and fewer where the merge of that many partials, or
+ * its launch, costs more than the workgroups give.  Any other count is run as it is given. */
+int32_t bd_step_splits(const bd_cache* c, int32_t packed_len);
+
 /* Bytes of device workspace bd_decode_attn needs for `num_splits`: num_splits partial
  * results, each batch*n_q_heads*(128 + 2) floats (unnormalised output row, running max
  * in log2 units, running sum).  The residual tokens are shared out over the splits. */
@@ -159,9 +164,7 @@ bd_status bd_append_kv(const bd_cache* c, const void* k_new, const void* v_new,
  * [B][n_q_heads][D], fp16 / bf16) the merge of the partials is enqueued too, so `out`
  * is complete when the stream passes this call; if NULL, call bd_splitk_combine.  (`out` has
  * the element type c->out_type names here and in every other call: fp16 / bf16, or fp32.)
- * num_splits >= 1 (any value; splits beyond the number of 128-token blocks stay empty).  A call that writes `out`
- * (this one and the decode steps of a bd_cache) shares the context out over fewer workgroups where that is
- * faster; the workspace then still holds num_splits partials, the last ones empty.
+ * num_splits >= 1 (any value; splits beyond the number of 128-token blocks stay empty).
  * With no tokens at all the output is zero. */
 bd_status bd_decode_attn(const bd_cache* c, const void* q, int32_t packed_len, int32_t res_len,
                          float softmax_scale, int32_t num_splits, void* workspace, void* out,

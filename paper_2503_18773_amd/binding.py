@@ -68,6 +68,7 @@ def lib() -> ctypes.CDLL:
         IP = ctypes.POINTER(ctypes.c_int32)
         L.bd_cache_bytes.restype, L.bd_cache_bytes.argtypes = S, [P, ctypes.c_int]
         L.bd_choose_splits.restype, L.bd_choose_splits.argtypes = I, [P, I]
+        L.bd_step_splits.restype, L.bd_step_splits.argtypes = I, [P, I]
         L.bd_workspace_bytes.restype, L.bd_workspace_bytes.argtypes = S, [P, I]
         L.bd_quant_pack_kv.restype, L.bd_quant_pack_kv.argtypes = ctypes.c_int, [P, V, V, I, IP, IP, V]
         L.bd_append_kv.restype, L.bd_append_kv.argtypes = ctypes.c_int, [P, V, V, IP, IP, V]
@@ -91,7 +92,7 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-EXPORTS = ["bd_cache_bytes", "bd_choose_splits", "bd_workspace_bytes", "bd_quant_pack_kv", "bd_append_kv",
+EXPORTS = ["bd_cache_bytes", "bd_choose_splits", "bd_step_splits", "bd_workspace_bytes", "bd_quant_pack_kv", "bd_append_kv",
            "bd_decode_attn", "bd_decode_attn_static", "bd_probe_stream_read", "bd_decode_step", "bd_decode_step_lazy", "bd_splitk_combine", "bd_strerror", "bd_last_hip_error",
            "bd_paged_cache_bytes", "bd_paged_workspace_bytes", "bd_paged_quant_pack_kv", "bd_paged_append_kv",
            "bd_paged_decode_attn", "bd_paged_decode_step", "bd_paged_decode_step_lazy"]
@@ -131,6 +132,10 @@ def bd_cache_bytes(c: bd_cache, which: int) -> int:
 
 def bd_choose_splits(c: bd_cache, packed_len: int) -> int:
     return int(lib().bd_choose_splits(ctypes.byref(c), packed_len))
+
+
+def bd_step_splits(c: bd_cache, packed_len: int) -> int:
+    return int(lib().bd_step_splits(ctypes.byref(c), packed_len))
 
 
 def bd_workspace_bytes(c: bd_cache, num_splits: int) -> int:
@@ -285,7 +290,9 @@ class KVCache:
 
     def decode_attn(self, q, softmax_scale: float, out, num_splits: int | None = None, fused: bool = True,
                     stream=None):
-        ns = self.choose_splits() if num_splits is None else num_splits
+        ns = num_splits
+        if ns is None:
+            ns = bd_step_splits(self.desc, self.packed_len) if fused else self.choose_splits()
         ws = self.workspace(ns)
         if fused:
             bd_decode_attn(self.desc, q, self.packed_len, self.res_len, softmax_scale, ns, ws, out, stream)
@@ -296,7 +303,7 @@ class KVCache:
 
     def decode_step(self, k_new, v_new, q, softmax_scale: float, out, num_splits: int | None = None, stream=None,
                     lazy: bool = False):
-        ns = self.choose_splits() if num_splits is None else num_splits
+        ns = bd_step_splits(self.desc, self.packed_len) if num_splits is None else num_splits
         step = bd_decode_step_lazy if lazy else bd_decode_step
         self.packed_len, self.res_len = step(self.desc, k_new, v_new, q, self.packed_len, self.res_len,
                                              softmax_scale, ns, self.workspace(ns), out, stream)

@@ -85,53 +85,6 @@ bd_status static_scratch_ptr(void** ptr) {
   return BD_OK;
 }
 
-// Splits a call that writes `out` runs with: as many as asked for, or fewer where fewer are faster, which the merge makes
-// no difference to (the workspace keeps the layout of the count asked for, the rest of its partials being empty).
-// Paged calls run the count asked for: the lengths are on the device, and a batch of one long sequence among short
-// ones needs every split of the long one (64K tokens among 23 of 500: 109 us with 3 splits, 147 with 2).
-int splits_to_run(const bd_cache* c, int packed_len, int asked) {
-  // (quantum: the 4 blocks that the 4 waves of a workgroup take in a round; 2 workgroups are resident per compute unit)
-  const long units = (long)c->batch * group_workgroups(c);
-  // (some kernel instances run one workgroup per compute unit: groups of 32 with more than 4 query heads
-  // per KV head, for 4-bit codes and for per-token K)
-  const bool one_wg = fmt_group(c->format) == 32 && (fmt_bits(c->format) == 4 || fmt_kt(c->format)) && c->n_q_heads / c->n_kv_heads > 4;
-  const long target = one_wg ? 256 : 512;
-  // (not more than one round of workgroups: the few of a second round run with most of the chip idle -- a step, 4 bits,
-  // 160 units at 6K tokens 31.3 us with 640 workgroups, 27.9 with 480; 192 units at 8K 46.9 with 576, 44.2 with 384)
-  int want = asked;
-  if (units < 256) want = (int)std::max(1L, std::min((long)asked, target / units));
-  const int quanta = std::max(1, ((packed_len + kBlock - 1) / kBlock + 3) / 4);
-  const int gq = c->n_q_heads / c->n_kv_heads;
-  // Two rounds of blocks in one workgroup take no longer than one round in two and the merge behind it, and are one
-  // launch less (1K tokens, up to 4 heads per KV head: 8.5 -> 8.4 us with 8 units, 10.1 -> 8.8 with 128, issued one by
-  // one 10.2 -> 8.3; with more heads, or in groups of 64 and 32, the second round costs more than the merge).
-  if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 4 && quanta <= 2) return 1;
-  // Few units, hence many partials per output row: the merge then costs more than a second workgroup per compute
-  // unit gives, if the kernel's arithmetic leaves one the time (4-bit codes with up to 4 heads per KV head: any
-  // context; other integer codes up to 3.5 blocks per wave; MXFP4 around two).  A step, 8 units, 4 bits: 24.6K tokens
-  // 13.1 us with 48 splits, 12.1 with 32; 32K 13.2 / 12.6; 48K 17.5 (94 splits) / 14.7; 128K 28.9 / 27.9; 2 bits 32K 12.1 /
-  // 11.5 but 128K 20.3 / 21.9; MXFP4 32K 16.3 / 15.6; 4 units, 128K 19.5 (128) / 18.6 (64); one unit, 128K 14.3 (256)
-  // / 13.0 (128).  From 17 units on the two are equal, and the groups of 64 and 32 want the waves.
-  if (fmt_group(c->format) == kBlock && units <= 16) {
-    const int one_round = units == 1 ? 128 : (int)(256 / units);
-    if (quanta <= one_round) return std::min(asked, quanta);
-    const bool light = fmt_is_int(c->format) && fmt_bits(c->format) == 4 && gq <= 4;
-    const bool moderate = fmt_is_int(c->format) ? 2 * quanta <= 7 * one_round
-                                                : units <= 8 && 2 * quanta >= 3 * one_round && 2 * quanta <= 5 * one_round;
-    if (light || moderate) return std::min(asked, one_round);
-  }
-  int splits = std::min(quanta, want);
-  // Two workgroups on a compute unit take nearly twice as long as one: one each, with fewer splits, if that leaves a
-  // unit fewer rounds of blocks and few units idle (64 units, 6K tokens: 3 rounds with 4 splits, 2 of 2 workgroups
-  // with 8, 15.6 / 17.6 us; 128 units with 8 heads per KV head, 3K: 18.9 / 20.0; 192 units, 1.5K, no split: 14.6 / 17.4).
-  if (units < 256 && fmt_is_int(c->format) && fmt_group(c->format) == kBlock) {
-    const int single = (int)(256 / units);
-    auto rounds = [&](int ns) { return (quanta + ns - 1) / ns * (int)((units * ns + 255) / 256); };
-    if (single < splits && rounds(single) < rounds(splits) && (single == 1 || units * single >= 224)) splits = single;
-  }
-  return splits;
-}
-
 }  // namespace
 
 extern "C" {
@@ -186,6 +139,51 @@ int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len) {
   // leaves a few workgroups one quantum short, which is faster than fewer workgroups of equal length)
   const int splits = quanta < want ? quanta : want;
   return splits < 1 ? 1 : splits;
+}
+
+int32_t bd_step_splits(const bd_cache* c, int32_t packed_len) {
+  if (check_shape(c) != BD_OK || packed_len <= 0) return 1;
+  const int most = bd_choose_splits(c, packed_len);
+  // (quantum: the 4 blocks that the 4 waves of a workgroup take in a round; 2 workgroups are resident per compute unit)
+  const long units = (long)c->batch * group_workgroups(c);
+  // (some kernel instances run one workgroup per compute unit: groups of 32 with more than 4 query heads
+  // per KV head, for 4-bit codes and for per-token K)
+  const bool one_wg = fmt_group(c->format) == 32 && (fmt_bits(c->format) == 4 || fmt_kt(c->format)) && c->n_q_heads / c->n_kv_heads > 4;
+  const long target = one_wg ? 256 : 512;
+  // (not more than one round of workgroups: the few of a second round run with most of the chip idle -- a step, 4 bits,
+  // 160 units at 6K tokens 31.3 us with 640 workgroups, 27.9 with 480; 192 units at 8K 46.9 with 576, 44.2 with 384)
+  int want = most;
+  if (units < 256) want = (int)std::max(1L, std::min((long)most, target / units));
+  const int quanta = std::max(1, ((packed_len + kBlock - 1) / kBlock + 3) / 4);
+  const int gq = c->n_q_heads / c->n_kv_heads;
+  // Two rounds of blocks in one workgroup take no longer than one round in two and the merge behind it, and are one
+  // launch less (1K tokens, up to 4 heads per KV head: 8.5 -> 8.4 us with 8 units, 10.1 -> 8.8 with 128, issued one by
+  // one 10.2 -> 8.3; with more heads, or in groups of 64 and 32, the second round costs more than the merge).
+  if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 4 && quanta <= 2) return 1;
+  // Few units, hence many partials per output row: the merge then costs more than a second workgroup per compute
+  // unit gives, if the kernel's arithmetic leaves one the time (4-bit codes with up to 4 heads per KV head: any
+  // context; other integer codes up to 3.5 blocks per wave; MXFP4 around two).  A step, 8 units, 4 bits: 24.6K tokens
+  // 13.1 us with 48 splits, 12.1 with 32; 32K 13.2 / 12.6; 48K 17.5 (94 splits) / 14.7; 128K 28.9 / 27.9; 2 bits 32K 12.1 /
+  // 11.5 but 128K 20.3 / 21.9; MXFP4 32K 16.3 / 15.6; 4 units, 128K 19.5 (128) / 18.6 (64); one unit, 128K 14.3 (256)
+  // / 13.0 (128).  From 17 units on the two are equal, and the groups of 64 and 32 want the waves.
+  if (fmt_group(c->format) == kBlock && units <= 16) {
+    const int one_round = units == 1 ? 128 : (int)(256 / units);
+    if (quanta <= one_round) return std::min(most, quanta);
+    const bool light = fmt_is_int(c->format) && fmt_bits(c->format) == 4 && gq <= 4;
+    const bool moderate = fmt_is_int(c->format) ? 2 * quanta <= 7 * one_round
+                                                : units <= 8 && 2 * quanta >= 3 * one_round && 2 * quanta <= 5 * one_round;
+    if (light || moderate) return std::min(most, one_round);
+  }
+  int splits = std::min(quanta, want);
+  // Two workgroups on a compute unit take nearly twice as long as one: one each, with fewer splits, if that leaves a
+  // unit fewer rounds of blocks and few units idle (64 units, 6K tokens: 3 rounds with 4 splits, 2 of 2 workgroups
+  // with 8, 15.6 / 17.6 us; 128 units with 8 heads per KV head, 3K: 18.9 / 20.0; 192 units, 1.5K, no split: 14.6 / 17.4).
+  if (units < 256 && fmt_is_int(c->format) && fmt_group(c->format) == kBlock) {
+    const int single = (int)(256 / units);
+    auto rounds = [&](int ns) { return (quanta + ns - 1) / ns * (int)((units * ns + 255) / 256); };
+    if (single < splits && rounds(single) < rounds(splits) && (single == 1 || units * single >= 224)) splits = single;
+  }
+  return splits;
 }
 
 size_t bd_workspace_bytes(const bd_cache* c, int32_t num_splits) {
@@ -266,23 +264,22 @@ bd_status bd_decode_attn(const bd_cache* c, const void* q, int32_t packed_len, i
   hipStream_t st = (hipStream_t)stream;
   float* part_o = ws_part_o(workspace);
   float* part_ml = ws_part_ml(c, workspace, num_splits);
-  const Splits ns = {out ? splits_to_run(c, packed_len, num_splits) : num_splits, num_splits};
   if (c->format == BD_FMT_MXFP4) {
     if (res_len != 0) return BD_ERR_INVALID_ARG;
-    s = hip_status(launch_decode_mx(c, q, packed_len, softmax_scale, ns, part_o, part_ml, nullptr, nullptr, out,
+    s = hip_status(launch_decode_mx(c, q, packed_len, softmax_scale, num_splits, part_o, part_ml, nullptr, nullptr, out,
                                     st));
   } else {
     if (packed_len % kBlock != 0 || res_len < 0 || res_len >= kBlock) return BD_ERR_INVALID_ARG;
     if (fmt_group(c->format) != kBlock)
-      s = hip_status(launch_decode_grp(c, q, packed_len, res_len, softmax_scale, ns, part_o, part_ml, nullptr,
+      s = hip_status(launch_decode_grp(c, q, packed_len, res_len, softmax_scale, num_splits, part_o, part_ml, nullptr,
                                        nullptr, out, st));
     else
-      s = hip_status(launch_decode_int(c, q, packed_len, res_len, softmax_scale, ns, part_o, part_ml,
+      s = hip_status(launch_decode_int(c, q, packed_len, res_len, softmax_scale, num_splits, part_o, part_ml,
                                        nullptr, nullptr, out, st));
   }
   if (s != BD_OK) return s;
   // (one split: the attention kernel has written `out` itself, there is nothing to merge)
-  if (out && ns.run > 1) s = hip_status(launch_combine(c, part_o, part_ml, ns.run, out, st));
+  if (out && num_splits > 1) s = hip_status(launch_combine(c, part_o, part_ml, num_splits, out, st));
   return s;
 }
 
@@ -336,10 +333,9 @@ static bd_status decode_step(const bd_cache* c, const void* k_new, const void* v
     }
     // one workgroup per split and KV head: the attention launch quantizes the token into the cache itself
     // (the workgroup that reads its block does, first thing)
-    const Splits ns = {splits_to_run(c, pl + 1, num_splits), num_splits};
-    if ((s = hip_status(launch_decode_mx(c, q, pl, softmax_scale, ns, part_o, part_ml, k_new, v_new, out, st))) != BD_OK)
+    if ((s = hip_status(launch_decode_mx(c, q, pl, softmax_scale, num_splits, part_o, part_ml, k_new, v_new, out, st))) != BD_OK)
       return s;
-    if (ns.run > 1 && (s = hip_status(launch_combine(c, part_o, part_ml, ns.run, out, st))) != BD_OK) return s;
+    if (num_splits > 1 && (s = hip_status(launch_combine(c, part_o, part_ml, num_splits, out, st))) != BD_OK) return s;
     *packed_len = pl + 1;
     return BD_OK;
   }
@@ -358,13 +354,12 @@ static bd_status decode_step(const bd_cache* c, const void* k_new, const void* v
   // the residual block it packs the block as well (before attending it, or, lazy, after)
   const int flush = !fills ? 0 : lazy ? 2 : 1;
   const int att_pl = flush == 1 ? pl + kBlock : pl, att_r = flush == 1 ? 0 : r + 1;
-  const Splits ns = {splits_to_run(c, att_pl, num_splits), num_splits};
-  s = hip_status(grp ? launch_decode_grp(c, q, att_pl, att_r, softmax_scale, ns, part_o, part_ml, k_new, v_new, out, st,
+  s = hip_status(grp ? launch_decode_grp(c, q, att_pl, att_r, softmax_scale, num_splits, part_o, part_ml, k_new, v_new, out, st,
                                          flush)
-                     : launch_decode_int(c, q, att_pl, att_r, softmax_scale, ns, part_o, part_ml, k_new, v_new, out, st,
+                     : launch_decode_int(c, q, att_pl, att_r, softmax_scale, num_splits, part_o, part_ml, k_new, v_new, out, st,
                                          flush));
   if (s != BD_OK) return s;
-  if (ns.run > 1 && (s = hip_status(launch_combine(c, part_o, part_ml, ns.run, out, st))) != BD_OK) return s;
+  if (num_splits > 1 && (s = hip_status(launch_combine(c, part_o, part_ml, num_splits, out, st))) != BD_OK) return s;
   *packed_len = fills ? pl + kBlock : pl;
   *res_len = fills ? 0 : r + 1;
   return BD_OK;
@@ -488,15 +483,14 @@ static bd_status paged_attention(const bd_paged_cache* c, const void* q, float s
   float* part_ml = ws_part_ml(&shape, workspace, num_splits);
   // one split: the attention kernel writes `out` itself and no merge runs (a fused step then raises the
   // lengths with the small kernel of bd_paged_append_kv instead of in the merge)
-  const Splits ns = {num_splits, num_splits};
   void* direct = num_splits == 1 ? out : nullptr;
   bd_status s = hip_status(c->format == BD_FMT_MXFP4
-                               ? launch_decode_mx_paged(c, q, softmax_scale, ns, part_o, part_ml, step, k_new, v_new,
+                               ? launch_decode_mx_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
                                                         direct, st)
                            : fmt_group(c->format) != kBlock
-                               ? launch_decode_grp_paged(c, q, softmax_scale, ns, part_o, part_ml, step, k_new, v_new,
+                               ? launch_decode_grp_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
                                                          direct, st, lazy)
-                               : launch_decode_paged(c, q, softmax_scale, ns, part_o, part_ml, step, k_new, v_new,
+                               : launch_decode_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
                                                      direct, st, lazy));
   if (s != BD_OK) return s;
   if (direct) return step ? hip_status(launch_paged_bump(c, st)) : BD_OK;

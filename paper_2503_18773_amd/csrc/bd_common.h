@@ -19,12 +19,6 @@ typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
 typedef int i8_t __attribute__((ext_vector_type(8)));
 
-// Workgroups that share the context of one (sequence, KV head), and the partials that the caller's workspace holds
-// (at least as many; those past `run` are left empty).
-struct Splits {
-  int run, held;
-};
-
 // Records a failing HIP call for bd_last_hip_error().
 void note_hip_error(hipError_t e);
 
@@ -60,13 +54,13 @@ hipError_t launch_paged_prefill(const bd_paged_cache* c, int seq, const void* k,
                                 hipStream_t st);
 hipError_t launch_paged_append(const bd_paged_cache* c, const void* k_new, const void* v_new, bool bump,
                                hipStream_t st);
-// `out` (all decode launchers): with ns.run == 1 and out != nullptr the kernel writes the final output
+// `out` (all decode launchers): with num_splits == 1 and out != nullptr the kernel writes the final output
 // rows itself and no merge is needed; otherwise it writes the split partials.
 // raises the length of every sequence whose step's token was appended (launch_paged_append with bump = false)
 hipError_t launch_paged_bump(const bd_paged_cache* c, hipStream_t st);
 // k_new / v_new non-null (with step): the launch appends the step's token itself -- no launch_paged_append
 // before it; query groups of up to 16 heads only
-hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float softmax_scale, Splits ns,
+hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
                                void* out, hipStream_t st, bool lazy = false);
 
@@ -76,24 +70,24 @@ hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float sof
 // the launch packs it as well -- 1: before attending it (packed_len counts the block, res_len == 0);
 // 2: after attending its 128 fp16 rows (res_len == 128; one more workgroup per KV head does the packing)
 hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, int res_len,
-                             float softmax_scale, Splits ns, float* part_o, float* part_ml,
+                             float softmax_scale, int num_splits, float* part_o, float* part_ml,
                              const void* k_new, const void* v_new, void* out, hipStream_t st, int flush = 0);
 // formats with a quantization group of 64 or 32 (k_new / v_new and flush as in launch_decode_int; the flush
 // forms for query groups of up to 8 heads only)
 hipError_t launch_decode_grp(const bd_cache* c, const void* q, int packed_len, int res_len, float softmax_scale,
-                             Splits ns, float* part_o, float* part_ml, const void* k_new, const void* v_new,
+                             int num_splits, float* part_o, float* part_ml, const void* k_new, const void* v_new,
                              void* out, hipStream_t st, int flush = 0);
 // (k_new / v_new as in launch_decode_paged; query groups of up to 8 heads only)
-hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float softmax_scale, Splits ns,
+hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                    float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
                                    void* out, hipStream_t st, bool lazy = false);
 // k_new / v_new non-null: the launch quantizes the step's token into the cache itself (contiguous: at index
 // `length`, and attends length + 1 tokens; paged: with `step`); query groups of up to 16 heads only
-hipError_t launch_decode_mx_paged(const bd_paged_cache* c, const void* q, float softmax_scale, Splits ns,
+hipError_t launch_decode_mx_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                   float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
                                   void* out, hipStream_t st);
 hipError_t launch_decode_mx(const bd_cache* c, const void* q, int length, float softmax_scale,
-                            Splits ns, float* part_o, float* part_ml, const void* k_new, const void* v_new,
+                            int num_splits, float* part_o, float* part_ml, const void* k_new, const void* v_new,
                             void* out, hipStream_t st);
 // step_of: the paged cache whose fused step this merge ends (it then raises the lengths), or nullptr
 hipError_t launch_combine(const bd_cache* c, const float* part_o, const float* part_ml, int nparts,

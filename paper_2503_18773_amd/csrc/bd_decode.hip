@@ -102,7 +102,6 @@ struct DecodeArgs {
   int nbcap;
   int res_len;
   int num_splits;
-  int held_splits;  // partials of the workspace, the ones past num_splits left empty
   float scale_log2; // softmax_scale * log2(e)
   // paged cache: block n of sequence b is page block_table[b][n], pool index page * Hkv + head;
   // nb and res_len then come from seq_lens[b]
@@ -954,13 +953,13 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       }
       const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * a.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
-      if (a.out) store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);   // one split: row == the output row
-      if (!a.out || a.held_splits > 1) {
+      if (a.out) {   // one split: row == the output row
+        store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);
+      } else {
         *reinterpret_cast<float2*>(a.part_o + row * kD + c0) = o;
         if ((tid & 63) == 0) {
           a.part_ml[row * 2] = M;
           a.part_ml[row * 2 + 1] = L;
-          empty_partials(a.part_ml, row, (size_t)gridDim.z * a.n_q_heads, split, a.num_splits, a.held_splits);
         }
       }
     }
@@ -1022,7 +1021,7 @@ __global__ __launch_bounds__(128 * G) void combine_kernel(const float* __restric
       const float fo = live ? __builtin_amdgcn_exp2f(M - Mn) : 1.0f;
       const float fn = live ? __builtin_amdgcn_exp2f(ml[i].x - Mn) : 0.0f;
       L = L * fo + fn * ml[i].y;
-      o = o * fo + fn * (live ? ov[i] : 0.0f);   // (the row of an empty partial may hold anything)
+      o = o * fo + fn * ov[i];
       M = Mn;
     }
   }
@@ -1084,9 +1083,8 @@ void launch_instance(int format, int gq, bool single, bool paged, const DecodeAr
 }  // namespace
 
 hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, int res_len, float softmax_scale,
-                             Splits ns, float* part_o, float* part_ml, const void* k_new, const void* v_new,
+                             int num_splits, float* part_o, float* part_ml, const void* k_new, const void* v_new,
                              void* out, hipStream_t st, int flush) {
-  const int num_splits = ns.run;
   DecodeArgs a;
   a.out = num_splits == 1 ? out : nullptr;
   a.out_kind = out_kind(c->format, c->out_type);
@@ -1113,7 +1111,6 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   a.nbcap = c->capacity / kBlock;
   a.res_len = res_len;
   a.num_splits = num_splits;
-  a.held_splits = ns.held;
   a.scale_log2 = softmax_scale * kLog2e;
   a.block_table = nullptr;
   a.seq_lens = nullptr;
@@ -1126,10 +1123,9 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   return hipGetLastError();
 }
 
-hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float softmax_scale, Splits ns,
+hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
                                void* out, hipStream_t st, bool lazy) {
-  const int num_splits = ns.run;
   DecodeArgs a;
   a.step = step ? 1 : 0;
   a.out = num_splits == 1 ? out : nullptr;
@@ -1155,7 +1151,6 @@ hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float sof
   a.gq = c->n_q_heads / c->n_kv_heads;
   a.nb = a.nbcap = a.res_len = 0;   // per sequence, from seq_lens
   a.num_splits = num_splits;
-  a.held_splits = ns.held;
   a.scale_log2 = softmax_scale * kLog2e;
   a.block_table = c->block_table;
   a.seq_lens = c->seq_lens;

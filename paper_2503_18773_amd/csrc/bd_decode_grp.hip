@@ -51,7 +51,6 @@ struct GrpArgs {
   int out_kind;     // element type of `out` (kOutF16 / kOutBf16 / kOutF32)
   int n_q_heads, n_kv_heads, gq;
   int nb, nbcap, res_len, num_splits;
-  int held_splits;  // partials of the workspace
   float scale_log2;
   // paged cache: block n of sequence b is page block_table[b][n], pool index page * Hkv + head;
   // nb and res_len then come from seq_lens[b]
@@ -760,13 +759,13 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
       }
       const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * a.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
-      if (a.out) store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);   // one split: row == the output row
-      if (!a.out || a.held_splits > 1) {
+      if (a.out) {   // one split: row == the output row
+        store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);
+      } else {
         *reinterpret_cast<float2*>(a.part_o + row * kD + c0) = o;
         if (lane == 0) {
           a.part_ml[row * 2] = M;
           a.part_ml[row * 2 + 1] = L;
-          empty_partials(a.part_ml, row, (size_t)gridDim.z * a.n_q_heads, split, a.num_splits, a.held_splits);
         }
       }
     }
@@ -803,9 +802,8 @@ hipError_t launch_format(int format, const GrpArgs& a, bool paged, int batch, hi
 }  // namespace
 
 hipError_t launch_decode_grp(const bd_cache* c, const void* q, int packed_len, int res_len, float softmax_scale,
-                             Splits ns, float* part_o, float* part_ml, const void* k_new, const void* v_new,
+                             int num_splits, float* part_o, float* part_ml, const void* k_new, const void* v_new,
                              void* out, hipStream_t st, int flush) {
-  const int num_splits = ns.run;
   GrpArgs a;
   a.k_new = (const uint16_t*)k_new;
   a.v_new = (const uint16_t*)v_new;
@@ -832,7 +830,6 @@ hipError_t launch_decode_grp(const bd_cache* c, const void* q, int packed_len, i
   a.nbcap = c->capacity / kBlock;
   a.res_len = res_len;
   a.num_splits = num_splits;
-  a.held_splits = ns.held;
   a.scale_log2 = softmax_scale * kLog2e;
   a.block_table = nullptr;
   a.seq_lens = nullptr;
@@ -841,10 +838,9 @@ hipError_t launch_decode_grp(const bd_cache* c, const void* q, int packed_len, i
   return launch_format(c->format, a, false, c->batch, st);
 }
 
-hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float softmax_scale, Splits ns,
+hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                    float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
                                    void* out, hipStream_t st, bool lazy) {
-  const int num_splits = ns.run;
   GrpArgs a;
   a.k_new = (const uint16_t*)k_new;   // non-null: the step's token, which this launch appends itself
   a.v_new = (const uint16_t*)v_new;
@@ -865,7 +861,6 @@ hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float
   a.gq = c->n_q_heads / c->n_kv_heads;
   a.nb = a.nbcap = a.res_len = 0;   // per sequence, from seq_lens
   a.num_splits = num_splits;
-  a.held_splits = ns.held;
   a.scale_log2 = softmax_scale * kLog2e;
   a.block_table = c->block_table;
   a.seq_lens = c->seq_lens;

@@ -42,7 +42,6 @@ struct MxArgs {
   int length;      // tokens in the cache
   int capacity;
   int num_splits;
-  int held_splits;  // partials of the workspace, the ones past num_splits left empty
   float scale_log2;
   // paged cache only: block n of sequence b is page block_table[b * max_pages + n]
   const int32_t* block_table;
@@ -402,14 +401,14 @@ __global__ __launch_bounds__(256, 2) void decode_mx_kernel(MxArgs a) {
         }
       }
       const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + head0 + h;
-      if (a.out) store_final_pair(a.out, row * kD + c0, a.out_kind, o0, o1, L);   // one split: row == the output row
-      if (!a.out || a.held_splits > 1) {
+      if (a.out) {   // one split: row == the output row
+        store_final_pair(a.out, row * kD + c0, a.out_kind, o0, o1, L);
+      } else {
         float2 o = {o0, o1};
         *reinterpret_cast<float2*>(a.part_o + row * kD + c0) = o;
         if ((tid & 63) == 0) {
           a.part_ml[row * 2] = M;
           a.part_ml[row * 2 + 1] = L;
-          empty_partials(a.part_ml, row, (size_t)gridDim.z * a.n_q_heads, split, a.num_splits, a.held_splits);
         }
       }
     }
@@ -658,14 +657,14 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
         }
       }
       const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + head0 + h;
-      if (a.out) store_final_pair(a.out, row * kD + c0, a.out_kind, o0, o1, L);   // one split: row == the output row
-      if (!a.out || a.held_splits > 1) {
+      if (a.out) {   // one split: row == the output row
+        store_final_pair(a.out, row * kD + c0, a.out_kind, o0, o1, L);
+      } else {
         float2 o = {o0, o1};
         *reinterpret_cast<float2*>(a.part_o + row * kD + c0) = o;
         if ((tid & 63) == 0) {
           a.part_ml[row * 2] = M;
           a.part_ml[row * 2 + 1] = L;
-          empty_partials(a.part_ml, row, (size_t)gridDim.z * a.n_q_heads, split, a.num_splits, a.held_splits);
         }
       }
     }
@@ -686,10 +685,9 @@ static hipError_t launch_mx(const MxArgs& a, int batch, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_decode_mx(const bd_cache* c, const void* q, int length, float softmax_scale, Splits ns,
+hipError_t launch_decode_mx(const bd_cache* c, const void* q, int length, float softmax_scale, int num_splits,
                             float* part_o, float* part_ml, const void* k_new, const void* v_new, void* out,
                             hipStream_t st) {
-  const int num_splits = ns.run;
   MxArgs a{};
   a.k_new = (const uint16_t*)k_new;
   a.v_new = (const uint16_t*)v_new;
@@ -708,15 +706,13 @@ hipError_t launch_decode_mx(const bd_cache* c, const void* q, int length, float 
   a.length = length;
   a.capacity = c->capacity;
   a.num_splits = num_splits;
-  a.held_splits = ns.held;
   a.scale_log2 = softmax_scale * kLog2e;
   return launch_mx<false>(a, c->batch, st);
 }
 
-hipError_t launch_decode_mx_paged(const bd_paged_cache* c, const void* q, float softmax_scale, Splits ns,
+hipError_t launch_decode_mx_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                   float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
                                   void* out, hipStream_t st) {
-  const int num_splits = ns.run;
   MxArgs a{};
   a.k_new = (const uint16_t*)k_new;
   a.v_new = (const uint16_t*)v_new;
@@ -735,7 +731,6 @@ hipError_t launch_decode_mx_paged(const bd_paged_cache* c, const void* q, float 
   a.gq = c->n_q_heads / c->n_kv_heads;
   a.capacity = kBlock;
   a.num_splits = num_splits;
-  a.held_splits = ns.held;
   a.scale_log2 = softmax_scale * kLog2e;
   a.block_table = c->block_table;
   a.seq_lens = c->seq_lens;

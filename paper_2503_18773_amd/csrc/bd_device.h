@@ -172,15 +172,5 @@ __device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_le
   return b;
 }
 
-// Split `split` of `run` marks the partials of a workspace that holds more than were run (its own row + multiples of
-// `rows`) as empty: no maximum, no weight.
-__device__ __forceinline__ void empty_partials(float* part_ml, size_t row, size_t rows, int split, int run, int held) {
-  for (int s = split + run; s < held; s += run) {
-    float* p = part_ml + (row + (size_t)(s - split) * rows) * 2;
-    p[0] = -INFINITY;
-    p[1] = 0.0f;
-  }
-}
-
 }  // namespace
 }  // namespace bd

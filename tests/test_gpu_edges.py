@@ -21,6 +21,14 @@ def _attend_f32(gc, w, q, num_splits):
     return out_to_f64(out)
 
 
+def _partials(ws, ns, batch, hq):
+    """The workspace's partial rows [ns, batch, hq, 128] and their (maximum, sum) [ns, batch, hq, 2]."""
+    import torch
+    f = ws.view(torch.float32)
+    n = ns * batch * hq
+    return f[:n * 128].view(ns, batch, hq, 128), f[n * 128:n * 130].view(ns, batch, hq, 2)
+
+
 @pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int4", 16), ("int2_kt", 7), ("int4_g32", 3), ("int2_kt_g64", 8)])
 def test_residual_slices_of_every_remainder(fmt, gq):
     """Nothing but residual tokens, 1 .. 127 of them, in one slice and in several: the slice ends on and beside
@@ -155,29 +163,56 @@ def test_ragged_batches_attend_their_own_lengths_in_any_order(fmt, hq, batch):
 
 
 @pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int2_kt", 8), ("int4_g32", 8), ("mxfp4", 4), ("mxfp4", 12)])
-@pytest.mark.parametrize("L,asked", [(600, 2), (600, 5), (128 * 9 + 40, 14), (0, 3)])
-def test_partials_stay_those_asked_for_when_fewer_splits_run(fmt, gq, L, asked):
-    """A call that writes `out` may run fewer splits than asked for; the workspace it leaves merges to the same rows
-    under the count asked for, whatever was in it before (NaNs here)."""
+@pytest.mark.parametrize("L,asked", [(600, 2), (600, 5), (128 * 9 + 40, 14), (0, 3), (128 * 9 + 40, None)])
+def test_a_call_that_merges_is_its_partials_and_a_merge(fmt, gq, L, asked):
+    """Whatever count is asked for (None: the one bd_choose_splits names) is run: the workspace holds that many
+    partials, whatever was in it before (NaNs here), which merge to the rows of the call that writes `out`, bit for
+    bit, by bd_splitk_combine and, to fp32 rounding, by the formula that the interface states."""
     import torch
     mx = fmt == "mxfp4"
     dt = torch.bfloat16 if mx else torch.float16
-    gen = torch.Generator(device="cuda:0").manual_seed(L + asked)
+    gen = torch.Generator(device="cuda:0").manual_seed(L + (asked or 0))
     gc = B.KVCache(3, 2 * gq, 2, fmt, 1280)
     k, v = (torch.randn((3, 2, L, 128), device="cuda:0", generator=gen).to(dt) for _ in range(2))
     gc.quant_pack_kv(k, v)
     gc.desc.out_type = B.BD_OUT_F32
+    asked = asked or gc.choose_splits()
     q = torch.randn((3, 2 * gq, 128), device="cuda:0", generator=gen).to(dt)
     out, merged, split = (torch.full((3, 2 * gq, 128), x, device="cuda:0") for x in (3.0, 5.0, 7.0))
     ws = gc.workspace(asked)
     ws.fill_(0xFF)
     B.bd_decode_attn(gc.desc, q, gc.packed_len, gc.res_len, 0.088, asked, ws, out)
     B.bd_splitk_combine(gc.desc, ws, asked, merged)
-    gc.decode_attn(q, 0.088, split, num_splits=asked, fused=False)   # really that many
+    rows, ml = (x.double() for x in _partials(ws, asked, 3, 2 * gq))
+    gc.decode_attn(q, 0.088, split, num_splits=asked, fused=False)
     torch.cuda.synchronize()
-    # (fp32 sums in another order; the second comparison also has weights rounded against other running maxima)
-    assert torch.allclose(merged, out, rtol=1e-5, atol=1e-6)
-    assert (split - out).norm() <= 5e-4 * out.norm().clamp(min=1e-30)
+    assert torch.equal(merged, out) and torch.equal(split, out)
+    blocks = (gc.packed_len + 127) // 128
+    assert ((ml[..., 1] > 0).all(-1).all(-1).sum().item() >= min(asked, (blocks + 3) // 4))
+    if L:
+        f = torch.exp2(ml[..., 0] - ml[..., 0].amax(0))
+        formula = (rows * f[..., None]).sum(0) / (ml[..., 1] * f).sum(0)[..., None]
+        assert torch.allclose(formula.float(), out, rtol=1e-5, atol=1e-6)
+    else:
+        assert not rows.any() and not out.any()
+
+
+@pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int2_kt", 8), ("int4_g32", 8), ("mxfp4", 4)])
+def test_the_count_of_a_step_left_to_the_library(fmt, gq):
+    """No count given: the call runs bd_step_splits, and its rows are those of that count given."""
+    import torch
+    dt = torch.bfloat16 if fmt == "mxfp4" else torch.float16
+    for L in (0, 100, 900, 5000, 40000):
+        gen = torch.Generator(device="cuda:0").manual_seed(L)
+        gc = B.KVCache(1, 2 * gq, 2, fmt, L // 128 * 128 + 128)
+        k, v = (torch.randn((1, 2, L, 128), device="cuda:0", generator=gen).to(dt) for _ in range(2))
+        gc.quant_pack_kv(k, v)
+        q = torch.randn((1, 2 * gq, 128), device="cuda:0", generator=gen).to(dt)
+        a, b = (torch.full((1, 2 * gq, 128), x, device="cuda:0", dtype=dt) for x in (3.0, 5.0))
+        gc.decode_attn(q, 0.088, a)
+        gc.decode_attn(q, 0.088, b, num_splits=B.bd_step_splits(gc.desc, gc.packed_len))
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), (fmt, L)
 
 
 def _caches_of(K, V, fmt, gq):
@@ -269,14 +304,6 @@ def test_residual_weights_enter_the_product_whole(fmt, gq, L):
             got = rows[h, i, :L]
             assert torch.equal(got[whole[h]], p[h][whole[h]]), (fmt, gq, L, (got - p[h]).abs().max().item())
             assert (got - p[h]).abs().max() <= 2.0 ** -38
-
-
-def _partials(ws, ns, batch, hq):
-    """The workspace's partial rows [ns, batch, hq, 128] and their (maximum, sum) [ns, batch, hq, 2]."""
-    import torch
-    f = ws.view(torch.float32)
-    n = ns * batch * hq
-    return f[:n * 128].view(ns, batch, hq, 128), f[n * 128:n * 130].view(ns, batch, hq, 2)
 
 
 @pytest.mark.parametrize("fmt", ["int4", "int2_kt", "int4_g32", "mxfp4"])

@@ -201,3 +201,18 @@ def test_split_heuristic_properties():
     assert B.bd_choose_splits(_desc(format=B.BD_FMT_INT4_G32), 32768) == 64
     assert B.bd_choose_splits(_desc(format=B.BD_FMT_INT4_G32, n_q_heads=64), 32768) == 32
     assert B.bd_choose_splits(_desc(format=B.BD_FMT_INT2_G64, n_q_heads=128), 32768) == 32   # two workgroups per KV head
+
+
+@needs_lib
+def test_the_count_of_a_step():
+    for fmt in range(13):
+        for batch, hkv, gq in [(1, 8, 4), (1, 1, 1), (3, 2, 8), (24, 8, 4), (40, 8, 8), (16, 4, 16), (64, 8, 4)]:
+            c = _desc(format=fmt, batch=batch, n_kv_heads=hkv, n_q_heads=hkv * gq)
+            for L in (1, 100, 128, 600, 1024, 3100, 8192, 32768, 131072):
+                assert 1 <= B.bd_step_splits(c, L) <= B.bd_choose_splits(c, L), (fmt, batch, hkv, gq, L)
+    # two rounds of blocks in one workgroup, one round of workgroups for few units, two where the blocks are long
+    assert [B.bd_step_splits(_desc(), L) for L in (1024, 1025, 6016, 32768, 131072)] == [1, 3, 12, 32, 32]
+    assert [B.bd_step_splits(_desc(format=B.BD_FMT_INT2), L) for L in (1024, 32768, 131072)] == [1, 32, 64]
+    assert [B.bd_step_splits(_desc(format=B.BD_FMT_INT4_G32), L) for L in (1024, 32768)] == [2, 64]
+    # bad arguments and an empty cache: one
+    assert B.bd_step_splits(_desc(), 0) == B.bd_step_splits(_desc(), -5) == B.bd_step_splits(_desc(head_dim=64), 999) == 1
