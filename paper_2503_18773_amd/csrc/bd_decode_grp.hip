@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   const uint16_t *kres = a.k_res + unit * kBlock * kD, *vres = a.v_res + unit * kBlock * kD;
   auto kres_row = [&](int t) { return rt0 + t == new_slot ? a.k_new + unit * kD : kres + (size_t)(rt0 + t) * kD; };
   auto vres_row = [&](int t) { return rt0 + t == new_slot ? a.v_new + unit * kD : vres + (size_t)(rt0 + t) * kD; };
-  constexpr bool kResidualFirst = PAGED && grp_waves_per_simd(BITS, G, GQP, KT) > 1;   // (see below)
+  constexpr bool kResidualFirst = grp_waves_per_simd(BITS, G, GQP, KT) > 1 && (PAGED || !KT);   // (see below)
   ResidualSlice res;
   if (!kResidualFirst && nres > 0) res.start(qbase, gq, nres, kres_row, vres_row, wave, lane);
 
@@ -493,11 +493,12 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   size_t bi = unit * a.nbcap + blk;
   if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
   // The residual slice is attended as in the group-128 kernel, its rows requested ahead and the first block on its way
-  // meanwhile -- but in pages with two workgroups per compute unit, where the registers of both and the page's are more
-  // than the 256 there are (up to 11 spilled in the loop; now at most 4), it comes first: 8 sequences of up to 8.2K tokens,
-  // per-token K, 4 bits, 4 heads, groups of 64 / 32 22.7 -> 22.3 / 26.9 -> 25.4 us, 2 bits, groups of 32 25.5 -> 24.7, groups
-  // of 64 with 8 heads 25.3 -> 24.4.  (One workgroup per compute unit would lose by it: groups of 32, 8 heads, contiguous
-  // 36.6 -> 38.7, in pages 36.6 -> 37.0.)
+  // meanwhile -- but with two workgroups per compute unit, where the registers of both (and the page's, or the parameters of
+  // K by channel) are more than the 256 there are (up to 11 spilled in the loop; now at most 4), it comes first: in pages, 8
+  // sequences of up to 8.2K tokens, per-token K, 4 bits, 4 heads, groups of 64 / 32 22.7 -> 22.3 / 26.9 -> 25.4 us, 2 bits,
+  // groups of 32 25.5 -> 24.7, groups of 64 with 8 heads 25.3 -> 24.4; contiguous, 16 of 2K tokens, 2 bits, groups of 32
+  // 18.1 -> 17.2, of 64 15.1 -> 14.8.  (Per-token K, contiguous, has the registers and is as fast either way; one workgroup
+  // per compute unit would lose by it: groups of 32, 8 heads, contiguous 36.6 -> 38.7, in pages 36.6 -> 37.0.)
   if constexpr (kResidualFirst) {
     if (nres > 0) {
       res.start(qbase, gq, nres, kres_row, vres_row, wave, lane);
