@@ -328,7 +328,7 @@ def run(args, workload: str, steps: int, warmup: int, with_cpu: bool) -> dict:
                 c.decode_step(kn, vn, qs[s], sm_scale, outs[li], splits, lazy=args.flush == "lazy")
                 nbytes += algorithmic_bytes(w, *lengths(w.context + s + 1))
             else:
-                c.decode_step(kn, vn, qs[s], sm_scale, outs[li], num_splits=splits, lazy=args.flush == "lazy")
+                c.decode_step(kn, vn, qs[s], sm_scale, outs[li], num_splits=args.splits or None, lazy=args.flush == "lazy")
                 nbytes += algorithmic_bytes(w, c.packed_len, c.res_len)
         step_bytes.append(nbytes)
 

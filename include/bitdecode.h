@@ -127,7 +127,9 @@ int32_t bd_choose_splits(const bd_cache* c, int32_t packed_len);
 
 /* The same for a call that merges its partials itself (bd_decode_attn with `out`, bd_decode_attn_static, the
  * decode steps of a bd_cache): at most bd_choose_splits, and fewer where the merge of that many partials, or
- * its launch, costs more than the workgroups give.  Any other count is run as it is given. */
+ * its launch, costs more than the workgroups give.  Any other count is run as it is given.  (The step of
+ * bd_decode_step_lazy that fills the residual block runs one more workgroup per KV head: bd_choose_splits is the
+ * better count there.) */
 int32_t bd_step_splits(const bd_cache* c, int32_t packed_len);
 
 /* Bytes of device workspace bd_decode_attn needs for `num_splits`: num_splits partial

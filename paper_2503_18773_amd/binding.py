@@ -303,7 +303,12 @@ class KVCache:
 
     def decode_step(self, k_new, v_new, q, softmax_scale: float, out, num_splits: int | None = None, stream=None,
                     lazy: bool = False):
-        ns = bd_step_splits(self.desc, self.packed_len) if num_splits is None else num_splits
+        ns = num_splits
+        if ns is None:
+            # (the lazy step that fills the residual has a quantizing workgroup per KV head beside the attending ones:
+            # where those are one per compute unit, some then share one, 128K tokens 40.4 us against 32.9)
+            fills = lazy and self.res_len == 127
+            ns = self.choose_splits() if fills else bd_step_splits(self.desc, self.packed_len)
         step = bd_decode_step_lazy if lazy else bd_decode_step
         self.packed_len, self.res_len = step(self.desc, k_new, v_new, q, self.packed_len, self.res_len,
                                              softmax_scale, ns, self.workspace(ns), out, stream)

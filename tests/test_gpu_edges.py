@@ -31,7 +31,7 @@ def _partials(ws, ns, batch, hq):
 
 @pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int4", 16), ("int2_kt", 7), ("int4_g32", 3), ("int2_kt_g64", 8)])
 def test_residual_slices_of_every_remainder(fmt, gq):
-    """Nothing but residual tokens, 1 .. 127 of them, in one slice and in several: the slice ends on and beside
+    """Nothing but residual tokens, 1 .. 127 of them, in one slice and in several, some empty: the slice ends on and beside
     the steps of the second product (4 tokens a load, 32 a k-step).  Scores and weights are fp32 (weights enter
     the product whole), so the bar is fp32's: a score is a sum of 128 products whose magnitudes add up to
     about 1e2, which the matrix unit rounds (truncating) at 2^-23 of its size, i.e. 1e-5 in the exponent; the
@@ -41,7 +41,7 @@ def test_residual_slices_of_every_remainder(fmt, gq):
         K, V, oc, gc = _int_cache_pair(w, 128)
         q = W.make_q(w)
         ref = O.decode_attn(oc, q, W.softmax_scale(w))
-        for ns in (1, 3):
+        for ns in (1, 3, 9):   # (9: empty slices among them at L < 9)
             ma, rl = attn_errors(_attend_f32(gc, w, q, ns), ref)
             assert rl <= 1e-5, f"{fmt} gq={gq} L={L} splits={ns}: rel-L2 {rl:.2e} max-abs {ma:.2e}"
 
@@ -213,6 +213,32 @@ def test_the_count_of_a_step_left_to_the_library(fmt, gq):
         gc.decode_attn(q, 0.088, b, num_splits=B.bd_step_splits(gc.desc, gc.packed_len))
         torch.cuda.synchronize()
         assert torch.equal(a, b), (fmt, L)
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int2_kt", "int4_g32"])
+def test_the_count_of_a_lazy_step_that_fills_the_residual(fmt):
+    """It has a quantizing workgroup per KV head beside the attending ones and runs bd_choose_splits of them; the step
+    after it, and the same step in the other order, bd_step_splits."""
+    import torch
+    L = 128 * 200 + 127
+    gen = torch.Generator(device="cuda:0").manual_seed(7)
+    k, v = (torch.randn((1, 8, L, 128), device="cuda:0", generator=gen).half() for _ in range(2))
+    kn, vn = (torch.randn((2, 1, 8, 128), device="cuda:0", generator=gen).half() for _ in range(2))
+    q = torch.randn((1, 32, 128), device="cuda:0", generator=gen).half()
+    for lazy in (True, False):
+        a, b = (B.KVCache(1, 32, 8, fmt, L + 1 + 128) for _ in range(2))
+        for step in range(2):
+            outs = [torch.full((1, 32, 128), x, device="cuda:0", dtype=torch.float16) for x in (3.0, 5.0)]
+            if step == 0:
+                a.quant_pack_kv(k, v)
+                b.quant_pack_kv(k, v)
+            counts = B.bd_choose_splits(b.desc, b.packed_len), B.bd_step_splits(b.desc, b.packed_len)
+            assert counts[0] > counts[1] or "_g" in fmt
+            a.decode_step(kn[step], vn[step], q, 0.088, outs[0], lazy=lazy)
+            b.decode_step(kn[step], vn[step], q, 0.088, outs[1], lazy=lazy, num_splits=counts[0 if lazy and step == 0 else 1])
+            torch.cuda.synchronize()
+            assert a.res_len == step and torch.equal(*outs), (fmt, lazy, step, counts)
+            assert all(np.array_equal(a.host_buffer(i), b.host_buffer(i)) for i in range(6))
 
 
 def _caches_of(K, V, fmt, gq):
