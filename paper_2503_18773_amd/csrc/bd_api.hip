@@ -157,15 +157,18 @@ int32_t bd_step_splits(const bd_cache* c, int32_t packed_len) {
   const int quanta = std::max(1, ((packed_len + kBlock - 1) / kBlock + 3) / 4);
   const int gq = c->n_q_heads / c->n_kv_heads;
   // Two rounds of blocks in one workgroup take no longer than one round in two and the merge behind it, and are one
-  // launch less (1K tokens, up to 4 heads per KV head: 8.5 -> 8.4 us with 8 units, 10.1 -> 8.8 with 128, issued one by
-  // one 10.2 -> 8.3; with more heads, or in groups of 64 and 32, the second round costs more than the merge).
+  // launch less (1K tokens, up to 4 heads per KV head: 9.0 -> 8.3 us in a graph and 9.9 -> 8.5 issued one by one with 8
+  // units, 11.2 -> 10.3 and 11.2 -> 9.5 with 128; behind 104 residual tokens in one slice 10.6 -> 11.8; with more heads, or
+  // in groups of 64 and 32, the second round costs more than the merge).
   if (fmt_is_int(c->format) && fmt_group(c->format) == kBlock && gq <= 4 && quanta <= 2) return 1;
   // Few units, hence many partials per output row: the merge then costs more than a second workgroup per compute
   // unit gives, if the kernel's arithmetic leaves one the time (4-bit codes with up to 4 heads per KV head: any
   // context; other integer codes up to 3.5 blocks per wave; MXFP4 around two).  A step, 8 units, 4 bits: 24.6K tokens
-  // 13.1 us with 48 splits, 12.1 with 32; 32K 13.2 / 12.6; 48K 17.5 (94 splits) / 14.7; 128K 28.9 / 27.9; 2 bits 32K 12.1 /
-  // 11.5 but 128K 20.3 / 21.9; MXFP4 32K 16.3 / 15.6; 4 units, 128K 19.5 (128) / 18.6 (64); one unit, 128K 14.3 (256)
-  // / 13.0 (128).  From 17 units on the two are equal, and the groups of 64 and 32 want the waves.
+  // 13.0 us with 48 splits, 12.2 with 32; 32K 13.5 / 13.0; 48K 19.6 (94 splits) / 15.9; 128K 29.4 / 28.9; 2 bits 32K 12.2 /
+  // 11.5, 56K 14.5 / 15.2, 128K 22.2 / 23.7; MXFP4 20K 12.6 (40) / 13.0, 24.6K 15.5 (48) / 13.5, 32K 16.1 / 15.7, 40K 16.7 / 16.1,
+  // 48K 16.9 / 18.4; 4 units, 4 bits, 128K 20.1 (128) / 19.1 (64), MXFP4 64K 17.5 / 16.1; one unit, 64K 12.0 (128) / 12.1 (64),
+  // 128K 14.9 (256) / 13.8 (128) / 16.3 (64), 2 bits 13.6 / 13.0 / 15.0, MXFP4 16.7 / 16.0.  From 17 units on the two are
+  // equal, and the groups of 64 and 32 want the waves.
   if (fmt_group(c->format) == kBlock && units <= 16) {
     const int one_round = units == 1 ? 128 : (int)(256 / units);
     if (quanta <= one_round) return std::min(most, quanta);

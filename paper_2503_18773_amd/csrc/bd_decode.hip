@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   using E = FmtF8<BITS>;
   // The next block's keys are requested as soon as this block's are consumed, not at the block's end, where the
   // arithmetic is short or the blocks are (8 x 32K tokens, 2 bits: 32.5 -> 29.3 us, with 8 heads 39.0 -> 37.7; 128K
-  // tokens, 4 bits: 26.3 -> 25.8, but with 8 heads 26.8 -> 28.2).
+  // tokens, 4 bits: 26.3 -> 25.8, but with 8 heads 26.8 -> 28.2; up to 4 heads measured with Q' in four pieces).
   constexpr bool kEarly = kF8 || (BITS == 2 && GQP == 8);
 
   __shared__ __attribute__((aligned(16))) unsigned char smem_raw[cmax(sizeof(ML), kWaves * sizeof(WL))];
