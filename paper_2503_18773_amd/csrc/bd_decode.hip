@@ -145,9 +145,11 @@ struct WaveLds<4> {
   uint32_t c8[4][8];       // per V token: centre code as e4m3, in B-operand order ([lane group][register])
   float zq[4];
 };
+// (every column's partial result, the copies of a head included; rows padded by 16 bytes: the 16 columns write the same
+// offset of their rows)
 template <int GQP>
 struct MergeLds {
-  float o[kWaves][GQP][kD];
+  float o[kWaves][16][kD + 4];
   float m[kWaves][GQP], l[kWaves][GQP], z[kWaves][GQP];
 };
 
@@ -515,7 +517,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 #pragma unroll
       for (int k = 0; k < kQueryPieces; ++k) {
         const float unit = pow2i(ek - 5 * k);
-        uint32_t ev = 0, od = 0;   // channels 0, 2, 4, 6 / 1, 3, 5, 7 of the lane's eight
+        uint32_t ev = any_bits(), od = any_bits();   // channels 0, 2, 4, 6 / 1, 3, 5, 7 of the lane's eight
         if (k < kQueryPieces - 1) {
           ev = e4m3_piece<true>(e4m3_piece<false>(ev, t[0], t[2], unit), t[4], t[6], unit);
           od = e4m3_piece<true>(e4m3_piece<false>(od, t[1], t[3], unit), t[5], t[7], unit);
@@ -788,7 +790,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
           l_run = __builtin_fmaf(e[r], par.y, l_run);
           z_run = __builtin_fmaf(e[r], par.z, z_run);
         }
-        uint32_t u[4] = {0u, 0u, 0u, 0u}, from[4];
+        uint32_t u[4] = {any_bits(), any_bits(), any_bits(), any_bits()}, from[4];
         float unit = 1.0f / (1 << E::kTop);
 #pragma unroll
         for (int k = 0; k < kWeightPieces; ++k) {
@@ -893,37 +895,21 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   z_run = head_sum<COPIES>(z_run);
   __syncthreads();   // every wave is done with its WaveLds before the space is reused
   ML& ml = *reinterpret_cast<ML*>(smem_raw);
-  // (all lane movement first, in passes over independent values, then one predicated run of stores)
+  // The column groups' shares are added below, by the threads that merge the waves: 12 (4) more LDS reads there for 288 (32)
+  // DPP moves and adds of every wave here.  A wave alone on its SIMD issues one instruction every 4 to 5 cycles, and at the
+  // end of the kernel nothing hides them: 0.25 us of a launch (32K tokens, 8 units: 12.6 -> 12.35 a step; with the shorter
+  // forms of masks and pieces, bd_fmt.h, 12.1).
 #pragma unroll
-  for (int mt = 0; mt < 8; ++mt) oacc[mt] -= xacc[0];
-  if (COPIES == 2) {
+  for (int mt = 0; mt < 8; ++mt) {
+    f4_t o;
 #pragma unroll
-    for (int mt = 0; mt < 8; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) oacc[mt][r] += dpp_f<kRowShl8>(oacc[mt][r]);
+    for (int r = 0; r < 4; ++r) o[r] = kF8 ? oacc[mt][r] - xacc[0] : (oacc[mt][r] - xacc[0]) * kTwo24;
+    *reinterpret_cast<f4_t*>(&ml.o[wave][col][16 * mt + 4 * g]) = o;
   }
-  if constexpr (kF8) {   // the column groups hold the pieces' shares: column group cg sums M tiles 2 cg and 2 cg + 1
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      f4_t o;
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        o[r] = reduce_scatter4(oacc[i][r], oacc[2 + i][r], oacc[4 + i][r], oacc[6 + i][r], cg);
-      *reinterpret_cast<f4_t*>(&ml.o[wave][head][16 * (2 * cg + i) + 4 * g]) = o;
-    }
-  }
-  if (col < GQP) {
-    if constexpr (!kF8) {
-#pragma unroll
-      for (int mt = 0; mt < 8; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ml.o[wave][col][16 * mt + 4 * g + r] = oacc[mt][r] * kTwo24;
-    }
-    if (g == 0) {
-      ml.m[wave][col] = m_run;
-      ml.l[wave][col] = l_run;
-      ml.z[wave][col] = z_run;
-    }
+  if (lane < GQP) {
+    ml.m[wave][col] = m_run;
+    ml.l[wave][col] = l_run;
+    ml.z[wave][col] = z_run;
   }
   __syncthreads();
 #pragma unroll
@@ -941,8 +927,15 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
           const float f = __builtin_amdgcn_exp2f(ml.m[w][h] - M);
           L += f * ml.l[w][h];
           Z += f * ml.z[w][h];
-          o0 += f * ml.o[w][h][c0];
-          o1 += f * ml.o[w][h][c0 + 1];
+          float2 o = *reinterpret_cast<const float2*>(&ml.o[w][h][c0]);
+#pragma unroll
+          for (int k = 1; k < COPIES; ++k) {
+            const float2 s = *reinterpret_cast<const float2*>(&ml.o[w][GQP * k + h][c0]);
+            o.x += s.x;
+            o.y += s.y;
+          }
+          o0 += f * o.x;
+          o1 += f * o.y;
         }
         if (nres > 0) {
           const float f = __builtin_amdgcn_exp2f(res_m[h] - M);

@@ -31,6 +31,28 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_f(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
 }
+// The value of the lane 16 (32) away joined to this lane's: v_permlane16_swap / 32_swap of two copies leave the pair's
+// values in the two results, in the same order in both lanes.  (8 cycles and no wait; a shuffle through LDS takes 56.)
+template <class Op>
+__device__ __forceinline__ float join_xor16(float x, Op op) {
+  const u2_t r = __builtin_bit_cast(u2_t, __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false));
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <class Op>
+__device__ __forceinline__ float join_xor32(float x, Op op) {
+  const u2_t r = __builtin_bit_cast(u2_t, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false));
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+struct Add {
+  __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+};
+struct Max {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+// over the four lane groups (lanes col, col + 16, col + 32, col + 48)
+template <class Op>
+__device__ __forceinline__ float join_groups(float x, Op op) { return join_xor32(join_xor16(x, op), op); }
+
 // sum over the 16 lanes of a row, result in every lane
 __device__ __forceinline__ float row_sum16(float x) {
   x += dpp_f<kQuadSwap1>(x);
@@ -66,17 +88,13 @@ template <int COPIES>
 __device__ __forceinline__ float head_sum(float x) {
   if (COPIES == 4) x += dpp_f<kRowRor4>(x);
   if (COPIES >= 2) x += dpp_f<kRowRor8>(x);
-  x += __shfl_xor(x, 16);
-  x += __shfl_xor(x, 32);
-  return x;
+  return join_groups(x, Add());
 }
 template <int COPIES>
 __device__ __forceinline__ float head_max(float x) {
   if (COPIES == 4) x = fmaxf(x, dpp_f<kRowRor4>(x));
   if (COPIES >= 2) x = fmaxf(x, dpp_f<kRowRor8>(x));
-  x = fmaxf(x, __shfl_xor(x, 16));
-  x = fmaxf(x, __shfl_xor(x, 32));
-  return x;
+  return join_groups(x, Max());
 }
 
 // Contiguous cache, fused step whose token fills the residual block (Sec. IV-B(1)): how the attention launch

@@ -8,6 +8,13 @@
 namespace bd {
 namespace {
 
+// A mask in a scalar register: an instruction with a literal is twice as long, and a wave alone on its SIMD issues one of
+// those every 5.1 cycles, the short form every 4.
+__device__ __forceinline__ uint32_t scalar_mask(uint32_t m) {
+  asm("" : "+s"(m));
+  return m;
+}
+
 // ---- format traits ---------------------------------------------------------------------
 // One lane loads WORDS 32-bit words (32 codes) per 16-row tile.  k-step j (of 4) of the tile
 // consumes 8 codes as 4 VGPRs; VGPR v holds two codes that arrive multiplied by 1/un(v).
@@ -40,10 +47,10 @@ struct Fmt<4> {
   __device__ static h8_t dequant(const uint32_t* w, int j) {
     const uint32_t x = w[j], y = x >> 8;
     u4_t r;
-    r[0] = x & 0x000F000Fu;   // nibbles 0, 4
-    r[1] = x & 0x00F000F0u;   // nibbles 1, 5 (x16)
-    r[2] = y & 0x000F000Fu;   // nibbles 2, 6
-    r[3] = y & 0x00F000F0u;   // nibbles 3, 7 (x16)
+    r[0] = x & scalar_mask(0x000F000Fu);   // nibbles 0, 4
+    r[1] = x & scalar_mask(0x00F000F0u);   // nibbles 1, 5 (x16)
+    r[2] = y & scalar_mask(0x000F000Fu);   // nibbles 2, 6
+    r[3] = y & scalar_mask(0x00F000F0u);   // nibbles 3, 7 (x16)
     return __builtin_bit_cast(h8_t, r);
   }
 };
@@ -69,10 +76,10 @@ struct Fmt<2> {
   __device__ static h8_t dequant(const uint32_t* w, int j) {
     const uint32_t x = (j & 1) ? (w[j >> 1] >> 8) : w[j >> 1];
     u4_t r;
-    r[0] = x & 0x00030003u;   // crumbs 0, 8      (of the selected byte pair)
-    r[1] = x & 0x000C000Cu;   // crumbs 1, 9  (x4)
-    r[2] = x & 0x00300030u;   // crumbs 2, 10 (x16)
-    r[3] = x & 0x00C000C0u;   // crumbs 3, 11 (x64)
+    r[0] = x & scalar_mask(0x00030003u);   // crumbs 0, 8      (of the selected byte pair)
+    r[1] = x & scalar_mask(0x000C000Cu);   // crumbs 1, 9  (x4)
+    r[2] = x & scalar_mask(0x00300030u);   // crumbs 2, 10 (x16)
+    r[3] = x & scalar_mask(0x00C000C0u);   // crumbs 3, 11 (x64)
     return __builtin_bit_cast(h8_t, r);
   }
 };
@@ -124,8 +131,8 @@ struct FmtF8<4> {   // both operands 8 bits wide: byte by byte the same order on
     i8_t r;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      r[2 * i] = (int)(w[i] & 0x0F0F0F0Fu);              // codes 0, 2, 4, 6
-      r[2 * i + 1] = (int)((w[i] >> 4) & 0x0F0F0F0Fu);   // codes 1, 3, 5, 7
+      r[2 * i] = (int)(w[i] & scalar_mask(0x0F0F0F0Fu));              // codes 0, 2, 4, 6
+      r[2 * i + 1] = (int)((w[i] >> 4) & scalar_mask(0x0F0F0F0Fu));   // codes 1, 3, 5, 7
     }
     return r;
   }
@@ -147,8 +154,8 @@ struct FmtF8<2> {
     i8_t r = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      r[2 * i] = (int)(w[i] & 0x33333333u);              // codes 0, 2, .. 14
-      r[2 * i + 1] = (int)((w[i] >> 2) & 0x33333333u);   // codes 1, 3, .. 15
+      r[2 * i] = (int)(w[i] & scalar_mask(0x33333333u));              // codes 0, 2, .. 14
+      r[2 * i + 1] = (int)((w[i] >> 2) & scalar_mask(0x33333333u));   // codes 1, 3, .. 15
     }
     return r;
   }
@@ -160,6 +167,12 @@ struct FmtF8<2> {
   __device__ static constexpr int b_byte(int x) { return (x & 7) >> 1; }
 };
 
+// A register that is about to be written in two halves.  (A zero, or an undefined value, costs a move each time.)
+__device__ __forceinline__ uint32_t any_bits() {
+  uint32_t x;
+  asm volatile("" : "=v"(x));
+  return x;
+}
 // Two values as e4m3 pieces in units of `unit` (a power of two), rounded to nearest, into half `hi` of a register;
 // the values are left with what the piece does not hold: at most 2^-5 of the largest, so that pieces in units 2^-5
 // apart stay below the same bound and take five more bits each.

@@ -86,8 +86,7 @@ struct ResidualSlice {
           mx = fmaxf(mx, s[u][r]);
         }
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      mx = join_groups(mx, Max());
       if (t0) {
         mx = fmaxf(m, mx);
         const float alpha = __builtin_amdgcn_exp2f(m - mx);
@@ -123,8 +122,7 @@ struct ResidualSlice {
         o[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v1, piece, o[1], 0, 0, 0);
       }
     }
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
+    l = join_groups(l, Add());
     if (col >= GQP) return;
 #pragma unroll
     for (int r = 0; r < 4; ++r)   // row 4g + r of the two tiles
