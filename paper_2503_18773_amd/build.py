@@ -13,6 +13,8 @@ LIB = os.path.join(HERE, "libbitdecode.so")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first 14 dwords of scalar kernel arguments are in registers when a wave starts
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wno-unused-command-line-argument", "-Wno-ignored-optimization-argument",
     "-I", os.path.join(ROOT, "include"),
 ]

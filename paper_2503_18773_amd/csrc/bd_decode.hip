@@ -103,6 +103,7 @@ struct DecodeArgs {
   int res_len;
   int num_splits;
   float scale_log2; // softmax_scale * log2(e)
+  uint32_t res_scale;   // residual_scale(num_splits)
   // paged cache: block n of sequence b is page block_table[b][n], pool index page * Hkv + head;
   // nb and res_len then come from seq_lens[b]
   const int32_t* block_table;
@@ -164,13 +165,15 @@ constexpr size_t cmax(size_t x, size_t y) { return x > y ? x : y; }
 //      presents their P' as its part of the B operand (zero in the k-steps it does not own);
 //      no probability moves between lanes, and the column groups' partial O^T are added
 //      once, after the loop.
-// SINGLE: no wave has more than one block (short contexts); the host picks the instance.
+// SINGLE: no wave has more than one block (short contexts) and no residual slice more than kResShort tokens; the host
+//      picks the instance.
 // PAGED: blocks are found through the block table and every sequence has its own length.
 // KT: K is quantized per token (Sec. IV-C(1)):  S[t] = s_t * sum_c Q_c code_tc + z_t * sum_c Q_c,
 //     so Q' = Q is prepared once per kernel instead of once per block and the per-token scale
 //     and zero are applied to the kept S^T values.
 template <int BITS, int GQP, bool SINGLE, bool PAGED, bool KT>
-__global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, DecodeArgs a) {
+  const HotArgs<PAGED> hot(BD_HOT_NAMES, a.k_params, a.k_res);
   using F = Fmt<BITS>;
   using WL = WaveLds<GQP>;
   using ML = MergeLds<GQP>;
@@ -192,32 +195,32 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) float q_s[HP > 1 ? GQP : 1][kD];   // larger groups: queries, normalised; padding heads zero
   __shared__ int kq_s[HP > 1 ? GQP : 1];                                     // larger groups: each head's normalising exponent
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(a.seq_lens, lane, seq_len, INT32_MAX) : blockIdx.z;
-  const bool flush_after = a.flush_mode == kFlushAfter;
+  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted) : blockIdx.z;
+  const bool flush_after = hot.flush_mode == kFlushAfter;
   const int split = (int)blockIdx.x - (flush_after ? 1 : 0);
   const int col = lane & 15, g = lane >> 4;            // MFMA column and contraction group
   const int head = col % GQP, cg = col / GQP;          // head carried by the column; column group
   // Query groups of more than 16 heads are taken 16 at a time by ceil(g_q / 16) workgroups per
   // (split, KV head), each of which reads the cache once.
   int hkv = blockIdx.y, head0 = 0;
-  if (GQP == 16 && a.gq > 16) {
-    const int nchunk = (a.gq + 15) >> 4;
+  if (GQP == 16 && hot.gq > 16) {
+    const int nchunk = (hot.gq + 15) >> 4;
     hkv = blockIdx.y / nchunk;
     head0 = 16 * (blockIdx.y % nchunk);
   }
-  const int gq = min(a.gq - head0, 16);                // heads of this workgroup
+  const int gq = min(hot.gq - head0, 16);                // heads of this workgroup
   WL& wl = reinterpret_cast<WL*>(smem_raw)[wave];
 
-  const size_t unit = (size_t)b * a.n_kv_heads + hkv;
-  int nb = a.nb, res_len = a.res_len;
-  int new_slot = a.new_slot;   // fused step: residual slot of the token that is still in the caller's buffer, or -1
+  const size_t unit = (size_t)b * hot.n_kv_heads + hkv;
+  int nb = hot.nb, res_len = hot.res_len;
+  int new_slot = hot.new_slot;   // fused step: residual slot of the token that is still in the caller's buffer, or -1
   int flush_page = -1;         // paged fused step that fills the residual: the page the block goes to
   if (PAGED) {
     int len = seq_len;
     new_slot = -1;
-    if (a.step && len >= 0) {
+    if (hot.step && len >= 0) {
       // fused step: this step's token counts (unless it needs a page the table does not name) and
       // the length is raised only after this kernel.  With a.k_new the token has not been appended
       // by a kernel of its own: it is read from the caller's buffer and filed by this launch, and
@@ -226,10 +229,10 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       int e = -1;
       if (len % kBlock == kBlock - 1) {
         const int n = len / kBlock;
-        e = n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1;
-        ok = e >= 0 && e < a.num_pages;
+        e = n < hot.max_pages ? scalar_load(hot.block_table + (size_t)b * hot.max_pages + n) : -1;
+        ok = e >= 0 && e < hot.num_pages;
       }
-      if (a.k_new) {
+      if (hot.append) {
         if (!ok) {
           if (a.status && tid == 0 && split == 0) atomicOr(a.status, 2);   // the token is dropped
         } else if (len % kBlock < kBlock - 1) {
@@ -253,15 +256,15 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   // workgroups of a (sequence, KV head) unit read one contiguous window of the cache.  (Contiguous
   // ranges per split put the workgroups' streams a power of two apart for the usual split counts,
   // and then all of them march over the same memory channels.)
-  const int blk0 = split * kWaves, blk1 = nb, bstep = kWaves * a.num_splits;
+  const int blk0 = split * kWaves, blk1 = nb, bstep = kWaves * hot.num_splits;
   if (flush_after && split < 0 && head0 != 0) return;   // (one quantizing workgroup per KV head is enough)
-  if (!PAGED && a.flush_mode != kFlushNone && head0 == 0 &&
-      (flush_after ? split < 0 : split == (a.flush_blk / kWaves) % a.num_splits)) {
+  if (!PAGED && hot.flush_mode != kFlushNone && head0 == 0 &&
+      (flush_after ? split < 0 : split == (a.flush_blk / kWaves) % hot.num_splits)) {
     // The step's token completes the residual block: file it, then quantize the 128 rows as block
     // flush_blk.  kFlushFirst: this workgroup is the block's only reader in this launch (one workgroup per
     // split and KV head: query groups of up to 16 heads).  kFlushAfter: nobody reads the block here, and
     // the others read the residual rows, which only gain the row they take from k_new / v_new anyway.
-    uint16_t* kr = const_cast<uint16_t*>(a.k_res) + unit * kBlock * kD;
+    uint16_t* kr = const_cast<uint16_t*>(hot.k_res) + unit * kBlock * kD;
     uint16_t* vr = const_cast<uint16_t*>(a.v_res) + unit * kBlock * kD;
     if (tid < 32) {
       const bool is_v = tid >= 16;
@@ -269,9 +272,9 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       *reinterpret_cast<u4_t*>((is_v ? vr : kr) + (kBlock - 1) * kD + 8 * (tid & 15)) = *reinterpret_cast<const u4_t*>(src);
     }
     workgroup_global_sync();
-    quant_block<BITS, KT, kBlock>(kr, vr, const_cast<uint32_t*>(a.k_codes), const_cast<uint32_t*>(a.v_codes),
-                                  const_cast<uint32_t*>(a.k_params), const_cast<uint32_t*>(a.v_params),
-                                  unit * a.nbcap + a.flush_blk);
+    quant_block<BITS, KT, kBlock>(kr, vr, const_cast<uint32_t*>(hot.k_codes), const_cast<uint32_t*>(a.v_codes),
+                                  const_cast<uint32_t*>(hot.k_params), const_cast<uint32_t*>(a.v_params),
+                                  unit * hot.nbcap + a.flush_blk);
     if (flush_after) return;   // (the whole workgroup: split < 0 is uniform)
     workgroup_global_sync();
   }
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     // lazy flush: the extra workgroup of a (sequence, KV head) packs the 128 rows into the page if this
     // step's token completes them, and does nothing else
     if (flush_page >= 0 && head0 == 0) {
-      uint16_t* kr = const_cast<uint16_t*>(a.k_res) + unit * kBlock * kD;
+      uint16_t* kr = const_cast<uint16_t*>(hot.k_res) + unit * kBlock * kD;
       uint16_t* vr = const_cast<uint16_t*>(a.v_res) + unit * kBlock * kD;
       if (tid < 32) {
         const bool is_v = tid >= 16;
@@ -287,17 +290,17 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
         *reinterpret_cast<u4_t*>((is_v ? vr : kr) + (kBlock - 1) * kD + 8 * (tid & 15)) = *reinterpret_cast<const u4_t*>(src);
       }
       workgroup_global_sync();
-      quant_block<BITS, KT, kBlock>(kr, vr, const_cast<uint32_t*>(a.k_codes), const_cast<uint32_t*>(a.v_codes),
-                                    const_cast<uint32_t*>(a.k_params), const_cast<uint32_t*>(a.v_params),
-                                    (size_t)flush_page * a.n_kv_heads + hkv);
+      quant_block<BITS, KT, kBlock>(kr, vr, const_cast<uint32_t*>(hot.k_codes), const_cast<uint32_t*>(a.v_codes),
+                                    const_cast<uint32_t*>(hot.k_params), const_cast<uint32_t*>(a.v_params),
+                                    (size_t)flush_page * hot.n_kv_heads + hkv);
     }
     return;
   }
-  if (PAGED && !flush_after && flush_page >= 0 && split == ((nb - 1) / kWaves) % a.num_splits) {
+  if (PAGED && !flush_after && flush_page >= 0 && split == ((nb - 1) / kWaves) % hot.num_splits) {
     // This step's token completes the residual (Sec. IV-B(1)): the 128 rows become block nb - 1, which
     // this workgroup alone reads in this launch.  (One workgroup per split and KV head: the host takes
     // this path only for query groups of up to 16 heads.)
-    uint16_t* kr = const_cast<uint16_t*>(a.k_res) + unit * kBlock * kD;
+    uint16_t* kr = const_cast<uint16_t*>(hot.k_res) + unit * kBlock * kD;
     uint16_t* vr = const_cast<uint16_t*>(a.v_res) + unit * kBlock * kD;
     if (tid < 32) {
       const bool is_v = tid >= 16;
@@ -305,14 +308,14 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       *reinterpret_cast<u4_t*>((is_v ? vr : kr) + (kBlock - 1) * kD + 8 * (tid & 15)) = *reinterpret_cast<const u4_t*>(src);
     }
     workgroup_global_sync();   // the row is read back below, and the block further down, by other threads of this workgroup
-    quant_block<BITS, KT, kBlock>(kr, vr, const_cast<uint32_t*>(a.k_codes), const_cast<uint32_t*>(a.v_codes),
-                                  const_cast<uint32_t*>(a.k_params), const_cast<uint32_t*>(a.v_params),
-                                  (size_t)flush_page * a.n_kv_heads + hkv);
+    quant_block<BITS, KT, kBlock>(kr, vr, const_cast<uint32_t*>(hot.k_codes), const_cast<uint32_t*>(a.v_codes),
+                                  const_cast<uint32_t*>(hot.k_params), const_cast<uint32_t*>(a.v_params),
+                                  (size_t)flush_page * hot.n_kv_heads + hkv);
     workgroup_global_sync();
   }
   // this workgroup's slice of the fp16 residual tokens
-  const int rt0 = (res_len * split) / a.num_splits, rt1 = (res_len * (split + 1)) / a.num_splits;
-  const uint16_t* qbase = a.q + ((size_t)b * a.n_q_heads + hkv * a.gq + head0) * kD;
+  const int rt0 = residual_bound(res_len, split, hot.num_splits, a.res_scale), rt1 = residual_bound(res_len, split + 1, hot.num_splits, a.res_scale);
+  const uint16_t* qbase = hot.q + ((size_t)b * (hot.gq * hot.n_kv_heads) + hkv * hot.gq + head0) * kD;
 
   float m_run = -INFINITY;   // running max of this lane's head (log2 units), equal in all lanes of the head
   float l_run = 0.0f;        // running sum of p over this lane's own tokens
@@ -340,9 +343,9 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   // contiguous cache, page * Hkv + head for the paged one.
   auto issue_kpar = [&](size_t bi) {
     if constexpr (KT) {
-      kp2 = *reinterpret_cast<const u2_t*>(a.k_params + bi * kBlock + 2 * lane);
+      kp2 = *reinterpret_cast<const u2_t*>(hot.k_params + bi * kBlock + 2 * lane);
     } else {
-      const uint32_t* pp = a.k_params + bi * kD;
+      const uint32_t* pp = hot.k_params + bi * kD;
       kp0 = *reinterpret_cast<const u4_t*>(pp + run0);
       kp1 = *reinterpret_cast<const u4_t*>(pp + run1);
     }
@@ -351,7 +354,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     vp2 = *reinterpret_cast<const u2_t*>(a.v_params + bi * kBlock + 2 * lane);
   };
   auto issue_ktile = [&](size_t bi, int T) {
-    const uint32_t* kp = a.k_codes + bi * (size_t)(kBlock * KROW) + WORDS * g;
+    const uint32_t* kp = hot.k_codes + bi * (size_t)(kBlock * KROW) + WORDS * g;
     kraw[T] = load_raw<WORDS>(kp + (size_t)row_token(T) * KROW);
   };
   auto issue_vtile = [&](size_t bi, int mt) {
@@ -372,34 +375,41 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
   } else {
 #pragma unroll
     for (int p = 0; p < HP; ++p) {
-      const int h = 4 * p + (tid >> 6);   // thread tid: head h, channels 2*(tid%64), +1
+      const int h = 4 * p + wave;   // thread tid: head h, channels 2*(tid%64), +1
       qld[p] = h < gq ? *reinterpret_cast<const uint32_t*>(qbase + h * kD + 2 * lane) : 0u;
     }
   }
-  const uint16_t *kres = a.k_res + unit * kBlock * kD, *vres = a.v_res + unit * kBlock * kD;
+  // fused step: the new token, which goes to the residual buffers for later steps, at the end of the kernel (a store here
+  // would wait for all that is requested above and below)
+  const bool files = new_slot >= 0 && split == 0 && head0 == 0 && tid < 32 && res_len < kBlock && (PAGED || hot.flush_mode == kFlushNone);
+  const u4_t filed = *reinterpret_cast<const u4_t*>((files ? (tid >= 16 ? a.v_new : a.k_new) + unit * kD : qbase) + 8 * (tid & 15));
+  const uint16_t *kres = hot.k_res + unit * kBlock * kD, *vres = a.v_res + unit * kBlock * kD;
   // rows of the residual slice: the newest token of a fused step is read from where the caller left it
   const int nres = rt1 - rt0;
-  auto kres_row = [&](int t) { return rt0 + t == new_slot ? a.k_new + unit * kD : kres + (size_t)(rt0 + t) * kD; };
-  auto vres_row = [&](int t) { return rt0 + t == new_slot ? a.v_new + unit * kD : vres + (size_t)(rt0 + t) * kD; };
+  ResidualRows rows;
+  rows.new_at = new_slot >= 0 ? new_slot - rt0 : -1;
+  rows.k = kres + (size_t)rt0 * kD;
+  rows.v = vres + (size_t)rt0 * kD;
+  rows.kn = a.k_new + ((long)unit - rows.new_at) * kD;
+  rows.vn = a.v_new + ((long)unit - rows.new_at) * kD;
   ResidualSlice res;
-  if (nres > 0) res.start(qbase, gq, nres, kres_row, vres_row, wave, lane);
-  if (new_slot >= 0 && split == 0 && head0 == 0 && tid < 32 && res_len < kBlock && (PAGED || a.flush_mode == kFlushNone)) {   // fused step: file the new token for later steps
-    const bool is_v = tid >= 16;
-    const uint16_t* src = (is_v ? a.v_new : a.k_new) + unit * kD + 8 * (tid & 15);
-    uint16_t* dst = const_cast<uint16_t*>(is_v ? a.v_res : a.k_res) + (unit * kBlock + new_slot) * kD + 8 * (tid & 15);
-    *reinterpret_cast<u4_t*>(dst) = *reinterpret_cast<const u4_t*>(src);
-  }
+  auto start_slice = [&]() {
+    if (nres > 0) res.template start<true, !SINGLE>(qbase, gq, nres, rows, wave, lane);
+  };
+  auto attend_slice = [&]() {
+    if (nres > 0) res.template attend<GQP, true, !SINGLE>(nres, a.scale_log2, *reinterpret_cast<ML*>(smem_raw), res_o, res_m, res_l, wave, lane);
+  };
   // (Where exactly the values are requested is fixed at compile time, so that the compiler knows
   // how many loads are in flight behind the one it waits for: half way through QK^T.)
   const int my_blocks = blk1 > blk0 + wave ? (blk1 - blk0 - wave + bstep - 1) / bstep : 0;
   // Paged: table entry of block n (-1 past the end of the row), and the first block at or after
   // n, in this wave's stride, whose entry names a page of the pool; entries that do not are
   // skipped and reported in *status.
-  auto table_entry = [&](int n) { return n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1; };
+  auto table_entry = [&](int n) { return n < hot.max_pages ? scalar_load(hot.block_table + (size_t)b * hot.max_pages + n) : -1; };
   auto first_valid = [&](int n, int entry, size_t& bi) {
     while (n < blk1) {
-      if (entry >= 0 && entry < a.num_pages) {
-        bi = (size_t)entry * a.n_kv_heads + hkv;
+      if (entry >= 0 && entry < hot.num_pages) {
+        bi = (size_t)entry * hot.n_kv_heads + hkv;
         break;
       }
       if (a.status && lane == 0) atomicOr(a.status, 1);
@@ -409,63 +419,56 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     return n;
   };
   int blk = blk0 + wave;
-  size_t bi = unit * a.nbcap + blk;
+  size_t bi = unit * hot.nbcap + blk;
   if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
-  // (the residual slice inside both branches: the loads behind its own are then known to the compiler, which
-  // otherwise waits for all of them)
-  if (blk < blk1) {   // parameters first: they are the block's first consumers
+  constexpr int kBlockLoads = (KT ? 1 : 2) + 1 + 8;   // parameters and key tiles
+  auto issue_first = [&]() {   // parameters first: they are the block's first consumers
     issue_kpar(bi);
     issue_vpar(bi);
 #pragma unroll
     for (int T = 0; T < 8; ++T) issue_ktile(bi, T);
-    if (nres > 0) res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
-  } else if (nres > 0) {
-    res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
-  }
-
-  // ---- larger groups: the queries, scaled, for everybody in the workgroup
-  if constexpr (HP > 1) {
-#pragma unroll
-    for (int p = 0; p < HP; ++p) {
-      const int h = 4 * p + (tid >> 6);   // this wave holds all 128 channels of head h
-      uint32_t qb = row_max16_u(max(qld[p] & 0x7FFFu, (qld[p] >> 16) & 0x7FFFu));
-      qb = max(max(__builtin_amdgcn_readlane(qb, 0), __builtin_amdgcn_readlane(qb, 16)),
-               max(__builtin_amdgcn_readlane(qb, 32), __builtin_amdgcn_readlane(qb, 48)));
-      const int kqh = norm_exponent(qb, kQTop);
-      const float f = pow2i(kqh);
-      float2 qq = {h2f((uint16_t)(qld[p] & 0xFFFFu)) * f, h2f((uint16_t)(qld[p] >> 16)) * f};
-      *reinterpret_cast<float2*>(&q_s[h][2 * lane]) = qq;
-      if (lane == 0) kq_s[h] = kqh;
-    }
-    __syncthreads();
-  }
-
-  // tokens whose softmax this lane runs: for its o-th owned k-step j = cg * OWN + o, the low
-  // (lh = 0) and high (lh = 1) fp16 halves of the P' registers come from tiles tile_lo / tile_hi
-  // of half j / 2; token = 32 g + 4 tile + row
+  };
   // Every head's queries times the power of two that brings the largest below 1 (kq); the factor comes
   // back out of the scores, together with softmax_scale * log2(e) and the 2^24 of the subnormal codes (kS).
   constexpr int kQTop8 = KT ? E::kTop : E::kTop - kSTop;   // f8f6f4: with the K scales below 2^kSTop, |Q'| < 2^kTop
   float qv[2][4];
   int kq_head = 0;   // of the head this lane's column carries
-  if constexpr (HP == 1) {
-    uint32_t qb = 0;
+  auto scale_queries = [&]() {
+    if constexpr (HP > 1) {   // larger groups: for everybody in the workgroup
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      qb = max(max(qb, max(qraw0[i] & 0x7FFFu, (qraw0[i] >> 16) & 0x7FFFu)), max(qraw1[i] & 0x7FFFu, (qraw1[i] >> 16) & 0x7FFFu));
-    qb = row_max16_u(qb);   // largest |q| of head lane / 16
-    const float f = pow2i(norm_exponent(qb, kQTop8));
+      for (int p = 0; p < HP; ++p) {
+        const int h = 4 * p + wave;   // this wave holds all 128 channels of head h
+        uint32_t qb = row_max16_u(max(qld[p] & 0x7FFFu, (qld[p] >> 16) & 0x7FFFu));
+        qb = max(max(__builtin_amdgcn_readlane(qb, 0), __builtin_amdgcn_readlane(qb, 16)),
+                 max(__builtin_amdgcn_readlane(qb, 32), __builtin_amdgcn_readlane(qb, 48)));
+        const int kqh = norm_exponent(qb, kQTop);
+        const float f = pow2i(kqh);
+        float2 qq = {h2f((uint16_t)(qld[p] & 0xFFFFu)) * f, h2f((uint16_t)(qld[p] >> 16)) * f};
+        *reinterpret_cast<float2*>(&q_s[h][2 * lane]) = qq;
+        if (lane == 0) kq_s[h] = kqh;
+      }
+      lds_barrier();
+      kq_head = kq_s[head];
+    } else {
+      uint32_t qb = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      qv[0][i] = h2f((uint16_t)((qraw0[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
-      qv[1][i] = h2f((uint16_t)((qraw1[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
+      for (int i = 0; i < 2; ++i)
+        qb = max(max(qb, max(qraw0[i] & 0x7FFFu, (qraw0[i] >> 16) & 0x7FFFu)), max(qraw1[i] & 0x7FFFu, (qraw1[i] >> 16) & 0x7FFFu));
+      qb = row_max16_u(qb);   // largest |q| of head lane / 16
+      const float f = pow2i(norm_exponent(qb, kQTop8));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        qv[0][i] = h2f((uint16_t)((qraw0[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
+        qv[1][i] = h2f((uint16_t)((qraw1[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
+      }
+      kq_head = norm_exponent((uint32_t)__shfl((int)qb, 16 * head), kQTop8);   // (head h's queries sit in lanes 16h ..)
     }
-    kq_head = norm_exponent((uint32_t)__shfl((int)qb, 16 * head), kQTop8);   // (head h's queries sit in lanes 16h ..)
-  } else {
-    kq_head = kq_s[head];
-  }
-  const float kS = a.scale_log2 * pow2i((KT || kF8 ? 0 : 24) - kq_head);   // what the kept scores still have to be multiplied by
-  const float kZ = a.scale_log2 * pow2i(-kq_head);                  // ... and the zero term sum_c Q_c z_c
+  };
+  float kS = 0.0f;   // what the kept scores still have to be multiplied by
+  float kZ = 0.0f;   // ... and the zero term sum_c Q_c z_c
+  // tokens whose softmax this lane runs: for its o-th owned k-step j = cg * OWN + o, the low
+  // (lh = 0) and high (lh = 1) fp16 halves of the P' registers come from tiles tile_lo / tile_hi
+  // of half j / 2; token = 32 g + 4 tile + row
   int tb[OWN][2];
 #pragma unroll
   for (int o = 0; o < OWN; ++o) {
@@ -591,39 +594,189 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       bql[j] = *reinterpret_cast<const h8_t*>(&wl.qlo[head][8 * (4 * g + j)]);
     }
   };
-  if constexpr (kF8)   // the columns of the eighth piece stay zero
-    *reinterpret_cast<u2_t*>(&wl.qp[1][lane >> 5][(lane >> 3) & 3][12 + ((lane & 7) >> 1)][2 * (lane & 1)]) = (u2_t){0u, 0u};
+  // per-token K: the operand stays in registers; 9 .. 16 heads have not enough of them (25 spilled: 32K tokens, 16 heads,
+  // 19.9 us a step) and read it for every block
+  constexpr bool kKeepQ = KT && GQP < 16;
   float zq = 0.0f, qsum = 0.0f;
-  if constexpr (KT) {
-    (void)prep_queries();
-    wave_sync();
+  auto set_scales = [&]() {
+    if constexpr (kF8)   // the columns of the eighth piece stay zero
+      *reinterpret_cast<u2_t*>(&wl.qp[1][lane >> 5][(lane >> 3) & 3][12 + ((lane & 7) >> 1)][2 * (lane & 1)]) = (u2_t){0u, 0u};
+    kS = a.scale_log2 * pow2i((KT || kF8 ? 0 : 24) - kq_head);
+    kZ = a.scale_log2 * pow2i(-kq_head);
+    if constexpr (KT) {
+      (void)prep_queries();
+      wave_sync();
+      if constexpr (kKeepQ) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      load_bq(j);
+        for (int j = 0; j < 4; ++j) load_bq(j);
+      }
+      qsum = wl.zq[head];
     }
-    qsum = wl.zq[head];
-  }
+  };
 
   // Two waves of different workgroups share each SIMD and the issue arbiter favours the older
   // one, which then runs a block ahead, finishes early and leaves the other to drain alone with
   // half the loads in flight.  Priority by remaining work keeps the pair in step.
   int done = 0;
   bool first = true;
-  while (blk < blk1) {
-    int nblk = SINGLE ? blk1 : blk + bstep;
-    size_t nbi = bi + bstep;
-    int next_entry = -1;   // requested a block ahead, like the parameters
+  float sc[OWN][2][4];   // scores of the block's tokens that this lane keeps
+  float kSb = 0.0f;      // kS for the block's K exponent
+  int nblk = blk1, next_entry = -1;
+  size_t nbi = 0;
+  bool has_next = false;
+  // the keys' registers are free: request the next block's
+  auto request_next = [&]() {
+    if (PAGED || kEarly) {   // parameters first: the next block's first consumers
+      issue_kpar(nbi);
+      issue_vpar(nbi);
+    }
+#pragma unroll
+    for (int T = 0; T < 8; ++T) issue_ktile(nbi, T);
+  };
+  auto attend_block = [&]() {
+  if constexpr (KT) {   // per-token scale and zero of K
+#pragma unroll
+    for (int o = 0; o < OWN; ++o)
+#pragma unroll
+      for (int lh = 0; lh < 2; ++lh)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float2 kq = wl.kpar[slot(tb[o][lh]) + r];
+          sc[o][lh][r] = __builtin_fmaf(sc[o][lh][r], kq.x, kq.y * qsum);
+        }
+  }
+  // ---- online softmax (Alg. 1) over this lane's 8 * OWN tokens of head `head`, on S + log2 of the
+  //      token's V scale (see "Range" at the top): av = score in log2 units, but for the block's zero term
+#pragma unroll
+  for (int o = 0; o < OWN; ++o)
+#pragma unroll
+    for (int lh = 0; lh < 2; ++lh)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        sc[o][lh][r] = __builtin_fmaf(sc[o][lh][r], kSb, wl.vpar[slot(tb[o][lh]) + r].x);
+  float bmax = sc[0][0][0];
+#pragma unroll
+  for (int o = 0; o < OWN; ++o)
+#pragma unroll
+    for (int lh = 0; lh < 2; ++lh)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bmax = fmaxf(bmax, sc[o][lh][r]);
+  bmax = head_max<COPIES>(bmax);
+  // channel-wise K: every score of the head still lacks the block's zero term
+  const float zqs = zq * kZ;
+  const float m_new = fmaxf(m_run, bmax + zqs);
+  const float zoff = zqs - m_new;
+  const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first block (m_run = -inf)
+  m_run = m_new;
+  l_run *= alpha;
+  z_run *= alpha;
+  if (!SINGLE && !first && __any(alpha != 1.0f)) {   // nothing to rescale on the first block
+#pragma unroll
+    for (int mt = 0; mt < 8; ++mt) oacc[mt] *= alpha;
+    xacc *= alpha;
+  }
+  u4_t pb[4];   // P' as the B operand of the 4 k-steps of O^T += V^T P'
+  i8_t pb8;     // groups of up to 4 heads: piece cg of P'
+  if constexpr (kF8) {   // the e4m3 pieces of this lane's 8 weights, to the column groups that take them
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      float e[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        e[r] = __builtin_amdgcn_exp2f(sc[0][half][r] + zoff);   // P' = weight * V scale, <= 1
+        const float4& par = wl.vpar[slot(tb[0][half]) + r];
+        l_run = __builtin_fmaf(e[r], par.y, l_run);
+        z_run = __builtin_fmaf(e[r], par.z, z_run);
+      }
+      uint32_t u[4] = {any_bits(), any_bits(), any_bits(), any_bits()}, from[4];
+      float unit = 1.0f / (1 << E::kTop);
+#pragma unroll
+      for (int k = 0; k < kWeightPieces; ++k) {
+        if (k < kWeightPieces - 1)
+          u[k] = e4m3_piece<true>(e4m3_piece<false>(u[k], e[0], e[2], unit), e[1], e[3], unit);
+        else
+          u[k] = e4m3_last<true>(e4m3_last<false>(u[k], e[0], e[2], unit), e[1], e[3], unit);
+        unit *= 1.0f / 32;
+      }
+      exchange_pieces(u, from);
+      // rows 0, 2 (low halves) and 1, 3 (high halves) of two neighbouring tiles make a register each
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        pb8[4 * half + E::b_reg(8 * w)] = (int)__builtin_amdgcn_perm(from[2 * w + 1], from[2 * w], 0x05040100u);
+        pb8[4 * half + E::b_reg(8 * w + 1)] = (int)__builtin_amdgcn_perm(from[2 * w + 1], from[2 * w], 0x07060302u);
+      }
+    }
+  } else {                       // zero where another column group owns the k-step
+    u4_t pair[OWN];
+#pragma unroll
+    for (int o = 0; o < OWN; ++o)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        uint32_t hv[2];
+#pragma unroll
+        for (int lh = 0; lh < 2; ++lh) {
+          const float e = __builtin_amdgcn_exp2f(sc[o][lh][r] + zoff);
+          const float4& par = wl.vpar[slot(tb[o][lh]) + r];
+          l_run = __builtin_fmaf(e, par.y, l_run);
+          z_run = __builtin_fmaf(e, par.z, z_run);
+          hv[lh] = (uint32_t)f2h(e * F::un(r));
+        }
+        pair[o][r] = hv[0] | (hv[1] << 16);
+      }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (COPIES == 1) pb[j][r] = pair[j][r];
+        else pb[j][r] = cg == (j >> 1) ? pair[j & 1][r] : 0u;
+      }
+  }
+  // ---- O^T += V^T P'
+  if constexpr (kF8) {
+    const u4_t c0 = *reinterpret_cast<const u4_t*>(&wl.c8[g][0]), c1 = *reinterpret_cast<const u4_t*>(&wl.c8[g][4]);
+    const i8_t ac = {(int)c0[0], (int)c0[1], (int)c0[2], (int)c0[3], (int)c1[0], (int)c1[1], (int)c1[2], (int)c1[3]};
+    xacc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ac, pb8, xacc, 0, 0, 0, 127, 0, sb_p);
+#pragma unroll
+    for (int mt = 0; mt < 8; ++mt)
+      oacc[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(E::a_operand(vraw[mt].w), pb8, oacc[mt], E::kFormatA, 0,
+                                                                  0, E::kScaleA, 0, sb_p);
+  } else {   // k-step j contracts 32 tokens (8 per lane group)
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const h8_t ac = *reinterpret_cast<const h8_t*>(&wl.c16[8 * (4 * g + j)]);
+    xacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ac, __builtin_bit_cast(h8_t, pb[j]), xacc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {   // k-step outermost: consecutive MFMAs go to different accumulators
+    const h8_t bp = __builtin_bit_cast(h8_t, pb[j]);
+#pragma unroll
+    for (int mt = 0; mt < 8; ++mt)
+      oacc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::dequant(vraw[mt].w, j), bp, oacc[mt], 0, 0, 0);
+  }
+  }
+  };
+  auto next_page = [&]() {
+    if (PAGED && has_next) {
+      nblk = first_valid(nblk, next_entry, nbi);
+      has_next = nblk < blk1;
+    }
+  };
+  // Prepares and scores block `blk`, up to the request of its values.
+  auto score_block = [&]() {
+    nblk = SINGLE ? blk1 : blk + bstep;
+    nbi = bi + bstep;
+    next_entry = -1;   // requested a block ahead, like the parameters
     if (PAGED && nblk < blk1) next_entry = table_entry(nblk);
     if (!SINGLE) {
-      const int q4 = (4 * done) / (my_blocks > 0 ? my_blocks : 1);   // quarter of the work done: 0..3
-      if (q4 == 0) __builtin_amdgcn_s_setprio(3);
-      else if (q4 == 1) __builtin_amdgcn_s_setprio(2);
-      else if (q4 == 2) __builtin_amdgcn_s_setprio(1);
+      // (quarter of the work done)
+      if (4 * done < my_blocks) __builtin_amdgcn_s_setprio(3);
+      else if (4 * done < 2 * my_blocks) __builtin_amdgcn_s_setprio(2);
+      else if (4 * done < 3 * my_blocks) __builtin_amdgcn_s_setprio(1);
       else __builtin_amdgcn_s_setprio(0);
       ++done;
     }
-    float kSb = kS;   // kS for this block's K exponent
-    if constexpr (!KT) kSb = kS * pow2i(prep_queries());
+    kSb = kS;
+    if constexpr (!KT) kSb *= pow2i(prep_queries());
     if constexpr (KT) {   // K parameters of the block's 128 tokens
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -654,14 +807,12 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
       }
     }
     wave_sync();
-    if constexpr (!KT) {
+    if constexpr (!kKeepQ) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        load_bq(j);
-      }
-      zq = wl.zq[head];
+      for (int j = 0; j < 4; ++j) load_bq(j);
     }
-    bool has_next = !SINGLE && nblk < blk1;
+    if constexpr (!KT) zq = wl.zq[head];
+    has_next = !SINGLE && nblk < blk1;
     if (!PAGED && !kEarly && has_next) {   // small, and the next block's first consumers: requested a block ahead
       issue_kpar(nbi);
       issue_vpar(nbi);
@@ -671,7 +822,6 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 
     // ---- S^T tiles (rows = tokens 32*(row/4) + 4T + row%4, all 16 columns valid); each lane
     //      keeps the tiles of the k-steps its column group owns: sc[o][low/high half][row]
-    float sc[OWN][2][4];
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       f4_t s[4];
@@ -726,156 +876,8 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
 #pragma unroll
       for (int mt = 0; mt < 8; ++mt) issue_vtile(bi, mt);
     }
-    // the keys' registers are free: request the next block's
-    auto request_next = [&]() {
-      if (PAGED || kEarly) {   // parameters first: the next block's first consumers
-        issue_kpar(nbi);
-        issue_vpar(nbi);
-      }
-#pragma unroll
-      for (int T = 0; T < 8; ++T) issue_ktile(nbi, T);
-    };
-    auto attend_block = [&]() {
-    if constexpr (KT) {   // per-token scale and zero of K
-#pragma unroll
-      for (int o = 0; o < OWN; ++o)
-#pragma unroll
-        for (int lh = 0; lh < 2; ++lh)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float2 kq = wl.kpar[slot(tb[o][lh]) + r];
-            sc[o][lh][r] = __builtin_fmaf(sc[o][lh][r], kq.x, kq.y * qsum);
-          }
-    }
-    // ---- online softmax (Alg. 1) over this lane's 8 * OWN tokens of head `head`, on S + log2 of the
-    //      token's V scale (see "Range" at the top): av = score in log2 units, but for the block's zero term
-#pragma unroll
-    for (int o = 0; o < OWN; ++o)
-#pragma unroll
-      for (int lh = 0; lh < 2; ++lh)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          sc[o][lh][r] = __builtin_fmaf(sc[o][lh][r], kSb, wl.vpar[slot(tb[o][lh]) + r].x);
-    float bmax = sc[0][0][0];
-#pragma unroll
-    for (int o = 0; o < OWN; ++o)
-#pragma unroll
-      for (int lh = 0; lh < 2; ++lh)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bmax = fmaxf(bmax, sc[o][lh][r]);
-    bmax = head_max<COPIES>(bmax);
-    // channel-wise K: every score of the head still lacks the block's zero term
-    const float zqs = zq * kZ;
-    const float m_new = fmaxf(m_run, bmax + zqs);
-    const float zoff = zqs - m_new;
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first block (m_run = -inf)
-    m_run = m_new;
-    l_run *= alpha;
-    z_run *= alpha;
-    if (!SINGLE && !first && __any(alpha != 1.0f)) {   // nothing to rescale on the first block
-#pragma unroll
-      for (int mt = 0; mt < 8; ++mt) oacc[mt] *= alpha;
-      xacc *= alpha;
-    }
-    u4_t pb[4];   // P' as the B operand of the 4 k-steps of O^T += V^T P'
-    i8_t pb8;     // groups of up to 4 heads: piece cg of P'
-    if constexpr (kF8) {   // the e4m3 pieces of this lane's 8 weights, to the column groups that take them
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        float e[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          e[r] = __builtin_amdgcn_exp2f(sc[0][half][r] + zoff);   // P' = weight * V scale, <= 1
-          const float4& par = wl.vpar[slot(tb[0][half]) + r];
-          l_run = __builtin_fmaf(e[r], par.y, l_run);
-          z_run = __builtin_fmaf(e[r], par.z, z_run);
-        }
-        uint32_t u[4] = {any_bits(), any_bits(), any_bits(), any_bits()}, from[4];
-        float unit = 1.0f / (1 << E::kTop);
-#pragma unroll
-        for (int k = 0; k < kWeightPieces; ++k) {
-          if (k < kWeightPieces - 1)
-            u[k] = e4m3_piece<true>(e4m3_piece<false>(u[k], e[0], e[2], unit), e[1], e[3], unit);
-          else
-            u[k] = e4m3_last<true>(e4m3_last<false>(u[k], e[0], e[2], unit), e[1], e[3], unit);
-          unit *= 1.0f / 32;
-        }
-        exchange_pieces(u, from);
-        // rows 0, 2 (low halves) and 1, 3 (high halves) of two neighbouring tiles make a register each
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-          pb8[4 * half + E::b_reg(8 * w)] = (int)__builtin_amdgcn_perm(from[2 * w + 1], from[2 * w], 0x05040100u);
-          pb8[4 * half + E::b_reg(8 * w + 1)] = (int)__builtin_amdgcn_perm(from[2 * w + 1], from[2 * w], 0x07060302u);
-        }
-      }
-    } else {                       // zero where another column group owns the k-step
-      u4_t pair[OWN];
-#pragma unroll
-      for (int o = 0; o < OWN; ++o)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          uint32_t hv[2];
-#pragma unroll
-          for (int lh = 0; lh < 2; ++lh) {
-            const float e = __builtin_amdgcn_exp2f(sc[o][lh][r] + zoff);
-            const float4& par = wl.vpar[slot(tb[o][lh]) + r];
-            l_run = __builtin_fmaf(e, par.y, l_run);
-            z_run = __builtin_fmaf(e, par.z, z_run);
-            hv[lh] = (uint32_t)f2h(e * F::un(r));
-          }
-          pair[o][r] = hv[0] | (hv[1] << 16);
-        }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if constexpr (COPIES == 1) pb[j][r] = pair[j][r];
-          else pb[j][r] = cg == (j >> 1) ? pair[j & 1][r] : 0u;
-        }
-    }
-    // ---- O^T += V^T P'
-    if constexpr (kF8) {
-      const u4_t c0 = *reinterpret_cast<const u4_t*>(&wl.c8[g][0]), c1 = *reinterpret_cast<const u4_t*>(&wl.c8[g][4]);
-      const i8_t ac = {(int)c0[0], (int)c0[1], (int)c0[2], (int)c0[3], (int)c1[0], (int)c1[1], (int)c1[2], (int)c1[3]};
-      xacc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ac, pb8, xacc, 0, 0, 0, 127, 0, sb_p);
-#pragma unroll
-      for (int mt = 0; mt < 8; ++mt)
-        oacc[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(E::a_operand(vraw[mt].w), pb8, oacc[mt], E::kFormatA, 0,
-                                                                    0, E::kScaleA, 0, sb_p);
-    } else {   // k-step j contracts 32 tokens (8 per lane group)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const h8_t ac = *reinterpret_cast<const h8_t*>(&wl.c16[8 * (4 * g + j)]);
-      xacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ac, __builtin_bit_cast(h8_t, pb[j]), xacc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {   // k-step outermost: consecutive MFMAs go to different accumulators
-      const h8_t bp = __builtin_bit_cast(h8_t, pb[j]);
-#pragma unroll
-      for (int mt = 0; mt < 8; ++mt)
-        oacc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F::dequant(vraw[mt].w, j), bp, oacc[mt], 0, 0, 0);
-    }
-    }
-    };
-    auto next_page = [&]() {
-      if (PAGED && has_next) {
-        nblk = first_valid(nblk, next_entry, nbi);
-        has_next = nblk < blk1;
-      }
-    };
-    if constexpr (kEarly) {
-      next_page();
-      if (!has_next) {   // (a branch of its own: the compiler then knows how many loads are behind the values)
-        attend_block();
-        break;
-      }
-      request_next();
-      attend_block();
-    } else {
-      attend_block();
-      next_page();
-      if (has_next) request_next();
-    }
+  };
+  auto advance = [&]() {
     // Both sums grow with the number of tokens, their difference (the signal) with its square root: every
     // 16 blocks the centre sum is taken out of the accumulators and starts again from zero.
     if (!SINGLE && (done & 15) == 0) {
@@ -887,13 +889,54 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     first = false;
     blk = nblk;
     bi = nbi;
+  };
+  // (The residual slice inside both branches: the loads behind its own are then known to the compiler, which otherwise
+  // waits for all of them.  Likewise the blocks inside the one that requests the first, and one way out of their loop, past
+  // no load whose use it skips: wherever the compiler sees a path, be it one that is never taken, on which a load has not
+  // been waited for, it waits for all of them the next time round.)
+  if (blk >= blk1) {
+    start_slice();
+    scale_queries();
+    attend_slice();
+  } else {
+    start_slice();
+    issue_first();
+    scale_queries();
+    attend_slice();
+    loads_left<kBlockLoads>();
+    set_scales();
+    if constexpr (kEarly) {
+      // (the loop's end is between a block's two halves, with the values on their way: 32K tokens 12.9 -> 12.45 us a
+      // step, 8 x 32K at 2 bits 34.7 -> 33.6, against a loop that is left in the middle)
+      score_block();
+      next_page();
+      while (has_next) {
+        request_next();
+        attend_block();
+        advance();
+        score_block();
+        next_page();
+      }
+      attend_block();
+    } else {
+      while (true) {
+        score_block();
+        attend_block();
+        next_page();
+        if (!has_next) break;
+        request_next();
+        advance();
+      }
+    }
   }
 
   // ---- merge the column groups (groups of 8 heads), then the waves of the workgroup
   //      (cross-wave step of the cooperative softmax)
   l_run = head_sum<COPIES>(l_run);
   z_run = head_sum<COPIES>(z_run);
-  __syncthreads();   // every wave is done with its WaveLds before the space is reused
+  if (files)
+    *reinterpret_cast<u4_t*>(const_cast<uint16_t*>(tid >= 16 ? a.v_res : hot.k_res) + (unit * kBlock + new_slot) * kD + 8 * (tid & 15)) = filed;
+  lds_barrier();   // every wave is done with its WaveLds before the space is reused
   ML& ml = *reinterpret_cast<ML*>(smem_raw);
   // The column groups' shares are added below, by the threads that merge the waves: 12 (4) more LDS reads there for 288 (32)
   // DPP moves and adds of every wave here.  A wave alone on its SIMD issues one instruction every 4 to 5 cycles, and at the
@@ -911,10 +954,10 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
     ml.l[wave][col] = l_run;
     ml.z[wave][col] = z_run;
   }
-  __syncthreads();
+  lds_barrier();
 #pragma unroll
   for (int p = 0; p < HP; ++p) {
-    const int h = 4 * p + (tid >> 6), c0 = 2 * (tid & 63);
+    const int h = 4 * p + wave, c0 = 2 * (tid & 63);
     if (h < gq) {
       float M = ml.m[0][h];
 #pragma unroll
@@ -944,7 +987,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(DecodeArgs a) {
           o1 += f * res_o[h][c0 + 1];
         }
       }
-      const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * a.gq + head0 + h;
+      const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
       if (a.out) {   // one split: row == the output row
         store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);
@@ -982,7 +1025,21 @@ __global__ __launch_bounds__(128 * G) void combine_kernel(const float* __restric
   constexpr int kBatch = kCombineBatch;
   __shared__ float sm[G][128], sl[G][128], so[G][128];
   const int row = blockIdx.x, tid = threadIdx.x, c = tid & 127, grp = tid >> 7;
-  if (bump.seq_lens && tid == 128 * G - 1 && row % bump.n_q_heads == 0) {   // one thread per sequence
+  float M = -INFINITY, L = 0.f, o = 0.f;
+  float2 ml[kBatch];
+  float ov[kBatch];
+  auto request = [&](int p0) {
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const int p = p0 + G * i;
+      const size_t r = (size_t)(p < nparts ? p : 0) * nrows + row;
+      ml[i] = *reinterpret_cast<const float2*>(part_ml + r * 2);
+      ov[i] = part_o[r * kD + c];
+    }
+  };
+  request(grp);
+  // one thread per sequence (here, with the partials on their way: its arguments are not among the preloaded ones)
+  if (bump.seq_lens && tid == 128 * G - 1 && row % bump.n_q_heads == 0) {
     const int b = row / bump.n_q_heads;
     const int len = bump.seq_lens[b];
     if (len >= 0) {
@@ -995,18 +1052,11 @@ __global__ __launch_bounds__(128 * G) void combine_kernel(const float* __restric
       if (ok) bump.seq_lens[b] = len + 1;
     }
   }
-  float M = -INFINITY, L = 0.f, o = 0.f;
   for (int p0 = grp; p0 < nparts; p0 += G * kBatch) {
-    float2 ml[kBatch];
-    float ov[kBatch];
+    if (p0 != grp) request(p0);
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      const int p = p0 + G * i;
-      const size_t r = (size_t)(p < nparts ? p : 0) * nrows + row;
-      ml[i] = *reinterpret_cast<const float2*>(part_ml + r * 2);
-      ov[i] = part_o[r * kD + c];
-      if (p >= nparts) ml[i].x = -INFINITY;
-    }
+    for (int i = 0; i < kBatch; ++i)
+      if (p0 + G * i >= nparts) ml[i].x = -INFINITY;
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       const float Mn = fmaxf(M, ml[i].x);
@@ -1050,9 +1100,12 @@ namespace {
 
 template <int BITS, int GQP, bool KT>
 void launch_mode(bool single, bool paged, const DecodeArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-  if (paged) decode_int_kernel<BITS, GQP, false, true, KT><<<grid, block, 0, st>>>(a);
-  else if (single) decode_int_kernel<BITS, GQP, true, false, KT><<<grid, block, 0, st>>>(a);
-  else decode_int_kernel<BITS, GQP, false, false, KT><<<grid, block, 0, st>>>(a);
+  if (paged)
+    decode_int_kernel<BITS, GQP, false, true, KT><<<grid, block, 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences(grid, INT32_MAX)), a);
+  else if (single)
+    decode_int_kernel<BITS, GQP, true, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
+  else
+    decode_int_kernel<BITS, GQP, false, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
 }
 
 template <int BITS, bool KT>
@@ -1105,13 +1158,15 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   a.res_len = res_len;
   a.num_splits = num_splits;
   a.scale_log2 = softmax_scale * kLog2e;
+  a.res_scale = residual_scale(num_splits);
   a.block_table = nullptr;
   a.seq_lens = nullptr;
   a.status = nullptr;
   a.max_pages = a.num_pages = 0;
   a.step = 0;
   dim3 grid(num_splits + (flush == 2 ? 1 : 0), c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);
-  const bool single = (a.nb + num_splits - 1) / num_splits <= kWaves;   // at most one block per wave
+  // at most one block per wave, and residual slices of one round
+  const bool single = (a.nb + num_splits - 1) / num_splits <= kWaves && res_len <= (kResShort - 2) * num_splits;
   launch_instance(c->format, a.gq, single, false, a, grid, block, st);
   return hipGetLastError();
 }
@@ -1145,6 +1200,7 @@ hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float sof
   a.nb = a.nbcap = a.res_len = 0;   // per sequence, from seq_lens
   a.num_splits = num_splits;
   a.scale_log2 = softmax_scale * kLog2e;
+  a.res_scale = residual_scale(num_splits);
   a.block_table = c->block_table;
   a.seq_lens = c->seq_lens;
   a.status = c->status;

@@ -51,7 +51,8 @@ struct GrpArgs {
   int out_kind;     // element type of `out` (kOutF16 / kOutBf16 / kOutF32)
   int n_q_heads, n_kv_heads, gq;
   int nb, nbcap, res_len, num_splits;
-  float scale_log2;
+  float scale_log2; // softmax_scale * log2(e)
+  uint32_t res_scale;   // residual_scale(num_splits)
   // paged cache: block n of sequence b is page block_table[b][n], pool index page * Hkv + head;
   // nb and res_len then come from seq_lens[b]
   const int32_t* block_table;
@@ -111,7 +112,8 @@ constexpr int grp_waves_per_simd(int bits, int group, int gqp, bool kt) {
 //   parameters in fp32 and the copies are added with DPP row rotations, after which every copy holds S^T as
 //   in the channel-wise case.
 template <int BITS, int G, int GQP, bool PAGED, bool KT>
-__global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void decode_grp_kernel(GrpArgs a) {
+__global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void decode_grp_kernel(BD_HOT_PARAMS, GrpArgs a) {
+  const HotArgs<PAGED> hot(BD_HOT_NAMES, a.k_params, a.k_res);
   // With one wave per SIMD nothing but the wave's own arithmetic hides its memory latency, so it
   // requests a block's values before its keys are consumed and the next block's keys right after
   // ("deep").  With two waves the other one covers and the short queue of the group-128 kernel is
@@ -141,32 +143,32 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   __shared__ __attribute__((aligned(16))) float q_s[GQP][kD];
   __shared__ float qinv_s[GQP];
 
-  const bool flush_after = a.flush_mode == kFlushAfter;
+  const bool flush_after = hot.flush_mode == kFlushAfter;
   const int split = (int)blockIdx.x - (flush_after ? 1 : 0);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(a.seq_lens, lane, seq_len, INT32_MAX) : blockIdx.z;
+  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   // Every copy of a head's column receives the same S^T; copy cp keeps the chunks c with
   // c % COPIES == cp, runs their softmax and writes their P', so that work is shared out.
   const int head = col % GQP, cp = col / GQP;
   int hkv = blockIdx.y, head0 = 0;
-  if (a.gq > kGrpHeads) {
-    const int nchunk = (a.gq + kGrpHeads - 1) / kGrpHeads;
+  if (hot.gq > kGrpHeads) {
+    const int nchunk = (hot.gq + kGrpHeads - 1) / kGrpHeads;
     hkv = blockIdx.y / nchunk;
     head0 = kGrpHeads * (blockIdx.y % nchunk);
   }
-  const int gq = min(a.gq - head0, kGrpHeads);
+  const int gq = min(hot.gq - head0, kGrpHeads);
   WL& wl = reinterpret_cast<WL*>(smem_raw)[wave];
 
-  const size_t unit = (size_t)b * a.n_kv_heads + hkv;
-  int nb = a.nb, res_len = a.res_len;
-  int new_slot = a.new_slot;   // fused step: residual slot of the token that is still in the caller's buffer, or -1
+  const size_t unit = (size_t)b * hot.n_kv_heads + hkv;
+  int nb = hot.nb, res_len = hot.res_len;
+  int new_slot = hot.new_slot;   // fused step: residual slot of the token that is still in the caller's buffer, or -1
   int flush_page = -1;         // paged fused step that fills the residual: the page the block goes to
   if (PAGED) {
     int len = seq_len;
     new_slot = -1;
-    if (a.step && len >= 0) {
+    if (hot.step && len >= 0) {
       // fused step: this step's token counts (unless it needs a page the table does not name) and
       // the length is raised only after this kernel.  With a.k_new no kernel has appended the token:
       // it is read from the caller's buffer and filed by this launch, and if it fills the residual,
@@ -175,10 +177,10 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
       int e = -1;
       if (len % kBlock == kBlock - 1) {
         const int n = len / kBlock;
-        e = n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1;
-        ok = e >= 0 && e < a.num_pages;
+        e = n < hot.max_pages ? scalar_load(hot.block_table + (size_t)b * hot.max_pages + n) : -1;
+        ok = e >= 0 && e < hot.num_pages;
       }
-      if (a.k_new) {
+      if (hot.append) {
         if (!ok) {
           if (a.status && tid == 0 && split == 0) atomicOr(a.status, 2);   // the token is dropped
         } else if (len % kBlock < kBlock - 1) {
@@ -200,13 +202,13 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   }
   // blocks are dealt to the splits four at a time (one per wave), round robin: the workgroups of a
   // unit read one contiguous window of the cache at any moment
-  const int blk0 = split * kWaves, blk1 = nb, bstep = kWaves * a.num_splits;
+  const int blk0 = split * kWaves, blk1 = nb, bstep = kWaves * hot.num_splits;
   if (flush_after && split < 0 && head0 != 0) return;   // (one quantizing workgroup per KV head is enough)
-  if (!PAGED && a.flush_mode != kFlushNone && head0 == 0 &&
-      (flush_after ? split < 0 : split == (a.flush_blk / kWaves) % a.num_splits)) {
+  if (!PAGED && hot.flush_mode != kFlushNone && head0 == 0 &&
+      (flush_after ? split < 0 : split == (a.flush_blk / kWaves) % hot.num_splits)) {
     // the step's token completes the residual block: file it, then pack the 128 rows as block flush_blk
     // (kFlushFirst: this workgroup is the block's only reader in this launch -- up to 8 heads per KV head)
-    uint16_t* kr = const_cast<uint16_t*>(a.k_res) + unit * kBlock * kD;
+    uint16_t* kr = const_cast<uint16_t*>(hot.k_res) + unit * kBlock * kD;
     uint16_t* vr = const_cast<uint16_t*>(a.v_res) + unit * kBlock * kD;
     if (tid < 32) {
       const bool is_v = tid >= 16;
@@ -214,9 +216,9 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
       *reinterpret_cast<u4_t*>((is_v ? vr : kr) + (kBlock - 1) * kD + 8 * (tid & 15)) = *reinterpret_cast<const u4_t*>(src);
     }
     workgroup_global_sync();
-    quant_block<BITS, KT, G>(kr, vr, const_cast<uint32_t*>(a.k_codes), const_cast<uint32_t*>(a.v_codes),
-                             const_cast<uint32_t*>(a.k_params), const_cast<uint32_t*>(a.v_params),
-                             unit * a.nbcap + a.flush_blk);
+    quant_block<BITS, KT, G>(kr, vr, const_cast<uint32_t*>(hot.k_codes), const_cast<uint32_t*>(a.v_codes),
+                             const_cast<uint32_t*>(hot.k_params), const_cast<uint32_t*>(a.v_params),
+                             unit * hot.nbcap + a.flush_blk);
     if (flush_after) return;   // (the whole workgroup: split < 0 is uniform)
     workgroup_global_sync();
   }
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
     // lazy flush: the extra workgroup of a (sequence, KV head) packs the 128 rows into the page if this
     // step's token completes them, and does nothing else
     if (flush_page >= 0 && head0 == 0) {
-      uint16_t* kr = const_cast<uint16_t*>(a.k_res) + unit * kBlock * kD;
+      uint16_t* kr = const_cast<uint16_t*>(hot.k_res) + unit * kBlock * kD;
       uint16_t* vr = const_cast<uint16_t*>(a.v_res) + unit * kBlock * kD;
       if (tid < 32) {
         const bool is_v = tid >= 16;
@@ -232,16 +234,16 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
         *reinterpret_cast<u4_t*>((is_v ? vr : kr) + (kBlock - 1) * kD + 8 * (tid & 15)) = *reinterpret_cast<const u4_t*>(src);
       }
       workgroup_global_sync();
-      quant_block<BITS, KT, G>(kr, vr, const_cast<uint32_t*>(a.k_codes), const_cast<uint32_t*>(a.v_codes),
-                               const_cast<uint32_t*>(a.k_params), const_cast<uint32_t*>(a.v_params),
-                               (size_t)flush_page * a.n_kv_heads + hkv);
+      quant_block<BITS, KT, G>(kr, vr, const_cast<uint32_t*>(hot.k_codes), const_cast<uint32_t*>(a.v_codes),
+                               const_cast<uint32_t*>(hot.k_params), const_cast<uint32_t*>(a.v_params),
+                               (size_t)flush_page * hot.n_kv_heads + hkv);
     }
     return;
   }
-  if (PAGED && !flush_after && flush_page >= 0 && split == ((nb - 1) / kWaves) % a.num_splits) {
+  if (PAGED && !flush_after && flush_page >= 0 && split == ((nb - 1) / kWaves) % hot.num_splits) {
     // the 128 residual rows become block nb - 1, which this workgroup alone reads in this launch (one
     // workgroup per split and KV head: the host takes this path for up to 8 heads per KV head)
-    uint16_t* kr = const_cast<uint16_t*>(a.k_res) + unit * kBlock * kD;
+    uint16_t* kr = const_cast<uint16_t*>(hot.k_res) + unit * kBlock * kD;
     uint16_t* vr = const_cast<uint16_t*>(a.v_res) + unit * kBlock * kD;
     if (tid < 32) {
       const bool is_v = tid >= 16;
@@ -249,22 +251,26 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
       *reinterpret_cast<u4_t*>((is_v ? vr : kr) + (kBlock - 1) * kD + 8 * (tid & 15)) = *reinterpret_cast<const u4_t*>(src);
     }
     workgroup_global_sync();
-    quant_block<BITS, KT, G>(kr, vr, const_cast<uint32_t*>(a.k_codes), const_cast<uint32_t*>(a.v_codes),
-                                const_cast<uint32_t*>(a.k_params), const_cast<uint32_t*>(a.v_params),
-                                (size_t)flush_page * a.n_kv_heads + hkv);
+    quant_block<BITS, KT, G>(kr, vr, const_cast<uint32_t*>(hot.k_codes), const_cast<uint32_t*>(a.v_codes),
+                                const_cast<uint32_t*>(hot.k_params), const_cast<uint32_t*>(a.v_params),
+                                (size_t)flush_page * hot.n_kv_heads + hkv);
     workgroup_global_sync();
   }
-  const int rt0 = (res_len * split) / a.num_splits, rt1 = (res_len * (split + 1)) / a.num_splits;
-  const uint16_t* qbase = a.q + ((size_t)b * a.n_q_heads + hkv * a.gq + head0) * kD;
+  const int rt0 = residual_bound(res_len, split, hot.num_splits, a.res_scale), rt1 = residual_bound(res_len, split + 1, hot.num_splits, a.res_scale);
+  const uint16_t* qbase = hot.q + ((size_t)b * (hot.gq * hot.n_kv_heads) + hkv * hot.gq + head0) * kD;
 
   // rows of the residual slice: the newest token of a fused step is read from where the caller left it
   const int nres = rt1 - rt0;
-  const uint16_t *kres = a.k_res + unit * kBlock * kD, *vres = a.v_res + unit * kBlock * kD;
-  auto kres_row = [&](int t) { return rt0 + t == new_slot ? a.k_new + unit * kD : kres + (size_t)(rt0 + t) * kD; };
-  auto vres_row = [&](int t) { return rt0 + t == new_slot ? a.v_new + unit * kD : vres + (size_t)(rt0 + t) * kD; };
+  const uint16_t *kres = hot.k_res + unit * kBlock * kD, *vres = a.v_res + unit * kBlock * kD;
+  ResidualRows rows;
+  rows.new_at = new_slot >= 0 ? new_slot - rt0 : -1;
+  rows.k = kres + (size_t)rt0 * kD;
+  rows.v = vres + (size_t)rt0 * kD;
+  rows.kn = a.k_new + ((long)unit - rows.new_at) * kD;
+  rows.vn = a.v_new + ((long)unit - rows.new_at) * kD;
   constexpr bool kResidualFirst = grp_waves_per_simd(BITS, G, GQP, KT) > 1 && (PAGED || !KT);   // (see below)
   ResidualSlice res;
-  if (!kResidualFirst && nres > 0) res.start(qbase, gq, nres, kres_row, vres_row, wave, lane);
+  if (!kResidualFirst && nres > 0) res.start(qbase, gq, nres, rows, wave, lane);
 
   // ---- queries, scaled, for everybody in the workgroup
 #pragma unroll
@@ -281,10 +287,10 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
     if (lane == 0) qinv_s[h] = pow2i(-kq);
   }
 
-  if (new_slot >= 0 && split == 0 && head0 == 0 && tid < 32 && res_len < kBlock && (PAGED || a.flush_mode == kFlushNone)) {   // fused step: file the new token for later steps
+  if (new_slot >= 0 && split == 0 && head0 == 0 && tid < 32 && res_len < kBlock && (PAGED || hot.flush_mode == kFlushNone)) {   // fused step: file the new token for later steps
     const bool is_v = tid >= 16;
     const uint16_t* src = (is_v ? a.v_new : a.k_new) + unit * kD + 8 * (tid & 15);
-    uint16_t* dst = const_cast<uint16_t*>(is_v ? a.v_res : a.k_res) + (unit * kBlock + new_slot) * kD + 8 * (tid & 15);
+    uint16_t* dst = const_cast<uint16_t*>(is_v ? a.v_res : hot.k_res) + (unit * kBlock + new_slot) * kD + 8 * (tid & 15);
     *reinterpret_cast<u4_t*>(dst) = *reinterpret_cast<const u4_t*>(src);
   }
   __syncthreads();   // q_s is complete
@@ -318,7 +324,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   uint32_t ktp[KT ? 2 * NV : 1];   // per-token K: K parameters (half2) of tokens 2*lane, 2*lane+1, per channel group
   auto issue_params = [&](size_t bi) {
     if constexpr (KT) {
-      const uint32_t* kpp = a.k_params + (bi * kBlock + 2 * lane) * NV;
+      const uint32_t* kpp = hot.k_params + (bi * kBlock + 2 * lane) * NV;
       if constexpr (NV == 4) {
         const u4_t x = *reinterpret_cast<const u4_t*>(kpp), y = *reinterpret_cast<const u4_t*>(kpp + 4);
 #pragma unroll
@@ -334,7 +340,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
     } else {
       // lane group g fetches token group g % NG (its 16 lanes cover the 128 channels); the token
       // groups meet in LDS, which keeps 8 registers in flight instead of 8 per token group
-      const uint32_t* pp = a.k_params + (bi * NG + (g % NG)) * kD;
+      const uint32_t* pp = hot.k_params + (bi * NG + (g % NG)) * kD;
       kp0 = *reinterpret_cast<const u4_t*>(pp + run0);
       kp1 = *reinterpret_cast<const u4_t*>(pp + run1);
     }
@@ -353,7 +359,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
     }
   };
   auto issue_keys = [&](size_t bi) {
-    const uint32_t* kp = a.k_codes + bi * (size_t)(kBlock * KROW) + WORDS * g;
+    const uint32_t* kp = hot.k_codes + bi * (size_t)(kBlock * KROW) + WORDS * g;
 #pragma unroll
     for (int T = 0; T < 8; ++T) {
       const int tok = F::run_base(4 * (T >> 1) + row_gamma, T & 1) + row_r;
@@ -426,6 +432,48 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
     const uint16_t* row = (v & 1) ? &wl.qlo[head][8 * (4 * g + j)] : &wl.qhi[head][8 * (4 * g + j)];
     return *reinterpret_cast<const h8_t*>(live ? row : wl.zeros);
   };
+  // Paged: table entry of block n (-1 past the end of the row), and the first block at or after
+  // n, in this wave's stride, whose entry names a page of the pool; entries that do not are
+  // skipped and reported in *status.
+  auto table_entry = [&](int n) { return n < hot.max_pages ? scalar_load(hot.block_table + (size_t)b * hot.max_pages + n) : -1; };
+  auto first_valid = [&](int n, int entry, size_t& idx) {
+    while (n < blk1) {
+      if (entry >= 0 && entry < hot.num_pages) {
+        idx = (size_t)entry * hot.n_kv_heads + hkv;
+        break;
+      }
+      if (a.status && lane == 0) atomicOr(a.status, 1);
+      n += bstep;
+      entry = n < blk1 ? table_entry(n) : -1;
+    }
+    return n;
+  };
+  int blk = blk0 + wave;
+  size_t bi = unit * hot.nbcap + blk;
+  if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
+  // The residual slice is attended as in the group-128 kernel, its rows requested ahead and the first block on its way
+  // meanwhile -- but with two workgroups per compute unit, where the registers of both (and the page's, or the parameters of
+  // K by channel) are more than the 256 there are (up to 11 spilled in the loop; now at most 4), it comes first: in pages, 8
+  // sequences of up to 8.2K tokens, per-token K, 4 bits, 4 heads, groups of 64 / 32 22.7 -> 22.3 / 26.9 -> 25.4 us, 2 bits,
+  // groups of 32 25.5 -> 24.7, groups of 64 with 8 heads 25.3 -> 24.4; contiguous, 16 of 2K tokens, 2 bits, groups of 32
+  // 18.1 -> 17.2, of 64 15.1 -> 14.8.  (Per-token K, contiguous, has the registers and is as fast either way; one workgroup
+  // per compute unit would lose by it: groups of 32, 8 heads, contiguous 36.6 -> 38.7, in pages 36.6 -> 37.0.)
+  if constexpr (kResidualFirst) {
+    if (nres > 0) {
+      res.start(qbase, gq, nres, rows, wave, lane);
+      res.template attend<GQP>(nres, a.scale_log2, *reinterpret_cast<ML*>(smem_raw), res_o, res_m, res_l, wave, lane);
+    }
+    if (blk < blk1) {
+      issue_params(bi);
+      issue_keys(bi);
+    }
+  } else if (blk < blk1) {
+    issue_params(bi);
+    issue_keys(bi);
+    if (nres > 0) res.template attend<GQP>(nres, a.scale_log2, *reinterpret_cast<ML*>(smem_raw), res_o, res_m, res_l, wave, lane);
+  } else if (nres > 0) {
+    res.template attend<GQP>(nres, a.scale_log2, *reinterpret_cast<ML*>(smem_raw), res_o, res_m, res_l, wave, lane);
+  }
   if constexpr (KT) {
     if (lane < 8) wl.zeros[lane] = 0;
 #pragma unroll
@@ -471,49 +519,6 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
 #pragma unroll
       for (int j = 0; j < 4; ++j) bqk[0][j] = chain_operand(0, j);
     }
-  }
-
-  // Paged: table entry of block n (-1 past the end of the row), and the first block at or after
-  // n, in this wave's stride, whose entry names a page of the pool; entries that do not are
-  // skipped and reported in *status.
-  auto table_entry = [&](int n) { return n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1; };
-  auto first_valid = [&](int n, int entry, size_t& idx) {
-    while (n < blk1) {
-      if (entry >= 0 && entry < a.num_pages) {
-        idx = (size_t)entry * a.n_kv_heads + hkv;
-        break;
-      }
-      if (a.status && lane == 0) atomicOr(a.status, 1);
-      n += bstep;
-      entry = n < blk1 ? table_entry(n) : -1;
-    }
-    return n;
-  };
-  int blk = blk0 + wave;
-  size_t bi = unit * a.nbcap + blk;
-  if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
-  // The residual slice is attended as in the group-128 kernel, its rows requested ahead and the first block on its way
-  // meanwhile -- but with two workgroups per compute unit, where the registers of both (and the page's, or the parameters of
-  // K by channel) are more than the 256 there are (up to 11 spilled in the loop; now at most 4), it comes first: in pages, 8
-  // sequences of up to 8.2K tokens, per-token K, 4 bits, 4 heads, groups of 64 / 32 22.7 -> 22.3 / 26.9 -> 25.4 us, 2 bits,
-  // groups of 32 25.5 -> 24.7, groups of 64 with 8 heads 25.3 -> 24.4; contiguous, 16 of 2K tokens, 2 bits, groups of 32
-  // 18.1 -> 17.2, of 64 15.1 -> 14.8.  (Per-token K, contiguous, has the registers and is as fast either way; one workgroup
-  // per compute unit would lose by it: groups of 32, 8 heads, contiguous 36.6 -> 38.7, in pages 36.6 -> 37.0.)
-  if constexpr (kResidualFirst) {
-    if (nres > 0) {
-      res.start(qbase, gq, nres, kres_row, vres_row, wave, lane);
-      res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
-    }
-    if (blk < blk1) {
-      issue_params(bi);
-      issue_keys(bi);
-    }
-  } else if (blk < blk1) {
-    issue_params(bi);
-    issue_keys(bi);
-    if (nres > 0) res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
-  } else if (nres > 0) {
-    res.template attend<GQP>(nres, a.scale_log2, kres_row, vres_row, res_o, res_m, res_l, wave, lane);
   }
   // this lane's 8 tokens of chunk c are block tokens tok0 + 32*c + {run_base offsets}: slot group 4*c + g
   while (blk < blk1) {
@@ -774,7 +779,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
           o1 += f * res_o[h][c0 + 1];
         }
       }
-      const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * a.gq + head0 + h;
+      const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
       if (a.out) {   // one split: row == the output row
         store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);
@@ -789,15 +794,18 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   }
 }
 
+template <int BITS, int G, int GQP, bool KT>
+void launch_mode(const GrpArgs& a, bool paged, dim3 grid, hipStream_t st) {
+  if (paged)
+    decode_grp_kernel<BITS, G, GQP, true, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences(grid, INT32_MAX)), a);
+  else
+    decode_grp_kernel<BITS, G, GQP, false, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
+}
+
 template <int BITS, int G, bool KT = false>
 void launch_heads(const GrpArgs& a, bool paged, dim3 grid, hipStream_t st) {
-  if (paged) {
-    if (a.gq <= 4) decode_grp_kernel<BITS, G, 4, true, KT><<<grid, dim3(256), 0, st>>>(a);
-    else decode_grp_kernel<BITS, G, 8, true, KT><<<grid, dim3(256), 0, st>>>(a);
-  } else {
-    if (a.gq <= 4) decode_grp_kernel<BITS, G, 4, false, KT><<<grid, dim3(256), 0, st>>>(a);
-    else decode_grp_kernel<BITS, G, 8, false, KT><<<grid, dim3(256), 0, st>>>(a);
-  }
+  if (a.gq <= 4) launch_mode<BITS, G, 4, KT>(a, paged, grid, st);
+  else launch_mode<BITS, G, 8, KT>(a, paged, grid, st);
 }
 
 hipError_t launch_format(int format, const GrpArgs& a, bool paged, int batch, hipStream_t st) {
@@ -848,6 +856,7 @@ hipError_t launch_decode_grp(const bd_cache* c, const void* q, int packed_len, i
   a.res_len = res_len;
   a.num_splits = num_splits;
   a.scale_log2 = softmax_scale * kLog2e;
+  a.res_scale = residual_scale(num_splits);
   a.block_table = nullptr;
   a.seq_lens = nullptr;
   a.status = nullptr;
@@ -879,6 +888,7 @@ hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float
   a.nb = a.nbcap = a.res_len = 0;   // per sequence, from seq_lens
   a.num_splits = num_splits;
   a.scale_log2 = softmax_scale * kLog2e;
+  a.res_scale = residual_scale(num_splits);
   a.block_table = c->block_table;
   a.seq_lens = c->seq_lens;
   a.status = c->status;

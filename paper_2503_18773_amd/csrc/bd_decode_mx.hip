@@ -164,31 +164,32 @@ __device__ __forceinline__ void mx_query_operand(const uint16_t* qp, i8_t& bhi, 
 // of a block is shared out over the copies (larger groups: decode_mxg_kernel).
 // PAGED: blocks are found through the block table and every sequence has its own length.
 template <bool PAGED>
-__global__ __launch_bounds__(256, 2) void decode_mx_kernel(MxArgs a) {
+__global__ __launch_bounds__(256, 2) void decode_mx_kernel(BD_HOT_PARAMS, MxArgs a) {
+  const HotArgs<PAGED, uint8_t> hot(BD_HOT_NAMES, a.k_scales, nullptr);
   __shared__ MergeLdsMx ml;
   const int split = blockIdx.x, hkv = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(a.seq_lens, lane, seq_len, 512) : blockIdx.z;
+  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   const int head = col & 3, cg = col >> 2;
-  const int head0 = hkv * a.gq;                  // first query head of this workgroup
-  const int nheads = min(4, a.gq);
-  const size_t unit = (size_t)b * a.n_kv_heads + hkv;
-  int length = a.length;
+  const int head0 = hkv * hot.gq;                  // first query head of this workgroup
+  const int nheads = min(4, hot.gq);
+  const size_t unit = (size_t)b * hot.n_kv_heads + hkv;
+  int length = hot.nb;
   long app_bi = -1;   // fused step without an append launch: array index of the block the token goes to
   int app_pos = 0;
   if (PAGED) {
     length = seq_len;
-    if (a.step && length >= 0) {
+    if (hot.step && length >= 0) {
       // fused step: this step's token counts if the table names a page for it (a preceding kernel
       // has appended it, or, with a.k_new, this launch does); the length is raised only after this kernel
       const int n = length / kBlock;
-      const int e = n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1;
-      const bool ok = e >= 0 && e < a.num_pages;
-      if (a.k_new) {
+      const int e = n < hot.max_pages ? scalar_load(hot.block_table + (size_t)b * hot.max_pages + n) : -1;
+      const bool ok = e >= 0 && e < hot.num_pages;
+      if (hot.append) {
         if (ok) {
-          app_bi = (long)e * a.n_kv_heads + hkv;
+          app_bi = (long)e * hot.n_kv_heads + hkv;
           app_pos = length % kBlock;
         } else if (a.status && tid == 0 && split == 0) {
           atomicOr(a.status, 2);   // the token is dropped
@@ -197,17 +198,17 @@ __global__ __launch_bounds__(256, 2) void decode_mx_kernel(MxArgs a) {
       length += ok ? 1 : 0;
     }
     length = max(0, length);
-  } else if (a.k_new) {
-    app_bi = (long)(unit * (a.capacity / kBlock) + length / kBlock);
+  } else if (hot.append) {
+    app_bi = (long)(unit * (hot.nbcap / kBlock) + length / kBlock);
     app_pos = length % kBlock;
     length += 1;
   }
   const int nb = (length + kBlock - 1) / kBlock;
-  if (app_bi >= 0 && split == ((nb - 1) / kWaves) % a.num_splits) mx_append_here(a, unit, (size_t)app_bi, app_pos);
+  if (app_bi >= 0 && split == ((nb - 1) / kWaves) % hot.num_splits) mx_append_here(a, unit, (size_t)app_bi, app_pos);
   // blocks are dealt to the splits four at a time (one per wave), round robin: the workgroups of a
   // unit read one contiguous window of the cache at any moment
-  const int blk0 = split * kWaves, blk1 = nb, bstep = kWaves * a.num_splits;
-  const int nbcap = a.capacity / kBlock;
+  const int blk0 = split * kWaves, blk1 = nb, bstep = kWaves * hot.num_splits;
+  const int nbcap = hot.nbcap / kBlock;
   const int tok_base = 32 * (col >> 2) + (col & 3);   // row `col` of tile T holds token tok_base + 4T
 
   i8_t bhi, blo;      // Q[head][32g .. 32g+31] as two fp8 (e4m3) pieces
@@ -225,8 +226,8 @@ __global__ __launch_bounds__(256, 2) void decode_mx_kernel(MxArgs a) {
 #pragma unroll
     for (int T = 0; T < 8; ++T) {
       const size_t t = tok0 + tok_base + 4 * T;
-      ksc[T] = *reinterpret_cast<const uint32_t*>(a.k_scales + t * 4);
-      kraw[T] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(a.k_codes + t * 64 + 16 * g));
+      ksc[T] = *reinterpret_cast<const uint32_t*>(hot.k_params + t * 4);
+      kraw[T] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(hot.k_codes + t * 64 + 16 * g));
     }
   };
   auto issue_v = [&](size_t bi) {
@@ -242,11 +243,11 @@ __global__ __launch_bounds__(256, 2) void decode_mx_kernel(MxArgs a) {
   // Paged: table entry of block n (-1 past the end of the row), and the first block at or after
   // n, in this wave's stride, whose entry names a page of the pool; entries that do not are
   // skipped and reported in *status.
-  auto table_entry = [&](int n) { return n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1; };
+  auto table_entry = [&](int n) { return n < hot.max_pages ? scalar_load(hot.block_table + (size_t)b * hot.max_pages + n) : -1; };
   auto first_valid = [&](int n, int entry, size_t& bi) {
     while (n < blk1) {
-      if (entry >= 0 && entry < a.num_pages) {
-        bi = (size_t)entry * a.n_kv_heads + hkv;
+      if (entry >= 0 && entry < hot.num_pages) {
+        bi = (size_t)entry * hot.n_kv_heads + hkv;
         break;
       }
       if (a.status && lane == 0) atomicOr(a.status, 1);
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(256, 2) void decode_mx_kernel(MxArgs a) {
   if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
   if (blk < blk1) issue_k(bi);
 
-  mx_query_operand(head < nheads ? a.q + ((size_t)b * a.n_q_heads + head0 + head) * kD + 16 * g : nullptr, bhi, blo,
+  mx_query_operand(head < nheads ? hot.q + ((size_t)b * (hot.gq * hot.n_kv_heads) + head0 + head) * kD + 16 * g : nullptr, bhi, blo,
                    sb_hi, sb_lo);
 
   float m_run = -INFINITY, l_run = 0.0f;
@@ -432,32 +433,33 @@ struct MergeLdsMxG {
 };
 
 template <int GQP, bool PAGED>
-__global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_kernel(MxArgs a) {
+__global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_kernel(BD_HOT_PARAMS, MxArgs a) {
+  const HotArgs<PAGED, uint8_t> hot(BD_HOT_NAMES, a.k_scales, nullptr);
   constexpr int COPIES = 16 / GQP;     // 2 or 1
   constexpr int NT = 8 / COPIES;       // S^T tiles a lane keeps
   __shared__ MergeLdsMxG<GQP> ml;
-  const int nwg = (a.gq + GQP - 1) / GQP;        // workgroups per (split, KV head)
+  const int nwg = (hot.gq + GQP - 1) / GQP;        // workgroups per (split, KV head)
   const int split = blockIdx.x, hkv = blockIdx.y / nwg, sub0 = GQP * (blockIdx.y % nwg);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(a.seq_lens, lane, seq_len, 512) : blockIdx.z;
+  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   const int head = col % GQP, cg = col / GQP;
-  const int head0 = hkv * a.gq + sub0;           // first query head of this workgroup
-  const int nheads = min(GQP, a.gq - sub0);
-  const size_t unit = (size_t)b * a.n_kv_heads + hkv;
-  int length = a.length;
+  const int head0 = hkv * hot.gq + sub0;           // first query head of this workgroup
+  const int nheads = min(GQP, hot.gq - sub0);
+  const size_t unit = (size_t)b * hot.n_kv_heads + hkv;
+  int length = hot.nb;
   long app_bi = -1;   // fused step without an append launch (see decode_mx_kernel)
   int app_pos = 0;
   if (PAGED) {
     length = seq_len;
-    if (a.step && length >= 0) {
+    if (hot.step && length >= 0) {
       const int n = length / kBlock;
-      const int e = n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1;
-      const bool ok = e >= 0 && e < a.num_pages;
-      if (a.k_new) {
+      const int e = n < hot.max_pages ? scalar_load(hot.block_table + (size_t)b * hot.max_pages + n) : -1;
+      const bool ok = e >= 0 && e < hot.num_pages;
+      if (hot.append) {
         if (ok) {
-          app_bi = (long)e * a.n_kv_heads + hkv;
+          app_bi = (long)e * hot.n_kv_heads + hkv;
           app_pos = length % kBlock;
         } else if (a.status && tid == 0 && split == 0) {
           atomicOr(a.status, 2);   // the token is dropped
@@ -466,17 +468,17 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
       length += ok ? 1 : 0;
     }
     length = max(0, length);
-  } else if (a.k_new) {
-    app_bi = (long)(unit * (a.capacity / kBlock) + length / kBlock);
+  } else if (hot.append) {
+    app_bi = (long)(unit * (hot.nbcap / kBlock) + length / kBlock);
     app_pos = length % kBlock;
     length += 1;
   }
   const int nb = (length + kBlock - 1) / kBlock;
-  if (app_bi >= 0 && split == ((nb - 1) / kWaves) % a.num_splits) mx_append_here(a, unit, (size_t)app_bi, app_pos);
+  if (app_bi >= 0 && split == ((nb - 1) / kWaves) % hot.num_splits) mx_append_here(a, unit, (size_t)app_bi, app_pos);
   // blocks are dealt to the splits four at a time (one per wave), round robin: the workgroups of a
   // unit read one contiguous window of the cache at any moment
-  const int blk0 = split * kWaves, blk1 = nb, bstep = kWaves * a.num_splits;
-  const int nbcap = a.capacity / kBlock;
+  const int blk0 = split * kWaves, blk1 = nb, bstep = kWaves * hot.num_splits;
+  const int nbcap = hot.nbcap / kBlock;
   const int tok_base = 32 * (col >> 2) + (col & 3);   // row `col` of tile T holds token tok_base + 4T
 
   i8_t bhi, blo;
@@ -489,8 +491,8 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
 #pragma unroll
     for (int T = 0; T < 8; ++T) {
       const size_t t = tok0 + tok_base + 4 * T;
-      ksc[T] = *reinterpret_cast<const uint32_t*>(a.k_scales + t * 4);
-      kraw[T] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(a.k_codes + t * 64 + 16 * g));
+      ksc[T] = *reinterpret_cast<const uint32_t*>(hot.k_params + t * 4);
+      kraw[T] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(hot.k_codes + t * 64 + 16 * g));
     }
   };
   auto issue_v = [&](size_t bi) {
@@ -503,11 +505,11 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
     for (int mt = 0; mt < 8; ++mt)
       vraw[mt] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(vp + (size_t)(16 * mt + col) * 64));
   };
-  auto table_entry = [&](int n) { return n < a.max_pages ? a.block_table[(size_t)b * a.max_pages + n] : -1; };
+  auto table_entry = [&](int n) { return n < hot.max_pages ? scalar_load(hot.block_table + (size_t)b * hot.max_pages + n) : -1; };
   auto first_valid = [&](int n, int entry, size_t& bi) {
     while (n < blk1) {
-      if (entry >= 0 && entry < a.num_pages) {
-        bi = (size_t)entry * a.n_kv_heads + hkv;
+      if (entry >= 0 && entry < hot.num_pages) {
+        bi = (size_t)entry * hot.n_kv_heads + hkv;
         break;
       }
       if (a.status && lane == 0) atomicOr(a.status, 1);
@@ -521,7 +523,7 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
   if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
   if (blk < blk1) issue_k(bi);
 
-  mx_query_operand(head < nheads ? a.q + ((size_t)b * a.n_q_heads + head0 + head) * kD + 16 * g : nullptr, bhi, blo,
+  mx_query_operand(head < nheads ? hot.q + ((size_t)b * (hot.gq * hot.n_kv_heads) + head0 + head) * kD + 16 * g : nullptr, bhi, blo,
                    sb_hi, sb_lo);
 
   float m_run = -INFINITY, l_run = 0.0f;
@@ -641,7 +643,7 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
   __syncthreads();
 #pragma unroll
   for (int p = 0; p < GQP / 4; ++p) {
-    const int h = 4 * p + (tid >> 6), c0 = 2 * (tid & 63);
+    const int h = 4 * p + wave, c0 = 2 * (tid & 63);
     if (h < nheads) {
       float M = ml.m[0][h];
 #pragma unroll
@@ -675,13 +677,16 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
 
 template <bool PAGED>
 static hipError_t launch_mx(const MxArgs& a, int batch, hipStream_t st) {
-  dim3 block(256);
-  if (a.gq <= 4)
-    decode_mx_kernel<PAGED><<<dim3(a.num_splits, a.n_kv_heads, batch), block, 0, st>>>(a);
-  else if (a.gq <= 8)
-    decode_mxg_kernel<8, PAGED><<<dim3(a.num_splits, a.n_kv_heads, batch), block, 0, st>>>(a);
-  else
-    decode_mxg_kernel<16, PAGED><<<dim3(a.num_splits, a.n_kv_heads * ((a.gq + 15) / 16), batch), block, 0, st>>>(a);
+  const dim3 block(256), grid(a.num_splits, a.n_kv_heads * ((a.gq + 15) / 16), batch);
+  auto launch = [&](auto kernel) {
+    if (PAGED) kernel<<<grid, block, 0, st>>>(BD_HOT_PAGED(a, 0, sorted_sequences(grid, 512)), a);
+    else   // (tokens and capacity in tokens in the places of the block counts)
+      kernel<<<grid, block, 0, st>>>(a.q, a.k_codes, a.k_scales, nullptr, a.gq, a.n_kv_heads, a.num_splits, a.length, a.capacity,
+                                 hot_word(0, 0, a.k_new != nullptr), a);
+  };
+  if (a.gq <= 4) launch(decode_mx_kernel<PAGED>);
+  else if (a.gq <= 8) launch(decode_mxg_kernel<8, PAGED>);
+  else launch(decode_mxg_kernel<16, PAGED>);
   return hipGetLastError();
 }
 

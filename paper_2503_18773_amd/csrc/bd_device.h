@@ -154,6 +154,55 @@ __device__ __forceinline__ void workgroup_global_sync() {
 constexpr int kParSlots = 128 + 8;
 __device__ __forceinline__ int par_slot(int t) { return t + 2 * (t >> 5); }
 
+// The arguments that a wave's first loads wait for come as scalars ahead of an attention kernel's struct: those are in
+// registers when it starts (build.py; there is room for 14 words), the struct has to be fetched first, 0.3 us.  With the
+// merge's arguments likewise: 6K tokens, 8 units 9.15 -> 8.9 us a step, 4 x 8K in groups of 32 16.7 -> 16.1.
+#define BD_HOT_PARAMS const uint16_t *hq, const void *hk, const void *hx, const void *hy, int hgq, int hkvh, int hns, int hi, int hj, int hm
+#define BD_HOT_NAMES hq, hk, hx, hy, hgq, hkvh, hns, hi, hj, hm
+#define BD_HOT_CONTIGUOUS(a) \
+  a.q, a.k_codes, a.k_params, a.k_res, a.gq, a.n_kv_heads, a.num_splits, a.nb, a.nbcap, hot_word(a.res_len, a.flush_mode, a.new_slot + 1)
+#define BD_HOT_PAGED(a, flush_mode, sorted) \
+  a.q, a.k_codes, a.seq_lens, a.block_table, a.gq, a.n_kv_heads, a.num_splits, a.max_pages, a.num_pages, \
+      hot_word(sorted, flush_mode, a.step + 2 * (a.k_new != nullptr))
+static inline int hot_word(int low, int flush_mode, int high) { return low | flush_mode << 8 | high << 16; }
+template <bool PAGED, class Codes = uint32_t>
+struct HotArgs {
+  const uint16_t *q, *k_res;
+  const Codes *k_codes, *k_params;
+  const int32_t *seq_lens, *block_table;
+  int gq, n_kv_heads, num_splits, flush_mode;
+  int nb, nbcap, res_len, new_slot;    // contiguous
+  int max_pages, num_pages;            // paged
+  int sorted;                          // ... sequences to be sorted (paged_sequence)
+  bool step;                           // ... the launch is the attention of a fused step
+  bool append;                         // the launch appends the step's token itself
+  // k_params_, k_res_: the struct's, for the paged form
+  __device__ __forceinline__ HotArgs(BD_HOT_PARAMS, const Codes* k_params_, const uint16_t* k_res_)
+      : q(hq), k_res(PAGED ? k_res_ : (const uint16_t*)hy), k_codes((const Codes*)hk),
+        k_params(PAGED ? k_params_ : (const Codes*)hx), seq_lens(PAGED ? (const int32_t*)hx : nullptr),
+        block_table(PAGED ? (const int32_t*)hy : nullptr), gq(hgq), n_kv_heads(hkvh), num_splits(hns),
+        flush_mode((hm >> 8) & 255), nb(PAGED ? 0 : hi), nbcap(PAGED ? 0 : hj), res_len(PAGED ? 0 : hm & 255),
+        new_slot(PAGED ? -1 : (hm >> 16) - 1), max_pages(PAGED ? hi : 0), num_pages(PAGED ? hj : 0),
+        sorted(PAGED ? hm & 255 : 0), step(PAGED && (hm >> 16 & 1)), append(PAGED ? (hm >> 16 & 2) != 0 : hm >> 16 > 0) {}
+};
+
+// Waits until at most N vector loads are outstanding.  Where the loads before them are known to have been used, this costs
+// nothing and tells the compiler so: after a load and its use behind one and the same condition it takes the load for
+// possibly outstanding, and waits for everything where its register is written next, be it in the loop that follows.
+template <int N>
+__device__ __forceinline__ void loads_left() {
+  static_assert(N >= 0 && N < 16, "vmcnt, low bits");
+  __builtin_amdgcn_s_waitcnt(0xF70 | N);
+}
+
+// A word that this launch does not write, at an address that is the same for the whole wave, through the scalar cache:
+// it comes past the wave's queue of vector loads, and what is computed from it stays scalar (page numbers: 8 sequences of
+// up to 3K tokens, one split 20.2 -> 18.7 us, 40 in groups of 64 32.4 -> 30.4).
+__device__ __forceinline__ int32_t scalar_load(const int32_t* p) {
+  typedef const __attribute__((address_space(4))) int32_t* Const;
+  return *(Const)p;
+}
+
 // Paged cache: the sequence of grid row z and its length.  Where the launch's last round of workgroups (one per
 // compute unit a round) would fill at most half of the units, a ragged batch runs longest sequence first (to 1/16 of
 // the length, then by index), so that those units get short ones.  The lengths' load then stands before everything
@@ -162,10 +211,14 @@ __device__ __forceinline__ int par_slot(int t) { return t + 2 * (t >> 5); }
 // 40 sequences of up to 3.1K tokens, one split, 2-bit codes and 8 heads per KV head 34.9 -> 30.9 us, 4 bits 33.9 -> 31.1,
 // MXFP4 34.8 -> 31.5; 24 of up to 5K, three splits, groups of 32 42.4 -> 39.3, groups of 128 28.0 as before.  Every wave
 // selects the z-th longest itself, a bit of the key at a time; batches of more than 64 sequences stay as they are.
-__device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_lens, int lane, int& seq_len, int max_wgs) {
-  const int n = gridDim.z, wgs = gridDim.x * gridDim.y * gridDim.z;
-  if (n < 2 || n > 64 || wgs <= 256 || wgs > max_wgs || (wgs - 1) % 256 >= 128) {
-    seq_len = seq_lens[blockIdx.z];
+// sorted_sequences (host): how many sequences there are to be sorted, 0 to leave them as they are.
+static inline int sorted_sequences(dim3 grid, int max_wgs) {
+  const long wgs = (long)grid.x * grid.y * grid.z;
+  return grid.z < 2 || grid.z > 64 || wgs <= 256 || wgs > max_wgs || (wgs - 1) % 256 >= 128 ? 0 : (int)grid.z;
+}
+__device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_lens, int lane, int& seq_len, int n) {
+  if (n == 0) {
+    seq_len = scalar_load(seq_lens + blockIdx.z);
     return blockIdx.z;
   }
   const int len = seq_lens[min(lane, n - 1)];

@@ -368,3 +368,40 @@ def test_a_paged_batch_runs_the_splits_asked_for(fmt, hq, asked):
     assert (ml[:, 0, :, 1] > 0).all()
     assert torch.equal(ml[:, :1], ml1) and torch.equal(rows[:, :1], rows1) and torch.equal(out[:1], ref)
     assert pc.status.item() == 0
+
+
+@pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int2_kt", 8), ("int4", 16), ("int4_g32", 8)])
+@pytest.mark.parametrize("r", [29, 30, 31, 32, 48, 63, 64, 95, 96, 126])
+def test_a_step_with_a_residual_slice_of_one_round_or_more(fmt, gq, r):
+    """r residual tokens and the step's own, in one, two and three slices: on either side of the 32 tokens that one round
+    takes, of the 16 of a tile and of the 32 of a wave, the new token first or last of one, beside one block per wave
+    and beside two, contiguous and in pages.  fp32 rows, so the bar is that of the blocks' weights: 1e-5 where they are held
+    whole (up to 4 heads), else half an fp16 step, 2^-12."""
+    bar = 1e-5 if gq <= 4 else 2.0 ** -12
+    import torch
+    H, hq = 2, 2 * gq
+    for nb in (3, 7):
+        L = 128 * nb + r
+        w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=hq, n_kv_heads=H, context=L, fmt=fmt)
+        K, V = W.make_kv(w)
+        kn, vn = W.make_new_kv(w, 0)
+        q = W.make_q(w)
+        oc, _ = _caches_of(K, V, fmt, gq)
+        oc.append_kv(kn, vn)
+        ref = O.decode_attn(oc, q, W.softmax_scale(w))
+        k, v, kd, vd, qd = (to_dev(x, "fp16") for x in (K, V, kn, vn, q))
+        for ns in (1, 2, 3):
+            _, gc = _caches_of(K, V, fmt, gq)
+            pc = B.PagedKVCache(1, hq, H, fmt, nb + 2, torch.arange(nb + 1, -1, -1, dtype=torch.int32)[None])
+            pc.quant_pack_kv(0, k[0], v[0])
+            rows = []
+            for c in (gc, pc):
+                c.desc.out_type = B.BD_OUT_F32
+                out = torch.full((1, hq, 128), 7.0, dtype=torch.float32, device="cuda:0")
+                c.decode_step(kd, vd, qd, W.softmax_scale(w), out, ns)
+                rows.append(out_to_f64(out))
+            torch.cuda.synchronize()
+            for got in rows:
+                ma, rl = attn_errors(got, ref)
+                assert rl <= bar, f"{fmt} {L} tokens, {ns} splits: rel-L2 {rl:.2e}"
+            assert np.array_equal(gc.host_buffer(4), pc.host_buffer(4)) and np.array_equal(gc.host_buffer(5), pc.host_buffer(5))
