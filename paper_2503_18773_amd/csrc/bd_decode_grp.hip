@@ -66,22 +66,35 @@ struct GrpArgs {
   int flush_mode, flush_blk;
 };
 
-template <int GQP, int NV, bool KT>
+// Q' of K by channel: QB token groups at a time, per head the high fp16 pieces and the low ones, in B-operand slot order
+// (rows here and of P' padded by 16 bytes: lanes of different heads read the same offset of their
+// rows, and rows a multiple of 256 bytes apart would all fall on the same LDS banks)
+template <int GQP, int QB>
+struct GrpQueries {
+  uint16_t q[QB][2][GQP][kD + 8];
+  float zq[QB][GQP];           // sum_c Q_c z_c of the token group
+  float ksb[QB][GQP];          // what turns the first product into scores (undoes the range normalisation of Q')
+};
+template <int GQP, int NV, int QB, bool KT>
 struct GrpWaveLds {
-  __attribute__((aligned(16))) uint16_t zeros[8];   // per-token K: what a lane outside a chain's channel group feeds the matrix unit
-  // (rows of qhi, qlo and pbuf padded by 16 bytes: lanes of different heads read the same offset of
-  // their rows, and rows a multiple of 256 bytes apart would all fall on the same LDS banks)
-  uint16_t qhi[GQP][kD + 8];   // Q' per head, high fp16 piece, in B-operand slot order
-  uint16_t qlo[GQP][kD + 8];   // low piece
   float2 vpar[NV][kParSlots];  // per (channel group, token): (scale * position factor, zero + scale * centre code)
   uint16_t c16[NV][kBlock];    // centre code * position factor, in A-operand slot order
-  uint16_t pbuf[GQP][kBlock + 8];  // P' of the channel group in work, in B-operand slot order
-  float zq[GQP];               // per head: sum_c Q_c z_c of the token group in work
-  float ksb[GQP];              // per head: what turns the first product into scores (undoes the range normalisation of Q')
-  uint32_t kpar[KT ? 1 : NV][kD];   // K parameters (half2) of the block, per token group and channel
-  // per-token K: (scale * 2^24, zero) per (channel group, token) of the block, and per head the sums of the
+  union {                      // Q' is used up before P' is made
+    GrpQueries<GQP, QB> qs;
+    uint16_t pbuf[GQP][kBlock + 8];   // P' of the channel group in work, in B-operand slot order
+  };
+};
+template <int GQP, int NV, int QB>
+struct GrpWaveLds<GQP, NV, QB, true> {
+  __attribute__((aligned(16))) uint16_t zeros[8];   // what a lane outside a chain's channel group feeds the matrix unit
+  uint16_t qhi[GQP][kD + 8];   // Q' per head, high fp16 piece, in B-operand slot order
+  uint16_t qlo[GQP][kD + 8];   // low piece
+  float2 vpar[NV][kParSlots];
+  uint16_t c16[NV][kBlock];
+  uint16_t pbuf[GQP][kBlock + 8];
+  // K parameters (scale * 2^24, zero) per (channel group, token) of the block, and per head the sums of the
   // (normalised, scaled) query over each channel group
-  float2 ktpar[KT ? NV : 1][kParSlots];
+  float2 ktpar[NV][kParSlots];
   float qsum[GQP][NV];
 };
 template <int GQP, int NV>
@@ -131,7 +144,9 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   constexpr int COPIES = 16 / GQP;           // MFMA columns per head
   static_assert(COPIES >= 2 && COPIES % 2 == 0, "the high / low pieces of Q' need an even number of copies");
   constexpr int OWN = 4 / COPIES;            // 32-token chunks whose softmax a lane runs
-  using WL = GrpWaveLds<GQP, NV, KT>;
+  // token groups whose Q' is made at a time: all four of 8 heads would leave no LDS for a second workgroup
+  constexpr int QB = GQP * NG > 16 && grp_waves_per_simd(BITS, G, GQP, KT) > 1 ? 2 : NG;
+  using WL = GrpWaveLds<GQP, NV, QB, KT>;
   constexpr int CH = KT ? 2 * NG / COPIES : 0;   // per-token K: MFMA chains per S^T tile
   static_assert(!KT || (2 * NG) % COPIES == 0, "virtual columns per head must fill the copies");
   using ML = GrpMergeLds<GQP, NV>;
@@ -338,8 +353,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
         for (int i = 0; i < 4; ++i) ktp[i] = x[i];
       }
     } else {
-      // lane group g fetches token group g % NG (its 16 lanes cover the 128 channels); the token
-      // groups meet in LDS, which keeps 8 registers in flight instead of 8 per token group
+      // lane group g fetches token group g % NG, whose Q' it makes (its 16 lanes cover the 128 channels)
       const uint32_t* pp = hot.k_params + (bi * NG + (g % NG)) * kD;
       kp0 = *reinterpret_cast<const u4_t*>(pp + run0);
       kp1 = *reinterpret_cast<const u4_t*>(pp + run1);
@@ -366,56 +380,69 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
       kraw[T] = load_raw<WORDS>(kp + (size_t)tok * KROW);
     }
   };
-  auto issue_values = [&](size_t bi) {
+  auto issue_values = [&](size_t bi, int mt0, int mt1) {
     const uint32_t* vpp = a.v_codes + bi * (size_t)(kD * VROW) + WORDS * g;
 #pragma unroll
-    for (int mt = 0; mt < 8; ++mt) vraw[mt] = load_raw<WORDS>(vpp + (size_t)(16 * mt + col) * VROW);
+    for (int mt = mt0; mt < mt1; ++mt) vraw[mt] = load_raw<WORDS>(vpp + (size_t)(16 * mt + col) * VROW);
   };
 
-  // Q' = Q * s_c as an fp16 high + low pair in B-operand order and the zero term sum_c Q_c z_c, per
-  // head, with the K parameters of token group tg: 16 lanes per head (slot group lane % 16).
-  auto prep_queries = [&](int tg) {
+  // Q' = Q * s_c as an fp16 high + low pair in B-operand order and the zero term sum_c Q_c z_c for the token groups
+  // tg0 .. tg0 + QB - 1.  A lane has its channels' parameters of one token group in registers and makes Q' for that
+  // group and every head (two token groups at a time: every other head, since two lane groups share a token group),
+  // so scales are converted and normalised once, the token groups are worked on at the same time and their parameters
+  // do not pass through LDS.  Before, the wave made one token group's Q' for all heads when a chunk opened it, from
+  // parameters in LDS: 4 sequences of 8K tokens in 4 splits, 4 bits, groups of 32 25.6 -> 24.4 us a step, 2 bits, 8 heads
+  // per KV head 31.2 -> 29.1; 4 of 4000 tokens, 4 bits, 8 heads 19.7 -> 18.5; one of 32K in 4 splits 76.5 -> 70.9.
+  auto prep_queries = [&](int tg0) {
+    if constexpr (!KT) {
+      const int tg = g % QB;
+      u4_t k0 = kp0, k1 = kp1;
+      if constexpr (QB < NG) {
 #pragma unroll
-    for (int p = 0; p < HP; ++p) {
-      const int ph = 4 * p + (lane >> 4);
-      const f4_t qa = *reinterpret_cast<const f4_t*>(&q_s[ph][run0]);
-      const f4_t qb = *reinterpret_cast<const f4_t*>(&q_s[ph][run1]);
-      const u4_t ka = *reinterpret_cast<const u4_t*>(&wl.kpar[tg][run0]);
-      const u4_t kb = *reinterpret_cast<const u4_t*>(&wl.kpar[tg][run1]);
+        for (int i = 0; i < 4; ++i) {
+          k0[i] = __shfl(kp0[i], 16 * (tg0 + tg) + prep_sg);
+          k1[i] = __shfl(kp1[i], 16 * (tg0 + tg) + prep_sg);
+        }
+      }
       // the token group's K scales are brought below 2^kSTop (queries are below 2^kQTop): |Q'| < 2^15
       uint32_t sb = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) sb = max(sb, max(ka[i] & 0xFFFFu, kb[i] & 0xFFFFu));
+      for (int i = 0; i < 4; ++i) sb = max(sb, max(k0[i] & 0xFFFFu, k1[i] & 0xFFFFu));
       const int ek = -norm_exponent(row_max16_u(sb), kSTop);
-      const float dn = pow2i(-ek);
-      float zsum = 0.0f;
-      uint16_t qh[8], ql[8];
+      const float dn = pow2i(-ek), ksb = pow2i(24 + ek);   // codes enter as code * 2^-24
+      float s[8], z[8];
 #pragma unroll
-      for (int run = 0; run < 2; ++run)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float qc = run ? qb[i] : qa[i];
-          const uint32_t pr = run ? kb[i] : ka[i];
-          const float s = h2f((uint16_t)(pr & 0xFFFFu)), z = h2f((uint16_t)(pr >> 16));
-          const float t = qc * (s * dn) * F::un(i);
-          const uint16_t hi = f2h(t);
-          qh[2 * i + run] = hi;
-          ql[2 * i + run] = f2h(t - h2f(hi));
-          zsum = __builtin_fmaf(qc, z, zsum);
-        }
-      const float qinv = qinv_s[ph];
-      zsum = row_sum16(zsum) * qinv;
-      u4_t phi, plo;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        phi[v] = (uint32_t)qh[2 * v] | ((uint32_t)qh[2 * v + 1] << 16);
-        plo[v] = (uint32_t)ql[2 * v] | ((uint32_t)ql[2 * v + 1] << 16);
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t pr = i & 1 ? k1[i >> 1] : k0[i >> 1];
+        s[i] = h2f((uint16_t)(pr & 0xFFFFu)) * dn * F::un(i >> 1);
+        z[i] = h2f((uint16_t)(pr >> 16));
       }
-      *reinterpret_cast<u4_t*>(&wl.qhi[ph][8 * prep_sg]) = phi;
-      *reinterpret_cast<u4_t*>(&wl.qlo[ph][8 * prep_sg]) = plo;
-      if (prep_sg == 0) {
-        wl.zq[ph] = zsum;
-        wl.ksb[ph] = pow2i(24 + ek) * qinv;   // codes enter as code * 2^-24
+#pragma unroll
+      for (int i0 = 0; i0 < GQP * QB / 4; ++i0) {
+        const int ph = i0 * (4 / QB) + g / QB;
+        const f4_t qa = *reinterpret_cast<const f4_t*>(&q_s[ph][run0]);
+        const f4_t qb = *reinterpret_cast<const f4_t*>(&q_s[ph][run1]);
+        const float qinv = qinv_s[ph];
+        float zsum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) zsum = __builtin_fmaf(qa[i], z[2 * i], zsum);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) zsum = __builtin_fmaf(qb[i], z[2 * i + 1], zsum);
+        u4_t phi, plo;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float t0 = qa[v] * s[2 * v], t1 = qb[v] * s[2 * v + 1];
+          const uint16_t h0 = f2h(t0), h1 = f2h(t1);
+          phi[v] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+          plo[v] = (uint32_t)f2h(t0 - h2f(h0)) | ((uint32_t)f2h(t1 - h2f(h1)) << 16);
+        }
+        zsum = row_sum16(zsum) * qinv;
+        *reinterpret_cast<u4_t*>(&wl.qs.q[tg][0][ph][8 * prep_sg]) = phi;
+        *reinterpret_cast<u4_t*>(&wl.qs.q[tg][1][ph][8 * prep_sg]) = plo;
+        if (prep_sg == 0) {
+          wl.qs.zq[tg][ph] = zsum;
+          wl.qs.ksb[tg][ph] = ksb * qinv;
+        }
       }
     }
   };
@@ -426,11 +453,14 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   float qinv = 1.0f;            // undoes the query's normalisation
   constexpr bool kKeepB = CH == 1;     // the chains' B operands stay in registers when there is one chain, else they are read per chunk
   h8_t bqk[1][4];
-  auto chain_operand = [&](int k, int j) {
-    const int v = k * COPIES + cp;                       // virtual column: piece v & 1, channel group v >> 1
-    const bool live = (g >> (G == 64 ? 1 : 0)) == (v >> 1);
-    const uint16_t* row = (v & 1) ? &wl.qlo[head][8 * (4 * g + j)] : &wl.qhi[head][8 * (4 * g + j)];
-    return *reinterpret_cast<const h8_t*>(live ? row : wl.zeros);
+  auto chain_operand = [&](int k, int j) -> h8_t {
+    if constexpr (KT) {
+      const int v = k * COPIES + cp;                       // virtual column: piece v & 1, channel group v >> 1
+      const bool live = (g >> (G == 64 ? 1 : 0)) == (v >> 1);
+      const uint16_t* row = (v & 1) ? &wl.qlo[head][8 * (4 * g + j)] : &wl.qhi[head][8 * (4 * g + j)];
+      return *reinterpret_cast<const h8_t*>(live ? row : wl.zeros);
+    }
+    return h8_t{};
   };
   // Paged: table entry of block n (-1 past the end of the row), and the first block at or after
   // n, in this wave's stride, whose entry names a page of the pool; entries that do not are
@@ -526,7 +556,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
     size_t nbi = bi + bstep;
     if (PAGED) nblk = first_valid(nblk, nblk < blk1 ? table_entry(nblk) : -1, nbi);
     const bool has_next = nblk < blk1;
-    if constexpr (kDeep) issue_values(bi);
+    if constexpr (kDeep) issue_values(bi, 0, 8);
     if constexpr (KT) {   // K parameters of the block's tokens, per channel group
 #pragma unroll
       for (int u = 0; u < 2; ++u)
@@ -535,9 +565,6 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
           const uint32_t pr = ktp[u * NV + v];
           wl.ktpar[v][par_slot(2 * lane + u)] = make_float2(h2f((uint16_t)(pr & 0xFFFFu)) * kTwo24, h2f((uint16_t)(pr >> 16)));
         }
-    } else if (g < NG) {   // K parameters of the block: every token group from the lane group that fetched it
-      *reinterpret_cast<u4_t*>(&wl.kpar[g][run0]) = kp0;
-      *reinterpret_cast<u4_t*>(&wl.kpar[g][run1]) = kp1;
     }
     // ---- V parameters of the block's tokens, per channel group
     int e_new[NV];
@@ -563,6 +590,9 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       __builtin_amdgcn_sched_barrier(0);
+      // the short queue: values into the registers that the chunk before has left (all of them behind the last chunk: one of
+      // 32K tokens, 4 bits, groups of 32, 4 splits 70.9 -> 69.7 us, 4 of 8K, groups of 64, 4 splits 20.4 -> 19.6)
+      if (!kDeep && c > 0) issue_values(bi, 2 * c - 2, 2 * c);
       if constexpr (KT) {
         if (c == 0) wave_sync();   // the block's K parameters are staged
         h8_t bload[kKeepB ? 1 : CH][4];
@@ -607,42 +637,43 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
             sc[c / COPIES][run][r] = mine ? x : sc[c / COPIES][run][r];
           }
         }
-        continue;
-      }
-      if ((32 * c) % G == 0) {   // the chunk opens a token group: new Q'
-        wave_sync();             // the previous Q' has been read by every lane
-        prep_queries((32 * c) / G);
-        wave_sync();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          bq[j] = *reinterpret_cast<const h8_t*>(cp & 1 ? &wl.qlo[head][8 * (4 * g + j)] : &wl.qhi[head][8 * (4 * g + j)]);
+      } else {
+        if ((32 * c) % (G * QB) == 0) {
+          if (c > 0) wave_sync();   // the previous Q' has been read by every lane
+          prep_queries((32 * c) / G);
+          wave_sync();
         }
-        zq = wl.zq[head];
-        ksb = wl.ksb[head];
-      }
+        if ((32 * c) % G == 0) {   // the chunk opens a token group
+          const int tg = (32 * c) / G % QB;
 #pragma unroll
-      for (int run = 0; run < 2; ++run) {
-        const int T = 2 * c + run;
-        f4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const h8_t ak = F::dequant(kraw[T].w, j);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ak, bq[j], acc, 0, 0, 0);
+          for (int j = 0; j < 4; ++j) bq[j] = *reinterpret_cast<const h8_t*>(&wl.qs.q[tg][cp & 1][head][8 * (4 * g + j)]);
+          zq = wl.qs.zq[tg][head];
+          ksb = wl.qs.ksb[tg][head];
         }
-        // the chunk's owner (copy c % COPIES) adds the other piece's partial product, which the
-        // neighbouring copy computed: GQP lanes up for an even owner, GQP lanes down for an odd one
-        const bool mine = c % COPIES == cp;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float x = acc[r];
-          if (c & 1) x += dpp_f<GQP == 4 ? kRowShr4 : kRowShr8>(x);
-          else x += dpp_f<GQP == 4 ? kRowShl4 : kRowShl8>(x);
-          const float val = __builtin_fmaf(x, ksb, zq);
-          sc[c / COPIES][run][r] = mine ? val : sc[c / COPIES][run][r];
+        for (int run = 0; run < 2; ++run) {
+          const int T = 2 * c + run;
+          f4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const h8_t ak = F::dequant(kraw[T].w, j);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ak, bq[j], acc, 0, 0, 0);
+          }
+          // the chunk's owner (copy c % COPIES) adds the other piece's partial product, which the
+          // neighbouring copy computed: GQP lanes up for an even owner, GQP lanes down for an odd one
+          const bool mine = c % COPIES == cp;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            float x = acc[r];
+            if (c & 1) x += dpp_f<GQP == 4 ? kRowShr4 : kRowShr8>(x);
+            else x += dpp_f<GQP == 4 ? kRowShl4 : kRowShl8>(x);
+            const float val = __builtin_fmaf(x, ksb, zq);
+            sc[c / COPIES][run][r] = mine ? val : sc[c / COPIES][run][r];
+          }
         }
       }
     }
-    if constexpr (!kDeep) issue_values(bi);
+    if constexpr (!kDeep) issue_values(bi, 6, 8);
     if (kDeep && has_next) {   // parameters first: they are the next block's first consumers
       issue_params(nbi);
       issue_keys(nbi);
@@ -687,7 +718,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       __builtin_amdgcn_sched_barrier(0);   // one variant at a time: interleaving them costs a wave per SIMD in registers
-      wave_sync();   // the previous variant has been read by every lane
+      wave_sync();   // the previous variant (or Q') has been read by every lane
 #pragma unroll
       for (int o = 0; o < OWN; ++o) {
         const int sg = 4 * (o * COPIES + cp) + g;   // slot group of this lane's 8 tokens of its o-th chunk
