@@ -197,8 +197,8 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted) : blockIdx.z;
   const bool flush_after = hot.flush_mode == kFlushAfter;
+  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, hot.append && !flush_after ? kFillWork : 0) : blockIdx.z;
   const int split = (int)blockIdx.x - (flush_after ? 1 : 0);
   const int col = lane & 15, g = lane >> 4;            // MFMA column and contraction group
   const int head = col % GQP, cg = col / GQP;          // head carried by the column; column group
@@ -1101,7 +1101,7 @@ namespace {
 template <int BITS, int GQP, bool KT>
 void launch_mode(bool single, bool paged, const DecodeArgs& a, dim3 grid, dim3 block, hipStream_t st) {
   if (paged)
-    decode_int_kernel<BITS, GQP, false, true, KT><<<grid, block, 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences(grid, INT32_MAX)), a);
+    decode_int_kernel<BITS, GQP, false, true, KT><<<grid, block, 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences(grid, INT32_MAX, true, a.max_pages / a.num_splits)), a);
   else if (single)
     decode_int_kernel<BITS, GQP, true, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
   else

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   const int split = (int)blockIdx.x - (flush_after ? 1 : 0);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted) : blockIdx.z;
+  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, hot.append && !flush_after ? kFillWork : 0) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   // Every copy of a head's column receives the same S^T; copy cp keeps the chunks c with
   // c % COPIES == cp, runs their softmax and writes their P', so that work is shared out.
@@ -828,7 +828,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
 template <int BITS, int G, int GQP, bool KT>
 void launch_mode(const GrpArgs& a, bool paged, dim3 grid, hipStream_t st) {
   if (paged)
-    decode_grp_kernel<BITS, G, GQP, true, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences(grid, INT32_MAX)), a);
+    decode_grp_kernel<BITS, G, GQP, true, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences(grid, INT32_MAX, grp_waves_per_simd(BITS, G, GQP, KT) > 1, a.max_pages / a.num_splits)), a);
   else
     decode_grp_kernel<BITS, G, GQP, false, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
 }

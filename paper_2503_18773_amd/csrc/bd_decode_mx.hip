@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256, 2) void decode_mx_kernel(BD_HOT_PARAMS, MxArgs
   const int split = blockIdx.x, hkv = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted) : blockIdx.z;
+  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, 0) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   const int head = col & 3, cg = col >> 2;
   const int head0 = hkv * hot.gq;                  // first query head of this workgroup
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
   const int split = blockIdx.x, hkv = blockIdx.y / nwg, sub0 = GQP * (blockIdx.y % nwg);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted) : blockIdx.z;
+  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, 0) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   const int head = col % GQP, cg = col / GQP;
   const int head0 = hkv * hot.gq + sub0;           // first query head of this workgroup
@@ -679,7 +679,7 @@ template <bool PAGED>
 static hipError_t launch_mx(const MxArgs& a, int batch, hipStream_t st) {
   const dim3 block(256), grid(a.num_splits, a.n_kv_heads * ((a.gq + 15) / 16), batch);
   auto launch = [&](auto kernel) {
-    if (PAGED) kernel<<<grid, block, 0, st>>>(BD_HOT_PAGED(a, 0, sorted_sequences(grid, 512)), a);
+    if (PAGED) kernel<<<grid, block, 0, st>>>(BD_HOT_PAGED(a, 0, sorted_sequences(grid, 512, true, a.max_pages / a.num_splits)), a);
     else   // (tokens and capacity in tokens in the places of the block counts)
       kernel<<<grid, block, 0, st>>>(a.q, a.k_codes, a.k_scales, nullptr, a.gq, a.n_kv_heads, a.num_splits, a.length, a.capacity,
                                  hot_word(0, 0, a.k_new != nullptr), a);

@@ -173,7 +173,7 @@ struct HotArgs {
   int gq, n_kv_heads, num_splits, flush_mode;
   int nb, nbcap, res_len, new_slot;    // contiguous
   int max_pages, num_pages;            // paged
-  int sorted;                          // ... sequences to be sorted (paged_sequence)
+  int sorted, second;                  // ... sequences to be sorted, those of the second layer (paged_sequence)
   bool step;                           // ... the launch is the attention of a fused step
   bool append;                         // the launch appends the step's token itself
   // k_params_, k_res_: the struct's, for the paged form
@@ -181,9 +181,9 @@ struct HotArgs {
       : q(hq), k_res(PAGED ? k_res_ : (const uint16_t*)hy), k_codes((const Codes*)hk),
         k_params(PAGED ? k_params_ : (const Codes*)hx), seq_lens(PAGED ? (const int32_t*)hx : nullptr),
         block_table(PAGED ? (const int32_t*)hy : nullptr), gq(hgq), n_kv_heads(hkvh), num_splits(hns),
-        flush_mode((hm >> 8) & 255), nb(PAGED ? 0 : hi), nbcap(PAGED ? 0 : hj), res_len(PAGED ? 0 : hm & 255),
+        flush_mode((hm >> 8) & 3), nb(PAGED ? 0 : hi), nbcap(PAGED ? 0 : hj), res_len(PAGED ? 0 : hm & 255),
         new_slot(PAGED ? -1 : (hm >> 16) - 1), max_pages(PAGED ? hi : 0), num_pages(PAGED ? hj : 0),
-        sorted(PAGED ? hm & 255 : 0), step(PAGED && (hm >> 16 & 1)), append(PAGED ? (hm >> 16 & 2) != 0 : hm >> 16 > 0) {}
+        sorted(PAGED ? hm & 255 : 0), second(PAGED ? (hm >> 10) & 63 : 0), step(PAGED && (hm >> 16 & 1)), append(PAGED ? (hm >> 16 & 2) != 0 : hm >> 16 > 0) {}
 };
 
 // Waits until at most N vector loads are outstanding.  Where the loads before them are known to have been used, this costs
@@ -203,29 +203,54 @@ __device__ __forceinline__ int32_t scalar_load(const int32_t* p) {
   return *(Const)p;
 }
 
-// Paged cache: the sequence of grid row z and its length.  Where the launch's last round of workgroups (one per
-// compute unit a round) would fill at most half of the units, a ragged batch runs longest sequence first (to 1/16 of
-// the length, then by index), so that those units get short ones.  The lengths' load then stands before everything
-// else of the workgroup, which costs 1.2 us: not worth it for fuller rounds (64 sequences of up to 700 tokens, 512
-// workgroups: 18.9 against 20.3 us a step), nor for MXFP4 past two rounds (24 of up to 5K: 29.4 / 30.1).  Gains, a step:
-// 40 sequences of up to 3.1K tokens, one split, 2-bit codes and 8 heads per KV head 34.9 -> 30.9 us, 4 bits 33.9 -> 31.1,
-// MXFP4 34.8 -> 31.5; 24 of up to 5K, three splits, groups of 32 42.4 -> 39.3, groups of 128 28.0 as before.  Every wave
-// selects the z-th longest itself, a bit of the key at a time; batches of more than 64 sequences stay as they are.
-// sorted_sequences (host): how many sequences there are to be sorted, 0 to leave them as they are.
-static inline int sorted_sequences(dim3 grid, int max_wgs) {
-  const long wgs = (long)grid.x * grid.y * grid.z;
-  return grid.z < 2 || grid.z > 64 || wgs <= 256 || wgs > max_wgs || (wgs - 1) % 256 >= 128 ? 0 : (int)grid.z;
+// Paged cache: the sequence of grid row z and its length.  A ragged batch whose workgroups do not make whole rounds (one
+// per compute unit a round) is dealt by length (to 1/16, then by index).
+// - Up to 512 workgroups, two to a compute unit, all run from the start, and workgroup 256 + j goes to j's unit (as the
+//   times show).  The shortest sequences form the second layer, shortest first, on top of the next shortest in order; the
+//   longest have a unit to themselves.  40 sequences of 1K to 3.1K tokens, one split, 2 bits, 8 heads per KV head 23.4 ->
+//   21.3 us a call against longest first; against the order as given 56 of 0.3K to 3.1K 26.7 -> 21.1, 4 bits 64 of 0.4K to 4K
+//   33.4 -> 29.7, 20 of 2K to 6K in three splits 24.6 -> 23.6, MXFP4 60 of 0.3K to 3K 25.4 -> 23.0.
+// - Past that, and where one workgroup fills a unit, rounds follow as units come free: where the last would fill at most
+//   half of them, longest first, so that they get short ones.  24 of up to 5K, three splits, groups of 32 42.4 -> 39.3;
+//   not MXFP4 (29.4 / 30.1).
+// The lengths' load then stands before everything else of the workgroup, which costs 0.3 to 0.6 us where the lengths are
+// equal after all (64 of 2000, 4 bits 27.9 -> 28.2, MXFP4 64 of 3000 37.1 -> 37.8) and more than it gives where all are
+// short (64 of 100 to 300 10.3 -> 10.7): fuller second layers only for tables of eight blocks a split and more.  Every wave
+// selects its sequence itself, a bit of the key at a time; batches of more than 64 sequences stay as they are.
+// A sequence whose residual this step's token fills is packed before it is attended: 5 us, the time of kFillWork tokens,
+// which count as length (steps of 40 / 56 sequences, one of which fills, 2 bits, 8 heads 26.7 -> 24.1 / 30.9 -> 27.5 us).
+// sorted_sequences (host): how many sequences are to be sorted (0: left as they are), and how many of them are in the
+// second layer, from bit 10.
+constexpr int kFillWork = 900;
+static inline int sorted_sequences(dim3 grid, int max_wgs, bool two_per_cu, int blocks_per_split) {
+  const long per_seq = (long)grid.x * grid.y, wgs = per_seq * grid.z;
+  if (grid.z < 2 || grid.z > 64 || wgs <= 256 || wgs > max_wgs) return 0;
+  if (two_per_cu && wgs <= (blocks_per_split >= 8 ? 512 : 384)) {
+    const long second = (wgs - 256 + per_seq - 1) / per_seq;
+    return (int)grid.z | (int)(second < grid.z / 2 ? second : grid.z / 2) << 10;
+  }
+  return (wgs - 1) % 256 >= 128 ? 0 : (int)grid.z;
 }
-__device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_lens, int lane, int& seq_len, int n) {
+__device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_lens, int lane, int& seq_len, int n, int second,
+                                              int fill_work) {
   if (n == 0) {
     seq_len = scalar_load(seq_lens + blockIdx.z);
     return blockIdx.z;
   }
   const int len = seq_lens[min(lane, n - 1)];
   // exponent and four bits of the length: 0 .. 30 * 16 + 15
-  const uint32_t key = len > 0 ? (__float_as_uint((float)len) >> 19) - (127u << 4) : 0u;
+  const float work = (float)len + ((len & 127) == 127 ? (float)fill_work : 0.0f);
+  const uint32_t key = len > 0 ? (__float_as_uint(work) >> 19) - (127u << 4) : 0u;
   uint64_t cand = __ballot(lane < n);   // those that share the key's leading bits
+  if (__all(key == (uint32_t)__builtin_amdgcn_readfirstlane(key))) {
+    seq_len = __builtin_amdgcn_readlane(len, blockIdx.z);
+    return blockIdx.z;
+  }
   int z = blockIdx.z;                   // of which this is the wanted one's place
+  if (second > 0) {
+    const int first = n - second;
+    z = z < second ? first - second + z : z < first ? z - second : n - 1 - (z - first);
+  }
 #pragma unroll
   for (int bit = 8; bit >= 0; --bit) {
     const uint64_t ones = __ballot(((key >> bit) & 1u) != 0) & cand;

@@ -162,6 +162,37 @@ def test_ragged_batches_attend_their_own_lengths_in_any_order(fmt, hq, batch):
     assert pc.status.item() == 0
 
 
+@pytest.mark.parametrize("fmt,batch,ns", [("int4", 64, 4), ("int2_kt", 49, 4), ("mxfp4", 29, 8), ("int4_g32", 3, 80),
+                                          ("int4_kt_g64", 2, 128), ("int4", 33, 4)])
+def test_second_layers_of_workgroups_attend_their_own_sequences(fmt, batch, ns):
+    """Up to 512 workgroups with tables of eight blocks a split: the shortest sequences share a compute unit with the
+    next shortest (512 = all of them, odd batches, a second layer of more than half of the sequences).  Every row is bit
+    for bit that of a batch of one."""
+    import torch
+    dt = torch.bfloat16 if fmt == "mxfp4" else torch.float16
+    rng = np.random.default_rng(batch)
+    lens = rng.integers(0, 500, batch)
+    lens[:2] = 1, 300
+    table = torch.full((batch, 8 * ns), -1, dtype=torch.int32)
+    table[:, :4] = torch.randperm(batch * 4).view(batch, 4).to(torch.int32)
+    gen = torch.Generator(device="cuda:0").manual_seed(batch)
+    pc = B.PagedKVCache(batch, 8, 2, fmt, batch * 4, table)
+    q = torch.randn((batch, 8, 128), device="cuda:0", generator=gen).to(dt)
+    kv = [tuple(torch.randn((2, int(n), 128), device="cuda:0", generator=gen).to(dt) for _ in range(2)) for n in lens]
+    for s, (k, v) in enumerate(kv):
+        pc.quant_pack_kv(s, k, v)
+    out = torch.full((batch, 8, 128), 7.0, dtype=dt, device="cuda:0")
+    pc.decode_attn(q, 0.088, out, num_splits=ns)
+    for s, (k, v) in enumerate(kv):
+        one = B.PagedKVCache(1, 8, 2, fmt, 4, torch.arange(4, dtype=torch.int32).view(1, 4))
+        one.quant_pack_kv(0, k, v)
+        ref = torch.full((1, 8, 128), 9.0, dtype=dt, device="cuda:0")
+        one.decode_attn(q[s:s + 1].contiguous(), 0.088, ref, num_splits=ns)
+        torch.cuda.synchronize()
+        assert torch.equal(out[s], ref[0]), f"{fmt} batch {batch} splits {ns}: sequence {s} of {lens[s]}"
+    assert pc.status.item() == 0
+
+
 @pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int2_kt", 8), ("int4_g32", 8), ("mxfp4", 4), ("mxfp4", 12)])
 @pytest.mark.parametrize("L,asked", [(600, 2), (600, 5), (128 * 9 + 40, 14), (0, 3), (128 * 9 + 40, None)])
 def test_a_call_that_merges_is_its_partials_and_a_merge(fmt, gq, L, asked):
