@@ -20,6 +20,8 @@ BLOCK = 128
 BD_OUT_HALF, BD_OUT_F32 = 0, 1
 BD_STATIC_SCRATCH_BYTES = 4 << 20   # include/bitdecode.h
 
+_byref, _c_int32 = ctypes.byref, ctypes.c_int32
+
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libbitdecode.so")
 _lib = None
 
@@ -115,7 +117,9 @@ def _stream(stream):
         if raw is None:
             _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
         else:
-            _raw_stream = lambda: raw(torch.cuda.current_device())
+            torch.cuda.current_device()   # (initialises; from here on the runtime's own answer does)
+            device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+            _raw_stream = lambda: raw(device())
     return _raw_stream()
 
 
@@ -309,9 +313,18 @@ class KVCache:
             # where those are one per compute unit, some then share one, 128K tokens 40.4 us against 32.9)
             fills = lazy and self.res_len == 127
             ns = self.choose_splits() if fills else bd_step_splits(self.desc, self.packed_len)
-        step = bd_decode_step_lazy if lazy else bd_decode_step
-        self.packed_len, self.res_len = step(self.desc, k_new, v_new, q, self.packed_len, self.res_len,
-                                             softmax_scale, ns, self.workspace(ns), out, stream)
+        # (bd_decode_step / bd_decode_step_lazy without a wrapper's second set of arguments: a step of short contexts is
+        # bound by the host)
+        rows = ns * self.desc.batch * self.desc.n_q_heads
+        ws = self._ws if 0 < rows <= self._ws_rows else self.workspace(ns)
+        pl, rl = _c_int32(self.packed_len), _c_int32(self.res_len)
+        library = _lib or lib()
+        status = (library.bd_decode_step_lazy if lazy else library.bd_decode_step)(
+            _byref(self.desc), _ptr(k_new), _ptr(v_new), _ptr(q), _byref(pl), _byref(rl), softmax_scale, ns, ws.data_ptr(),
+            _ptr(out), _stream(stream))
+        if status != 0:
+            raise BitDecodeError(status, "bd_decode_step_lazy" if lazy else "bd_decode_step")
+        self.packed_len, self.res_len = pl.value, rl.value
         return out
 
     def host_buffer(self, i: int):
