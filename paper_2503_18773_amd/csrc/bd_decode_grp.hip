@@ -7,7 +7,7 @@
 //     s_c and z_c belong to (channel, token group), so every 16-token tile lies inside one
 //     32-token chunk of the block and the B operand (Q', an fp16 high + low pair: the high piece in
 //     the even copies of a head's MFMA column, the low piece in the odd ones, their partial
-//     products added with one DPP move) is rebuilt whenever the chunk enters a new token group.
+//     products added with one DPP move) is another one in every token group.
 //   O^T[c, head] = sum_t code[t, c] * P'_g[t, head],  P'_g = p * s_(t, g) for the channel group g of
 //     c: one variant of P' per channel group, each feeding the M tiles of its channels.  The
 //     variants pass through LDS, which also carries them from the lanes that hold a token's
