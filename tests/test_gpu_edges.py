@@ -193,6 +193,72 @@ def test_second_layers_of_workgroups_attend_their_own_sequences(fmt, batch, ns):
     assert pc.status.item() == 0
 
 
+@pytest.mark.parametrize("lazy", [False, True])
+@pytest.mark.parametrize("fmt,hq,batch,ns", [("int4", 8, 48, 4), ("int4", 8, 40, 7), ("int2_kt", 16, 60, 4), ("int4_g32", 8, 44, 4),
+                                             ("int4_g32", 16, 64, 3), ("mxfp4", 8, 40, 4), ("mxfp4", 32, 50, 4)])
+def test_steps_of_batches_dealt_by_length(fmt, hq, batch, ns, lazy):
+    """Two fused steps in launches that deal the sequences by length (2 KV heads: 320 to 560 workgroups, tables of eight blocks
+    a split): each sequence's token goes to its own residual or page, a block that it fills to the sequence's own page, one that
+    needs a page it does not have is dropped.  Eager, against append + attention on a twin; lazy, each sequence against a
+    lazy step of a batch of one: outputs, residual rows, pages and lengths bit for bit."""
+    import torch
+    mx, H, P = fmt == "mxfp4", 2, 5
+    dt = torch.bfloat16 if mx else torch.float16
+    rng = np.random.default_rng(batch + ns)
+    lens = rng.integers(0, 500, batch)
+    lens[:8] = 127, 128 * 3 + 127, 0, 128 * 2 + 127, 128 * 3 + 127, 126, 128, 300
+    lens[-3:] = 128 + 127, 1, 128 * 2 + 126
+    table = torch.full((batch, 8 * ns), -1, dtype=torch.int32)
+    table[:, :P] = torch.as_tensor(rng.permutation(batch * P).reshape(batch, P).astype(np.int32))
+    table[4, 3 if not mx else 4] = -1   # (128 * 3 + 127 tokens: no page for the block that is filled, or begun, next)
+    if mx:
+        lens[4] = 128 * 4
+    gen = torch.Generator(device="cuda:0").manual_seed(batch)
+    rows = lambda *shape: torch.randn(shape, device="cuda:0", generator=gen).to(dt)
+    kv = [(rows(H, int(n), 128), rows(H, int(n), 128)) for n in lens]
+
+    def paged(seqs, t):
+        c = B.PagedKVCache(len(seqs), hq, H, fmt, batch * P, t)
+        for i, s in enumerate(seqs):
+            c.quant_pack_kv(i, *kv[s])
+        return c
+
+    a = paged(range(batch), table)
+    twin = None if lazy else paged(range(batch), table)
+    ones = [paged([s], table[s:s + 1]) for s in range(batch)] if lazy else []
+    for step in range(2):
+        kn, vn, q = rows(batch, H, 128), rows(batch, H, 128), rows(batch, hq, 128)
+        out, ref = (torch.full((batch, hq, 128), x, dtype=dt, device="cuda:0") for x in (7.0, 9.0))
+        a.decode_step(kn, vn, q, 0.088, out, ns, lazy=lazy)
+        if lazy:
+            for s, one in enumerate(ones):
+                one.decode_step(*(x[s:s + 1].contiguous() for x in (kn, vn, q)), 0.088, ref[s:s + 1], ns, lazy=True)
+        else:
+            twin.append_kv(kn, vn)
+            twin.decode_attn(q, 0.088, ref, ns)
+        torch.cuda.synchronize()
+        for s in range(batch):
+            assert torch.equal(out[s], ref[s]), f"{fmt} step {step}: sequence {s} of {lens[s]}"
+        assert a.status.item() == 2
+    want = [int(n) + 2 for n in lens]
+    want[4] = int(lens[4])
+    assert a.seq_lens.tolist() == want
+    per_page = [n // (batch * P) for n in a.sizes[:4]]
+    per_seq = [n // batch for n in a.sizes[4:6]]
+    if lazy:
+        for s, one in enumerate(ones):
+            assert one.seq_lens.item() == want[s]
+            for i in range(0 if mx else 2):
+                assert torch.equal(a.buffers[4 + i][s * per_seq[i]:(s + 1) * per_seq[i]], one.buffers[4 + i][:per_seq[i]]), (s, i)
+            for page in table[s, :P].tolist():
+                for i in range(4):
+                    at = slice(page * per_page[i], (page + 1) * per_page[i])
+                    assert page < 0 or torch.equal(a.buffers[i][at], one.buffers[i][at]), (s, page, i)
+    else:
+        for i in range(4 if mx else 6):
+            assert torch.equal(a.buffers[i], twin.buffers[i]), i
+
+
 @pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int2_kt", 8), ("int4_g32", 8), ("mxfp4", 4), ("mxfp4", 12)])
 @pytest.mark.parametrize("L,asked", [(600, 2), (600, 5), (128 * 9 + 40, 14), (0, 3), (128 * 9 + 40, None)])
 def test_a_call_that_merges_is_its_partials_and_a_merge(fmt, gq, L, asked):
