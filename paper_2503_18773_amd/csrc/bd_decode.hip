@@ -1101,7 +1101,7 @@ namespace {
 template <int BITS, int GQP, bool KT>
 void launch_mode(bool single, bool paged, const DecodeArgs& a, dim3 grid, dim3 block, hipStream_t st) {
   if (paged)
-    decode_int_kernel<BITS, GQP, false, true, KT><<<grid, block, 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences(grid, INT32_MAX, true, a.max_pages / a.num_splits)), a);
+    decode_int_kernel<BITS, GQP, false, true, KT><<<grid, block, 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences((long)grid.x * grid.y, grid.z, INT32_MAX, 2, a.max_pages / a.num_splits)), a);
   else if (single)
     decode_int_kernel<BITS, GQP, true, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
   else

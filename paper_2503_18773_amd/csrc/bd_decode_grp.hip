@@ -105,12 +105,6 @@ struct GrpMergeLds {
 
 constexpr size_t gmax(size_t x, size_t y) { return x > y ? x : y; }
 
-// Every instance fits 256 registers (two waves per SIMD) but those for groups of 32 with more than 4 heads
-// per workgroup and 4-bit codes or per-token K, which would spill and run one wave per SIMD instead.
-constexpr int grp_waves_per_simd(int bits, int group, int gqp, bool kt) {
-  return (bits == 4 || kt) && group == 32 && gqp == 8 ? 1 : 2;
-}
-
 // G: quantization group (64 or 32).  GQP: heads per workgroup, padded to 4 or 8 (larger query groups
 // take ceil(g_q / 8) workgroups per split and KV head; 16 heads' LDS scratch would not fit); MFMA
 // column c carries head c % GQP (the copies compute the same numbers).
@@ -828,7 +822,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
 template <int BITS, int G, int GQP, bool KT>
 void launch_mode(const GrpArgs& a, bool paged, dim3 grid, hipStream_t st) {
   if (paged)
-    decode_grp_kernel<BITS, G, GQP, true, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences(grid, INT32_MAX, grp_waves_per_simd(BITS, G, GQP, KT) > 1, a.max_pages / a.num_splits)), a);
+    decode_grp_kernel<BITS, G, GQP, true, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences((long)grid.x * grid.y, grid.z, INT32_MAX, grp_waves_per_simd(BITS, G, GQP, KT), a.max_pages / a.num_splits)), a);
   else
     decode_grp_kernel<BITS, G, GQP, false, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
 }

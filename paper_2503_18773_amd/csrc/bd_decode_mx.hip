@@ -164,7 +164,7 @@ __device__ __forceinline__ void mx_query_operand(const uint16_t* qp, i8_t& bhi, 
 // of a block is shared out over the copies (larger groups: decode_mxg_kernel).
 // PAGED: blocks are found through the block table and every sequence has its own length.
 template <bool PAGED>
-__global__ __launch_bounds__(256, 2) void decode_mx_kernel(BD_HOT_PARAMS, MxArgs a) {
+__global__ __launch_bounds__(256, mx_waves_per_simd(4, PAGED)) void decode_mx_kernel(BD_HOT_PARAMS, MxArgs a) {
   const HotArgs<PAGED, uint8_t> hot(BD_HOT_NAMES, a.k_scales, nullptr);
   __shared__ MergeLdsMx ml;
   const int split = blockIdx.x, hkv = blockIdx.y;
@@ -433,7 +433,7 @@ struct MergeLdsMxG {
 };
 
 template <int GQP, bool PAGED>
-__global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_kernel(BD_HOT_PARAMS, MxArgs a) {
+__global__ __launch_bounds__(256, mx_waves_per_simd(GQP, PAGED)) void decode_mxg_kernel(BD_HOT_PARAMS, MxArgs a) {
   const HotArgs<PAGED, uint8_t> hot(BD_HOT_NAMES, a.k_scales, nullptr);
   constexpr int COPIES = 16 / GQP;     // 2 or 1
   constexpr int NT = 8 / COPIES;       // S^T tiles a lane keeps
@@ -678,15 +678,15 @@ __global__ __launch_bounds__(256, (GQP == 8 || !PAGED) ? 2 : 1) void decode_mxg_
 template <bool PAGED>
 static hipError_t launch_mx(const MxArgs& a, int batch, hipStream_t st) {
   const dim3 block(256), grid(a.num_splits, a.n_kv_heads * ((a.gq + 15) / 16), batch);
-  auto launch = [&](auto kernel) {
-    if (PAGED) kernel<<<grid, block, 0, st>>>(BD_HOT_PAGED(a, 0, sorted_sequences(grid, 512, true, a.max_pages / a.num_splits)), a);
+  auto launch = [&](auto kernel, int gqp) {
+    if (PAGED) kernel<<<grid, block, 0, st>>>(BD_HOT_PAGED(a, 0, sorted_sequences((long)grid.x * grid.y, batch, 512, mx_waves_per_simd(gqp, PAGED), a.max_pages / a.num_splits)), a);
     else   // (tokens and capacity in tokens in the places of the block counts)
       kernel<<<grid, block, 0, st>>>(a.q, a.k_codes, a.k_scales, nullptr, a.gq, a.n_kv_heads, a.num_splits, a.length, a.capacity,
                                  hot_word(0, 0, a.k_new != nullptr), a);
   };
-  if (a.gq <= 4) launch(decode_mx_kernel<PAGED>);
-  else if (a.gq <= 8) launch(decode_mxg_kernel<8, PAGED>);
-  else launch(decode_mxg_kernel<16, PAGED>);
+  if (a.gq <= 4) launch(decode_mx_kernel<PAGED>, 4);
+  else if (a.gq <= 8) launch(decode_mxg_kernel<8, PAGED>, 8);
+  else launch(decode_mxg_kernel<16, PAGED>, 16);
   return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "bd_common.h"
+#include "bd_rules.h"
 
 namespace bd {
 namespace {
@@ -203,34 +204,26 @@ __device__ __forceinline__ int32_t scalar_load(const int32_t* p) {
   return *(Const)p;
 }
 
-// Paged cache: the sequence of grid row z and its length.  A ragged batch whose workgroups do not make whole rounds (one
-// per compute unit a round) is dealt by length (to 1/16, then by index).
-// - Up to 512 workgroups, two to a compute unit, all run from the start, and workgroup 256 + j goes to j's unit (as the
-//   times show).  The shortest sequences form the second layer, shortest first, on top of the next shortest in order; the
-//   longest have a unit to themselves.  40 sequences of 1K to 3.1K tokens, one split, 2 bits, 8 heads per KV head 23.4 ->
-//   21.3 us a call against longest first; against the order as given 56 of 0.3K to 3.1K 26.7 -> 21.1, 4 bits 64 of 0.4K to 4K
-//   33.4 -> 29.7, 20 of 2K to 6K in three splits 24.6 -> 23.6, MXFP4 60 of 0.3K to 3K 25.4 -> 23.0.
-// - Past that, and where one workgroup fills a unit, rounds follow as units come free: where the last would fill at most
-//   half of them, longest first, so that they get short ones.  24 of up to 5K, three splits, groups of 32 42.4 -> 39.3;
-//   not MXFP4 (29.4 / 30.1).
+// Paged cache: the sequence of grid row z and its length.  A ragged batch of 257 workgroups and more (one per compute unit
+// is 256) is dealt by length (to 1/16, then by index):
+// - Up to 384 workgroups, 512 where the table has eight blocks a split and more.  An instance of which two share a compute
+//   unit runs them all from the start, and workgroup 256 + j goes to j's unit (as the times show).  The shortest sequences
+//   form the second layer, shortest first, on top of the next shortest in order; the longest have a unit to themselves.  40
+//   sequences of 1K to 3.1K tokens, one split, 2 bits, 8 heads per KV head 23.4 -> 21.3 us a call against longest first;
+//   against the order as given 56 of 0.3K to 3.1K 26.7 -> 21.1, 4 bits 64 of 0.4K to 4K 33.4 -> 29.7, 20 of 2K to 6K in three
+//   splits 24.6 -> 23.6, MXFP4 60 of 0.3K to 3K 25.4 -> 23.0.
+// - An instance that fills a unit alone (MXFP4 with 9 and more heads per KV head, groups of 32 with more than 4) runs the
+//   rest as units come free: longest first.  MXFP4, 16 heads, 48 sequences of 1K to 3K tokens 48.3 us a step (two layers
+//   51.6, as given 59 for 56 of them, where this takes 51.7); groups of 32, 8 heads, 56 of 1K to 3K 74.5 as given, 62.7.
+// - Past that, rounds follow as units come free: where the last would fill at most half of them, longest first, so that they
+//   get short ones.  24 of up to 5K, three splits, groups of 32 42.4 -> 39.3; not MXFP4 (29.4 / 30.1).
 // The lengths' load then stands before everything else of the workgroup, which costs 0.3 to 0.6 us where the lengths are
-// equal after all (64 of 2000, 4 bits 27.9 -> 28.2, MXFP4 64 of 3000 37.1 -> 37.8) and more than it gives where all are
-// short (64 of 100 to 300 10.3 -> 10.7): fuller second layers only for tables of eight blocks a split and more.  Every wave
+// equal after all (64 of 2000, 4 bits 27.9 -> 28.2, MXFP4 64 of 3000 37.1 -> 37.8, groups of 32 with 8 heads 64 of 2000 62.3 ->
+// 62.9) and more than it gives where all are short (64 of 100 to 300 10.3 -> 10.7): hence the table's width.  Every wave
 // selects its sequence itself, a bit of the key at a time; batches of more than 64 sequences stay as they are.
 // A sequence whose residual this step's token fills is packed before it is attended: 5 us, the time of kFillWork tokens,
 // which count as length (steps of 40 / 56 sequences, one of which fills, 2 bits, 8 heads 26.7 -> 24.1 / 30.9 -> 27.5 us).
-// sorted_sequences (host): how many sequences are to be sorted (0: left as they are), and how many of them are in the
-// second layer, from bit 10.
 constexpr int kFillWork = 900;
-static inline int sorted_sequences(dim3 grid, int max_wgs, bool two_per_cu, int blocks_per_split) {
-  const long per_seq = (long)grid.x * grid.y, wgs = per_seq * grid.z;
-  if (grid.z < 2 || grid.z > 64 || wgs <= 256 || wgs > max_wgs) return 0;
-  if (two_per_cu && wgs <= (blocks_per_split >= 8 ? 512 : 384)) {
-    const long second = (wgs - 256 + per_seq - 1) / per_seq;
-    return (int)grid.z | (int)(second < grid.z / 2 ? second : grid.z / 2) << 10;
-  }
-  return (wgs - 1) % 256 >= 128 ? 0 : (int)grid.z;
-}
 __device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_lens, int lane, int& seq_len, int n, int second,
                                               int fill_work) {
   if (n == 0) {
@@ -246,11 +239,7 @@ __device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_le
     seq_len = __builtin_amdgcn_readlane(len, blockIdx.z);
     return blockIdx.z;
   }
-  int z = blockIdx.z;                   // of which this is the wanted one's place
-  if (second > 0) {
-    const int first = n - second;
-    z = z < second ? first - second + z : z < first ? z - second : n - 1 - (z - first);
-  }
+  int z = place_by_length(blockIdx.z, n, second);   // the wanted one's place among them
 #pragma unroll
   for (int bit = 8; bit >= 0; --bit) {
     const uint64_t ones = __ballot(((key >> bit) & 1u) != 0) & cand;

@@ -1,0 +1,30 @@
+// Answers questions about the launch rules (bd_rules.h), one per argument group, one line each:
+//   grp BITS GROUP GQP KT | mx GQP PAGED     waves per SIMD that the launch counts on
+//   order PER_SEQ BATCH MAX_WGS WAVES BPS    places by length in launch order, or "as given"; then the second layer's size
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "bd_rules.h"
+
+int main(int argc, char** argv) {
+  auto arg = [&](int i) { return i < argc ? atoi(argv[i]) : 0; };
+  for (int i = 1; i < argc;) {
+    if (!strcmp(argv[i], "grp")) {
+      printf("%d\n", bd::grp_waves_per_simd(arg(i + 1), arg(i + 2), arg(i + 3), arg(i + 4) != 0));
+      i += 5;
+    } else if (!strcmp(argv[i], "mx")) {
+      printf("%d\n", bd::mx_waves_per_simd(arg(i + 1), arg(i + 2) != 0));
+      i += 3;
+    } else if (!strcmp(argv[i], "order")) {
+      const int r = bd::sorted_sequences(arg(i + 1), arg(i + 2), arg(i + 3), arg(i + 4), arg(i + 5)), n = r & 255, second = r >> 10;
+      if (n == 0) printf("as given");
+      for (int z = 0; z < n; ++z) printf("%d ", bd::place_by_length(z, n, second));
+      printf("; %d\n", second);
+      i += 6;
+    } else {
+      return 2;
+    }
+  }
+  return 0;
+}

@@ -1,0 +1,87 @@
+"""Host checks of what an attention launch takes for granted (csrc/bd_rules.h): the rules themselves, compiled for the CPU,
+and the registers and LDS of the kernels in the built library, read from their metadata.  No GPU."""
+import glob
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2503_18773_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2503_18773_amd", "csrc")
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+VGPRS, LDS = 512, 160 * 1024   # of a SIMD, per lane; of a compute unit
+
+needs_gxx = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+needs_kernels = pytest.mark.skipif(not os.path.exists(B._LIB_PATH) or not os.path.exists(os.path.join(LLVM, "llvm-readelf")),
+                                   reason="needs the built library and the LLVM tools")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rules") / "launch_rules_check")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, os.path.join(HERE, "host", "launch_rules_check.cpp"),
+                    "-o", exe], check=True)
+    return lambda *q: subprocess.run([exe, *map(str, q)], capture_output=True, text=True, check=True).stdout.splitlines()
+
+
+@pytest.fixture(scope="module")
+def resident(tmp_path_factory):
+    """{mangled kernel name: workgroups of 256 threads that a compute unit holds}"""
+    where = tmp_path_factory.mktemp("objects")
+    shutil.copy(B._LIB_PATH, where)
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", os.path.basename(B._LIB_PATH)], cwd=where, check=True,
+                   capture_output=True)
+    found = {}
+    for obj in glob.glob(str(where / "*gfx950")):
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", obj], capture_output=True, text=True, check=True).stdout
+        for kernel in notes.split("- .agpr_count:")[1:]:
+            name, = re.findall(r"^    \.name: +(\S+)", kernel, re.M)
+            vgprs, = re.findall(r"^    \.vgpr_count: +(\d+)", kernel, re.M)
+            lds, = re.findall(r"^    \.group_segment_fixed_size: +(\d+)", kernel, re.M)
+            granules = (int(vgprs) + 7) // 8 * 8
+            found[name] = min(VGPRS // max(granules, 8), LDS // max(int(lds), 1))
+    assert len(found) > 60, sorted(found)
+    return found
+
+
+@needs_gxx
+@needs_kernels
+def test_kernels_are_as_many_on_a_unit_as_their_launch_counts_on(rules, resident):
+    """Where two of an instance's workgroups share a compute unit, the order of a ragged batch puts them in layers."""
+    seen = 0
+    for name, held in resident.items():
+        mx = re.search(r"decode_mxg?_kernelI(?:Li(\d+)E)?Lb([01])E", name)
+        grp = re.search(r"decode_grp_kernelILi(\d)ELi(\d+)ELi(\d+)ELb[01]ELb([01])E", name)
+        if mx:
+            said, = rules("mx", mx.group(1) or 4, mx.group(2))
+        elif grp:
+            said, = rules("grp", *grp.groups())
+        else:
+            continue
+        seen += 1
+        assert int(said) == min(held, 2), f"{name}: {held} on a compute unit, launched as {said}"
+    assert seen == 38   # 6 of MXFP4, 2 bits x 2 groups x 2 head counts x 2 K modes x paged or not of the groups
+
+
+@needs_gxx
+@pytest.mark.parametrize("batch", [33, 48, 49, 64])
+def test_instances_that_fill_a_unit_run_longest_first(rules, batch):
+    """8 KV heads, one split, tables of 24 blocks: 257 to 512 workgroups, of which 256 run at a time."""
+    waves, = rules("mx", 16, 1)
+    line, = rules("order", 8, batch, 512, waves, 24)
+    assert line == " ".join(map(str, range(batch))) + " ; 0"
+
+
+@needs_gxx
+@pytest.mark.parametrize("per_seq,batch", [(8, 33), (8, 40), (8, 64), (24, 16), (80, 4), (129, 2), (172, 2), (256, 2)])
+def test_two_layers_hold_every_sequence_once(rules, per_seq, batch):
+    line, = rules("order", per_seq, batch, 512, 2, 8)
+    order, second = line.split(" ; ")
+    order, second = list(map(int, order.split())), int(second)
+    assert sorted(order) == list(range(batch)) and 0 < second <= batch // 2
+    assert order[batch - second:] == list(range(batch - 1, batch - 1 - second, -1))     # shortest first, on top of ...
+    assert order[:second] == list(range(batch - 2 * second, batch - second))            # ... the next shortest
