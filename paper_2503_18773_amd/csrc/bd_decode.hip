@@ -97,7 +97,7 @@ struct DecodeArgs {
   float* part_ml;   // [nparts][B][Hq][2]   (running max in log2 units, running sum)
   void* out;    // one split only: the output [B][Hq][128], written instead of the partials; else nullptr
   int out_kind;     // element type of `out` (kOutF16 / kOutBf16 / kOutF32)
-  int n_q_heads, n_kv_heads, gq;
+  int batch, n_q_heads, n_kv_heads, gq;
   int nb;           // packed 128-token blocks
   int nbcap;
   int res_len;
@@ -118,6 +118,7 @@ struct DecodeArgs {
   //   kFlushAfter: the step attends the 128 fp16 rows (the paper's Residual Kernel: attention on the
   //                half-precision block, quantization of it in the same launch); one extra workgroup per
   //                (sequence, KV head), blockIdx.x == 0, does nothing but quantize.
+  // (kFlushLast, paged: the same with the extra workgroups last, paged_grid)
   int flush_mode, flush_blk;
 };
 
@@ -196,10 +197,11 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
   __shared__ int kq_s[HP > 1 ? GQP : 1];                                     // larger groups: each head's normalising exponent
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool flush_after = hot.flush_mode >= kFlushAfter;
+  int split = (int)blockIdx.x - (hot.flush_mode == kFlushAfter ? 1 : 0);
   int seq_len = 0;
-  const bool flush_after = hot.flush_mode == kFlushAfter;
-  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, hot.append && !flush_after ? kFillWork : 0) : blockIdx.z;
-  const int split = (int)blockIdx.x - (flush_after ? 1 : 0);
+  int b = blockIdx.z;
+  if (PAGED && !paged_workgroup(hot, lane, split, b, seq_len)) return;
   const int col = lane & 15, g = lane >> 4;            // MFMA column and contraction group
   const int head = col % GQP, cg = col / GQP;          // head carried by the column; column group
   // Query groups of more than 16 heads are taken 16 at a time by ceil(g_q / 16) workgroups per
@@ -987,7 +989,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
           o1 += f * res_o[h][c0 + 1];
         }
       }
-      const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
+      const size_t row = ((size_t)split * a.batch + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
       if (a.out) {   // one split: row == the output row
         store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);
@@ -1100,12 +1102,14 @@ namespace {
 
 template <int BITS, int GQP, bool KT>
 void launch_mode(bool single, bool paged, const DecodeArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-  if (paged)
-    decode_int_kernel<BITS, GQP, false, true, KT><<<grid, block, 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences((long)grid.x * grid.y, grid.z, INT32_MAX, 2, a.max_pages / a.num_splits)), a);
-  else if (single)
+  if (paged) {
+    const PagedGrid g = paged_grid(grid.x, grid.y, grid.z, a.flush_mode != kFlushNone, INT32_MAX, 2, a.max_pages);
+    decode_int_kernel<BITS, GQP, false, true, KT><<<dim3(g.x, g.y, g.z), block, 0, st>>>(BD_HOT_PAGED(a, g, (int)grid.z), a);
+  } else if (single) {
     decode_int_kernel<BITS, GQP, true, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
-  else
+  } else {
     decode_int_kernel<BITS, GQP, false, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
+  }
 }
 
 template <int BITS, bool KT>
@@ -1150,6 +1154,7 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   a.new_slot = k_new && flush != 1 ? res_len - 1 : -1;
   a.part_o = part_o;
   a.part_ml = part_ml;
+  a.batch = c->batch;
   a.n_q_heads = c->n_q_heads;
   a.n_kv_heads = c->n_kv_heads;
   a.gq = c->n_q_heads / c->n_kv_heads;
@@ -1189,11 +1194,12 @@ hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float sof
   a.v_new = (const uint16_t*)v_new;
   a.new_slot = -1;
   // lazy: a sequence whose residual this step's token fills is attended with its 128 fp16 rows, and one extra
-  // workgroup per (sequence, KV head), blockIdx.x == 0, packs them into the sequence's next page
+  // workgroup per (sequence, KV head) packs them into the sequence's next page
   a.flush_mode = lazy ? kFlushAfter : kFlushNone;
   a.flush_blk = 0;
   a.part_o = part_o;
   a.part_ml = part_ml;
+  a.batch = c->batch;
   a.n_q_heads = c->n_q_heads;
   a.n_kv_heads = c->n_kv_heads;
   a.gq = c->n_q_heads / c->n_kv_heads;
@@ -1206,7 +1212,7 @@ hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float sof
   a.status = c->status;
   a.max_pages = c->max_pages_per_seq;
   a.num_pages = c->num_pages;
-  dim3 grid(num_splits + (lazy ? 1 : 0), c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);
+  dim3 grid(num_splits, c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);   // (paged_grid)
   launch_instance(c->format, a.gq, false, true, a, grid, block, st);
   return hipGetLastError();
 }

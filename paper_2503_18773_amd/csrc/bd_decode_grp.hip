@@ -49,7 +49,7 @@ struct GrpArgs {
   float* part_ml;   // [nparts][B][Hq][2]
   void* out;    // one split only: the output [B][Hq][128], written instead of the partials; else nullptr
   int out_kind;     // element type of `out` (kOutF16 / kOutBf16 / kOutF32)
-  int n_q_heads, n_kv_heads, gq;
+  int batch, n_q_heads, n_kv_heads, gq;
   int nb, nbcap, res_len, num_splits;
   float scale_log2; // softmax_scale * log2(e)
   uint32_t res_scale;   // residual_scale(num_splits)
@@ -152,11 +152,12 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   __shared__ __attribute__((aligned(16))) float q_s[GQP][kD];
   __shared__ float qinv_s[GQP];
 
-  const bool flush_after = hot.flush_mode == kFlushAfter;
-  const int split = (int)blockIdx.x - (flush_after ? 1 : 0);
+  const bool flush_after = hot.flush_mode >= kFlushAfter;
+  int split = (int)blockIdx.x - (hot.flush_mode == kFlushAfter ? 1 : 0);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
-  const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, hot.append && !flush_after ? kFillWork : 0) : blockIdx.z;
+  int b = blockIdx.z;
+  if (PAGED && !paged_workgroup(hot, lane, split, b, seq_len)) return;
   const int col = lane & 15, g = lane >> 4;
   // Every copy of a head's column receives the same S^T; copy cp keeps the chunks c with
   // c % COPIES == cp, runs their softmax and writes their P', so that work is shared out.
@@ -804,7 +805,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
           o1 += f * res_o[h][c0 + 1];
         }
       }
-      const size_t row = ((size_t)split * gridDim.z + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
+      const size_t row = ((size_t)split * a.batch + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
       if (a.out) {   // one split: row == the output row
         store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);
@@ -821,10 +822,12 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
 
 template <int BITS, int G, int GQP, bool KT>
 void launch_mode(const GrpArgs& a, bool paged, dim3 grid, hipStream_t st) {
-  if (paged)
-    decode_grp_kernel<BITS, G, GQP, true, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_PAGED(a, a.flush_mode, sorted_sequences((long)grid.x * grid.y, grid.z, INT32_MAX, grp_waves_per_simd(BITS, G, GQP, KT), a.max_pages / a.num_splits)), a);
-  else
+  if (paged) {
+    const PagedGrid g = paged_grid(grid.x, grid.y, grid.z, a.flush_mode != kFlushNone, INT32_MAX, grp_waves_per_simd(BITS, G, GQP, KT), a.max_pages);
+    decode_grp_kernel<BITS, G, GQP, true, KT><<<dim3(g.x, g.y, g.z), dim3(256), 0, st>>>(BD_HOT_PAGED(a, g, (int)grid.z), a);
+  } else {
     decode_grp_kernel<BITS, G, GQP, false, KT><<<grid, dim3(256), 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
+  }
 }
 
 template <int BITS, int G, bool KT = false>
@@ -834,7 +837,7 @@ void launch_heads(const GrpArgs& a, bool paged, dim3 grid, hipStream_t st) {
 }
 
 hipError_t launch_format(int format, const GrpArgs& a, bool paged, int batch, hipStream_t st) {
-  dim3 grid(a.num_splits + (a.flush_mode == kFlushAfter ? 1 : 0), a.n_kv_heads * ((a.gq + kGrpHeads - 1) / kGrpHeads), batch);
+  dim3 grid(a.num_splits + (!paged && a.flush_mode == kFlushAfter ? 1 : 0), a.n_kv_heads * ((a.gq + kGrpHeads - 1) / kGrpHeads), batch);
   switch (format) {
     case BD_FMT_INT4_G64: launch_heads<4, 64>(a, paged, grid, st); break;
     case BD_FMT_INT4_G32: launch_heads<4, 32>(a, paged, grid, st); break;
@@ -873,6 +876,7 @@ hipError_t launch_decode_grp(const bd_cache* c, const void* q, int packed_len, i
   a.q = (const uint16_t*)q;
   a.part_o = part_o;
   a.part_ml = part_ml;
+  a.batch = c->batch;
   a.n_q_heads = c->n_q_heads;
   a.n_kv_heads = c->n_kv_heads;
   a.gq = c->n_q_heads / c->n_kv_heads;
@@ -907,6 +911,7 @@ hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float
   a.q = (const uint16_t*)q;
   a.part_o = part_o;
   a.part_ml = part_ml;
+  a.batch = c->batch;
   a.n_q_heads = c->n_q_heads;
   a.n_kv_heads = c->n_kv_heads;
   a.gq = c->n_q_heads / c->n_kv_heads;

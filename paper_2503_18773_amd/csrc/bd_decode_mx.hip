@@ -679,7 +679,7 @@ template <bool PAGED>
 static hipError_t launch_mx(const MxArgs& a, int batch, hipStream_t st) {
   const dim3 block(256), grid(a.num_splits, a.n_kv_heads * ((a.gq + 15) / 16), batch);
   auto launch = [&](auto kernel, int gqp) {
-    if (PAGED) kernel<<<grid, block, 0, st>>>(BD_HOT_PAGED(a, 0, sorted_sequences((long)grid.x * grid.y, batch, 512, mx_waves_per_simd(gqp, PAGED), a.max_pages / a.num_splits)), a);
+    if (PAGED) kernel<<<grid, block, 0, st>>>(BD_HOT_PAGED(a, paged_grid(grid.x, grid.y, batch, false, 512, mx_waves_per_simd(gqp, PAGED), a.max_pages), batch), a);
     else   // (tokens and capacity in tokens in the places of the block counts)
       kernel<<<grid, block, 0, st>>>(a.q, a.k_codes, a.k_scales, nullptr, a.gq, a.n_kv_heads, a.num_splits, a.length, a.capacity,
                                  hot_word(0, 0, a.k_new != nullptr), a);

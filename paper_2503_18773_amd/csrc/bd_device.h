@@ -98,10 +98,6 @@ __device__ __forceinline__ float head_max(float x) {
   return join_groups(x, Max());
 }
 
-// Contiguous cache, fused step whose token fills the residual block (Sec. IV-B(1)): how the attention launch
-// packs the block (DecodeArgs / GrpArgs flush_mode).
-constexpr int kFlushNone = 0, kFlushFirst = 1, kFlushAfter = 2;
-
 // Element type of the output rows: the format's own half type (fp16; bf16 for MXFP4) or fp32
 // (bd_cache.out_type).
 constexpr int kOutF16 = 0, kOutBf16 = 1, kOutF32 = 2;
@@ -162,10 +158,10 @@ __device__ __forceinline__ int par_slot(int t) { return t + 2 * (t >> 5); }
 #define BD_HOT_NAMES hq, hk, hx, hy, hgq, hkvh, hns, hi, hj, hm
 #define BD_HOT_CONTIGUOUS(a) \
   a.q, a.k_codes, a.k_params, a.k_res, a.gq, a.n_kv_heads, a.num_splits, a.nb, a.nbcap, hot_word(a.res_len, a.flush_mode, a.new_slot + 1)
-#define BD_HOT_PAGED(a, flush_mode, sorted) \
+#define BD_HOT_PAGED(a, grid, batch) \
   a.q, a.k_codes, a.seq_lens, a.block_table, a.gq, a.n_kv_heads, a.num_splits, a.max_pages, a.num_pages, \
-      hot_word(sorted, flush_mode, a.step + 2 * (a.k_new != nullptr))
-static inline int hot_word(int low, int flush_mode, int high) { return low | flush_mode << 8 | high << 16; }
+      hot_word((grid).order, (grid).flush_mode, a.step + 2 * (a.k_new != nullptr) + 4 * ((grid).flush_mode == kFlushLast ? batch : 0))
+static inline int hot_word(int low, int flush_mode, int high) { return (int)((uint32_t)low | (uint32_t)flush_mode << 8 | (uint32_t)high << 16); }
 template <bool PAGED, class Codes = uint32_t>
 struct HotArgs {
   const uint16_t *q, *k_res;
@@ -175,6 +171,7 @@ struct HotArgs {
   int nb, nbcap, res_len, new_slot;    // contiguous
   int max_pages, num_pages;            // paged
   int sorted, second;                  // ... sequences to be sorted, those of the second layer (paged_sequence)
+  int batch;                           // ... kFlushLast: sequences
   bool step;                           // ... the launch is the attention of a fused step
   bool append;                         // the launch appends the step's token itself
   // k_params_, k_res_: the struct's, for the paged form
@@ -184,7 +181,7 @@ struct HotArgs {
         block_table(PAGED ? (const int32_t*)hy : nullptr), gq(hgq), n_kv_heads(hkvh), num_splits(hns),
         flush_mode((hm >> 8) & 3), nb(PAGED ? 0 : hi), nbcap(PAGED ? 0 : hj), res_len(PAGED ? 0 : hm & 255),
         new_slot(PAGED ? -1 : (hm >> 16) - 1), max_pages(PAGED ? hi : 0), num_pages(PAGED ? hj : 0),
-        sorted(PAGED ? hm & 255 : 0), second(PAGED ? (hm >> 10) & 63 : 0), step(PAGED && (hm >> 16 & 1)), append(PAGED ? (hm >> 16 & 2) != 0 : hm >> 16 > 0) {}
+        sorted(PAGED ? hm & 255 : 0), second(PAGED ? (hm >> 10) & 63 : 0), batch(PAGED ? (int)((uint32_t)hm >> 18) : 0), step(PAGED && (hm >> 16 & 1)), append(PAGED ? (hm >> 16 & 2) != 0 : hm >> 16 > 0) {}
 };
 
 // Waits until at most N vector loads are outstanding.  Where the loads before them are known to have been used, this costs
@@ -255,6 +252,21 @@ __device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_le
   const int b = __builtin_ctzll(__ballot((cand >> lane & 1u) != 0 && before == z));
   seq_len = __builtin_amdgcn_readlane(len, b);
   return b;
+}
+
+// Of an integer format's workgroup: its sequence, the sequence's length, and whether it only packs (split -1).  False: it has
+// nothing to do.
+template <class Hot>
+__device__ __forceinline__ bool paged_workgroup(const Hot& hot, int lane, int& split, int& b, int& seq_len) {
+  if (hot.flush_mode == kFlushLast && (int)blockIdx.z >= hot.batch) {
+    split = -1;
+    b = packed_sequence(blockIdx.x, blockIdx.z, hot.num_splits, hot.batch);
+    if (b >= hot.batch) return false;
+    seq_len = scalar_load(hot.seq_lens + b);
+    return true;
+  }
+  b = paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, hot.append && hot.flush_mode == kFlushNone ? kFillWork : 0);
+  return true;
 }
 
 }  // namespace

@@ -30,4 +30,42 @@ constexpr int place_by_length(int z, int n, int second) {
   return second <= 0 ? z : z < second ? first - second + z : z < first ? z - second : n - 1 - (z - first);
 }
 
+// A launch of attention over pages: `splits` x `groups` (KV heads x pieces of the query group) workgroups for each of
+// `batch` sequences, of which `order` says how they are dealt (sorted_sequences).
+struct PagedGrid {
+  int x, y, z;
+  int order;
+  int flush_mode;   // kFlushNone, kFlushAfter, kFlushLast
+};
+// How a step whose token fills a residual block packs the block in the attention launch (Sec. IV-B(1); DecodeArgs / GrpArgs
+// flush_mode): not at all, before it is attended, or while its fp16 rows are, by workgroups of their own: blockIdx.x == 0 of
+// every split row, or rows of grid z behind the last sequence's.
+constexpr int kFlushNone = 0, kFlushFirst = 1, kFlushAfter = 2, kFlushLast = 3;
+// Lazy: one packing workgroup per (sequence, KV head), which ends at once if the sequence's residual is not full.
+// - An odd number of splits: behind the attending ones, in rows of grid z of their own, so that the attending ones lie on the
+//   chip as if they were alone.  At blockIdx.x == 0 of rows of an even length they all went to the same XCDs and left those
+//   without attending ones (one split: half of the chip).  40 sequences of 1K to 3.1K tokens, one split, 2 bits, 8 heads per KV
+//   head 40.3 -> 23.0 us a step (eager 23.5); 4 bits 24 of up to 5K, three splits 31.3 -> 26.9, 12 of 4K, five 17.6 -> 14.6.
+// - An even one: blockIdx.x == 0.  There the rows go round the XCDs, and the packing ones start first: 4 splits 24 of 4K 25.0
+//   us, behind the others 25.9, 8 splits 8 of 5K 16.1 / 16.6, 2 splits 48 of 2K 26.2 / 27.1 (but 32 of 4K 28.1 / 24.2).  They
+//   take places as the others do and count as such.
+// (Fewer sequences than splits would leave most of a row of grid z without work, and from 2^14 sequences on their number does
+// not fit the preloaded arguments: as with an even number.)
+inline PagedGrid paged_grid(int splits, int groups, int batch, bool lazy, int max_wgs, int waves, int max_pages) {
+  PagedGrid g{splits, groups, batch, 0, kFlushNone};
+  const bool last = splits % 2 == 1 && batch >= splits && batch < 1 << 14;
+  if (lazy && !last) {
+    g.x += 1;
+    g.flush_mode = kFlushAfter;
+  }
+  g.order = sorted_sequences((long)g.x * g.y, batch, max_wgs, waves, max_pages / splits);
+  if (lazy && last) {
+    g.z += (batch + splits - 1) / splits;
+    g.flush_mode = kFlushLast;
+  }
+  return g;
+}
+// The sequence of the packing workgroup at (x, z) of such a grid; `batch` and more: none.
+constexpr int packed_sequence(int x, int z, int splits, int batch) { return (z - batch) * splits + x; }
+
 }  // namespace bd

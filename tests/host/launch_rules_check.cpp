@@ -1,5 +1,7 @@
 // Answers questions about the launch rules (bd_rules.h), one per argument group, one line each:
 //   grp BITS GROUP GQP KT | mx GQP PAGED     waves per SIMD that the launch counts on
+//   lazy SPLITS GROUPS BATCH MAX_PAGES        grid x, y, z of a lazy step, its order and flush mode; then the sequence of every
+//                                            (x, z) whose workgroups pack
 //   order PER_SEQ BATCH MAX_WGS WAVES BPS    places by length in launch order, or "as given"; then the second layer's size
 #include <cstdio>
 #include <cstdlib>
@@ -22,6 +24,14 @@ int main(int argc, char** argv) {
       for (int z = 0; z < n; ++z) printf("%d ", bd::place_by_length(z, n, second));
       printf("; %d\n", second);
       i += 6;
+    } else if (!strcmp(argv[i], "lazy")) {
+      const int splits = arg(i + 1), batch = arg(i + 3);
+      const bd::PagedGrid g = bd::paged_grid(splits, arg(i + 2), batch, true, 1 << 30, 2, arg(i + 4));
+      printf("%d %d %d %d %d ;", g.x, g.y, g.z, g.order, g.flush_mode);
+      for (int z = batch; z < g.z && batch < 1000; ++z)
+        for (int x = 0; x < g.x; ++x) printf(" %d", bd::packed_sequence(x, z, splits, batch));
+      printf("\n");
+      i += 5;
     } else {
       return 2;
     }

@@ -85,3 +85,30 @@ def test_two_layers_hold_every_sequence_once(rules, per_seq, batch):
     assert sorted(order) == list(range(batch)) and 0 < second <= batch // 2
     assert order[batch - second:] == list(range(batch - 1, batch - 1 - second, -1))     # shortest first, on top of ...
     assert order[:second] == list(range(batch - 2 * second, batch - second))            # ... the next shortest
+
+
+FLUSH_AFTER, FLUSH_LAST = 2, 3
+
+
+@needs_gxx
+@pytest.mark.parametrize("splits,batch", [(1, 1), (1, 24), (1, 40), (1, 64), (3, 3), (3, 24), (5, 12), (7, 65), (1, 2 ** 14 - 1)])
+def test_lazy_steps_order_and_place_what_attends_as_the_eager_ones(rules, splits, batch):
+    """Odd split counts: the attending workgroups' grid and order are the eager step's, every sequence has one row of packing
+    workgroups behind them, and the grid is one that a launch takes."""
+    eager, = rules("order", splits * 8, batch, 2 ** 30, 2, 32 // splits)
+    line, = rules("lazy", splits, 8, batch, 32)
+    grid, packed = line.split(" ;")
+    x, y, z, order, mode = map(int, grid.split())
+    assert (x, y, mode) == (splits, 8, FLUSH_LAST) and batch < z <= 65535
+    assert (order & 255 == 0) == eager.startswith("as given") and order >> 10 == int(eager.split(";")[1])
+    if batch < 1000:
+        packed = list(map(int, packed.split()))
+        assert packed[:batch] == list(range(batch)) and all(s >= batch for s in packed[batch:]) and len(packed) < batch + splits
+
+
+@needs_gxx
+@pytest.mark.parametrize("splits,batch", [(2, 40), (4, 24), (3, 2), (1, 2 ** 14), (1, 65535), (65533, 1)])
+def test_lazy_steps_whose_packing_workgroups_stay_in_front(rules, splits, batch):
+    line, = rules("lazy", splits, 1, batch, 32)
+    x, y, z, order, mode = map(int, line.split(" ;")[0].split())
+    assert (x, y, z, mode) == (splits + 1, 1, batch, FLUSH_AFTER)
