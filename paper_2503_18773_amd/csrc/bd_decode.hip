@@ -97,7 +97,7 @@ struct DecodeArgs {
   float* part_ml;   // [nparts][B][Hq][2]   (running max in log2 units, running sum)
   void* out;    // one split only: the output [B][Hq][128], written instead of the partials; else nullptr
   int out_kind;     // element type of `out` (kOutF16 / kOutBf16 / kOutF32)
-  int batch, n_q_heads, n_kv_heads, gq;
+  int n_q_heads, n_kv_heads, gq;
   int nb;           // packed 128-token blocks
   int nbcap;
   int res_len;
@@ -120,6 +120,7 @@ struct DecodeArgs {
   //                (sequence, KV head), blockIdx.x == 0, does nothing but quantize.
   // (kFlushLast, paged: the same with the extra workgroups last, paged_grid)
   int flush_mode, flush_blk;
+  int batch;
 };
 
 // Per-wave LDS scratch.  GQP = query heads per KV head, padded to 4, 8 or 16.
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
   __shared__ int kq_s[HP > 1 ? GQP : 1];                                     // larger groups: each head's normalising exponent
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool flush_after = hot.flush_mode >= kFlushAfter;
+  const bool flush_after = hot.flush_mode == kFlushAfter || (PAGED && hot.flush_mode == kFlushLast);
   int split = (int)blockIdx.x - (hot.flush_mode == kFlushAfter ? 1 : 0);
   int seq_len = 0;
   int b = blockIdx.z;
@@ -989,7 +990,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
           o1 += f * res_o[h][c0 + 1];
         }
       }
-      const size_t row = ((size_t)split * a.batch + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
+      const size_t row = ((size_t)split * (PAGED ? (uint32_t)a.batch : gridDim.z) + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
       if (a.out) {   // one split: row == the output row
         store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);

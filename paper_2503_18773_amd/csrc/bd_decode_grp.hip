@@ -49,7 +49,7 @@ struct GrpArgs {
   float* part_ml;   // [nparts][B][Hq][2]
   void* out;    // one split only: the output [B][Hq][128], written instead of the partials; else nullptr
   int out_kind;     // element type of `out` (kOutF16 / kOutBf16 / kOutF32)
-  int batch, n_q_heads, n_kv_heads, gq;
+  int n_q_heads, n_kv_heads, gq;
   int nb, nbcap, res_len, num_splits;
   float scale_log2; // softmax_scale * log2(e)
   uint32_t res_scale;   // residual_scale(num_splits)
@@ -64,6 +64,7 @@ struct GrpArgs {
   // (kFlushFirst: the workgroup that reads block flush_blk packs it first; kFlushAfter: the step attends the
   // 128 fp16 rows and one extra workgroup per KV head, blockIdx.x == 0, packs them)
   int flush_mode, flush_blk;
+  int batch;
 };
 
 // Q' of K by channel: QB token groups at a time, per head the high fp16 pieces and the low ones, in B-operand slot order
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
   __shared__ __attribute__((aligned(16))) float q_s[GQP][kD];
   __shared__ float qinv_s[GQP];
 
-  const bool flush_after = hot.flush_mode >= kFlushAfter;
+  const bool flush_after = hot.flush_mode == kFlushAfter || (PAGED && hot.flush_mode == kFlushLast);
   int split = (int)blockIdx.x - (hot.flush_mode == kFlushAfter ? 1 : 0);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
@@ -805,7 +806,7 @@ __global__ __launch_bounds__(256, grp_waves_per_simd(BITS, G, GQP, KT)) void dec
           o1 += f * res_o[h][c0 + 1];
         }
       }
-      const size_t row = ((size_t)split * a.batch + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
+      const size_t row = ((size_t)split * (PAGED ? (uint32_t)a.batch : gridDim.z) + b) * a.n_q_heads + hkv * hot.gq + head0 + h;
       float2 o = {o0 + Z, o1 + Z};
       if (a.out) {   // one split: row == the output row
         store_final_pair(a.out, row * kD + c0, a.out_kind, o.x, o.y, L);
