@@ -167,15 +167,16 @@ constexpr size_t cmax(size_t x, size_t y) { return x > y ? x : y; }
 //      presents their P' as its part of the B operand (zero in the k-steps it does not own);
 //      no probability moves between lanes, and the column groups' partial O^T are added
 //      once, after the loop.
-// SINGLE: no wave has more than one block (short contexts) and no residual slice more than kResShort tokens; the host
-//      picks the instance.
+// BLOCKS: kManyBlocks, or no wave has more than one (short contexts): kOneBlock, and no residual slice more than kResShort
+//      tokens; kOneBlockSlice, and residual slices of any length (one_block_instance picks).
 // PAGED: blocks are found through the block table and every sequence has its own length.
 // KT: K is quantized per token (Sec. IV-C(1)):  S[t] = s_t * sum_c Q_c code_tc + z_t * sum_c Q_c,
 //     so Q' = Q is prepared once per kernel instead of once per block and the per-token scale
 //     and zero are applied to the kept S^T values.
-template <int BITS, int GQP, bool SINGLE, bool PAGED, bool KT>
+template <int BITS, int GQP, int BLOCKS, bool PAGED, bool KT>
 __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, DecodeArgs a) {
   const HotArgs<PAGED> hot(BD_HOT_NAMES, a.k_params, a.k_res);
+  constexpr bool kSingle = BLOCKS != kManyBlocks, kShortSlices = BLOCKS != kOneBlockSlice, kLongSlices = BLOCKS != kOneBlock;
   using F = Fmt<BITS>;
   using WL = WaveLds<GQP>;
   using ML = MergeLds<GQP>;
@@ -397,10 +398,10 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
   rows.vn = a.v_new + ((long)unit - rows.new_at) * kD;
   ResidualSlice res;
   auto start_slice = [&]() {
-    if (nres > 0) res.template start<true, !SINGLE>(qbase, gq, nres, rows, wave, lane);
+    if (nres > 0) res.template start<kShortSlices, kLongSlices>(qbase, gq, nres, rows, wave, lane);
   };
   auto attend_slice = [&]() {
-    if (nres > 0) res.template attend<GQP, true, !SINGLE>(nres, a.scale_log2, *reinterpret_cast<ML*>(smem_raw), res_o, res_m, res_l, wave, lane);
+    if (nres > 0) res.template attend<GQP, kShortSlices, kLongSlices>(nres, a.scale_log2, *reinterpret_cast<ML*>(smem_raw), res_o, res_m, res_l, wave, lane);
   };
   // (Where exactly the values are requested is fixed at compile time, so that the compiler knows
   // how many loads are in flight behind the one it waits for: half way through QK^T.)
@@ -673,7 +674,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
   m_run = m_new;
   l_run *= alpha;
   z_run *= alpha;
-  if (!SINGLE && !first && __any(alpha != 1.0f)) {   // nothing to rescale on the first block
+  if (!kSingle && !first && __any(alpha != 1.0f)) {   // nothing to rescale on the first block
 #pragma unroll
     for (int mt = 0; mt < 8; ++mt) oacc[mt] *= alpha;
     xacc *= alpha;
@@ -766,11 +767,11 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
   };
   // Prepares and scores block `blk`, up to the request of its values.
   auto score_block = [&]() {
-    nblk = SINGLE ? blk1 : blk + bstep;
+    nblk = kSingle ? blk1 : blk + bstep;
     nbi = bi + bstep;
     next_entry = -1;   // requested a block ahead, like the parameters
     if (PAGED && nblk < blk1) next_entry = table_entry(nblk);
-    if (!SINGLE) {
+    if (!kSingle) {
       // (quarter of the work done)
       if (4 * done < my_blocks) __builtin_amdgcn_s_setprio(3);
       else if (4 * done < 2 * my_blocks) __builtin_amdgcn_s_setprio(2);
@@ -815,7 +816,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
       for (int j = 0; j < 4; ++j) load_bq(j);
     }
     if constexpr (!KT) zq = wl.zq[head];
-    has_next = !SINGLE && nblk < blk1;
+    has_next = !kSingle && nblk < blk1;
     if (!PAGED && !kEarly && has_next) {   // small, and the next block's first consumers: requested a block ahead
       issue_kpar(nbi);
       issue_vpar(nbi);
@@ -883,7 +884,7 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
   auto advance = [&]() {
     // Both sums grow with the number of tokens, their difference (the signal) with its square root: every
     // 16 blocks the centre sum is taken out of the accumulators and starts again from zero.
-    if (!SINGLE && (done & 15) == 0) {
+    if (!kSingle && (done & 15) == 0) {
 #pragma unroll
       for (int mt = 0; mt < 8; ++mt) oacc[mt] -= xacc[0];
       xacc = (f4_t){0.f, 0.f, 0.f, 0.f};
@@ -897,7 +898,19 @@ __global__ __launch_bounds__(256, 2) void decode_int_kernel(BD_HOT_PARAMS, Decod
   // waits for all of them.  Likewise the blocks inside the one that requests the first, and one way out of their loop, past
   // no load whose use it skips: wherever the compiler sees a path, be it one that is never taken, on which a load has not
   // been waited for, it waits for all of them the next time round.)
-  if (blk >= blk1) {
+  // (A long slice beside a block's registers would leave two workgroups of one block a wave on a compute unit, not three: it
+  // comes first.)
+  if constexpr (BLOCKS == kOneBlockSlice) {
+    start_slice();
+    scale_queries();
+    attend_slice();
+    if (blk < blk1) {
+      issue_first();
+      set_scales();
+      score_block();
+      attend_block();
+    }
+  } else if (blk >= blk1) {
     start_slice();
     scale_queries();
     attend_slice();
@@ -1102,32 +1115,34 @@ __global__ __launch_bounds__(128 * G) void combine_kernel(const float* __restric
 namespace {
 
 template <int BITS, int GQP, bool KT>
-void launch_mode(bool single, bool paged, const DecodeArgs& a, dim3 grid, dim3 block, hipStream_t st) {
+void launch_mode(int blocks, bool paged, const DecodeArgs& a, dim3 grid, dim3 block, hipStream_t st) {
   if (paged) {
     const PagedGrid g = paged_grid(grid.x, grid.y, grid.z, a.flush_mode != kFlushNone, INT32_MAX, 2, a.max_pages);
-    decode_int_kernel<BITS, GQP, false, true, KT><<<dim3(g.x, g.y, g.z), block, 0, st>>>(BD_HOT_PAGED(a, g, (int)grid.z), a);
-  } else if (single) {
-    decode_int_kernel<BITS, GQP, true, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
+    decode_int_kernel<BITS, GQP, kManyBlocks, true, KT><<<dim3(g.x, g.y, g.z), block, 0, st>>>(BD_HOT_PAGED(a, g, (int)grid.z), a);
+  } else if (blocks == kOneBlock) {
+    decode_int_kernel<BITS, GQP, kOneBlock, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
+  } else if (blocks == kOneBlockSlice) {
+    decode_int_kernel<BITS, GQP, kOneBlockSlice, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
   } else {
-    decode_int_kernel<BITS, GQP, false, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
+    decode_int_kernel<BITS, GQP, kManyBlocks, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
   }
 }
 
 template <int BITS, bool KT>
-void launch_group(int gq, bool single, bool paged, const DecodeArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-  if (gq <= 4) launch_mode<BITS, 4, KT>(single, paged, a, grid, block, st);
-  else if (gq <= 8) launch_mode<BITS, 8, KT>(single, paged, a, grid, block, st);
-  else launch_mode<BITS, 16, KT>(single, paged, a, grid, block, st);
+void launch_group(int gq, int blocks, bool paged, const DecodeArgs& a, dim3 grid, dim3 block, hipStream_t st) {
+  if (gq <= 4) launch_mode<BITS, 4, KT>(blocks, paged, a, grid, block, st);
+  else if (gq <= 8) launch_mode<BITS, 8, KT>(blocks, paged, a, grid, block, st);
+  else launch_mode<BITS, 16, KT>(blocks, paged, a, grid, block, st);
 }
 
 // picks the kernel instance: format, query group padded to 4 / 8 / 16 heads, loop structure
-void launch_instance(int format, int gq, bool single, bool paged, const DecodeArgs& a, dim3 grid, dim3 block,
+void launch_instance(int format, int gq, int blocks, bool paged, const DecodeArgs& a, dim3 grid, dim3 block,
                      hipStream_t st) {
   switch (format) {
-    case BD_FMT_INT4: launch_group<4, false>(gq, single, paged, a, grid, block, st); break;
-    case BD_FMT_INT2: launch_group<2, false>(gq, single, paged, a, grid, block, st); break;
-    case BD_FMT_INT4_KT: launch_group<4, true>(gq, single, paged, a, grid, block, st); break;
-    default: launch_group<2, true>(gq, single, paged, a, grid, block, st); break;
+    case BD_FMT_INT4: launch_group<4, false>(gq, blocks, paged, a, grid, block, st); break;
+    case BD_FMT_INT2: launch_group<2, false>(gq, blocks, paged, a, grid, block, st); break;
+    case BD_FMT_INT4_KT: launch_group<4, true>(gq, blocks, paged, a, grid, block, st); break;
+    default: launch_group<2, true>(gq, blocks, paged, a, grid, block, st); break;
   }
 }
 
@@ -1171,9 +1186,8 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   a.max_pages = a.num_pages = 0;
   a.step = 0;
   dim3 grid(num_splits + (flush == 2 ? 1 : 0), c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);
-  // at most one block per wave, and residual slices of one round
-  const bool single = (a.nb + num_splits - 1) / num_splits <= kWaves && res_len <= (kResShort - 2) * num_splits;
-  launch_instance(c->format, a.gq, single, false, a, grid, block, st);
+  const int blocks = one_block_instance(a.nb, num_splits, res_len, (long)num_splits * grid.y * grid.z);
+  launch_instance(c->format, a.gq, blocks, false, a, grid, block, st);
   return hipGetLastError();
 }
 
@@ -1214,7 +1228,7 @@ hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float sof
   a.max_pages = c->max_pages_per_seq;
   a.num_pages = c->num_pages;
   dim3 grid(num_splits, c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);   // (paged_grid)
-  launch_instance(c->format, a.gq, false, true, a, grid, block, st);
+  launch_instance(c->format, a.gq, kManyBlocks, true, a, grid, block, st);
   return hipGetLastError();
 }
 

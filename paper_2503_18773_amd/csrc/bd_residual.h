@@ -29,8 +29,6 @@ namespace bd {
 namespace {
 
 constexpr float kResTop = 16384.0f;
-constexpr int kResShort = 32;   // tokens of a slice that one round takes
-
 // Tokens [first, last) of the residual's `res_len` are split `split`'s slice (scale: ceil(2^32 / number of splits), so that
 // no workgroup starts with a division).
 __device__ __forceinline__ int residual_bound(int res_len, int split, int num_splits, uint32_t scale) {

@@ -13,6 +13,24 @@ constexpr int grp_waves_per_simd(int bits, int group, int gqp, bool kt) {
 // MXFP4: 9 .. 16 heads in pages take 267.
 constexpr int mx_waves_per_simd(int gqp, bool paged) { return gqp == 16 && paged ? 1 : 2; }
 
+// The integer kernel in its three forms (BLOCKS), and the workgroups of up to 8 heads of each that share a unit; of 9 .. 16
+// heads two do in every form.
+constexpr int kManyBlocks = 0, kOneBlock = 1, kOneBlockSlice = 2;
+constexpr int int_waves_per_simd(int gqp, int blocks) { return gqp <= 8 && blocks != kManyBlocks ? 3 : 2; }
+
+constexpr int kResShort = 32;   // residual tokens that a workgroup attends in one round
+// Which form a call over `nb` blocks and `res_len` residual tokens a unit in `splits` splits takes, `wgs` workgroups in all.
+// One block a wave at most takes half the registers, a residual slice of more than a round beside that block all of them
+// again.  Ahead of the block it does not, but is not hidden by the block's way here: better once a unit has two workgroups
+// (256 units), most where a third one on it spares a second round.  A step, 4 bits, the slice beside the block / ahead of it:
+// 8 heads per KV head 320 workgroups with 36 residual tokens 11.4 / 11.1 us, 512 with 116 14.9 / 14.6, 640 with 45 19.4 / 15.5,
+// with 100 21.1 / 17.6; 4 heads 640 with 45 16.5 / 14.0; but 192 with 116 9.9 / 10.3, 264 with 84 11.9 / 12.0.
+inline int one_block_instance(int nb, int splits, int res_len, long wgs) {
+  if ((nb + splits - 1) / splits > 4) return kManyBlocks;   // (four waves)
+  if (res_len <= (kResShort - 2) * splits) return kOneBlock;
+  return wgs > 256 ? kOneBlockSlice : kManyBlocks;
+}
+
 // Paged cache: how many sequences of a batch are to be sorted by length (0: left as they are), and how many of them are in
 // the second layer, from bit 10 (paged_sequence has the rule and its reasons).  per_seq: workgroups of a sequence; waves: per
 // SIMD, of the instance that the launch takes.

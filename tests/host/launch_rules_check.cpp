@@ -1,5 +1,6 @@
 // Answers questions about the launch rules (bd_rules.h), one per argument group, one line each:
-//   grp BITS GROUP GQP KT | mx GQP PAGED     waves per SIMD that the launch counts on
+//   grp BITS GROUP GQP KT | mx GQP PAGED | int GQP BLOCKS   waves per SIMD that the launch counts on
+//   blocks NB SPLITS RES_LEN WGS             the form of the integer kernel that a contiguous call takes
 //   lazy SPLITS GROUPS BATCH MAX_PAGES        grid x, y, z of a lazy step, its order and flush mode; then the sequence of every
 //                                            (x, z) whose workgroups pack
 //   order PER_SEQ BATCH MAX_WGS WAVES BPS    places by length in launch order, or "as given"; then the second layer's size
@@ -18,6 +19,12 @@ int main(int argc, char** argv) {
     } else if (!strcmp(argv[i], "mx")) {
       printf("%d\n", bd::mx_waves_per_simd(arg(i + 1), arg(i + 2) != 0));
       i += 3;
+    } else if (!strcmp(argv[i], "int")) {
+      printf("%d\n", bd::int_waves_per_simd(arg(i + 1), arg(i + 2)));
+      i += 3;
+    } else if (!strcmp(argv[i], "blocks")) {
+      printf("%d\n", bd::one_block_instance(arg(i + 1), arg(i + 2), arg(i + 3), arg(i + 4)));
+      i += 5;
     } else if (!strcmp(argv[i], "order")) {
       const int r = bd::sorted_sequences(arg(i + 1), arg(i + 2), arg(i + 3), arg(i + 4), arg(i + 5)), n = r & 255, second = r >> 10;
       if (n == 0) printf("as given");

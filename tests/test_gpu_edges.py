@@ -502,3 +502,42 @@ def test_a_step_with_a_residual_slice_of_one_round_or_more(fmt, gq, r):
                 ma, rl = attn_errors(got, ref)
                 assert rl <= bar, f"{fmt} {L} tokens, {ns} splits: rel-L2 {rl:.2e}"
             assert np.array_equal(gc.host_buffer(4), pc.host_buffer(4)) and np.array_equal(gc.host_buffer(5), pc.host_buffer(5))
+
+
+@pytest.mark.parametrize("fmt,gq", [("int4", 4), ("int2", 8), ("int2_kt", 3), ("int4_kt", 8), ("int4", 16)])
+@pytest.mark.parametrize("r,lazy", [(29, False), (30, False), (31, False), (33, False), (63, False), (64, False), (95, False),
+                                    (96, False), (126, False), (127, True)])
+def test_long_residual_slices_of_many_workgroups(fmt, gq, r, lazy):
+    """257 and more workgroups of one block a wave: a residual slice of more than 32 tokens is attended ahead of the block.
+    Steps with 1 to 4 blocks (and none) a unit, in one split and in two, against a batch of one, whose workgroups are few:
+    residual and packed block bit for bit; the fp32 rows come from another form of the kernel, whose sums and products are
+    fused as its compilation has it, so that a score differs by an fp32 step or two of its size (scores up to 2^6 in log2
+    units: 2^-17 in a weight, 1e-5), and where weights are rounded to fp16 (5 and more heads) some round the other way: not
+    more than 2^-11 of each, half of that in the row."""
+    import torch
+    bar = 1e-5 if gq <= 4 else 2.0 ** -12
+    H, hq, batch = 2, 2 * gq, 129
+    gen = torch.Generator(device="cuda:0").manual_seed(r)
+    rows = lambda *shape: torch.randn(shape, device="cuda:0", generator=gen).to(torch.float16)
+    for nb, ns in ((0, 1), (1, 1), (3, 1), (4, 1), (5, 2), (8, 2)):
+        L = 128 * nb + r
+        k, v, kn, vn, q = rows(batch, H, L, 128), rows(batch, H, L, 128), rows(batch, H, 128), rows(batch, H, 128), rows(batch, hq, 128)
+
+        def step(s):
+            c = B.KVCache(k[s].shape[0], hq, H, fmt, 128 * (nb + 1))
+            c.desc.out_type = B.BD_OUT_F32
+            out = torch.full((k[s].shape[0], hq, 128), 7.0, dtype=torch.float32, device="cuda:0")
+            c.quant_pack_kv(k[s].contiguous(), v[s].contiguous())
+            c.decode_step(kn[s].contiguous(), vn[s].contiguous(), q[s].contiguous(), 0.088, out, ns, lazy=lazy)
+            return c, out
+
+        many, got = step(slice(0, batch))
+        for s in (0, 1, 63, 127, 128):
+            one, ref = step(slice(s, s + 1))
+            torch.cuda.synchronize()
+            off = ((got[s] - ref[0]).double().norm() / ref[0].double().norm()).item()
+            assert off <= bar, f"{fmt} gq {gq}, {L} tokens, {ns} splits: sequence {s}: {off:.2e}"
+            for i in range(6):
+                n = one.sizes[i]
+                assert torch.equal(many.buffers[i][s * n:(s + 1) * n], one.buffers[i][:n]), (s, i)
+        assert (many.packed_len, many.res_len) == (one.packed_len, one.res_len)

@@ -56,15 +56,22 @@ def test_kernels_are_as_many_on_a_unit_as_their_launch_counts_on(rules, resident
     for name, held in resident.items():
         mx = re.search(r"decode_mxg?_kernelI(?:Li(\d+)E)?Lb([01])E", name)
         grp = re.search(r"decode_grp_kernelILi(\d)ELi(\d+)ELi(\d+)ELb[01]ELb([01])E", name)
+        integer = re.search(r"decode_int_kernelILi\d+ELi(\d+)ELi(\d)E", name)
+        most = 2
         if mx:
             said, = rules("mx", mx.group(1) or 4, mx.group(2))
         elif grp:
             said, = rules("grp", *grp.groups())
+        elif integer:
+            said, = rules("int", *integer.groups())
+            most = 3
         else:
             continue
         seen += 1
-        assert int(said) == min(held, 2), f"{name}: {held} on a compute unit, launched as {said}"
-    assert seen == 38   # 6 of MXFP4, 2 bits x 2 groups x 2 head counts x 2 K modes x paged or not of the groups
+        assert int(said) == min(held, most), f"{name}: {held} on a compute unit, launched as {said}"
+    # 6 of MXFP4; 2 bits x 2 groups x 2 head counts x 2 K modes x paged or not of the groups; 2 bits x 3 head counts x 2 K
+    # modes x paged and the three forms
+    assert seen == 6 + 32 + 48
 
 
 @needs_gxx
@@ -85,6 +92,33 @@ def test_two_layers_hold_every_sequence_once(rules, per_seq, batch):
     assert sorted(order) == list(range(batch)) and 0 < second <= batch // 2
     assert order[batch - second:] == list(range(batch - 1, batch - 1 - second, -1))     # shortest first, on top of ...
     assert order[:second] == list(range(batch - 2 * second, batch - second))            # ... the next shortest
+
+
+MANY_BLOCKS, ONE_BLOCK, ONE_BLOCK_SLICE = 0, 1, 2
+
+
+@needs_gxx
+@pytest.mark.parametrize("gqp", [4, 8])
+def test_calls_of_three_workgroups_a_unit_take_a_form_that_fits_three_times(rules, gqp):
+    """bd_choose_splits hands out up to 768 workgroups where no wave has more than one block; so many are one round whatever
+    residual they carry."""
+    asked = [(nb, splits, res_len, wgs) for splits in (1, 2, 3, 4, 16, 64) for nb in (0, 1, 4 * splits - 3, 4 * splits)
+             for res_len in (0, 1, 30, 31, 32, 33, 60, 61, 64, 127, 128) for wgs in (513, 640, 768)]
+    forms = rules(*(x for q in asked for x in ("blocks", *q)))
+    fits = dict(zip("012", rules(*(x for form in range(3) for x in ("int", gqp, form)))))
+    assert [q for q, form in zip(asked, forms) if fits[form] != "3"] == []
+
+
+@needs_gxx
+@pytest.mark.parametrize("splits", [1, 2, 5])
+def test_forms_of_the_integer_kernel(rules, splits):
+    """More than one block a wave: the loop; slices of more than one round beside one block: the loop up to one workgroup per
+    unit."""
+    ask = lambda nb, res_len, wgs: int(rules("blocks", nb, splits, res_len, wgs)[0])
+    assert ask(4 * splits + 1, 0, 768) == ask(4 * splits + 1, 100, 768) == MANY_BLOCKS
+    assert ask(4 * splits, 30 * splits, 768) == ask(0, 0, 1) == ask(4 * splits, 30 * splits, 8) == ONE_BLOCK
+    if 30 * splits < 128:
+        assert ask(4 * splits, 30 * splits + 1, 256) == MANY_BLOCKS and ask(4 * splits, 30 * splits + 1, 257) == ONE_BLOCK_SLICE
 
 
 FLUSH_AFTER, FLUSH_LAST = 2, 3
