@@ -170,6 +170,9 @@ __global__ __launch_bounds__(256, mx_waves_per_simd(4, PAGED)) void decode_mx_ke
   const int split = blockIdx.x, hkv = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
+  // (the first page's number for the order as given, beside the lengths' load, for batches whose lengths are equal after all:
+  // 64 sequences of 3000 tokens 46.9 -> 46.7 us a step, 56 of them 43.0 -> 42.75, where an order as given takes 46.5 and 42.7)
+  const int first_entry = PAGED ? scalar_load(hot.block_table + (size_t)blockIdx.z * hot.max_pages + min(split * kWaves + wave, hot.max_pages - 1)) : 0;
   const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, 0) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   const int head = col & 3, cg = col >> 2;
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(256, mx_waves_per_simd(4, PAGED)) void decode_mx_ke
   };
   int blk = blk0 + wave;
   size_t bi = unit * nbcap + blk;
-  if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
+  if (PAGED) blk = first_valid(blk, blk < blk1 ? (b == (int)blockIdx.z && blk < hot.max_pages ? first_entry : table_entry(blk)) : -1, bi);
   if (blk < blk1) issue_k(bi);
 
   mx_query_operand(head < nheads ? hot.q + ((size_t)b * (hot.gq * hot.n_kv_heads) + head0 + head) * kD + 16 * g : nullptr, bhi, blo,
@@ -442,6 +445,7 @@ __global__ __launch_bounds__(256, mx_waves_per_simd(GQP, PAGED)) void decode_mxg
   const int split = blockIdx.x, hkv = blockIdx.y / nwg, sub0 = GQP * (blockIdx.y % nwg);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int seq_len = 0;
+  const int first_entry = PAGED ? scalar_load(hot.block_table + (size_t)blockIdx.z * hot.max_pages + min(split * kWaves + wave, hot.max_pages - 1)) : 0;
   const int b = PAGED ? paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, 0) : blockIdx.z;
   const int col = lane & 15, g = lane >> 4;
   const int head = col % GQP, cg = col / GQP;
@@ -520,7 +524,7 @@ __global__ __launch_bounds__(256, mx_waves_per_simd(GQP, PAGED)) void decode_mxg
   };
   int blk = blk0 + wave;
   size_t bi = unit * nbcap + blk;
-  if (PAGED) blk = first_valid(blk, blk < blk1 ? table_entry(blk) : -1, bi);
+  if (PAGED) blk = first_valid(blk, blk < blk1 ? (b == (int)blockIdx.z && blk < hot.max_pages ? first_entry : table_entry(blk)) : -1, bi);
   if (blk < blk1) issue_k(bi);
 
   mx_query_operand(head < nheads ? hot.q + ((size_t)b * (hot.gq * hot.n_kv_heads) + head0 + head) * kD + 16 * g : nullptr, bhi, blo,

@@ -193,6 +193,29 @@ def test_second_layers_of_workgroups_attend_their_own_sequences(fmt, batch, ns):
     assert pc.status.item() == 0
 
 
+@pytest.mark.parametrize("hq", [8, 16, 32])
+@pytest.mark.parametrize("batch,ns,pages,L", [(40, 4, 3, 300), (40, 4, 3, 0), (64, 4, 32, 129), (33, 4, 17, 128 * 17), (3, 43, 1, 128)])
+def test_mx_batches_of_equal_lengths_in_launches_that_sort(hq, batch, ns, pages, L):
+    """Equal lengths keep the order as given, for which a wave asks for its first page's number before it knows: tables
+    narrower and wider than the waves of a sequence, every row bit for bit that of a batch of one."""
+    import torch
+    gen = torch.Generator(device="cuda:0").manual_seed(L)
+    rows = lambda *shape: torch.randn(shape, device="cuda:0", generator=gen).to(torch.bfloat16)
+    table = torch.randperm(batch * pages).view(batch, pages).to(torch.int32)
+    pc = B.PagedKVCache(batch, hq, 2, "mxfp4", batch * pages, table)
+    q, kv = rows(batch, hq, 128), [(rows(2, L, 128), rows(2, L, 128)) for _ in range(batch)]
+    for s, (k, v) in enumerate(kv):
+        pc.quant_pack_kv(s, k, v)
+    out, ref = (torch.full((batch, hq, 128), x, dtype=torch.bfloat16, device="cuda:0") for x in (7.0, 9.0))
+    pc.decode_attn(q, 0.088, out, num_splits=ns)
+    for s, (k, v) in enumerate(kv):
+        one = B.PagedKVCache(1, hq, 2, "mxfp4", pages, torch.arange(pages - 1, -1, -1, dtype=torch.int32).view(1, pages))
+        one.quant_pack_kv(0, k, v)
+        one.decode_attn(q[s:s + 1].contiguous(), 0.088, ref[s:s + 1], num_splits=ns)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref) and pc.status.item() == 0
+
+
 @pytest.mark.parametrize("lazy", [False, True])
 @pytest.mark.parametrize("fmt,hq,batch,ns", [("int4", 8, 48, 4), ("int4", 8, 40, 7), ("int2_kt", 16, 60, 4), ("int4_g32", 8, 44, 4),
                                              ("int4_g32", 16, 64, 3), ("mxfp4", 8, 40, 4), ("mxfp4", 32, 50, 4)])
