@@ -214,12 +214,15 @@ __device__ __forceinline__ int32_t scalar_load(const int32_t* p) {
 //   51.6, as given 59 for 56 of them, where this takes 51.7); groups of 32, 8 heads, 56 of 1K to 3K 74.5 as given, 62.7.
 // - Past that, rounds follow as units come free: where the last would fill at most half of them, longest first, so that they
 //   get short ones.  24 of up to 5K, three splits, groups of 32 42.4 -> 39.3; not MXFP4 (29.4 / 30.1).
-// The lengths' load then stands before everything else of the workgroup, which costs 0.3 to 0.6 us where the lengths are
-// equal after all (64 of 2000, 4 bits 27.9 -> 28.2, MXFP4 64 of 3000 37.1 -> 37.8, groups of 32 with 8 heads 64 of 2000 62.3 ->
-// 62.9) and more than it gives where all are short (64 of 100 to 300 10.3 -> 10.7): hence the table's width.  Every wave
-// selects its sequence itself, a bit of the key at a time; batches of more than 64 sequences stay as they are.
+// The lengths' load then stands before everything else of the workgroup, which costs up to 0.6 us where the lengths are
+// equal after all (64 of 2000, 4 bits 27.9 -> 28.2 us, groups of 32 with 8 heads 62.3 -> 62.9; MXFP4 64 of 3000 46.5 -> 46.7)
+// and more than it gives where all are short (64 of 100 to 300 10.3 -> 10.7): hence the table's width, which is what the host
+// knows of the lengths.  Every wave selects its sequence itself, a bit of the key at a time; batches of more than 64
+// sequences stay as they are.
 // A sequence whose residual this step's token fills is packed before it is attended: 5 us, the time of kFillWork tokens,
 // which count as length (steps of 40 / 56 sequences, one of which fills, 2 bits, 8 heads 26.7 -> 24.1 / 30.9 -> 27.5 us).
+// One number for all formats, though their time a token differs: it only has to keep such a sequence from a shared unit, and
+// 450 and 1800 give what 900 does within 2 % from 2 bits with 4 heads to groups of 32 with 8.
 constexpr int kFillWork = 900;
 __device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_lens, int lane, int& seq_len, int n, int second,
                                               int fill_work) {

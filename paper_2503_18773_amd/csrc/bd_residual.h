@@ -1,23 +1,23 @@
 // The fp16 residual tokens (Sec. IV-B) in the decode kernels of the integer formats, gfx950.
 //
-// A workgroup attends a slice of at most 128 residual tokens, on the matrix unit and in registers only.  Every
-// wave scores the whole slice (S^T[token, head], key rows as A and queries as B, 16 tokens a tile) and multiplies
-// its own 32 channels of the value rows, O^T[c, head] = sum_t V[t, c] p[t, head]: the accumulator layout of the
-// scores (tokens 4g .. 4g + 3 of a tile in lane group g) is the B-operand layout of the second product, so nothing
-// passes between lanes or waves.  Wave w takes channels 32w .. 32w + 31; a lane loads the channel pair
-// 32w + 2 (lane % 16) of a token, and the halves of the loaded words are two A tiles (row i of tile u: channel
-// 32w + 2i + u).  Weights are fp32 up to the product, which takes all 24 bits of p * 2^14 as three fp16 pieces: the last
+// A workgroup attends a slice of at most 128 residual tokens on the matrix unit: S^T[token, head], key rows as A and
+// queries as B, 16 tokens a tile, then O^T[c, head] = sum_t V[t, c] p[t, head].  The accumulator layout of the scores
+// (tokens 4g .. 4g + 3 of a tile in lane group g) is the B-operand layout of the second product, so that no weight
+// passes between lanes; the lane groups are joined for the maximum and the sum alone.  Of a slice of up to 32 tokens
+// every wave scores all and multiplies its own 32 channels of the value rows, and nothing passes between waves: a lane
+// of wave w loads the channel pair 32w + 2 (lane % 16) of a token, and the halves of the loaded words are two A tiles
+// (row i of tile u: channel 32w + 2i + u).  Weights are fp32 up to the product, which takes all 24 bits of p * 2^14 as three fp16 pieces: the last
 // is clear of the subnormals' step for every weight above 2^-15, and what a smaller one loses is below 2^-39.
 //
 // The rows are requested when the kernel starts, ahead of the first packed block, and attended while that block is
-// on its way: an idle wave's time.  What bounds a slice is latency: folding its tokens in one by one at the end of
+// on its way (where their registers allow it; else before it is requested): an idle wave's time.  What bounds a slice is latency: folding its tokens in one by one at the end of
 // the kernel, each behind a load of its own, took 50 us of a launch with up to 127 tokens in a slice (40 ragged
 // sequences of up to 3.1K tokens, 2-bit codes, 8 heads per KV head, one split: 77 us a step, now 35; 24 of up to
 // 5K, 4-bit codes, three splits: 38.2, now 29.0).  The same products at the end of the kernel cost a slice of one
 // token 0.9 us (32K tokens, 64 splits: 14.2 against 13.3 us a step).
 //
 // A slice of more than 32 tokens would take a second round of loads and another 1.3 us for each 32.  It is shared out over
-// the waves instead, 32 tokens of all channels each, and their sums are added in LDS: 40 ragged sequences of up to 3.1K
+// the waves instead, 32 tokens of all channels each, and their maxima and sums meet in LDS, behind three barriers: 40 ragged sequences of up to 3.1K
 // tokens, one split, 2 bits and 8 heads per KV head 29.5 -> 26.6 us a step, 4 bits 31.0 -> 27.2; 750 tokens, 8 units
 // 11.6 -> 10.2.  (A short slice that way, a few tokens a wave, would cost two barriers and more matrix instructions.)
 #pragma once

@@ -564,3 +564,31 @@ def test_long_residual_slices_of_many_workgroups(fmt, gq, r, lazy):
                 n = one.sizes[i]
                 assert torch.equal(many.buffers[i][s * n:(s + 1) * n], one.buffers[i][:n]), (s, i)
         assert (many.packed_len, many.res_len) == (one.packed_len, one.res_len)
+
+
+@pytest.mark.parametrize("lazy", [False, True])
+@pytest.mark.parametrize("fmt", ["int4", "int2_kt_g32", "mxfp4"])
+def test_the_step_wrappers_are_the_caches_step(fmt, lazy):
+    """bd_decode_step / bd_decode_step_lazy of the binding, which KVCache.decode_step does not go through: the lengths they
+    return, the row and the cache bit for bit those of the method, over the step that fills the residual; the same error."""
+    import torch
+    dt = torch.bfloat16 if fmt == "mxfp4" else torch.float16
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    rows = lambda *shape: torch.randn(shape, device="cuda:0", generator=gen).to(dt)
+    a, b = (B.KVCache(2, 8, 2, fmt, 512) for _ in range(2))
+    k, v = rows(2, 2, 382, 128), rows(2, 2, 382, 128)
+    for c in (a, b):
+        c.quant_pack_kv(k, v)
+    wrapper = B.bd_decode_step_lazy if lazy else B.bd_decode_step
+    for ns in (1, 3, 2):
+        kn, vn, q = rows(2, 2, 128), rows(2, 2, 128), rows(2, 8, 128)
+        got, ref = (torch.full((2, 8, 128), x, dtype=dt, device="cuda:0") for x in (7.0, 9.0))
+        a.decode_step(kn, vn, q, 0.088, ref, ns, lazy=lazy)
+        b.packed_len, b.res_len = wrapper(b.desc, kn, vn, q, b.packed_len, b.res_len, 0.088, ns, b.workspace(ns), got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, ref) and (a.packed_len, a.res_len) == (b.packed_len, b.res_len)
+        assert all(torch.equal(x, y) for x, y in zip(a.buffers, b.buffers))
+    for call in (lambda: a.decode_step(kn, vn, None, 0.088, ref, 1, lazy=lazy),
+                 lambda: wrapper(b.desc, kn, vn, None, b.packed_len, b.res_len, 0.088, 1, b.workspace(1), got)):
+        with pytest.raises(B.BitDecodeError, match=wrapper.__name__ + ": invalid argument"):
+            call()
