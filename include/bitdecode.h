@@ -305,7 +305,8 @@ bd_status bd_paged_decode_attn(const bd_paged_cache* c, const void* q, float sof
  * and files it (integer formats: the workgroup that reads the block a step fills quantizes it
  * first; MXFP4: the workgroup that reads the token's block quantizes the token), and the merge,
  * the last kernel, raises the lengths.  Larger query groups: three -- append, attention, merge.
- * (With num_splits == 1 there is no merge and a small kernel raises the lengths.)  A sequence
+ * (With num_splits == 1 there is no merge, and the attention launch raises the lengths itself; it
+ * counts its workgroups in `workspace`, whatever that holds, so steps that may overlap need one each.)  A sequence
  * whose token is dropped for want of a valid page (bit 1 of *status) attends the tokens it had. */
 bd_status bd_paged_decode_step(const bd_paged_cache* c, const void* k_new, const void* v_new,
                                const void* q, float softmax_scale, int32_t num_splits,

@@ -19,6 +19,12 @@ typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
 typedef int i8_t __attribute__((ext_vector_type(8)));
 
+// A step's attention launch that raises the lengths itself (LengthRaise): its counters, nullptr: it does not.
+struct RaiseArgs {
+  unsigned long long* words;
+  int per_seq;   // workgroups of a sequence
+};
+
 // Records a failing HIP call for bd_last_hip_error().
 void note_hip_error(hipError_t e);
 
@@ -54,6 +60,7 @@ hipError_t launch_paged_prefill(const bd_paged_cache* c, int seq, const void* k,
                                 hipStream_t st);
 hipError_t launch_paged_append(const bd_paged_cache* c, const void* k_new, const void* v_new, bool bump,
                                hipStream_t st);
+// (the launches of a paged step in one split raise the lengths too, or have launch_paged_bump do it)
 // `out` (all decode launchers): with num_splits == 1 and out != nullptr the kernel writes the final output
 // rows itself and no merge is needed; otherwise it writes the split partials.
 // raises the length of every sequence whose step's token was appended (launch_paged_append with bump = false)

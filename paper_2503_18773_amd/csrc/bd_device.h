@@ -201,6 +201,28 @@ __device__ __forceinline__ int32_t scalar_load(const int32_t* p) {
   return *(Const)p;
 }
 
+// A length.  RAISE: not to be loaded again later, when LengthRaise may have changed it.
+template <bool RAISE>
+__device__ __forceinline__ int32_t length_of(const int32_t* p) {
+  int32_t x = scalar_load(p);
+  if constexpr (RAISE) asm volatile("" : "+s"(x));
+  return x;
+}
+
+// Raises the length of sequence b if its step went through: a page is needed when the step fills the residual, or, if
+// `every_token`, by every token.
+__device__ __forceinline__ void raise_length(int32_t* seq_lens, const int32_t* block_table, int b, int max_pages, int num_pages,
+                                             bool every_token) {
+  const int len = seq_lens[b];
+  if (len < 0) return;
+  if (every_token || len % kBlock == kBlock - 1) {
+    const int n = len / kBlock;
+    const int page = n < max_pages ? block_table[(size_t)b * max_pages + n] : -1;
+    if (page < 0 || page >= num_pages) return;
+  }
+  seq_lens[b] = len + 1;
+}
+
 // Paged cache: the sequence of grid row z and its length.  A ragged batch of 257 workgroups and more (one per compute unit
 // is 256) is dealt by length (to 1/16, then by index):
 // - Up to 384 workgroups, 512 where the table has eight blocks a split and more.  An instance of which two share a compute
@@ -224,10 +246,11 @@ __device__ __forceinline__ int32_t scalar_load(const int32_t* p) {
 // One number for all formats, though their time a token differs: it only has to keep such a sequence from a shared unit, and
 // 450 and 1800 give what 900 does within 2 % from 2 bits with 4 heads to groups of 32 with 8.
 constexpr int kFillWork = 900;
+template <bool RAISE>
 __device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_lens, int lane, int& seq_len, int n, int second,
                                               int fill_work) {
   if (n == 0) {
-    seq_len = scalar_load(seq_lens + blockIdx.z);
+    seq_len = length_of<RAISE>(seq_lens + blockIdx.z);
     return blockIdx.z;
   }
   const int len = seq_lens[min(lane, n - 1)];
@@ -257,18 +280,78 @@ __device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_le
   return b;
 }
 
+// Raises the lengths of a paged step in its only launch.  Every workgroup reads its sequence's length, where
+// sequences are sorted everybody's, so no length may change before all workgroups have read.  Each counts itself once its waves have,
+// at the counter of its sequence's shard; the one that completes a shard's count counts the shard, and the one that completes
+// those raises.  The atomics are relaxed and at device scope (no cache to write back: the counters are all that is exchanged).
+// A step against a launch of its own for the lengths, one by one: 40 sequences of 1K to 3.1K tokens, 2 bits, 8 heads per KV
+// head 23.4 -> 22.0 us; 58 of 0.5K to 1.5K, 2 bits, 5 heads 21.1 -> 19.5; 9 of up to 26 tokens, 4 bits 9.3 -> 6.5; MXFP4 9 of up
+// to 242 9.2 -> 6.9.
+// A counter is kRaiseMark | count.  The workspace comes as it is: a word without the mark is not a counter yet, and whoever
+// counts there first makes it one (44 bits; the partials that other calls leave there hold no such bits, a NaN).  The last to count leaves it at zero, for the next launch.
+constexpr unsigned long long kRaiseMark = 0x7FB5A3C19E5ull << kRaiseCountBits;
+struct LengthRaise {
+  unsigned long long seen;   // the shard's counter as it was
+
+  __device__ __forceinline__ static unsigned long long* word(const RaiseArgs& r, int i) { return r.words + kRaiseStride * i; }
+  __device__ __forceinline__ static unsigned long long add(unsigned long long* w) {
+    return __hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // add(w) gave `old`: how many had counted before.
+  __device__ __forceinline__ static int counted(unsigned long long* w, unsigned long long old) {
+    if ((old >> kRaiseCountBits) == (kRaiseMark >> kRaiseCountBits)) return (int)(old & ((1u << kRaiseCountBits) - 1));
+    unsigned long long cur = old + 1, next;   // (an exchange fails only where another workgroup has counted)
+    do {
+      next = (cur >> kRaiseCountBits) == (kRaiseMark >> kRaiseCountBits) ? cur + 1 : kRaiseMark + 1;
+    } while (!__hip_atomic_compare_exchange_strong(w, &cur, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return (int)((next - 1) & ((1u << kRaiseCountBits) - 1));
+  }
+  // The whole workgroup, which has read all lengths that it needs; `b` its sequence.
+  __device__ __forceinline__ void arrive(const RaiseArgs& r, int b, int batch) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (not __syncthreads: vector loads stay on their way)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    seen = 0;
+    if (threadIdx.x == blockDim.x - 64) seen = add(word(r, 1 + b % raise_shards(batch)));   // (the last wave has the fewest blocks)
+  }
+  // Behind the workgroup's first loads and what else it can do meanwhile.
+  template <class Hot>
+  __device__ __forceinline__ void finish(const RaiseArgs& r, int b, int batch, const Hot& hot, bool every_token) const {
+    if (threadIdx.x < blockDim.x - 64) return;
+    const int shards = raise_shards(batch), s = b % shards;
+    bool last = false;
+    if (threadIdx.x == blockDim.x - 64 && counted(word(r, 1 + s), seen) + 1 == (int)raise_arrivals(s, r.per_seq, batch)) {
+      __hip_atomic_store(word(r, 1 + s), kRaiseMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (counted(word(r, 0), add(word(r, 0))) + 1 == shards) {
+        __hip_atomic_store(word(r, 0), kRaiseMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = true;
+      }
+    }
+    if (!__any(last)) return;
+    for (int i = threadIdx.x & 63; i < batch; i += 64)
+      raise_length(const_cast<int32_t*>(hot.seq_lens), hot.block_table, i, hot.max_pages, hot.num_pages, every_token);
+  }
+};
+
+// For the attention launch of a call in one split: `per_seq` workgroups of a sequence; `workspace` is free but for the counters.
+static inline RaiseArgs raise_args(const bd_paged_cache* c, bool wanted, long per_seq, void* workspace) {
+  const long bytes = (long)c->batch * c->n_q_heads * (kD + 2) * (long)sizeof(float);   // (bd_workspace_bytes of one split)
+  if (!wanted || !raises_in_launch(per_seq, c->batch, bytes)) return {nullptr, 0};
+  return {reinterpret_cast<unsigned long long*>(workspace), (int)per_seq};
+}
+
 // Of an integer format's workgroup: its sequence, the sequence's length, and whether it only packs (split -1).  False: it has
 // nothing to do.
-template <class Hot>
+template <bool RAISE, class Hot>
 __device__ __forceinline__ bool paged_workgroup(const Hot& hot, int lane, int& split, int& b, int& seq_len) {
   if (hot.flush_mode == kFlushLast && (int)blockIdx.z >= hot.batch) {
     split = -1;
     b = packed_sequence(blockIdx.x, blockIdx.z, hot.num_splits, hot.batch);
     if (b >= hot.batch) return false;
-    seq_len = scalar_load(hot.seq_lens + b);
+    seq_len = length_of<RAISE>(hot.seq_lens + b);
     return true;
   }
-  b = paged_sequence(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, hot.append && hot.flush_mode == kFlushNone ? kFillWork : 0);
+  b = paged_sequence<RAISE>(hot.seq_lens, lane, seq_len, hot.sorted, hot.second, hot.append && hot.flush_mode == kFlushNone ? kFillWork : 0);
   return true;
 }
 

@@ -135,20 +135,11 @@ __global__ __launch_bounds__(256) void paged_append_kernel(PagedArgs a, const ui
   quant_block<BITS, KT, G>(kr, vr, a.k_codes, a.v_codes, a.k_params, a.v_params, (size_t)page * a.n_kv_heads + h);
 }
 
-// seq_lens[b] += 1 for every sequence whose step went through (same test as the append kernel:
-// a page is needed when the step fills the residual, or, if `every_token`, by every token).
+// seq_lens[b] += 1 for every sequence whose step went through (same test as the append kernel).
 __global__ void paged_bump_kernel(PagedArgs a, int batch, bool every_token) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= batch) return;
-  const int len = a.seq_lens[b];
-  if (len < 0) return;
-  if (every_token || len % kBlock == kBlock - 1) {
-    const int n = len / kBlock;
-    int page = -1;
-    if (n < a.max_pages) page = a.block_table[(size_t)b * a.max_pages + n];
-    if (page < 0 || page >= a.num_pages) return;
-  }
-  a.seq_lens[b] = len + 1;
+  raise_length(a.seq_lens, a.block_table, b, a.max_pages, a.num_pages, every_token);
 }
 
 // Copies `ntok` token rows of K and of V between [unit][token][128] arrays of 16-bit values (an append: one row).

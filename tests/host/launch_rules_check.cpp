@@ -3,6 +3,7 @@
 //   blocks NB SPLITS RES_LEN WGS             the form of the integer kernel that a contiguous call takes
 //   lazy SPLITS GROUPS BATCH MAX_PAGES        grid x, y, z of a lazy step, its order and flush mode; then the sequence of every
 //                                            (x, z) whose workgroups pack
+//   raise PER_SEQ BATCH WORKSPACE             the count that each shard of a step in one split reaches, or "no"
 //   order PER_SEQ BATCH MAX_WGS WAVES BPS    places by length in launch order, or "as given"; then the second layer's size
 #include <cstdio>
 #include <cstdlib>
@@ -25,6 +26,12 @@ int main(int argc, char** argv) {
     } else if (!strcmp(argv[i], "blocks")) {
       printf("%d\n", bd::one_block_instance(arg(i + 1), arg(i + 2), arg(i + 3), arg(i + 4)));
       i += 5;
+    } else if (!strcmp(argv[i], "raise")) {
+      const int batch = arg(i + 2);
+      if (!bd::raises_in_launch(arg(i + 1), batch, arg(i + 3))) printf("no");
+      else for (int k = 0; k < bd::raise_shards(batch); ++k) printf("%ld ", bd::raise_arrivals(k, arg(i + 1), batch));
+      printf("\n");
+      i += 4;
     } else if (!strcmp(argv[i], "order")) {
       const int r = bd::sorted_sequences(arg(i + 1), arg(i + 2), arg(i + 3), arg(i + 4), arg(i + 5)), n = r & 255, second = r >> 10;
       if (n == 0) printf("as given");

@@ -592,3 +592,66 @@ def test_the_step_wrappers_are_the_caches_step(fmt, lazy):
                  lambda: wrapper(b.desc, kn, vn, None, b.packed_len, b.res_len, 0.088, 1, b.workspace(1), got)):
         with pytest.raises(B.BitDecodeError, match=wrapper.__name__ + ": invalid argument"):
             call()
+
+
+@pytest.mark.parametrize("fmt,hq,batch,lazy", [
+    ("int4", 2, 1, False), ("int4", 8, 5, True), ("int2_kt", 16, 40, False), ("int4", 34, 17, True), ("int4_g32", 8, 16, True),
+    ("int2_g64", 34, 33, False), ("mxfp4", 8, 70, False), ("mxfp4", 16, 150, False), ("mxfp4", 40, 15, False)])
+def test_a_step_in_one_split_raises_the_lengths_in_any_workspace(fmt, hq, batch, lazy):
+    """Paged steps in one split, whose launch counts its workgroups in the workspace (2 KV heads; 1 to 16 counters, 300
+    workgroups and more that are dealt by length among them): in a workspace of random bytes, of zeros, of another call's
+    partials, as the step before left it, and replayed from a graph, every step raises every length by one, but not that of a
+    sequence without a page for its token and of a negative one, and attends as append and attention do."""
+    import torch
+    mx, H, P = fmt == "mxfp4", 2, 4
+    dt = torch.bfloat16 if mx else torch.float16
+    rng = np.random.default_rng(batch + hq)
+    lens = rng.integers(1, 380, batch)
+    lens[-1] = 127
+    table = torch.as_tensor(rng.permutation(batch * P).reshape(batch, P).astype(np.int32))
+    gen = torch.Generator(device="cuda:0").manual_seed(batch)
+    rows = lambda *shape: torch.randn(shape, device="cuda:0", generator=gen).to(dt)
+    kv = [(rows(H, int(n), 128), rows(H, int(n), 128)) for n in lens]
+    a, twin = (B.PagedKVCache(batch, hq, H, fmt, batch * P, table) for _ in range(2))
+    for c in (a, twin):
+        for s, (k, v) in enumerate(kv):
+            c.quant_pack_kv(s, k, v)
+        if batch > 2:
+            c.seq_lens[1] = -3
+            if mx:
+                c.seq_lens[0] = 128 * P   # no page for the next token
+    want = np.array([int(n) for n in a.seq_lens.tolist()])
+    still = (want < 0) | (want == 128 * P)
+    kn, vn, q = rows(batch, H, 128), rows(batch, H, 128), rows(batch, hq, 128)
+    out, ref = (torch.full((batch, hq, 128), x, dtype=dt, device="cuda:0") for x in (7.0, 9.0))
+    ws = a.workspace(4)
+
+    def step():
+        a.decode_step(kn, vn, q, 0.088, out, 1, lazy=lazy)
+
+    graph = None
+    for i in range(8):
+        if i == 0:
+            ws.copy_(torch.randint(0, 256, ws.shape, device="cuda:0", generator=gen, dtype=torch.uint8))
+        elif i == 1:
+            ws.zero_()
+        elif i == 3:
+            a.decode_attn(q, 0.088, out, 4)   # its partials
+        elif i == 5:
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                step()
+        if graph is not None:
+            graph.replay()
+        else:
+            step()
+        twin.append_kv(kn, vn)
+        twin.decode_attn(q, 0.088, ref, 1)
+        torch.cuda.synchronize()
+        want += ~still
+        assert a.seq_lens.tolist() == want.tolist() == twin.seq_lens.tolist(), i
+        full = torch.as_tensor(lazy & (want % 128 == 0) & ~still, device="cuda:0")   # (a lazy step attends those in fp16)
+        assert torch.equal(out[~full], ref[~full]), i
+    for i in range(4 if mx else 6):
+        assert torch.equal(a.buffers[i], twin.buffers[i]), i

@@ -146,3 +146,14 @@ def test_lazy_steps_whose_packing_workgroups_stay_in_front(rules, splits, batch)
     line, = rules("lazy", splits, 1, batch, 32)
     x, y, z, order, mode = map(int, line.split(" ;")[0].split())
     assert (x, y, z, mode) == (splits + 1, 1, batch, FLUSH_AFTER)
+
+
+@needs_gxx
+@pytest.mark.parametrize("per_seq,batch", [(1, 1), (2, 1), (8, 15), (8, 16), (8, 17), (16, 40), (3, 64), (1, 65535), (65535, 1)])
+def test_counters_of_a_step_in_one_split_count_every_workgroup_once(rules, per_seq, batch):
+    """What the shards' counters of a launch that raises the lengths wait for, against the sequences b that count at shard
+    b % shards; they fit the smallest workspace (one query head)."""
+    counts = [int(x) for x in rules("raise", per_seq, batch, 520 * batch)[0].split()]
+    assert counts == [per_seq * len(range(s, batch, len(counts))) for s in range(min(batch, 16))]
+    assert rules("raise", per_seq, batch, 64 * (len(counts) + 1) - 1) == ["no"]
+    assert rules("raise", 1 << 20, batch, 520 * batch) == ["no"]
