@@ -77,7 +77,6 @@
 namespace bd {
 namespace {
 
-constexpr int kWaves = 4;          // waves per workgroup, all spread along the token axis (W_m = 1)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kTwo24 = 16777216.0f;          // codes enter the MFMAs as code * 2^-24
 constexpr float kTwoM24 = 1.0f / 16777216.0f;
@@ -151,14 +150,15 @@ struct WaveLds<4> {
 };
 // (every column's partial result, the copies of a head included; rows padded by 16 bytes: the 16 columns write the same
 // offset of their rows)
-template <int GQP>
+template <int GQP, int WAVES>
 struct MergeLds {
-  float o[kWaves][16][kD + 4];
-  float m[kWaves][GQP], l[kWaves][GQP], z[kWaves][GQP];
+  float o[WAVES][16][kD + 4];
+  float m[WAVES][GQP], l[WAVES][GQP], z[WAVES][GQP];
 };
 
 constexpr size_t cmax(size_t x, size_t y) { return x > y ? x : y; }
 
+#define BD_WAVES 4
 #define BD_RAISE false
 #define BD_KERNEL(name) decode_##name##_kernel
 #include "bd_int_kernel.h"
@@ -167,6 +167,14 @@ constexpr size_t cmax(size_t x, size_t y) { return x > y ? x : y; }
 #define BD_RAISE true
 #define BD_KERNEL(name) step_##name##_kernel
 #include "bd_int_kernel.h"
+#undef BD_RAISE
+#undef BD_KERNEL
+#undef BD_WAVES
+#define BD_WAVES 8
+#define BD_RAISE false
+#define BD_KERNEL(name) wide_##name##_kernel
+#include "bd_int_kernel.h"
+#undef BD_WAVES
 #undef BD_RAISE
 #undef BD_KERNEL
 
@@ -263,6 +271,8 @@ void launch_mode(int blocks, bool paged, const DecodeArgs& a, dim3 grid, dim3 bl
     const PagedGrid g = paged_grid(grid.x, grid.y, grid.z, a.flush_mode != kFlushNone, INT32_MAX, 2, a.max_pages);
     if (a.raise.words) step_int_kernel<BITS, GQP, kManyBlocks, true, KT><<<dim3(g.x, g.y, g.z), block, 0, st>>>(BD_HOT_PAGED(a, g, (int)grid.z), a);
     else decode_int_kernel<BITS, GQP, kManyBlocks, true, KT><<<dim3(g.x, g.y, g.z), block, 0, st>>>(BD_HOT_PAGED(a, g, (int)grid.z), a);
+  } else if (blocks == kOneBlockWide) {
+    if constexpr (GQP == 4 && !KT) wide_int_kernel<BITS, GQP, kOneBlockWide, false, KT><<<grid, dim3(512), 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
   } else if (blocks == kOneBlock) {
     decode_int_kernel<BITS, GQP, kOneBlock, false, KT><<<grid, block, 0, st>>>(BD_HOT_CONTIGUOUS(a), a);
   } else if (blocks == kOneBlockSlice) {
@@ -331,7 +341,8 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   a.max_pages = a.num_pages = 0;
   a.step = 0;
   dim3 grid(num_splits + (flush == 2 ? 1 : 0), c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);
-  const int blocks = one_block_instance(a.nb, num_splits, res_len, (long)num_splits * grid.y * grid.z);
+  const long wgs = (long)num_splits * grid.y * grid.z;
+  const int blocks = wide_instance(a.nb, num_splits, a.gq, fmt_kt(c->format), wgs, flush != 0) ? kOneBlockWide : one_block_instance(a.nb, num_splits, res_len, wgs);
   launch_instance(c->format, a.gq, blocks, false, a, grid, block, st);
   return hipGetLastError();
 }

@@ -1,5 +1,6 @@
-// The kernel of bd_decode.hip, included twice there: as decode_*_kernel, and, with BD_RAISE, as step_*_kernel, the instances in pages
-// that are a step's only launch and raise the lengths as well (LengthRaise).  (Two sets: the instances that do not raise are up
+// The kernel of bd_decode.hip, included three times there: as decode_*_kernel; with BD_RAISE, as step_*_kernel, the instances in
+// pages that are a step's only launch and raise the lengths as well (LengthRaise); and in BD_WAVES eight waves, as
+// wide_*_kernel (kOneBlockWide).  (Sets of their own: the instances that do not raise are up
 // to 5 % slower where they carry the code along, and another wrapping of the same code moves their registers.)
 // GQP: the query group padded to 4, 8 or 16 heads; the 16 MFMA columns carry it 16/GQP times
 //      (column c holds head c % GQP, "column group" c / GQP) and the softmax work of a block
@@ -11,19 +12,22 @@
 //      no probability moves between lanes, and the column groups' partial O^T are added
 //      once, after the loop.
 // BLOCKS: kManyBlocks, or no wave has more than one (short contexts): kOneBlock, and no residual slice more than kResShort
-//      tokens; kOneBlockSlice, and residual slices of any length (one_block_instance picks).
+//      tokens; kOneBlockSlice, and residual slices of any length (one_block_instance picks).  kOneBlockWide: the same in eight
+//      waves, the slice beside the block (wide_instance).
 // PAGED: blocks are found through the block table and every sequence has its own length.
 // KT: K is quantized per token (Sec. IV-C(1)):  S[t] = s_t * sum_c Q_c code_tc + z_t * sum_c Q_c,
 //     so Q' = Q is prepared once per kernel instead of once per block and the per-token scale
 //     and zero are applied to the kept S^T values.
 template <int BITS, int GQP, int BLOCKS, bool PAGED, bool KT>
-__global__ __launch_bounds__(256, 2) void BD_KERNEL(int)(BD_HOT_PARAMS, DecodeArgs a) {
+__global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS, DecodeArgs a) {
   constexpr bool RAISE = BD_RAISE;
+  constexpr int kWaves = BD_WAVES;   // all spread along the token axis (W_m = 1)
+  static_assert(kWaves == 4 || (GQP == 4 && BLOCKS == kOneBlockWide && !PAGED && !RAISE), "heads, slices and packing are shared out over four waves");
   const HotArgs<PAGED> hot(BD_HOT_NAMES, a.k_params, a.k_res);
   constexpr bool kSingle = BLOCKS != kManyBlocks, kShortSlices = BLOCKS != kOneBlockSlice, kLongSlices = BLOCKS != kOneBlock;
   using F = Fmt<BITS>;
   using WL = WaveLds<GQP>;
-  using ML = MergeLds<GQP>;
+  using ML = MergeLds<GQP, kWaves>;
   constexpr int WORDS = F::WORDS;            // words per lane per tile
   constexpr int KROW = kD * BITS / 32;       // K words per token
   constexpr int VROW = kBlock * BITS / 32;   // V words per channel per block
@@ -111,7 +115,7 @@ __global__ __launch_bounds__(256, 2) void BD_KERNEL(int)(BD_HOT_PARAMS, DecodeAr
     raise.finish(a.raise, b, a.batch, hot, false);
   }
   if (flush_after && split < 0 && head0 != 0) return;   // (one quantizing workgroup per KV head is enough)
-  if (!PAGED && hot.flush_mode != kFlushNone && head0 == 0 &&
+  if (!PAGED && kWaves == 4 && hot.flush_mode != kFlushNone && head0 == 0 &&
       (flush_after ? split < 0 : split == (a.flush_blk / kWaves) % hot.num_splits)) {
     // The step's token completes the residual block: file it, then quantize the 128 rows as block
     // flush_blk.  kFlushFirst: this workgroup is the block's only reader in this launch (one workgroup per
@@ -247,10 +251,10 @@ __global__ __launch_bounds__(256, 2) void BD_KERNEL(int)(BD_HOT_PARAMS, DecodeAr
   rows.vn = a.v_new + ((long)unit - rows.new_at) * kD;
   ResidualSlice res;
   auto start_slice = [&]() {
-    if (nres > 0) res.template start<kShortSlices, kLongSlices>(qbase, gq, nres, rows, wave, lane);
+    if (nres > 0) res.template start<kShortSlices, kLongSlices, (kWaves > 4)>(qbase, gq, nres, rows, wave, lane);
   };
   auto attend_slice = [&]() {
-    if (nres > 0) res.template attend<GQP, kShortSlices, kLongSlices>(nres, a.scale_log2, *reinterpret_cast<ML*>(smem_raw), res_o, res_m, res_l, wave, lane);
+    if (nres > 0) res.template attend<GQP, kShortSlices, kLongSlices, (kWaves > 4)>(nres, a.scale_log2, *reinterpret_cast<ML*>(smem_raw), res_o, res_m, res_l, wave, lane);
   };
   // (Where exactly the values are requested is fixed at compile time, so that the compiler knows
   // how many loads are in flight behind the one it waits for: half way through QK^T.)

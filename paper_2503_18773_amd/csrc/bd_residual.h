@@ -81,11 +81,12 @@ struct ResidualSlice {
   u4_t vl[kTiles][4];        // long slices: 8 channels of the token
 
   // The queries and the slice's n > 0 tokens, of a long one the wave's 32: qbase the group's first query row, gq its heads.
-  // (SHORT, LONG: the lengths that the caller has.)
-  template <bool SHORT = true, bool LONG = true>
+  // (SHORT, LONG: the lengths that the caller has.  MORE: the workgroup has more than the four waves that share a slice.)
+  template <bool SHORT = true, bool LONG = true, bool MORE = false>
   __device__ __forceinline__ void start(const uint16_t* qbase, int gq, int n, const ResidualRows& rows, int wave, int lane) {
     const int col = lane & 15, g = lane >> 4;
     const bool is_short = !LONG || (SHORT && n <= kResShort);
+    if (MORE && wave >= 4) return;
     const int t0 = is_short ? 0 : 32 * wave;
     // (rows past the slice repeat its last token)
     const uint16_t *kl = rows.k + 8 * g, *knl = rows.kn + 8 * g;
@@ -158,13 +159,14 @@ struct ResidualSlice {
   // Leaves the slice's partial result in LDS for the merge: out_o[head][128], relative to 2^out_m[head], and the
   // sum of weights out_l[head].  The caller synchronises before it reads them.  ml: LDS of the final merge (MergeLds),
   // free until then; every wave of the workgroup calls this.
-  template <int GQP, bool SHORT = true, bool LONG = true, class ML>
+  template <int GQP, bool SHORT = true, bool LONG = true, bool MORE = false, class ML>
   __device__ __forceinline__ void attend(int n, float scale_log2, ML& ml, float (*out_o)[kD], float* out_m, float* out_l,
                                          int wave, int lane) {
     const int col = lane & 15, g = lane >> 4;
     ResidualWeights p;
     float s[2][4];
     if (!LONG || (SHORT && n <= kResShort)) {
+      if (MORE && wave >= 4) return;
       const float m = score(n, scale_log2, g, s), l = weigh(n, s, m, p);
       u4_t a0 = {0u, 0u, 0u, 0u}, a1 = a0;
 #pragma unroll
@@ -233,6 +235,7 @@ struct ResidualSlice {
     lds_barrier();
 #pragma unroll
     for (int h0 = 0; h0 < GQP; h0 += 4) {
+      if (MORE && wave >= 4) break;
       const int h = h0 + wave, c0 = 2 * lane;
       float L = 0.f, x = 0.f, y = 0.f;
       for (int w = 0; w < waves; ++w) {

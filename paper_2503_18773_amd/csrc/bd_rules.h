@@ -16,6 +16,7 @@ constexpr int mx_waves_per_simd(int gqp, bool paged) { return gqp == 16 && paged
 // The integer kernel in its three forms (BLOCKS), and the workgroups of up to 8 heads of each that share a unit; of 9 .. 16
 // heads two do in every form.
 constexpr int kManyBlocks = 0, kOneBlock = 1, kOneBlockSlice = 2;
+constexpr int kOneBlockWide = 3;   // one block a wave in workgroups of eight (wide_int_kernel)
 constexpr int int_waves_per_simd(int gqp, int blocks) { return gqp <= 8 && blocks != kManyBlocks ? 3 : 2; }
 
 constexpr int kResShort = 32;   // residual tokens that a workgroup attends in one round
@@ -29,6 +30,15 @@ inline int one_block_instance(int nb, int splits, int res_len, long wgs) {
   if ((nb + splits - 1) / splits > 4) return kManyBlocks;   // (four waves)
   if (res_len <= (kResShort - 2) * splits) return kOneBlock;
   return wgs > 256 ? kOneBlockSlice : kManyBlocks;
+}
+
+// Whether a call, `packs` no block, runs workgroups of eight waves: where four would have two blocks each, eight have one, and a
+// second block's first bytes are not waited for.  K by channel, up to 4 heads per KV head, while a unit has one workgroup.  A
+// step issued one by one, four waves / eight: 1K tokens, 8 units, 4 bits 7.9 / 7.5 us, 2 bits 7.6 / 7.1; 256 units of 900 9.1 /
+// 8.5; 20K and 24K, 8 units, 32 splits 11.1 / 10.6; 32K 11.6 / 11.6, 2 bits 10.2 / 9.9.  No more than that: the two waves of a
+// SIMD issue as many instructions as one with two blocks does.  Per-token K, whose blocks have fewer: 32K 11.0 / 11.45.
+inline bool wide_instance(int nb, int splits, int gq, bool kt, long wgs, bool packs) {
+  return gq <= 4 && !kt && !packs && nb > 4 * splits && nb <= 8 * splits && wgs <= 256;
 }
 
 // Paged cache: how many sequences of a batch are to be sorted by length (0: left as they are), and how many of them are in

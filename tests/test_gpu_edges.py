@@ -655,3 +655,29 @@ def test_a_step_in_one_split_raises_the_lengths_in_any_workspace(fmt, hq, batch,
         assert torch.equal(out[~full], ref[~full]), i
     for i in range(4 if mx else 6):
         assert torch.equal(a.buffers[i], twin.buffers[i]), i
+
+
+@pytest.mark.parametrize("fmt,gq", [("int4", 1), ("int4", 4), ("int2", 3), ("int4_kt", 4)])
+@pytest.mark.parametrize("nb,ns", [(4, 1), (5, 1), (8, 1), (9, 1), (9, 2), (16, 2), (33, 8), (64, 8)])
+def test_workgroups_of_eight_waves(fmt, gq, nb, ns):
+    """On either side of one block and two for each of a workgroup's four waves (where eight take one each), with no residual,
+    slices of one token, of one round and more, and the step that packs a block.  fp32 rows against the oracle; 1e-5, as weights
+    are held whole."""
+    import torch
+    H, hq = 2, 2 * gq
+    for r in (0, 40 * ns, 127):
+        if r > 127:
+            continue
+        w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=hq, n_kv_heads=H, context=128 * nb + r, fmt=fmt, seed=nb)
+        K, V = W.make_kv(w)
+        kn, vn = W.make_new_kv(w, 0)
+        q = W.make_q(w)
+        oc, gc = _caches_of(K, V, fmt, gq)
+        oc.append_kv(kn, vn)
+        ref = O.decode_attn(oc, q, W.softmax_scale(w))
+        gc.desc.out_type = B.BD_OUT_F32
+        out = torch.full((1, hq, 128), 7.0, dtype=torch.float32, device="cuda:0")
+        gc.decode_step(*(to_dev(x, "fp16") for x in (kn, vn, q)), W.softmax_scale(w), out, ns)
+        torch.cuda.synchronize()
+        _, rl = attn_errors(out_to_f64(out), ref)
+        assert rl <= 1e-5, f"{fmt} {nb} blocks and {r} tokens, {ns} splits: rel-L2 {rl:.2e}"
