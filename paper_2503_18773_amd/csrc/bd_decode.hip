@@ -18,22 +18,22 @@
 // inside a word are chosen so that this holds (the analogue, for MFMA, of inducing the packed
 // layout from the consumer instruction, Sec. III-A(1)).
 //
-// Query groups of up to 4 heads run both products on v_mfma_scale_f32_16x16x128_f8f6f4 instead: one instruction
-// contracts all 128 channels (tokens) of a 16-row tile, with the codes as e4m3 / e2m1 numbers (masking again, bd_fmt.h)
-// and Q' and P' as sums of e4m3 pieces, 2^-5 apart: piece k of head h in column 4 (k % 4) + h.  So the 16 columns hold
-// four pieces of four heads; P' takes one matrix instruction of 32 cycles a tile, Q' two (its pieces 4 .. 6 are the
-// second's), against four of 16, and the codes 3 instead of 5 (8) mask instructions per word of 4-bit (2-bit) codes.
-// The pieces' partial scores are added over the column groups with DPP moves, column group c keeping tiles c and 4 + c (8
+// Query groups of up to 4 heads have the 16 columns for four parts of each number, part k of head h in column 4 k + h:
+// * Q' in fixed point, 30 bits from the head's largest of the block down, as four signed bytes, on v_mfma_i32_16x16x64_i8 with
+//   the codes as bytes (masking again, bd_fmt.h): two instructions of 16 cycles contract the 128 channels of a 16-token tile in
+//   exact integers.
+// * P' as a sum of e4m3 pieces, 2^-5 apart, on v_mfma_scale_f32_16x16x128_f8f6f4: one instruction of 32 cycles for the 128
+//   tokens of a 16-channel tile.  Every product of codes and pieces is exact, and the instruction adds to its accumulator as
+//   fp32 does (measured: 1e-7 of the larger of the two).
+// The parts' partial scores are added over the column groups with DPP moves, column group c keeping tiles c and 4 + c (8
 // values per lane per block, every lane doing useful work); the pieces of the weights are exchanged between the column
-// groups likewise, and the column groups' partial O^T are added once, after the loop.  Every product of codes and
-// pieces is exact, and the instruction adds to its accumulator as fp32 does (measured: 1e-7 of the larger of the two).
+// groups likewise, and the column groups' partial O^T are added once, after the loop.
 //
-// Seven pieces of Q' reach 40 (42, 2 bits) bits below its bound max|q| * max scale, 34 below its own leading bit: they
-// hold the 22-bit product q * scale whole wherever the fp16 high + low pair of the larger groups does (whose low piece
-// ends 39 bits below that bound).  Four, one instruction, end after 25 (27), which costs |Q'| far below the bound their
-// bits: with an outlier channel in q that is not K's, a relative L2 error of 5e-5 (x 30), 2.5e-4 (x 100) and 5e-3
-// (x 1000) against 8e-7, 1.5e-6 and 4e-6 with seven.  The three cost 0.3 .. 2 us a step (4 bits, 32K tokens 12.4 -> 12.7
-// us, 24 ragged sequences of up to 5K 28.4 -> 29.5; 2 bits, 8 x 32K 30.8 -> 32.7).
+// The bytes hold the 22-bit product q * scale whole down to 2^-8 of the head's largest in the block, and what smaller ones lose
+// is below an fp32 step of the score.  Relative L2 error of fp32 outputs, against 64 bits, as seven e4m3 pieces had it (two
+// f8f6f4 instructions of 32 cycles a tile; the pieces' conversions take 8 cycles each, 52 a block): 4e-7 .. 6e-7 from 300 to
+// 64K tokens; with an outlier channel in q that is not K's, x 30 .. x 1000, 4e-6 either way.  A step, seven pieces / bytes: 4
+// bits, 1K tokens 7.6 / 7.0 us, 8 units of 24K 10.7 / 10.25, 32K 11.6 / 11.05, 128K 28.0 / 27.35; 2 bits, 8 x 32K 30.1 / 29.1.
 // fp32 outputs are 4e-7 .. 5e-7 off at 4096 tokens, with fp16 weights 1.8e-4 .. 2.2e-4.
 // Groups of 5 .. 16 heads have no columns to spare for the pieces and stay on fp16.
 //
@@ -47,7 +47,7 @@
 //   * K is quantized per channel, so  S = sum_c (Q_c s_c) code_c + sum_c Q_c z_c : the query is
 //     rescaled once per 128-token block and the zero term is one scalar per head and block.
 //     Q' = Q*s, 22 bits, is carried whole, as an fp16 high + low pair (two MFMAs on the same A
-//     operand) or in e4m3 pieces: a single fp16 Q' is not enough when a channel holds outliers.
+//     operand) or in bytes: a single fp16 Q' is not enough when a channel holds outliers.
 //   * V is quantized per token, so  O = sum_t (P_t s_t) code_t + sum_t P_t z_t.
 //   * Raw codes are offset by the token's zero-point, so sum_t P'_t code_t and sum_t P_t z_t are
 //     two large numbers that nearly cancel; the fp16 rounding of P' and the last bits of two
@@ -135,18 +135,16 @@ struct WaveLds {
   uint16_t c16[kBlock];    // per V token: centre code * position factor, in the A-operand order of P'
   float zq[GQP];           // per head: sum_c Q_c z_c * 2^-24 (Q as normalised below)
 };
-// Groups of up to 4 heads: Q' as seven e4m3 pieces, the B operands of two f8f6f4 instructions per tile (pieces 0 .. 3,
-// pieces 4 .. 6 and zeros), as their lanes read them: [instruction][register half][lane group][column = 4 * (piece % 4) +
-// head][register].  (Four columns of padding: the lanes that prepare eight consecutive channels of a head write to eight
-// (half, lane group) rows at once, which then spread over the banks.)
-constexpr int kQueryPieces = 7;
+// Groups of up to 4 heads: Q' as signed bytes, the B operands of two i8 instructions per tile as their lanes read them:
+// [instruction][lane group][column = 4 * byte + head][register].  (Four columns of padding spread the lanes that prepare eight
+// consecutive channels of a head over the banks.)
 template <>
 struct WaveLds<4> {
-  uint32_t qp[2][2][4][20][4];
+  uint32_t qd[2][4][20][4];
   float4 vpar[kParSlots];
   float2 kpar[kParSlots];  // per-token K only: (scale, zero)
   uint32_t c8[4][8];       // per V token: centre code as e4m3, in B-operand order ([lane group][register])
-  float zq[4];
+  float2 zq[4];            // per head: (sum_c Q_c z_c, what a unit of the bytes' integer is of Q')
 };
 // (every column's partial result, the copies of a head included; rows padded by 16 bytes: the 16 columns write the same
 // offset of their rows)
@@ -342,7 +340,7 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   a.step = 0;
   dim3 grid(num_splits + (flush == 2 ? 1 : 0), c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);
   const long wgs = (long)num_splits * grid.y * grid.z;
-  const int blocks = wide_instance(a.nb, num_splits, a.gq, fmt_kt(c->format), wgs, flush != 0) ? kOneBlockWide : one_block_instance(a.nb, num_splits, res_len, wgs);
+  const int blocks = wide_instance(a.nb, num_splits, fmt_bits(c->format), a.gq, fmt_kt(c->format), wgs) ? kOneBlockWide : one_block_instance(a.nb, num_splits, res_len, wgs);
   launch_instance(c->format, a.gq, blocks, false, a, grid, block, st);
   return hipGetLastError();
 }

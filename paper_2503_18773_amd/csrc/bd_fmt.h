@@ -194,6 +194,48 @@ __device__ __forceinline__ uint32_t e4m3_last(uint32_t reg, float x, float y, fl
   return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(__builtin_bit_cast(s2_t, reg), x, y, unit, HI));
 }
 
+// ---- K codes and Q' as operands of v_mfma_i32_16x16x64_i8 --------------------------------
+// Two instructions contract the 128 channels of a 16-token tile, 64 each, 16 of every lane group.  A lane group's 32 codes of a
+// token are bytes after masks as above: 4-bit ones in the order of the words, words 0 and 1 first; 2-bit ones a word each, the
+// odd crumbs of a nibble where they are, that is times 4, and Q' there a quarter.  Q' is an integer x below 2^30; x + 0x808080
+// has the bytes of its four signed digits, the lower three plus 128.
+template <int BITS>
+struct FmtI8;
+template <>
+struct FmtI8<4> {
+  __device__ static i8_t a_operand(const uint32_t* w) { return FmtF8<4>::a_operand(w); }
+  __device__ static constexpr float position(int) { return 1.0f; }   // what channel n of a lane's eight is to be multiplied by
+};
+template <>
+struct FmtI8<2> {
+  __device__ static i8_t a_operand(const uint32_t* w) {
+    i8_t r;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t x = w[i], y = x >> 4;
+      r[4 * i] = (int)(x & scalar_mask(0x03030303u));       // codes 0, 4, 8, 12
+      r[4 * i + 1] = (int)(x & scalar_mask(0x0C0C0C0Cu));   // codes 1, 5, 9, 13
+      r[4 * i + 2] = (int)(y & scalar_mask(0x03030303u));
+      r[4 * i + 3] = (int)(y & scalar_mask(0x0C0C0C0Cu));
+    }
+    return r;
+  }
+  __device__ static constexpr float position(int n) { return n & 1 ? 0.25f : 1.0f; }
+};
+// Bytes of a, b, c, d: out[k] has byte k of each.
+__device__ __forceinline__ void transpose_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&out)[4]) {
+  const uint32_t t0 = __builtin_amdgcn_perm(b, a, 0x05010400u), t1 = __builtin_amdgcn_perm(b, a, 0x07030602u);
+  const uint32_t t2 = __builtin_amdgcn_perm(d, c, 0x05010400u), t3 = __builtin_amdgcn_perm(d, c, 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+  out[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+  out[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+  out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
+}
+// An accumulator starts at the bits of 1.5 * 2^23: as a float it is then 1.5 * 2^23 + sum, for sums below 2^22 (at most 128 *
+// 15 * 128).
+constexpr int kSumBits = 0x4B400000;
+constexpr float kSumBase = 12582912.0f;
+
 // DPP move into the column groups (4 lanes of each 16) named by BANKS; the others keep `old`
 template <int CTRL, int BANKS>
 __device__ __forceinline__ uint32_t dpp_banks(uint32_t old, uint32_t src) {
@@ -208,13 +250,33 @@ __device__ __forceinline__ void exchange_pieces(const uint32_t (&u)[4], uint32_t
   g[2] = dpp_banks<kRowShr4, 0xA>(y0, y1);
   g[3] = dpp_banks<kRowShl4, 0x5>(y1, y0);
 }
-// Sum over the four column groups, shared out: column group c gets the total of v[c].
-__device__ __forceinline__ float reduce_scatter4(float v0, float v1, float v2, float v3, int cg) {
-  const float a0 = v0 + dpp_f<kRowRor8>(v0), b0 = v2 + dpp_f<kRowRor8>(v2);
-  const float a1 = v1 + dpp_f<kRowRor8>(v1), b1 = v3 + dpp_f<kRowRor8>(v3);
-  const float x = cg & 2 ? b0 : a0, y = cg & 2 ? b1 : a1;   // of the even, of the odd group of the pair
-  const float p = x + dpp_f<kRowShl4>(x), q = y + dpp_f<kRowShr4>(y);
-  return cg & 1 ? q : p;
+// Sum over the four column groups, shared out: column group c gets the totals of v[c][0 .. 3].  Groups 2 and 3 (the upper banks
+// of a row) keep v[2] and v[3] in the first step, the odd ones the second of the two in the next: bank masks write just those,
+// where the compiler's own would take 12 selects.  (No DPP move reads a register that one of the two instructions before it has
+// written; the first wait covers the operands.)
+__device__ __forceinline__ void reduce_scatter(const f4_t (&v)[4], float (&out)[4]) {
+  float y0, y1, y2, y3;
+#define BD_ADD(d, s, how, banks) "v_add_f32_dpp " d ", " s ", " s " " how " row_mask:0xf bank_mask:" banks "\n\t"
+  asm("s_nop 1\n\t"
+      BD_ADD("%0", "%8", "row_ror:8", "0xf") BD_ADD("%1", "%9", "row_ror:8", "0xf") BD_ADD("%2", "%10", "row_ror:8", "0xf")
+      BD_ADD("%3", "%11", "row_ror:8", "0xf") BD_ADD("%4", "%12", "row_ror:8", "0xf") BD_ADD("%5", "%13", "row_ror:8", "0xf")
+      BD_ADD("%6", "%14", "row_ror:8", "0xf") BD_ADD("%7", "%15", "row_ror:8", "0xf")
+      BD_ADD("%0", "%16", "row_ror:8", "0xc") BD_ADD("%1", "%17", "row_ror:8", "0xc") BD_ADD("%2", "%18", "row_ror:8", "0xc")
+      BD_ADD("%3", "%19", "row_ror:8", "0xc") BD_ADD("%4", "%20", "row_ror:8", "0xc") BD_ADD("%5", "%21", "row_ror:8", "0xc")
+      BD_ADD("%6", "%22", "row_ror:8", "0xc") BD_ADD("%7", "%23", "row_ror:8", "0xc")
+      BD_ADD("%0", "%0", "row_shl:4", "0x5") BD_ADD("%1", "%1", "row_shl:4", "0x5") BD_ADD("%2", "%2", "row_shl:4", "0x5")
+      BD_ADD("%3", "%3", "row_shl:4", "0x5") BD_ADD("%0", "%4", "row_shr:4", "0xa") BD_ADD("%1", "%5", "row_shr:4", "0xa")
+      BD_ADD("%2", "%6", "row_shr:4", "0xa") BD_ADD("%3", "%7", "row_shr:4", "0xa")
+      : "=&v"(out[0]), "=&v"(out[1]), "=&v"(out[2]), "=&v"(out[3]), "=&v"(y0), "=&v"(y1), "=&v"(y2), "=&v"(y3)
+      : "v"(v[0][0]), "v"(v[0][1]), "v"(v[0][2]), "v"(v[0][3]), "v"(v[1][0]), "v"(v[1][1]), "v"(v[1][2]), "v"(v[1][3]),
+        "v"(v[2][0]), "v"(v[2][1]), "v"(v[2][2]), "v"(v[2][3]), "v"(v[3][0]), "v"(v[3][1]), "v"(v[3][2]), "v"(v[3][3]));
+#undef BD_ADD
+}
+// Nearest integer (halves up).
+__device__ __forceinline__ int nearest(float x) {
+  int n;
+  asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(n) : "v"(x));
+  return n;
 }
 
 }  // namespace

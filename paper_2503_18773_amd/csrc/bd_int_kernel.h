@@ -22,7 +22,7 @@ template <int BITS, int GQP, int BLOCKS, bool PAGED, bool KT>
 __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS, DecodeArgs a) {
   constexpr bool RAISE = BD_RAISE;
   constexpr int kWaves = BD_WAVES;   // all spread along the token axis (W_m = 1)
-  static_assert(kWaves == 4 || (GQP == 4 && BLOCKS == kOneBlockWide && !PAGED && !RAISE), "heads, slices and packing are shared out over four waves");
+  static_assert(kWaves == 4 || (GQP == 4 && BLOCKS == kOneBlockWide && !PAGED && !RAISE), "heads and slices are shared out over four waves");
   const HotArgs<PAGED> hot(BD_HOT_NAMES, a.k_params, a.k_res);
   constexpr bool kSingle = BLOCKS != kManyBlocks, kShortSlices = BLOCKS != kOneBlockSlice, kLongSlices = BLOCKS != kOneBlock;
   using F = Fmt<BITS>;
@@ -36,6 +36,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
   constexpr int HP = GQP / 4;                // passes over the heads where 16 lanes work on one head
   constexpr bool kF8 = GQP == 4;             // both products on f8f6f4 instructions (see the top of the file)
   using E = FmtF8<BITS>;
+  using I = FmtI8<BITS>;
   // The next block's keys are requested as soon as this block's are consumed, not at the block's end, where the
   // arithmetic is short or the blocks are (8 x 32K tokens, 2 bits: 32.5 -> 29.3 us, with 8 heads 39.0 -> 37.7; 128K
   // tokens, 4 bits: 26.3 -> 25.8, but with 8 heads 26.8 -> 28.2; up to 4 heads measured with Q' in four pieces).
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
     raise.finish(a.raise, b, a.batch, hot, false);
   }
   if (flush_after && split < 0 && head0 != 0) return;   // (one quantizing workgroup per KV head is enough)
-  if (!PAGED && kWaves == 4 && hot.flush_mode != kFlushNone && head0 == 0 &&
+  if (!PAGED && hot.flush_mode != kFlushNone && head0 == 0 &&
       (flush_after ? split < 0 : split == (a.flush_blk / kWaves) % hot.num_splits)) {
     // The step's token completes the residual block: file it, then quantize the 128 rows as block
     // flush_blk.  kFlushFirst: this workgroup is the block's only reader in this launch (one workgroup per
@@ -129,9 +130,13 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
       *reinterpret_cast<u4_t*>((is_v ? vr : kr) + (kBlock - 1) * kD + 8 * (tid & 15)) = *reinterpret_cast<const u4_t*>(src);
     }
     workgroup_global_sync();
-    quant_block<BITS, KT, kBlock>(kr, vr, const_cast<uint32_t*>(hot.k_codes), const_cast<uint32_t*>(a.v_codes),
-                                  const_cast<uint32_t*>(hot.k_params), const_cast<uint32_t*>(a.v_params),
-                                  unit * hot.nbcap + a.flush_blk);
+    if (kWaves == 4 || wave < 4) {
+      quant_block<BITS, KT, kBlock>(kr, vr, const_cast<uint32_t*>(hot.k_codes), const_cast<uint32_t*>(a.v_codes),
+                                    const_cast<uint32_t*>(hot.k_params), const_cast<uint32_t*>(a.v_params),
+                                    unit * hot.nbcap + a.flush_blk);
+    } else {
+      for (int i = 0; i < quant_block_barriers(KT); ++i) __syncthreads();
+    }
     if (flush_after) return;   // (the whole workgroup: split < 0 is uniform)
     workgroup_global_sync();
   }
@@ -287,7 +292,6 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
   };
   // Every head's queries times the power of two that brings the largest below 1 (kq); the factor comes
   // back out of the scores, together with softmax_scale * log2(e) and the 2^24 of the subnormal codes (kS).
-  constexpr int kQTop8 = KT ? E::kTop : E::kTop - kSTop;   // f8f6f4: with the K scales below 2^kSTop, |Q'| < 2^kTop
   float qv[2][4];
   int kq_head = 0;   // of the head this lane's column carries
   auto scale_queries = [&]() {
@@ -312,13 +316,13 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
       for (int i = 0; i < 2; ++i)
         qb = max(max(qb, max(qraw0[i] & 0x7FFFu, (qraw0[i] >> 16) & 0x7FFFu)), max(qraw1[i] & 0x7FFFu, (qraw1[i] >> 16) & 0x7FFFu));
       qb = row_max16_u(qb);   // largest |q| of head lane / 16
-      const float f = pow2i(norm_exponent(qb, kQTop8));
+      const float f = pow2i(norm_exponent(qb, 0));
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         qv[0][i] = h2f((uint16_t)((qraw0[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
         qv[1][i] = h2f((uint16_t)((qraw1[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
       }
-      kq_head = norm_exponent((uint32_t)__shfl((int)qb, 16 * head), kQTop8);   // (head h's queries sit in lanes 16h ..)
+      kq_head = norm_exponent((uint32_t)__shfl((int)qb, 16 * head), 0);   // (head h's queries sit in lanes 16h ..)
     }
   };
   auto count_in = [&]() {
@@ -344,10 +348,10 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
     tb[0][1] = E::token(g, 4 + cg);
   }
 
-  // Q' = Q * s_c as an fp16 high + low pair in B-operand order, and the zero term sum_c Q_c z_c, per
+  // Q' = Q * s_c in B-operand order, as an fp16 high + low pair or in bytes, and the zero term sum_c Q_c z_c, per
   // head: once per block for channel-wise K (with the block's parameters), once per kernel for
   // per-token K.  16 lanes per head (slot group lane % 16: two runs of 4 consecutive channels).
-  // Channel-wise K: the block's scales are first brought below 1 by a power of two (2^-ek, from the largest
+  // The pair, channel-wise K: the block's scales are first brought below 1 by a power of two (2^-ek, from the largest
   // of the block), so that with |q| < 1 the products neither overflow nor sink into the fp16 subnormals;
   // the factor comes back out of the scores with kS.  Returns ek.
   auto prep_queries = [&]() -> int {
@@ -355,16 +359,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
     float nrm[4];   // 2^-ek times the position factor of register i
 #pragma unroll
     for (int i = 0; i < 4; ++i) nrm[i] = F::un(i);
-    if constexpr (!KT) {
-      uint32_t sb = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sb = max(sb, max(kp0[i] & 0xFFFFu, kp1[i] & 0xFFFFu));
-      ek = -norm_exponent(row_max16_u(sb), kSTop);   // scale * 2^-ek < 2^kSTop for every channel of the block
-      const float f = pow2i(-ek);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) nrm[i] = f * F::un(i);
-    }
-    if constexpr (kF8) {   // e4m3 pieces of Q' in units of 2^ek, 2^(ek - 5), ..
+    if constexpr (kF8) {
       float t[8], zsum = 0.0f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -379,24 +374,50 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
         }
       }
       zsum = row_sum16(zsum);
-      const int h = lane >> 4;
+      // the power of two that brings the head's largest into [2^29, 2^30), and back (all zero: any)
+      float top = fmaxf(fabsf(t[0]), fabsf(t[1]));
 #pragma unroll
-      for (int k = 0; k < kQueryPieces; ++k) {
-        const float unit = pow2i(ek - 5 * k);
-        uint32_t ev = any_bits(), od = any_bits();   // channels 0, 2, 4, 6 / 1, 3, 5, 7 of the lane's eight
-        if (k < kQueryPieces - 1) {
-          ev = e4m3_piece<true>(e4m3_piece<false>(ev, t[0], t[2], unit), t[4], t[6], unit);
-          od = e4m3_piece<true>(e4m3_piece<false>(od, t[1], t[3], unit), t[5], t[7], unit);
-        } else {
-          ev = e4m3_last<true>(e4m3_last<false>(ev, t[0], t[2], unit), t[4], t[6], unit);
-          od = e4m3_last<true>(e4m3_last<false>(od, t[1], t[3], unit), t[5], t[7], unit);
-        }
-        uint32_t* dst = wl.qp[k >> 2][E::b_half(run0)][E::b_group(run0)][4 * (k & 3) + h];
-        dst[E::b_reg(run0)] = ev;
-        dst[E::b_reg(run0 + 1)] = od;
+      for (int i = 2; i < 8; i += 2) top = fmaxf(top, fmaxf(fabsf(t[i]), fabsf(t[i + 1])));
+      const uint32_t e = max(row_max16_u(__float_as_uint(top)) & 0x7F800000u, 30u << 23);
+      const float up = __uint_as_float((283u << 23) - e), down = __uint_as_float(e - (29u << 23));
+      uint32_t x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = (uint32_t)nearest(t[i] * (up * I::position(i))) + 0x00808080u;
+      const int h = lane >> 4;
+      uint32_t d0[4], d1[4];
+      if constexpr (BITS == 4) {
+        transpose_bytes(x[0], x[2], x[4], x[6], d0);
+        transpose_bytes(x[1], x[3], x[5], x[7], d1);
+      } else {
+        transpose_bytes(x[0], x[4], x[1], x[5], d0);
+        transpose_bytes(x[2], x[6], x[3], x[7], d1);
       }
-      if (prep_sg == 0) wl.zq[h] = zsum;
-      return ek;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t sign = k < 3 ? 0x80808080u : 0u;
+        d0[k] ^= sign;
+        d1[k] ^= sign;
+        if constexpr (BITS == 4) {   // word prep_sg % 4 of the lane group's four: even channels, odd channels
+          *reinterpret_cast<u2_t*>(&wl.qd[(prep_sg >> 1) & 1][prep_sg >> 2][4 * k + h][2 * (prep_sg & 1)]) = (u2_t){d0[k], d1[k]};
+        } else {                     // half of a word of its two: two bytes of each register
+          uint16_t* dst = reinterpret_cast<uint16_t*>(wl.qd[(prep_sg >> 1) & 1][prep_sg >> 2][4 * k + h]) + (prep_sg & 1);
+          dst[0] = (uint16_t)d0[k];
+          dst[2] = (uint16_t)(d0[k] >> 16);
+          dst[4] = (uint16_t)d1[k];
+          dst[6] = (uint16_t)(d1[k] >> 16);
+        }
+      }
+      if (prep_sg == 0) wl.zq[h] = make_float2(KT ? zsum * up : zsum, down);   // (per-token K adds it to the sums)
+      return 0;
+    }
+    if constexpr (!KT) {
+      uint32_t sb = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sb = max(sb, max(kp0[i] & 0xFFFFu, kp1[i] & 0xFFFFu));
+      ek = -norm_exponent(row_max16_u(sb), kSTop);   // scale * 2^-ek < 2^kSTop for every channel of the block
+      const float f = pow2i(-ek);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) nrm[i] = f * F::un(i);
     }
     if constexpr (!kF8) {
 #pragma unroll
@@ -442,14 +463,12 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
   // groups afterwards); groups of 9..16 have no columns to spare and run two MFMAs per k-step.
   constexpr bool kSplitCols = COPIES == 2;
   h8_t bqh[4], bql[4];
-  i8_t bq8[2];   // groups of up to 4 heads: pieces cg and 4 + cg of Q'
-  const int sb_q = 127 - 5 * cg;              // block scale of the first, 2^-20 of it that of the second
+  i4_t bq8[2];   // groups of up to 4 heads: byte cg of Q', the two halves of the contraction
+  const float w_q = pow2i(8 * cg);            // what the byte counts
   const int sb_p = 127 - E::kTop - 5 * cg;    // that of piece cg of P'
   auto load_bq = [&](int j) {
     if constexpr (kF8) {
-      const u4_t x = *reinterpret_cast<const u4_t*>(wl.qp[j >> 1][j & 1][g][col]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) bq8[j >> 1][4 * (j & 1) + i] = (int)x[i];
+      if (j < 2) bq8[j] = __builtin_bit_cast(i4_t, *reinterpret_cast<const u4_t*>(wl.qd[j][g][col]));
     } else if constexpr (kSplitCols) {
       bqh[j] = *reinterpret_cast<const h8_t*>(cg & 1 ? &wl.qlo[head][8 * (4 * g + j)] : &wl.qhi[head][8 * (4 * g + j)]);
     } else {
@@ -462,8 +481,6 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
   constexpr bool kKeepQ = KT && GQP < 16;
   float zq = 0.0f, qsum = 0.0f;
   auto set_scales = [&]() {
-    if constexpr (kF8)   // the columns of the eighth piece stay zero
-      *reinterpret_cast<u2_t*>(&wl.qp[1][lane >> 5][(lane >> 3) & 3][12 + ((lane & 7) >> 1)][2 * (lane & 1)]) = (u2_t){0u, 0u};
     kS = a.scale_log2 * pow2i((KT || kF8 ? 0 : 24) - kq_head);
     kZ = a.scale_log2 * pow2i(-kq_head);
     if constexpr (KT) {
@@ -473,7 +490,12 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
 #pragma unroll
         for (int j = 0; j < 4; ++j) load_bq(j);
       }
-      qsum = wl.zq[head];
+      if constexpr (kF8) {
+        qsum = wl.zq[head].x;
+        kS *= wl.zq[head].y;
+      } else {
+        qsum = wl.zq[head];
+      }
     }
   };
 
@@ -639,7 +661,10 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
       ++done;
     }
     kSb = kS;
-    if constexpr (!KT) kSb *= pow2i(prep_queries());
+    if constexpr (!KT) {
+      const int ek = prep_queries();
+      if constexpr (!kF8) kSb *= pow2i(ek);
+    }
     if constexpr (KT) {   // K parameters of the block's 128 tokens
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -674,7 +699,13 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
 #pragma unroll
       for (int j = 0; j < 4; ++j) load_bq(j);
     }
-    if constexpr (!KT) zq = wl.zq[head];
+    if constexpr (!KT && kF8) {
+      const float2 z = wl.zq[head];
+      zq = z.x;
+      kSb = kS * z.y;
+    } else if constexpr (!KT) {
+      zq = wl.zq[head];
+    }
     has_next = !kSingle && nblk < blk1;
     if (!PAGED && !kEarly && has_next) {   // small, and the next block's first consumers: requested a block ahead
       issue_kpar(nbi);
@@ -692,9 +723,12 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
       for (int tt = 0; tt < 4; ++tt) {
         f4_t acc = {0.f, 0.f, 0.f, 0.f};   // (the zero term, one number per head, joins in the softmax)
         if constexpr (kF8) {
-          const i8_t ak = E::a_operand(kraw[4 * half + tt].w);
-          acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ak, bq8[1], acc, E::kFormatA, 0, 0, E::kScaleA, 0, sb_q - 20);
-          acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ak, bq8[0], acc, E::kFormatA, 0, 0, E::kScaleA, 0, sb_q);
+          const i8_t ak = I::a_operand(kraw[4 * half + tt].w);
+          i4_t n = {kSumBits, kSumBits, kSumBits, kSumBits};
+          n = __builtin_amdgcn_mfma_i32_16x16x64_i8((i4_t){ak[0], ak[1], ak[2], ak[3]}, bq8[0], n, 0, 0, 0);
+          n = __builtin_amdgcn_mfma_i32_16x16x64_i8((i4_t){ak[4], ak[5], ak[6], ak[7]}, bq8[1], n, 0, 0, 0);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[r] = __builtin_fmaf(__int_as_float(n[r]), w_q, -kSumBase * w_q);   // exact
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -731,8 +765,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
             sc[jj][1][r] = (half == 0 || cg == 1) ? hi : sc[jj][1][r];
           }
       } else {                              // column group cg keeps tile cg of each half: the sum of the four pieces' products
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sc[0][half][r] = reduce_scatter4(s[0][r], s[1][r], s[2][r], s[3][r], cg);
+        reduce_scatter(s, sc[0][half]);
       }
     }
     if (kValuesAfterQK) {

@@ -214,6 +214,8 @@ __device__ __forceinline__ h2_t lanes_min(h2_t m) {
 // token and one V word per channel at 4 bits, half words at 2 bits.  Minima and maxima are taken on the fp16 pairs as loaded (packed
 // instructions), across lanes with shuffles and, for channel-wise K, across waves through LDS
 // (the reduction ladder of Sec. IV-B(2)).
+// (256 threads.  Other waves of a larger workgroup meet them at as many barriers.)
+constexpr int quant_block_barriers(bool kt) { return kt ? 1 : 2; }
 template <int BITS, bool KT, int G = kBlock>
 __device__ __forceinline__ void quant_block(const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc,
                                             uint32_t* __restrict__ k_codes, uint32_t* __restrict__ v_codes,

@@ -32,13 +32,15 @@ inline int one_block_instance(int nb, int splits, int res_len, long wgs) {
   return wgs > 256 ? kOneBlockSlice : kManyBlocks;
 }
 
-// Whether a call, `packs` no block, runs workgroups of eight waves: where four would have two blocks each, eight have one, and a
+// Whether a call runs workgroups of eight waves: where four would have two blocks each, eight have one, and a
 // second block's first bytes are not waited for.  K by channel, up to 4 heads per KV head, while a unit has one workgroup.  A
-// step issued one by one, four waves / eight: 1K tokens, 8 units, 4 bits 7.9 / 7.5 us, 2 bits 7.6 / 7.1; 256 units of 900 9.1 /
-// 8.5; 20K and 24K, 8 units, 32 splits 11.1 / 10.6; 32K 11.6 / 11.6, 2 bits 10.2 / 9.9.  No more than that: the two waves of a
-// SIMD issue as many instructions as one with two blocks does.  Per-token K, whose blocks have fewer: 32K 11.0 / 11.45.
-inline bool wide_instance(int nb, int splits, int gq, bool kt, long wgs, bool packs) {
-  return gq <= 4 && !kt && !packs && nb > 4 * splits && nb <= 8 * splits && wgs <= 256;
+// step issued one by one, four waves / eight: 4 bits, 640 tokens, 8 units 7.4 / 6.6 us, 1K 7.5 / 7.0, 256 units of 700 10.5 /
+// 10.05, of 1.1K 11.45 / 11.45; 2 bits 1K 7.2 / 6.9.  In several splits until most waves have a second block, and further with
+// 2 bits, whose blocks are half the bytes: 8 units, 32 splits 20K 10.7 / 10.1, 24K 10.8 / 10.25, 26K 10.55 / 10.55, 32K 11.06 /
+// 11.55; 2 bits 17K 9.9 / 9.6, 32K 10.05 / 9.8.  No more than that: the two waves of a SIMD issue as many instructions as one
+// with two blocks does.  Per-token K, whose blocks have fewer: 32K 11.0 / 11.45.
+inline bool wide_instance(int nb, int splits, int bits, int gq, bool kt, long wgs) {
+  return gq <= 4 && !kt && nb > 4 * splits && nb <= (bits == 4 && splits > 1 ? 6 : 8) * splits && wgs <= 256;
 }
 
 // Paged cache: how many sequences of a batch are to be sorted by length (0: left as they are), and how many of them are in
