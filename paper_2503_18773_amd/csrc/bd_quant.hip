@@ -14,8 +14,9 @@
 namespace bd {
 namespace {
 
-// Copies `ntok` token rows (0 <= ntok < 128) of K and of V, the end of a prompt, to the residual buffers (whole
-// workgroup); a thread has four pieces of each tensor on the way at a time.
+// Copies `ntok` token rows (0 <= ntok < 128) of K and of V (PART: or of one of them), the end of a prompt, to the residual
+// buffers (whole workgroup); a thread has four pieces of each tensor on the way at a time.
+template <int PART>
 __device__ __forceinline__ void copy_tail(const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc,
                                           uint16_t* __restrict__ kdst, uint16_t* __restrict__ vdst, int ntok) {
   const int n = ntok * (kD / 8);   // 16-byte pieces of a tensor
@@ -25,23 +26,34 @@ __device__ __forceinline__ void copy_tail(const uint16_t* __restrict__ ksrc, con
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int at = min(at0 + 256 * i, n - 1);
-      k[i] = reinterpret_cast<const u4_t*>(ksrc)[at];
-      v[i] = reinterpret_cast<const u4_t*>(vsrc)[at];
+      if (PART & kPartK) k[i] = reinterpret_cast<const u4_t*>(ksrc)[at];
+      if (PART & kPartV) v[i] = reinterpret_cast<const u4_t*>(vsrc)[at];
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (at0 + 256 * i >= n) break;
-      reinterpret_cast<u4_t*>(kdst)[at0 + 256 * i] = k[i];
-      reinterpret_cast<u4_t*>(vdst)[at0 + 256 * i] = v[i];
+      if (PART & kPartK) reinterpret_cast<u4_t*>(kdst)[at0 + 256 * i] = k[i];
+      if (PART & kPartV) reinterpret_cast<u4_t*>(vdst)[at0 + 256 * i] = v[i];
     }
   }
+}
+
+// K and V of a block go to workgroups of their own (blockIdx.z): a block's chain of loads, statistics and codes is half as
+// long, and a unit holds six workgroups (80 registers) for four of both.  A launch in a graph, both in one workgroup / each in
+// its own: 4 bits, 8 heads of 128 tokens 6.4 / 4.4 us, 1333 6.7 / 4.7, 4000 7.2 / 6.35, 6000 9.4 / 7.9, 64K 59.2 / 58.0, 32 of 3000 13.4 /
+// 12.2 (13.3 with the 84 registers that let five on a unit), 64 of 4096 30.6 / 29.4; 2 bits 64K 55.3 / 53.9; MXFP4 128 6.1 / 4.2, 32
+// of 3000 12.2 / 10.9, 64 of 4096 29.1 / 28.8.
+template <class Run>
+__device__ __forceinline__ void run_part(Run run) {
+  if (blockIdx.z == 0) run(std::integral_constant<int, kPartK>{});
+  else run(std::integral_constant<int, kPartV>{});
 }
 
 // Contiguous cache: block blockIdx.x of unit blockIdx.y; the workgroups past the last whole block (tail > 0) take
 // the rest of a prompt, `tail` token rows that go to the residual buffers as they are.  (A launch of its own for
 // those rows cost a short prompt 3 us: 8 paged prompts of up to 1333 tokens 11.3 us each with it, 8.3 without.)
 template <int BITS, bool KT, int G>
-__global__ __launch_bounds__(256, KT ? 3 : 4) void quant_block_kernel(const uint16_t* __restrict__ ksrc,
+__global__ __launch_bounds__(256, 6) void quant_block_kernel(const uint16_t* __restrict__ ksrc,
                                                            const uint16_t* __restrict__ vsrc,
                                                            long src_unit_stride, int src_tok0,
                                                            uint32_t* __restrict__ k_codes,
@@ -55,10 +67,12 @@ __global__ __launch_bounds__(256, KT ? 3 : 4) void quant_block_kernel(const uint
   const size_t src_off = (size_t)unit * src_unit_stride + ((size_t)src_tok0 + (size_t)blk * kBlock) * kD;
   if (tail > 0 && blk == (int)gridDim.x - 1) {
     const size_t res = (size_t)unit * kBlock * kD;
-    copy_tail(ksrc + src_off, vsrc + src_off, k_res + res, v_res + res, tail);
+    run_part([&](auto part) { copy_tail<part>(ksrc + src_off, vsrc + src_off, k_res + res, v_res + res, tail); });
     return;
   }
-  quant_block<BITS, KT, G>(ksrc + src_off, vsrc + src_off, k_codes, v_codes, k_params, v_params, dblk);
+  run_part([&](auto part) {
+    quant_block_at<BITS, KT, G, part>(ksrc + src_off, vsrc + src_off, k_codes, v_codes, k_params, v_params, [&] { return (long)dblk; });
+  });
 }
 
 // ---- paged cache (page = one 128-token block; pool index of (page, head) = page * H + head) ---
@@ -87,20 +101,25 @@ __device__ __forceinline__ int page_of(const PagedArgs& a, int b, int n, int fla
 // Prefill of one sequence: block blockIdx.x of KV head blockIdx.y, source [H][L][128]; the last workgroup of a head
 // copies the L mod 128 newest tokens to the sequence's residual, and that of head 0 records the length.
 template <int BITS, bool KT, int G>
-__global__ __launch_bounds__(256, KT ? 3 : 4) void paged_quant_kernel(PagedArgs a, const uint16_t* __restrict__ ksrc,
+__global__ __launch_bounds__(256, 6) void paged_quant_kernel(PagedArgs a, const uint16_t* __restrict__ ksrc,
                                                            const uint16_t* __restrict__ vsrc, int seq, int L) {
   const int blk = blockIdx.x, h = blockIdx.y;
   const size_t src_off = ((size_t)h * L + (size_t)blk * kBlock) * kD;
   if (blk == (int)gridDim.x - 1) {
     const size_t res = ((size_t)seq * a.n_kv_heads + h) * kBlock * kD;
-    copy_tail(ksrc + src_off, vsrc + src_off, a.k_res + res, a.v_res + res, L % kBlock);
-    if (h == 0 && threadIdx.x == 0) a.seq_lens[seq] = L;
+    run_part([&](auto part) { copy_tail<part>(ksrc + src_off, vsrc + src_off, a.k_res + res, a.v_res + res, L % kBlock); });
+    if (h == 0 && threadIdx.x == 0 && blockIdx.z == 0) a.seq_lens[seq] = L;
     return;
   }
-  const int page = page_of(a, seq, blk, 2);
-  if (page < 0) return;
-  quant_block<BITS, KT, G>(ksrc + src_off, vsrc + src_off, a.k_codes, a.v_codes, a.k_params, a.v_params,
-                           (size_t)page * a.n_kv_heads + h);
+  // (the page's number comes while the rows do)
+  const int entry = blk < a.max_pages ? scalar_load(a.block_table + (size_t)seq * a.max_pages + blk) : -1;
+  run_part([&](auto part) {
+    quant_block_at<BITS, KT, G, part>(ksrc + src_off, vsrc + src_off, a.k_codes, a.v_codes, a.k_params, a.v_params, [&]() -> long {
+      if (entry >= 0 && entry < a.num_pages) return (long)entry * a.n_kv_heads + h;
+      if (a.status && threadIdx.x == 0) atomicOr(a.status, 2);
+      return -1;
+    });
+  });
 }
 
 // One decode step of sequence blockIdx.y, KV head blockIdx.x: the new token row goes to residual
@@ -171,15 +190,17 @@ struct MxDst {
   int32_t* status;
   int n_kv_heads, num_pages, max_pages;
 };
-__device__ __forceinline__ long mx_block_index(const MxDst& d, int u, int blk) {
+// (entry: the table's for that block, -1 past its end)
+__device__ __forceinline__ int mx_table_entry(const MxDst& d, int blk) {
+  return d.table_row && blk < d.max_pages ? scalar_load(d.table_row + blk) : -1;
+}
+__device__ __forceinline__ long mx_block_index(const MxDst& d, int u, int blk, int entry) {
   if (!d.table_row) return (long)u * d.nbcap + blk;
-  int page = -1;
-  if (blk < d.max_pages) page = d.table_row[blk];
-  if (page < 0 || page >= d.num_pages) {
+  if (entry < 0 || entry >= d.num_pages) {
     if (d.status && threadIdx.x == 0) atomicOr(d.status, 2);
     return -1;
   }
-  return (long)page * d.n_kv_heads + u;
+  return (long)entry * d.n_kv_heads + u;
 }
 
 // Prefill of an MXFP4 cache, one workgroup per 128-token block, in the tiling of the integer block
@@ -198,9 +219,10 @@ __device__ __forceinline__ long mx_block_index(const MxDst& d, int u, int blk) {
 // written, and V's bytes past them stay as they are (an odd last token's byte gets a zero high nibble).  (A
 // kernel of its own with a thread per token -- 128 values in turn, 47 us for 31 tokens -- served this block
 // before, whatever the prompt's length: 57.5 us for 4 prompts of 2079 tokens.)
-template <bool TAIL>
+// place(): the block's index in the arrays, asked for when the rows are on their way; negative: nowhere.
+template <bool TAIL, int PART, class Place>
 __device__ __forceinline__ void mx_quant_block(const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc,
-                                               size_t src_blk, const MxDst& d, long bi, int ntok,
+                                               size_t src_blk, const MxDst& d, Place place, int ntok,
                                                uint32_t (*vw)[kBlock / 8 + 1]) {
   constexpr int C = 8, T = 8, NCG = kD / C, WPC = kBlock / 8;   // 16 lanes per row; 16 words per channel
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -208,19 +230,16 @@ __device__ __forceinline__ void mx_quant_block(const uint16_t* __restrict__ ksrc
   auto krow = [&](int t) { return 32 * wave + (lane >> 4) + 4 * t; };
   auto vrow = [&](int t) { return T * tg + t; };
   auto live = [&](int row) { return !TAIL || row < ntok; };
-  u4_t kraw[T], vraw[T];
+  const uint16_t* src = PART == kPartK ? ksrc : vsrc;
+  u4_t raw[T];
 #pragma unroll
   for (int t = 0; t < T; ++t) {
-    kraw[t] = (u4_t){0u, 0u, 0u, 0u};
-    if (live(krow(t)))
-      kraw[t] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(ksrc + src_blk + (size_t)krow(t) * kD + C * cg));
+    const int row = PART == kPartK ? krow(t) : vrow(t);
+    raw[t] = (u4_t){0u, 0u, 0u, 0u};
+    if (live(row)) raw[t] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(src + src_blk + (size_t)row * kD + C * cg));
   }
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    vraw[t] = (u4_t){0u, 0u, 0u, 0u};
-    if (live(vrow(t)))
-      vraw[t] = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(vsrc + src_blk + (size_t)vrow(t) * kD + C * cg));
-  }
+  const long bi = place();
+  if (bi < 0) return;
 
   // the 8 codes of one row of this lane (channel C*cg + n at nibble n) and the group's scale byte
   auto row_codes = [&](const u4_t& raw, uint32_t& word, uint32_t& ebyte) {
@@ -269,23 +288,26 @@ __device__ __forceinline__ void mx_quant_block(const uint16_t* __restrict__ ksrc
   };
 
   // ---- K: token-major codes, one word per lane and row
+  if constexpr (PART == kPartK) {
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    uint32_t word, ebyte;
-    row_codes(kraw[t], word, ebyte);
-    const size_t tok = (size_t)bi * kBlock + krow(t);
-    const uint32_t sc4 = row_scales(ebyte);
-    if (live(krow(t))) {
-      __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(d.k_codes + tok * (kD / 2)) + cg);
-      if (cg == 0) *reinterpret_cast<uint32_t*>(d.k_scales + tok * 4) = sc4;
+    for (int t = 0; t < T; ++t) {
+      uint32_t word, ebyte;
+      row_codes(raw[t], word, ebyte);
+      const size_t tok = (size_t)bi * kBlock + krow(t);
+      const uint32_t sc4 = row_scales(ebyte);
+      if (live(krow(t))) {
+        __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(d.k_codes + tok * (kD / 2)) + cg);
+        if (cg == 0) *reinterpret_cast<uint32_t*>(d.k_scales + tok * 4) = sc4;
+      }
     }
+    return;
   }
   // ---- V: channel-major codes
   uint32_t lo[T], hi[T];   // per token: the codes of channels 0..3 / 4..7 of this lane, one per byte
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     uint32_t word, ebyte;
-    row_codes(vraw[t], word, ebyte);
+    row_codes(raw[t], word, ebyte);
     const size_t tok = (size_t)bi * kBlock + vrow(t);
     const uint32_t sc4 = row_scales(ebyte);
     if (cg == 0 && live(vrow(t))) *reinterpret_cast<uint32_t*>(d.v_scales + tok * 4) = sc4;
@@ -322,14 +344,16 @@ __global__ __launch_bounds__(256, 4) void mx_quant_block_kernel(const uint16_t* 
                                                                  const uint16_t* __restrict__ vsrc,
                                                                  long src_unit_stride, MxDst d, int L, int32_t* seq_len) {
   const int unit = blockIdx.y, blk = blockIdx.x;
-  if (seq_len && unit == 0 && blk == 0 && threadIdx.x == 0) *seq_len = L;
-  const long bi = mx_block_index(d, unit, blk);
-  if (bi < 0) return;
+  if (seq_len && unit == 0 && blk == 0 && blockIdx.z == 0 && threadIdx.x == 0) *seq_len = L;
   const size_t src_blk = (size_t)unit * src_unit_stride + (size_t)blk * kBlock * kD;
   const int ntok = L - blk * kBlock;
+  const int entry = mx_table_entry(d, blk);   // (comes while the rows do)
+  auto place = [&] { return mx_block_index(d, unit, blk, entry); };
   __shared__ uint32_t vw[kD][kBlock / 8 + 1];
-  if (ntok >= kBlock) mx_quant_block<false>(ksrc, vsrc, src_blk, d, bi, kBlock, vw);
-  else mx_quant_block<true>(ksrc, vsrc, src_blk, d, bi, ntok, vw);
+  run_part([&](auto part) {
+    if (ntok >= kBlock) mx_quant_block<false, part>(ksrc, vsrc, src_blk, d, place, kBlock, vw);
+    else mx_quant_block<true, part>(ksrc, vsrc, src_blk, d, place, ntok, vw);
+  });
 }
 
 // Decode-step append for MXFP4: one token of one (sequence, KV head) goes to position i of block bi
@@ -358,7 +382,7 @@ __global__ __launch_bounds__(128) void mx_paged_append_kernel(MxDst d, const int
   const int len = seq_lens[b];
   if (len < 0) return;
   d.table_row = block_table + (size_t)b * d.max_pages;
-  const long bi = mx_block_index(d, h, len / kBlock);
+  const long bi = mx_block_index(d, h, len / kBlock, mx_table_entry(d, len / kBlock));
   if (bi < 0) return;
   const size_t unit = (size_t)b * d.n_kv_heads + h;
   mx_append_token(k_new + unit * kD, v_new + unit * kD, d, bi, len % kBlock);
@@ -373,7 +397,7 @@ __global__ void set_len_kernel(int32_t* seq_lens, int seq, int L) {
 // Tokens [0, L) of every unit, L > 0.
 static hipError_t launch_mx_prefill(const void* k, const void* v, int L, int units, const MxDst& d, int32_t* seq_len,
                                     hipStream_t st) {
-  mx_quant_block_kernel<<<dim3((L + kBlock - 1) / kBlock, units), dim3(256), 0, st>>>(
+  mx_quant_block_kernel<<<dim3((L + kBlock - 1) / kBlock, units, 2), dim3(256), 0, st>>>(
       (const uint16_t*)k, (const uint16_t*)v, (long)L * kD, d, L, seq_len);
   return hipGetLastError();
 }
@@ -381,7 +405,7 @@ static hipError_t launch_mx_prefill(const void* k, const void* v, int L, int uni
 hipError_t launch_quant_blocks(const void* k, const void* v, long src_unit_stride, int src_tok0, int nblocks,
                                int units, const bd_cache* c, int dst_blk0, int tail, hipStream_t st) {
   if (nblocks <= 0 && tail <= 0) return hipSuccess;
-  dim3 grid(nblocks + (tail > 0 ? 1 : 0), units), block(256);
+  dim3 grid(nblocks + (tail > 0 ? 1 : 0), units, 2), block(256);
   const int nbcap = c->capacity / kBlock;
   const uint16_t *kk = (const uint16_t*)k, *vv = (const uint16_t*)v;
   uint32_t *kc = (uint32_t*)c->k_codes, *vc = (uint32_t*)c->v_codes, *kp = (uint32_t*)c->k_params,
@@ -453,7 +477,7 @@ hipError_t launch_paged_prefill(const bd_paged_cache* c, int seq, const void* k,
     return hipGetLastError();
   }
   const PagedArgs a = paged_args(c);
-  dim3 grid(L / kBlock + 1, c->n_kv_heads), block(256);
+  dim3 grid(L / kBlock + 1, c->n_kv_heads, 2), block(256);
   const uint16_t *kk = (const uint16_t*)k, *vv = (const uint16_t*)v;
   switch (c->format) {
     case BD_FMT_INT4: paged_quant_kernel<4, false, 128><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;

@@ -216,11 +216,13 @@ __device__ __forceinline__ h2_t lanes_min(h2_t m) {
 // (the reduction ladder of Sec. IV-B(2)).
 // (256 threads.  Other waves of a larger workgroup meet them at as many barriers.)
 constexpr int quant_block_barriers(bool kt) { return kt ? 1 : 2; }
-template <int BITS, bool KT, int G = kBlock>
-__device__ __forceinline__ void quant_block(const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc,
-                                            uint32_t* __restrict__ k_codes, uint32_t* __restrict__ v_codes,
-                                            uint32_t* __restrict__ k_params, uint32_t* __restrict__ v_params,
-                                            size_t dblk) {
+// PART: K, V or both.  place(): the block's index in the arrays, asked for when the rows are on their way; negative: nowhere.
+constexpr int kPartK = 1, kPartV = 2, kBothParts = 3;
+template <int BITS, bool KT, int G, int PART, class Place>
+__device__ __forceinline__ void quant_block_at(const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc,
+                                               uint32_t* __restrict__ k_codes, uint32_t* __restrict__ v_codes,
+                                               uint32_t* __restrict__ k_params, uint32_t* __restrict__ v_params,
+                                               Place place) {
   constexpr int QMAX = (1 << BITS) - 1;
   constexpr int CPT = 32 / BITS;     // codes per word
   constexpr int NG = kBlock / G;     // K token groups per block == V channel groups per token
@@ -241,16 +243,22 @@ __device__ __forceinline__ void quant_block(const uint16_t* __restrict__ ksrc, c
   // at prefill sizes is worth about a tenth of the kernel's time.
   uint32_t kraw[T][C / 2], vraw[T][C / 2];
   const uint32_t koff = (uint32_t)(krow(0) * kD + C * cg) * 2u, voff = (uint32_t)(vrow(0) * kD + C * cg) * 2u;
+  if constexpr ((PART & kPartK) != 0)
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const u4_t ld = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(reinterpret_cast<const char*>(ksrc) + koff + t * (4 * kD * 2)));
     kraw[t][0] = ld[0]; kraw[t][1] = ld[1]; kraw[t][2] = ld[2]; kraw[t][3] = ld[3];
   }
+  if constexpr ((PART & kPartV) != 0)
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const u4_t ld = __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(reinterpret_cast<const char*>(vsrc) + voff + t * (kD * 2)));
     vraw[t][0] = ld[0]; vraw[t][1] = ld[1]; vraw[t][2] = ld[2]; vraw[t][3] = ld[3];
   }
+
+  const long at = place();
+  if (at < 0) return;
+  const size_t dblk = (size_t)at;
 
   // Rows with statistics per token (V; K with KT): parameters of each row over the LPG consecutive
   // lanes that hold one group of it, stored by put_params(t, packed); codes one per byte in lo / hi.
@@ -279,7 +287,7 @@ __device__ __forceinline__ void quant_block(const uint16_t* __restrict__ ksrc, c
 
   // ---- K: one K word of a token at 4 bits, half a word at 2 bits (stored as such: the two halves of a
   //      word come from neighbouring lanes)
-  {
+  if constexpr ((PART & kPartK) != 0) {
     auto store_k_row = [&](int t, uint32_t lo, uint32_t hi) {
       const uint32_t w = pack_code_bytes<BITS>(lo, hi);
       const uint32_t at = (uint32_t)(krow(t) * NCG + cg);   // inside the block
@@ -362,7 +370,7 @@ __device__ __forceinline__ void quant_block(const uint16_t* __restrict__ ksrc, c
 
   // ---- V: statistics per token.  8 tokens of a channel are one V word at 4 bits and half a word at 2
   //      bits (the halves meet in LDS).
-  {
+  if constexpr ((PART & kPartV) != 0) {
     constexpr int WPC = kBlock / CPT;   // words per channel: 16 at 4 bits, 8 at 2 bits
     constexpr int LPG = NCG / NG;       // consecutive lanes that hold one channel group of a token row
     const int tg = tid / NCG;
@@ -394,6 +402,14 @@ __device__ __forceinline__ void quant_block(const uint16_t* __restrict__ ksrc, c
       __builtin_nontemporal_store(w4, dstp);
     }
   }
+}
+
+template <int BITS, bool KT, int G = kBlock>
+__device__ __forceinline__ void quant_block(const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc,
+                                            uint32_t* __restrict__ k_codes, uint32_t* __restrict__ v_codes,
+                                            uint32_t* __restrict__ k_params, uint32_t* __restrict__ v_params,
+                                            size_t dblk) {
+  quant_block_at<BITS, KT, G, kBothParts>(ksrc, vsrc, k_codes, v_codes, k_params, v_params, [&] { return (long)dblk; });
 }
 
 }  // namespace
