@@ -39,10 +39,13 @@ __device__ __forceinline__ void copy_tail(const uint16_t* __restrict__ ksrc, con
 }
 
 // K and V of a block go to workgroups of their own (blockIdx.z): a block's chain of loads, statistics and codes is half as
-// long, and a unit holds six workgroups (80 registers) for four of both.  A launch in a graph, both in one workgroup / each in
-// its own: 4 bits, 8 heads of 128 tokens 6.4 / 4.4 us, 1333 6.7 / 4.7, 4000 7.2 / 6.35, 6000 9.4 / 7.9, 64K 59.2 / 58.0, 32 of 3000 13.4 /
-// 12.2 (13.3 with the 84 registers that let five on a unit), 64 of 4096 30.6 / 29.4; 2 bits 64K 55.3 / 53.9; MXFP4 128 6.1 / 4.2, 32
-// of 3000 12.2 / 10.9, 64 of 4096 29.1 / 28.8.
+// long.  A launch in a graph, both in one workgroup / each in its own: 4 bits, 8 heads of 128 tokens 6.4 / 4.4 us, 1333 6.7 / 4.7,
+// 4000 7.2 / 6.35, 6000 9.4 / 7.9, 64 of 4096 30.6 / 29.5; 2 bits 64K 55.3 / 54.1; MXFP4 128 6.1 / 4.2, 32 of 3000 12.2 / 10.9, 64 of
+// 4096 29.1 / 28.8.
+// With 80 registers six share a unit, with the 84 that K by channel takes unasked five.  Six while that is one round (32 of
+// 3000 tokens 12.2 us, five 13.3), five past it, where six have more streams under way than the memory serves well (128K, issued
+// one by one, 113.0 us, five 108.3); per-token K six always (64K 57.3, five 58.6).
+static inline bool six_on_a_unit(bool kt, long blocks) { return kt || 2 * blocks <= 6 * 256; }
 template <class Run>
 __device__ __forceinline__ void run_part(Run run) {
   if (blockIdx.z == 0) run(std::integral_constant<int, kPartK>{});
@@ -52,8 +55,8 @@ __device__ __forceinline__ void run_part(Run run) {
 // Contiguous cache: block blockIdx.x of unit blockIdx.y; the workgroups past the last whole block (tail > 0) take
 // the rest of a prompt, `tail` token rows that go to the residual buffers as they are.  (A launch of its own for
 // those rows cost a short prompt 3 us: 8 paged prompts of up to 1333 tokens 11.3 us each with it, 8.3 without.)
-template <int BITS, bool KT, int G>
-__global__ __launch_bounds__(256, 6) void quant_block_kernel(const uint16_t* __restrict__ ksrc,
+template <int BITS, bool KT, int G, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void quant_block_kernel(const uint16_t* __restrict__ ksrc,
                                                            const uint16_t* __restrict__ vsrc,
                                                            long src_unit_stride, int src_tok0,
                                                            uint32_t* __restrict__ k_codes,
@@ -100,8 +103,8 @@ __device__ __forceinline__ int page_of(const PagedArgs& a, int b, int n, int fla
 
 // Prefill of one sequence: block blockIdx.x of KV head blockIdx.y, source [H][L][128]; the last workgroup of a head
 // copies the L mod 128 newest tokens to the sequence's residual, and that of head 0 records the length.
-template <int BITS, bool KT, int G>
-__global__ __launch_bounds__(256, 6) void paged_quant_kernel(PagedArgs a, const uint16_t* __restrict__ ksrc,
+template <int BITS, bool KT, int G, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void paged_quant_kernel(PagedArgs a, const uint16_t* __restrict__ ksrc,
                                                            const uint16_t* __restrict__ vsrc, int seq, int L) {
   const int blk = blockIdx.x, h = blockIdx.y;
   const size_t src_off = ((size_t)h * L + (size_t)blk * kBlock) * kD;
@@ -411,11 +414,12 @@ hipError_t launch_quant_blocks(const void* k, const void* v, long src_unit_strid
   uint32_t *kc = (uint32_t*)c->k_codes, *vc = (uint32_t*)c->v_codes, *kp = (uint32_t*)c->k_params,
            *vp = (uint32_t*)c->v_params;
   uint16_t *kr = (uint16_t*)c->k_res, *vr = (uint16_t*)c->v_res;
-#define BD_QUANT_CASE(FMT, BITS, KT, G)                                                                          \
-  case FMT:                                                                                                      \
-    quant_block_kernel<BITS, KT, G><<<grid, block, 0, st>>>(kk, vv, src_unit_stride, src_tok0, kc, vc, kp, vp, \
-                                                            nbcap, dst_blk0, kr, vr, tail);                      \
-    break;
+  const bool six = six_on_a_unit(fmt_kt(c->format), (long)grid.x * units);
+#define BD_QUANT_CASE(FMT, BITS, KT, G)                                                                                         \
+  case FMT: {                                                                                                                   \
+    const auto kernel = six ? quant_block_kernel<BITS, KT, G, 6> : quant_block_kernel<BITS, KT, G, KT ? 6 : 5>;                 \
+    kernel<<<grid, block, 0, st>>>(kk, vv, src_unit_stride, src_tok0, kc, vc, kp, vp, nbcap, dst_blk0, kr, vr, tail);           \
+  } break;
   switch (c->format) {
     BD_QUANT_CASE(BD_FMT_INT4, 4, false, 128)
     BD_QUANT_CASE(BD_FMT_INT2, 2, false, 128)
@@ -479,21 +483,28 @@ hipError_t launch_paged_prefill(const bd_paged_cache* c, int seq, const void* k,
   const PagedArgs a = paged_args(c);
   dim3 grid(L / kBlock + 1, c->n_kv_heads, 2), block(256);
   const uint16_t *kk = (const uint16_t*)k, *vv = (const uint16_t*)v;
+  const bool six = six_on_a_unit(fmt_kt(c->format), (long)grid.x * grid.y);
+#define BD_PAGED_QUANT_CASE(FMT, BITS, KT, G)                                                                   \
+  case FMT: {                                                                                                   \
+    const auto kernel = six ? paged_quant_kernel<BITS, KT, G, 6> : paged_quant_kernel<BITS, KT, G, KT ? 6 : 5>; \
+    kernel<<<grid, block, 0, st>>>(a, kk, vv, seq, L);                                                          \
+  } break;
   switch (c->format) {
-    case BD_FMT_INT4: paged_quant_kernel<4, false, 128><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT2: paged_quant_kernel<2, false, 128><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT4_KT: paged_quant_kernel<4, true, 128><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT2_KT: paged_quant_kernel<2, true, 128><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT4_G64: paged_quant_kernel<4, false, 64><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT4_G32: paged_quant_kernel<4, false, 32><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT2_G64: paged_quant_kernel<2, false, 64><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT2_G32: paged_quant_kernel<2, false, 32><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT4_KT_G64: paged_quant_kernel<4, true, 64><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT4_KT_G32: paged_quant_kernel<4, true, 32><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT2_KT_G64: paged_quant_kernel<2, true, 64><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
-    case BD_FMT_INT2_KT_G32: paged_quant_kernel<2, true, 32><<<grid, block, 0, st>>>(a, kk, vv, seq, L); break;
+    BD_PAGED_QUANT_CASE(BD_FMT_INT4, 4, false, 128)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT2, 2, false, 128)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT4_KT, 4, true, 128)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT2_KT, 2, true, 128)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT4_G64, 4, false, 64)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT4_G32, 4, false, 32)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT2_G64, 2, false, 64)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT2_G32, 2, false, 32)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT4_KT_G64, 4, true, 64)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT4_KT_G32, 4, true, 32)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT2_KT_G64, 2, true, 64)
+    BD_PAGED_QUANT_CASE(BD_FMT_INT2_KT_G32, 2, true, 32)
     default: return hipErrorInvalidValue;
   }
+#undef BD_PAGED_QUANT_CASE
   return hipGetLastError();
 }
 
