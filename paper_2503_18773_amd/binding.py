@@ -6,6 +6,7 @@ or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 BD_FMT_INT4, BD_FMT_INT2, BD_FMT_MXFP4, BD_FMT_INT4_KT, BD_FMT_INT2_KT = 0, 1, 2, 3, 4
@@ -20,10 +21,9 @@ BLOCK = 128
 BD_OUT_HALF, BD_OUT_F32 = 0, 1
 BD_STATIC_SCRATCH_BYTES = 4 << 20   # include/bitdecode.h
 
-_byref, _c_int32 = ctypes.byref, ctypes.c_int32
-
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libbitdecode.so")
 _lib = None
+_entry = {}   # entry points' addresses in the loaded library, for _call
 
 
 class bd_cache(ctypes.Structure):
@@ -90,6 +90,7 @@ def lib() -> ctypes.CDLL:
         L.bd_paged_decode_step_lazy.restype, L.bd_paged_decode_step_lazy.argtypes = ctypes.c_int, [PP, V, V, V, F, I, V, V, V]
         L.bd_strerror.restype, L.bd_strerror.argtypes = ctypes.c_char_p, [ctypes.c_int]
         L.bd_last_hip_error.restype, L.bd_last_hip_error.argtypes = ctypes.c_int, []
+        _entry.update((name, ctypes.cast(getattr(L, name), V).value) for name in EXPORTS)
         _lib = L
     return _lib
 
@@ -121,6 +122,58 @@ def _stream(stream):
             device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
             _raw_stream = lambda: raw(device())
     return _raw_stream()
+
+
+class _CtypesCall:
+    """The functions of csrc/bd_call.c, for where it has not been built."""
+
+    @staticmethod
+    @functools.lru_cache(maxsize=32)
+    def _function(address, restype, *argtypes):
+        return ctypes.CFUNCTYPE(restype, *argtypes)(address)
+
+    @staticmethod
+    def splits(fn, c, packed_len):
+        return _CtypesCall._function(fn, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32)(ctypes.addressof(c), packed_len)
+
+    @staticmethod
+    def step(fn, c, k_new, v_new, q, packed_len, res_len, scale, num_splits, ws, out, stream):
+        V, I, F, pl, rl = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float, ctypes.c_int32(packed_len), ctypes.c_int32(res_len)
+        status = _CtypesCall._function(fn, ctypes.c_int, V, V, V, V, V, V, F, I, V, V, V)(
+            ctypes.addressof(c), _ptr(k_new), _ptr(v_new), _ptr(q), ctypes.addressof(pl), ctypes.addressof(rl), scale, num_splits,
+            _ptr(ws), _ptr(out), stream)
+        return status, pl.value, rl.value
+
+    @staticmethod
+    def paged_step(fn, c, k_new, v_new, q, scale, num_splits, ws, out, stream):
+        V, I, F = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float
+        return _CtypesCall._function(fn, ctypes.c_int, V, V, V, V, F, I, V, V, V)(
+            ctypes.addressof(c), _ptr(k_new), _ptr(v_new), _ptr(q), scale, num_splits, _ptr(ws), _ptr(out), stream)
+
+    @staticmethod
+    def paged_quant(fn, c, seq, k, v, L, stream):
+        V, I = ctypes.c_void_p, ctypes.c_int32
+        return _CtypesCall._function(fn, ctypes.c_int, V, I, V, V, I, V)(ctypes.addressof(c), seq, _ptr(k), _ptr(v), L, stream)
+
+    @staticmethod
+    def quant(fn, c, k, v, L, stream):
+        V, I, pl, rl = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32(0), ctypes.c_int32(0)
+        status = _CtypesCall._function(fn, ctypes.c_int, V, V, V, I, V, V, V)(
+            ctypes.addressof(c), _ptr(k), _ptr(v), L, ctypes.addressof(pl), ctypes.addressof(rl), stream)
+        return status, pl.value, rl.value
+
+
+try:
+    from . import _bdcall as _call   # what the cache classes call the library through
+except ImportError:
+    _call = _CtypesCall
+
+
+def _address(name: str) -> int:
+    """The entry point's address in the library, which is loaded if it is not."""
+    if _lib is None:
+        lib()
+    return _entry[name]
 
 
 def _check(status: int, where: str):
@@ -269,7 +322,9 @@ class KVCache:
 
     def quant_pack_kv(self, k, v, stream=None):
         assert k.is_contiguous() and v.is_contiguous() and k.shape == v.shape
-        self.packed_len, self.res_len = bd_quant_pack_kv(self.desc, k, v, k.shape[2], stream)
+        status, packed, res = _call.quant(_address("bd_quant_pack_kv"), self.desc, k, v, k.shape[2], _stream(stream))
+        _check(status, "bd_quant_pack_kv")
+        self.packed_len, self.res_len = packed, res
 
     def append_kv(self, k_new, v_new, stream=None):
         self.packed_len, self.res_len = bd_append_kv(self.desc, k_new, v_new, self.packed_len, self.res_len, stream)
@@ -311,20 +366,15 @@ class KVCache:
         if ns is None:
             # (the lazy step that fills the residual has a quantizing workgroup per KV head beside the attending ones:
             # where those are one per compute unit, some then share one, 128K tokens 40.4 us against 32.9)
-            fills = lazy and self.res_len == 127
-            ns = self.choose_splits() if fills else bd_step_splits(self.desc, self.packed_len)
-        # (bd_decode_step / bd_decode_step_lazy without a wrapper's second set of arguments: a step of short contexts is
-        # bound by the host)
+            name = "bd_choose_splits" if lazy and self.res_len == 127 else "bd_step_splits"
+            ns = _call.splits(_address(name), self.desc, self.packed_len)
         rows = ns * self.desc.batch * self.desc.n_q_heads
         ws = self._ws if 0 < rows <= self._ws_rows else self.workspace(ns)
-        pl, rl = _c_int32(self.packed_len), _c_int32(self.res_len)
-        library = _lib or lib()
-        status = (library.bd_decode_step_lazy if lazy else library.bd_decode_step)(
-            _byref(self.desc), _ptr(k_new), _ptr(v_new), _ptr(q), _byref(pl), _byref(rl), softmax_scale, ns, ws.data_ptr(),
-            _ptr(out), _stream(stream))
-        if status != 0:
-            raise BitDecodeError(status, "bd_decode_step_lazy" if lazy else "bd_decode_step")
-        self.packed_len, self.res_len = pl.value, rl.value
+        name = "bd_decode_step_lazy" if lazy else "bd_decode_step"
+        status, packed, res = _call.step(_address(name), self.desc, k_new, v_new, q, self.packed_len, self.res_len, softmax_scale, ns,
+                                         ws, out, _stream(stream))
+        _check(status, name)
+        self.packed_len, self.res_len = packed, res
         return out
 
     def host_buffer(self, i: int):
@@ -363,7 +413,8 @@ class PagedKVCache:
 
     def quant_pack_kv(self, seq: int, k, v, stream=None):
         assert k.is_contiguous() and v.is_contiguous() and k.shape == v.shape
-        bd_paged_quant_pack_kv(self.desc, seq, k, v, k.shape[1], stream)
+        _check(_call.paged_quant(_address("bd_paged_quant_pack_kv"), self.desc, seq, k, v, k.shape[1], _stream(stream)),
+               "bd_paged_quant_pack_kv")
 
     def append_kv(self, k_new, v_new, stream=None):
         bd_paged_append_kv(self.desc, k_new, v_new, stream)
@@ -387,8 +438,9 @@ class PagedKVCache:
         return out
 
     def decode_step(self, k_new, v_new, q, softmax_scale: float, out, num_splits: int, stream=None, lazy: bool = False):
-        step = bd_paged_decode_step_lazy if lazy else bd_paged_decode_step
-        step(self.desc, k_new, v_new, q, softmax_scale, num_splits, self.workspace(num_splits), out, stream)
+        name = "bd_paged_decode_step_lazy" if lazy else "bd_paged_decode_step"
+        _check(_call.paged_step(_address(name), self.desc, k_new, v_new, q, softmax_scale, num_splits, self.workspace(num_splits), out,
+                                _stream(stream)), name)
         return out
 
     def host_buffer(self, i: int):

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -41,7 +42,23 @@ def build(verbose: bool = False, jobs: int = 6) -> str:
     out = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if out.returncode != 0:
         raise RuntimeError("link failed:\n" + out.stdout)
+    _build_call()
     return LIB
+
+
+def _build_call() -> None:
+    """The Python side's calling module (csrc/bd_call.c).  Without a C compiler or Python's headers binding.py does its work."""
+    out = os.path.join(HERE, "_bdcall" + sysconfig.get_config_var("EXT_SUFFIX"))
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+           os.path.join(HERE, "csrc", "bd_call.c"), "-o", out]
+    try:
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if res.returncode == 0:
+            return
+        why = res.stdout
+    except OSError as e:
+        why = str(e)
+    print(f"not built: {out}\n{why}", file=sys.stderr)
 
 
 def _drain(procs):

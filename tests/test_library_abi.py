@@ -3,6 +3,8 @@ validates arguments before touching the GPU (no kernel is launched here)."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -216,3 +218,50 @@ def test_the_count_of_a_step():
     assert [B.bd_step_splits(_desc(format=B.BD_FMT_INT4_G32), L) for L in (1024, 32768)] == [2, 64]
     # bad arguments and an empty cache: one
     assert B.bd_step_splits(_desc(), 0) == B.bd_step_splits(_desc(), -5) == B.bd_step_splits(_desc(head_dim=64), 999) == 1
+
+
+ECHO = """
+#include <stdint.h>
+#include <string.h>
+int64_t seen[16];
+static int64_t bits(float f) { uint32_t u; memcpy(&u, &f, 4); return u; }
+#define P(x) (int64_t)(uintptr_t)(x)
+int splits(const int32_t* c, int32_t n) { seen[0] = c[0]; seen[1] = n; return 7; }
+int step(const int32_t* c, void* k, void* v, void* q, int32_t* p, int32_t* r, float s, int32_t n, void* w, void* o, void* st) {
+  int64_t x[] = {c[0], P(k), P(v), P(q), *p, *r, bits(s), n, P(w), P(o), P(st)}; memcpy(seen, x, sizeof x); *p += 128; *r = -1; return -3; }
+int paged_step(const int32_t* c, void* k, void* v, void* q, float s, int32_t n, void* w, void* o, void* st) {
+  int64_t x[] = {c[0], P(k), P(v), P(q), bits(s), n, P(w), P(o), P(st)}; memcpy(seen, x, sizeof x); return -4; }
+int paged_quant(const int32_t* c, int32_t b, void* k, void* v, int32_t n, void* st) {
+  int64_t x[] = {c[0], b, P(k), P(v), n, P(st)}; memcpy(seen, x, sizeof x); return 0; }
+int quant(const int32_t* c, void* k, void* v, int32_t n, int32_t* p, int32_t* r, void* st) {
+  int64_t x[] = {c[0], P(k), P(v), n, P(st)}; memcpy(seen, x, sizeof x); *p = n - 5; *r = 5; return 2; }
+"""
+
+
+@pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
+@pytest.mark.parametrize("call", [B._CtypesCall, B._call])
+def test_calls_pass_every_argument_and_give_back_what_comes(call, tmp_path):
+    """Both ways that the cache classes call the library, against functions that record what they are given: tensors, None,
+    addresses beyond 32 bits, negative integers."""
+    (tmp_path / "echo.c").write_text(ECHO)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", str(tmp_path / "echo.c"), "-o", str(tmp_path / "echo.so")], check=True)
+    L = ctypes.CDLL(str(tmp_path / "echo.so"))
+    at = lambda name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+    seen = lambda n: list((ctypes.c_int64 * 16).in_dll(L, "seen"))[:n]
+
+    class Tensor:
+        def __init__(self, at):
+            self.data_ptr = lambda: at
+
+    k, v, q, w, o = (Tensor(x) for x in (0x7F0012345670, 16, 2 ** 40, 48, 64))
+    c, half = B.bd_cache(batch=11), 0x3F000000
+    assert call.splits(at("splits"), c, -5) == 7 and seen(2) == [11, -5]
+    assert call.step(at("step"), c, k, v, q, 256, 127, 0.5, 3, w, o, 2 ** 41) == (-3, 384, -1)
+    assert seen(11) == [11, 0x7F0012345670, 16, 2 ** 40, 256, 127, half, 3, 48, 64, 2 ** 41]
+    assert call.step(at("step"), c, k, v, q, -1, 0, 1, -7, w, None, 0)[0] == -3
+    assert seen(11)[4:] == [-1, 0, 0x3F800000, -7, 48, 0, 0]
+    p = B.bd_paged_cache(batch=12)
+    assert call.paged_step(at("paged_step"), p, k, None, q, 0.5, 9, w, o, 0) == -4
+    assert seen(9) == [12, 0x7F0012345670, 0, 2 ** 40, half, 9, 48, 64, 0]
+    assert call.paged_quant(at("paged_quant"), p, 6, k, v, 1333, 80) == 0 and seen(6) == [12, 6, 0x7F0012345670, 16, 1333, 80]
+    assert call.quant(at("quant"), c, k, v, 133, 0) == (2, 128, 5) and seen(5) == [11, 0x7F0012345670, 16, 133, 0]
