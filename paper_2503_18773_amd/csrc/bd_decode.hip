@@ -222,15 +222,21 @@ __global__ __launch_bounds__(128 * G) void combine_kernel(const float* __restric
 #pragma unroll
     for (int i = 0; i < kBatch; ++i)
       if (p0 + G * i >= nparts) ml[i].x = -INFINITY;
+    // (all weights relative to the round's maximum: a chain of running maxima and rescalings is 8 times as long and has twice
+    // the exponentials: a step of 4 x 4000 tokens 8.74 -> 8.63 us, 32K 11.19 -> 11.12, one head of 64K 10.12 -> 9.95)
+    float Mn = M;
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) Mn = fmaxf(Mn, ml[i].x);
+    const float base = Mn > -INFINITY ? Mn : 0.0f;   // (nothing so far: all weights 0)
+    const float fo = __builtin_amdgcn_exp2f(M - base);
+    L *= fo;
+    o *= fo;
+    M = Mn;
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-      const float Mn = fmaxf(M, ml[i].x);
-      const bool live = ml[i].x > -INFINITY;
-      const float fo = live ? __builtin_amdgcn_exp2f(M - Mn) : 1.0f;
-      const float fn = live ? __builtin_amdgcn_exp2f(ml[i].x - Mn) : 0.0f;
-      L = L * fo + fn * ml[i].y;
-      o = o * fo + fn * ov[i];
-      M = Mn;
+      const float fn = __builtin_amdgcn_exp2f(ml[i].x - base);
+      L = __builtin_fmaf(fn, ml[i].y, L);
+      o = __builtin_fmaf(fn, ov[i], o);
     }
   }
   sm[grp][c] = M;
