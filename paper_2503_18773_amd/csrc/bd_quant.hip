@@ -44,7 +44,9 @@ __device__ __forceinline__ void copy_tail(const uint16_t* __restrict__ ksrc, con
 // 4096 29.1 / 28.8.
 // With 80 registers six share a unit, with the 84 that K by channel takes unasked five.  Six while that is one round (32 of
 // 3000 tokens 12.2 us, five 13.3), five past it, where six have more streams under way than the memory serves well (128K, issued
-// one by one, 113.0 us, five 108.3); per-token K six always (64K 57.3, five 58.6).
+// one by one, 113.0 us, five 108.3); per-token K six always (64K 57.3, five 58.6), but five where the 80 registers do not hold it: in groups
+// of 64 and 32 and in pages (in scratch, six: groups of 32, 4 of 32K 115.5 us, 2 bits 111.0, 16 of 3000 46.3; five 113.7, 108.1, 45.2,
+// and scratch costs a process's first launch some 100 us).
 static inline bool six_on_a_unit(bool kt, long blocks) { return kt || 2 * blocks <= 6 * 256; }
 template <class Run>
 __device__ __forceinline__ void run_part(Run run) {
@@ -206,7 +208,7 @@ __device__ __forceinline__ long mx_block_index(const MxDst& d, int u, int blk, i
   return (long)entry * d.n_kv_heads + u;
 }
 
-// Prefill of an MXFP4 cache, one workgroup per 128-token block, in the tiling of the integer block
+// Prefill of an MXFP4 cache, two workgroups per 128-token block (K and V), in the tiling of the integer block
 // quantizer: 256 threads, a thread holds 8 token rows x 8 consecutive channels of each tensor (one 16-byte
 // load per row; 16 lanes per token row, so every load of a wave covers 1 KB of contiguous source and the
 // four lanes of a DPP quad hold one MX group).  K rows are four apart inside the wave's 32 tokens, so that
@@ -417,7 +419,8 @@ hipError_t launch_quant_blocks(const void* k, const void* v, long src_unit_strid
   const bool six = six_on_a_unit(fmt_kt(c->format), (long)grid.x * units);
 #define BD_QUANT_CASE(FMT, BITS, KT, G)                                                                                         \
   case FMT: {                                                                                                                   \
-    const auto kernel = six ? quant_block_kernel<BITS, KT, G, 6> : quant_block_kernel<BITS, KT, G, KT ? 6 : 5>;                 \
+    constexpr int kSix = KT && G < 128 ? 5 : 6, kFive = KT && G == 128 ? 6 : 5;                                                 \
+    const auto kernel = six ? quant_block_kernel<BITS, KT, G, kSix> : quant_block_kernel<BITS, KT, G, kFive>;                   \
     kernel<<<grid, block, 0, st>>>(kk, vv, src_unit_stride, src_tok0, kc, vc, kp, vp, nbcap, dst_blk0, kr, vr, tail);           \
   } break;
   switch (c->format) {
@@ -486,7 +489,7 @@ hipError_t launch_paged_prefill(const bd_paged_cache* c, int seq, const void* k,
   const bool six = six_on_a_unit(fmt_kt(c->format), (long)grid.x * grid.y);
 #define BD_PAGED_QUANT_CASE(FMT, BITS, KT, G)                                                                   \
   case FMT: {                                                                                                   \
-    const auto kernel = six ? paged_quant_kernel<BITS, KT, G, 6> : paged_quant_kernel<BITS, KT, G, KT ? 6 : 5>; \
+    const auto kernel = six ? paged_quant_kernel<BITS, KT, G, KT ? 5 : 6> : paged_quant_kernel<BITS, KT, G, 5>; \
     kernel<<<grid, block, 0, st>>>(a, kk, vv, seq, L);                                                          \
   } break;
   switch (c->format) {
