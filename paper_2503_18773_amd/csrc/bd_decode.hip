@@ -29,10 +29,12 @@
 // values per lane per block, every lane doing useful work); the pieces of the weights are exchanged between the column
 // groups likewise, and the column groups' partial O^T are added once, after the loop.
 //
-// The bytes hold the 22-bit product q * scale whole down to 2^-8 of the head's largest in the block, and what smaller ones lose
-// is below an fp32 step of the score.  Relative L2 error of fp32 outputs, against 64 bits, as seven e4m3 pieces had it (two
+// The bytes hold the 22-bit product q * scale whole down to 2^-8 of the head's largest in the block; smaller ones are rounded at
+// 2^-31 of that largest.  Relative L2 error of fp32 outputs, against 64 bits, as seven e4m3 pieces had it (two
 // f8f6f4 instructions of 32 cycles a tile; the pieces' conversions take 8 cycles each, 52 a block): 4e-7 .. 6e-7 from 300 to
-// 64K tokens; with an outlier channel in q that is not K's, x 30 .. x 1000, 4e-6 either way.  A step, seven pieces / bytes: 4
+// 64K tokens; with an outlier channel in q that is not K's, x 30 .. x 1000, 4e-6 either way.  (One
+// K value a block of 10^4 among ones of 1, in a channel with a query of -30: 2e-6 / 4 .. 7e-5, 2 bits 1.7e-4; of 100: no
+// difference.)  A step, seven pieces / bytes: 4
 // bits, 1K tokens 7.6 / 7.0 us, 8 units of 24K 10.7 / 10.25, 32K 11.6 / 11.05, 128K 28.0 / 27.35; 2 bits, 8 x 32K 30.1 / 29.1.
 // fp32 outputs are 4e-7 .. 5e-7 off at 4096 tokens, with fp16 weights 1.8e-4 .. 2.2e-4.
 // Groups of 5 .. 16 heads have no columns to spare for the pieces and stay on fp16.
