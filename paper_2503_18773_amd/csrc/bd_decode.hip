@@ -29,13 +29,16 @@
 // values per lane per block, every lane doing useful work); the pieces of the weights are exchanged between the column
 // groups likewise, and the column groups' partial O^T are added once, after the loop.
 //
-// The bytes hold the 22-bit product q * scale whole down to 2^-8 of the head's largest in the block; smaller ones are rounded at
-// 2^-31 of that largest.  Relative L2 error of fp32 outputs, against 64 bits, as seven e4m3 pieces had it (two
-// f8f6f4 instructions of 32 cycles a tile; the pieces' conversions take 8 cycles each, 52 a block): 4e-7 .. 6e-7 from 300 to
-// 64K tokens; with an outlier channel in q that is not K's, x 30 .. x 1000, 4e-6 either way.  (One
-// K value a block of 10^4 among ones of 1, in a channel with a query of -30: 2e-6 / 4 .. 7e-5, 2 bits 1.7e-4; of 100: no
-// difference.)  A step, seven pieces / bytes: 4
-// bits, 1K tokens 7.6 / 7.0 us, 8 units of 24K 10.7 / 10.25, 32K 11.6 / 11.05, 128K 28.0 / 27.35; 2 bits, 8 x 32K 30.1 / 29.1.
+// The bytes hold the 22-bit product q * scale whole down to 2^-8 of the head's largest in the block (2-bit codes: odd channels
+// 2^-6); smaller ones are rounded at 2^-30 (2^-28) of that largest.  Where that may show in the scores, a second four bytes hold
+// what the rounding took, down to 2^-60, and the block's keys are multiplied by those as well (FmtI8, kFineScore, has the rule:
+// one key of 10^4 among others of 1 makes its channel's products the largest of the block while the other tokens' codes
+// there are 0).  Relative L2 error of fp32 outputs, against 64 bits, seven e4m3 pieces (two
+// f8f6f4 instructions of 32 cycles a tile; the pieces' conversions take 8 cycles each, 52 a block) / bytes: 2048 tokens of
+// normal keys 8.7e-7 / 8.6e-7, 2 bits 7.9e-7 / 4.4e-7; one key a block of 10^3 .. 6 * 10^4 with a query of -30 there 8.2e-7 /
+// 7.7e-7, 2 bits 7.5e-7 / 6.0e-7 (without the second four 3e-6 .. 2e-4, 2 bits 2e-5 .. 1e-3); an outlier channel in q that is
+// not K's, x 30 .. x 1000, 9e-7 .. 2e-6 either way.  A step, seven pieces / bytes: 4
+// bits, 1K tokens 7.9 / 7.2 us, 32K 11.6 / 11.2, 128K 28.0 / 27.2; 2 bits, 8 x 32K 31.4 / 29.8.
 // fp32 outputs are 4e-7 .. 5e-7 off at 4096 tokens, with fp16 weights 1.8e-4 .. 2.2e-4.
 // Groups of 5 .. 16 heads have no columns to spare for the pieces and stay on fp16.
 //
@@ -138,11 +141,11 @@ struct WaveLds {
   float zq[GQP];           // per head: sum_c Q_c z_c * 2^-24 (Q as normalised below)
 };
 // Groups of up to 4 heads: Q' as signed bytes, the B operands of two i8 instructions per tile as their lanes read them:
-// [instruction][lane group][column = 4 * byte + head][register].  (Four columns of padding spread the lanes that prepare eight
+// [..][instruction][lane group][column = 4 * byte + head][register].  (Four columns of padding spread the lanes that prepare eight
 // consecutive channels of a head over the banks.)
 template <>
 struct WaveLds<4> {
-  uint32_t qd[2][4][20][4];
+  uint32_t qd[2][2][4][20][4];   // [0]: of Q'; [1]: of what their rounding took
   float4 vpar[kParSlots];
   float2 kpar[kParSlots];  // per-token K only: (scale, zero)
   uint32_t c8[4][8];       // per V token: centre code as e4m3, in B-operand order ([lane group][register])

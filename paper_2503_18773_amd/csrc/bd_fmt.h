@@ -199,12 +199,22 @@ __device__ __forceinline__ uint32_t e4m3_last(uint32_t reg, float x, float y, fl
 // token are bytes after masks as above: 4-bit ones in the order of the words, words 0 and 1 first; 2-bit ones a word each, the
 // odd crumbs of a nibble where they are, that is times 4, and Q' there a quarter.  Q' is an integer x below 2^30; x + 0x808080
 // has the bytes of its four signed digits, the lower three plus 128.
+//
+// What rounding to x takes may show, and the block's scores take it as well (in units of 2^-30), where K is by channel and one
+// of a head's products q * scale counts kFineScore and more in the scores (log2 units, per code step) while the channel's zero
+// is below kFineZero scales.  Below that score, T, the roundings of 128 channels add 4e-8 T (2 bits: 2.5e-8 T) to a score, less
+// than the 4e-7 .. 8e-7 that an output is off anyway (T = 2.6 .. 8, and 13 with 2 bits: no difference).  And with a larger
+// zero the fp32 sums lose as much: either other tokens have codes there, whose scores are that much larger, or the zero
+// term is (a channel of 200 among others of 1, one key of 1200, a query of -30: 3e-5 with or without).  So a channel that is an
+// outlier as a whole, its zero at half its range, takes nothing extra.  Per-token K, whose Q' is Q: where anything was lost.
+// (Issued one by one, no block / every block with them: 32K tokens 10.8 / 11.4 us, 1K 6.5 / 7.6; 2 bits, 4 x 32K 17.5 / 20.5.)
 template <int BITS>
 struct FmtI8;
 template <>
 struct FmtI8<4> {
   __device__ static i8_t a_operand(const uint32_t* w) { return FmtF8<4>::a_operand(w); }
   __device__ static constexpr float position(int) { return 1.0f; }   // what channel n of a lane's eight is to be multiplied by
+  static constexpr float kFineZero = 5.0f, kFineScore = 8.0f;
 };
 template <>
 struct FmtI8<2> {
@@ -221,7 +231,9 @@ struct FmtI8<2> {
     return r;
   }
   __device__ static constexpr float position(int n) { return n & 1 ? 0.25f : 1.0f; }
+  static constexpr float kFineZero = 1.25f, kFineScore = 16.0f;
 };
+constexpr float kFineUnits = 1073741824.0f;   // 2^30
 // Bytes of a, b, c, d: out[k] has byte k of each.
 __device__ __forceinline__ void transpose_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&out)[4]) {
   const uint32_t t0 = __builtin_amdgcn_perm(b, a, 0x05010400u), t1 = __builtin_amdgcn_perm(b, a, 0x07030602u);

@@ -293,6 +293,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
   // Every head's queries times the power of two that brings the largest below 1 (kq); the factor comes
   // back out of the scores, together with softmax_scale * log2(e) and the 2^24 of the subnormal codes (kS).
   float qv[2][4];
+  float fine_from = 0.0f;   // up to 4 heads: kFineScore as a product of head lane / 16
   int kq_head = 0;   // of the head this lane's column carries
   auto scale_queries = [&]() {
     if constexpr (HP > 1) {   // larger groups: for everybody in the workgroup
@@ -317,6 +318,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
         qb = max(max(qb, max(qraw0[i] & 0x7FFFu, (qraw0[i] >> 16) & 0x7FFFu)), max(qraw1[i] & 0x7FFFu, (qraw1[i] >> 16) & 0x7FFFu));
       qb = row_max16_u(qb);   // largest |q| of head lane / 16
       const float f = pow2i(norm_exponent(qb, 0));
+      fine_from = f * (I::kFineScore / fabsf(a.scale_log2));
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         qv[0][i] = h2f((uint16_t)((qraw0[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)) * f;
@@ -354,6 +356,8 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
   // The pair, channel-wise K: the block's scales are first brought below 1 by a power of two (2^-ek, from the largest
   // of the block), so that with |q| < 1 the products neither overflow nor sink into the fp16 subnormals;
   // the factor comes back out of the scores with kS.  Returns ek.
+  // Bytes: `fine` says whether the block (per-token K: every block) takes the second four as well.
+  bool fine = false;
   auto prep_queries = [&]() -> int {
     int ek = 0;
     float nrm[4];   // 2^-ek times the position factor of register i
@@ -380,32 +384,67 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
       for (int i = 2; i < 8; i += 2) top = fmaxf(top, fmaxf(fabsf(t[i]), fabsf(t[i + 1])));
       const uint32_t e = max(row_max16_u(__float_as_uint(top)) & 0x7F800000u, 30u << 23);
       const float up = __uint_as_float((283u << 23) - e), down = __uint_as_float(e - (29u << 23));
-      uint32_t x[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] = (uint32_t)nearest(t[i] * (up * I::position(i))) + 0x00808080u;
       const int h = lane >> 4;
-      uint32_t d0[4], d1[4];
-      if constexpr (BITS == 4) {
-        transpose_bytes(x[0], x[2], x[4], x[6], d0);
-        transpose_bytes(x[1], x[3], x[5], x[7], d1);
-      } else {
-        transpose_bytes(x[0], x[4], x[1], x[5], d0);
-        transpose_bytes(x[2], x[6], x[3], x[7], d1);
-      }
+      auto put_bytes = [&](const int (&n)[8], int level) {
+        uint32_t x[8], d0[4], d1[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t sign = k < 3 ? 0x80808080u : 0u;
-        d0[k] ^= sign;
-        d1[k] ^= sign;
-        if constexpr (BITS == 4) {   // word prep_sg % 4 of the lane group's four: even channels, odd channels
-          *reinterpret_cast<u2_t*>(&wl.qd[(prep_sg >> 1) & 1][prep_sg >> 2][4 * k + h][2 * (prep_sg & 1)]) = (u2_t){d0[k], d1[k]};
-        } else {                     // half of a word of its two: two bytes of each register
-          uint16_t* dst = reinterpret_cast<uint16_t*>(wl.qd[(prep_sg >> 1) & 1][prep_sg >> 2][4 * k + h]) + (prep_sg & 1);
-          dst[0] = (uint16_t)d0[k];
-          dst[2] = (uint16_t)(d0[k] >> 16);
-          dst[4] = (uint16_t)d1[k];
-          dst[6] = (uint16_t)(d1[k] >> 16);
+        for (int i = 0; i < 8; ++i) x[i] = (uint32_t)n[i] + 0x00808080u;
+        if constexpr (BITS == 4) {
+          transpose_bytes(x[0], x[2], x[4], x[6], d0);
+          transpose_bytes(x[1], x[3], x[5], x[7], d1);
+        } else {
+          transpose_bytes(x[0], x[4], x[1], x[5], d0);
+          transpose_bytes(x[2], x[6], x[3], x[7], d1);
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t sign = k < 3 ? 0x80808080u : 0u;
+          d0[k] ^= sign;
+          d1[k] ^= sign;
+          uint32_t* const reg = wl.qd[level][(prep_sg >> 1) & 1][prep_sg >> 2][4 * k + h];
+          if constexpr (BITS == 4) {   // word prep_sg % 4 of the lane group's four: even channels, odd channels
+            *reinterpret_cast<u2_t*>(reg + 2 * (prep_sg & 1)) = (u2_t){d0[k], d1[k]};
+          } else {                     // half of a word of its two: two bytes of each register
+            uint16_t* dst = reinterpret_cast<uint16_t*>(reg) + (prep_sg & 1);
+            dst[0] = (uint16_t)d0[k];
+            dst[2] = (uint16_t)(d0[k] >> 16);
+            dst[4] = (uint16_t)d1[k];
+            dst[6] = (uint16_t)(d1[k] >> 16);
+          }
+        }
+      };
+      int n[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) n[i] = nearest(t[i] * (up * I::position(i)));
+      put_bytes(n, 0);
+      float rest[8];   // what the rounding took (exact)
+      auto rests = [&]() {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rest[i] = __builtin_fmaf(t[i], up * I::position(i), -(float)n[i]);
+      };
+      if constexpr (KT) {
+        rests();
+        bool some = false;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) some |= rest[i] != 0.0f;
+        fine = __any(some);
+      } else {
+        fine = __any(top > fine_from);
+        if (fine) {
+          bool some = false;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const h2_t pr = __builtin_bit_cast(h2_t, i < 4 ? kp0[i] : kp1[i - 4]);
+            some |= fabsf(t[i]) > fine_from && fabsf((float)pr[1]) < I::kFineZero * (float)pr[0];
+          }
+          fine = __any(some);
+        }
+      }
+      if (fine) {
+        if constexpr (!KT) rests();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) n[i] = nearest(rest[i] * kFineUnits);
+        put_bytes(n, 1);
       }
       if (prep_sg == 0) wl.zq[h] = make_float2(KT ? zsum * up : zsum, down);   // (per-token K adds it to the sums)
       return 0;
@@ -468,7 +507,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
   const int sb_p = 127 - E::kTop - 5 * cg;    // that of piece cg of P'
   auto load_bq = [&](int j) {
     if constexpr (kF8) {
-      if (j < 2) bq8[j] = __builtin_bit_cast(i4_t, *reinterpret_cast<const u4_t*>(wl.qd[j][g][col]));
+      if (j < 2) bq8[j] = __builtin_bit_cast(i4_t, *reinterpret_cast<const u4_t*>(wl.qd[0][j][g][col]));
     } else if constexpr (kSplitCols) {
       bqh[j] = *reinterpret_cast<const h8_t*>(cg & 1 ? &wl.qlo[head][8 * (4 * g + j)] : &wl.qhi[head][8 * (4 * g + j)]);
     } else {
@@ -714,6 +753,17 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
     // groups of 9..16 heads: only once the keys' registers are free, which lets two waves fit a SIMD
     constexpr bool kValuesAfterQK = GQP == 16;
 
+    // bytes: the partial scores of a tile, `weight` what the byte counts
+    auto tile_scores = [&](const uint32_t* codes, const i4_t (&bytes)[2], float weight) {
+      const i8_t ak = I::a_operand(codes);
+      i4_t n = {kSumBits, kSumBits, kSumBits, kSumBits};
+      n = __builtin_amdgcn_mfma_i32_16x16x64_i8((i4_t){ak[0], ak[1], ak[2], ak[3]}, bytes[0], n, 0, 0, 0);
+      n = __builtin_amdgcn_mfma_i32_16x16x64_i8((i4_t){ak[4], ak[5], ak[6], ak[7]}, bytes[1], n, 0, 0, 0);
+      f4_t acc;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = __builtin_fmaf(__int_as_float(n[r]), weight, -kSumBase * weight);   // exact
+      return acc;
+    };
     // ---- S^T tiles (rows = tokens 32*(row/4) + 4T + row%4, all 16 columns valid); each lane
     //      keeps the tiles of the k-steps its column group owns: sc[o][low/high half][row]
 #pragma unroll
@@ -723,12 +773,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
       for (int tt = 0; tt < 4; ++tt) {
         f4_t acc = {0.f, 0.f, 0.f, 0.f};   // (the zero term, one number per head, joins in the softmax)
         if constexpr (kF8) {
-          const i8_t ak = I::a_operand(kraw[4 * half + tt].w);
-          i4_t n = {kSumBits, kSumBits, kSumBits, kSumBits};
-          n = __builtin_amdgcn_mfma_i32_16x16x64_i8((i4_t){ak[0], ak[1], ak[2], ak[3]}, bq8[0], n, 0, 0, 0);
-          n = __builtin_amdgcn_mfma_i32_16x16x64_i8((i4_t){ak[4], ak[5], ak[6], ak[7]}, bq8[1], n, 0, 0, 0);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[r] = __builtin_fmaf(__int_as_float(n[r]), w_q, -kSumBase * w_q);   // exact
+          acc = tile_scores(kraw[4 * half + tt].w, bq8, w_q);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -766,6 +811,29 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
           }
       } else {                              // column group cg keeps tile cg of each half: the sum of the four pieces' products
         reduce_scatter(s, sc[0][half]);
+      }
+    }
+    if constexpr (kF8) {
+      if (fine) {
+        const float w_f = w_q * (1.0f / kFineUnits);
+        i4_t f8[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) f8[j] = __builtin_bit_cast(i4_t, *reinterpret_cast<const u4_t*>(wl.qd[1][j][g][col]));
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          f4_t s[4];
+          float rest[4];
+#pragma unroll
+          for (int tt = 0; tt < 4; ++tt) {
+            RawTile<WORDS> again = kraw[4 * half + tt];   // (hidden: the masked codes would be kept, 28 registers of every block)
+#pragma unroll
+            for (int i = 0; i < WORDS; ++i) asm volatile("" : "+v"(again.w[i]));
+            s[tt] = tile_scores(again.w, f8, w_f);
+          }
+          reduce_scatter(s, rest);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sc[0][half][r] += rest[r];
+        }
       }
     }
     if (kValuesAfterQK) {

@@ -399,6 +399,43 @@ def test_outlier_queries_keep_their_bits(fmt, factor):
 
 
 @pytest.mark.parametrize("fmt", ["int4", "int2", "int4_kt", "int2_kt"])
+@pytest.mark.parametrize("gq", [1, 4])
+@pytest.mark.parametrize("nb,ns", [(3, 1), (6, 1), (9, 1), (9, 2)])
+def test_a_large_product_takes_no_bits_from_the_others(fmt, gq, nb, ns):
+    """Query groups of up to 4 heads, Q' relative to its largest in the block.  K by channel: every third block has one token
+    of 10^4 and more in a channel of zeros, where the query is negative: the token weighs nothing and the others' codes there
+    are 0, but the channel's scale is the block's largest.  Per-token K: keys of one sign, so that the zero terms are 0, and a
+    query of 6 * 10^4 where every key is 0.  The bar is that of test_outlier_queries_keep_their_bits, M that of the tokens
+    that weigh something."""
+    import torch
+    kt, L = "_kt" in fmt, 128 * nb
+    for big, factor in [(1e4, 30), (1e4, 1000), (6e4, 30), (6e4, 1000)][:1 if kt else 4]:
+        rng = np.random.default_rng(nb + gq)
+        q = rng.standard_normal((1, 2 * gq, 128))
+        K, V = (rng.standard_normal((1, 2, L, 128)) for _ in range(2))
+        K[..., 9] = 0
+        scale = W.softmax_scale(W.CONFIGS["cfg1"])
+        if kt:
+            K, q, scale = np.abs(K), 0.02 * q, 50 * scale
+            q[..., 9] = 6e4
+        else:
+            q[..., 9] = -factor
+        ka = np.abs(K.astype(np.float16).astype(np.float64))[0]
+        if not kt:
+            K[:, :, 5::384, 9] = big
+        q, K, V = (x.astype(np.float16) for x in (q, K, V))
+        M = scale * 1.4427 * max((np.abs(q.astype(np.float64)).reshape(2, gq, 128)[h] @ ka[h].T).max() for h in range(2))
+        bar = 12 * 2.0 ** -23 * M + 2.0 ** -20
+        oc, gc = _caches_of(K, V, fmt, gq)
+        gc.desc.out_type = B.BD_OUT_F32
+        out = torch.full((1, 2 * gq, 128), 7.0, dtype=torch.float32, device="cuda:0")
+        gc.decode_attn(to_dev(q, "fp16"), scale, out, num_splits=ns)
+        torch.cuda.synchronize()
+        ma, rl = attn_errors(out_to_f64(out), O.decode_attn(oc, q, scale))
+        assert rl <= bar, f"{fmt} gq={gq} {nb} blocks, {big:g} x {factor}: rel-L2 {rl:.2e} against {bar:.2e} (M {M:.3g})"
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int2", "int4_kt", "int2_kt"])
 @pytest.mark.parametrize("x", [8, 13, 18, 23.5])
 def test_a_long_tail_behind_one_dominating_token_is_kept(fmt, x):
     """6144 tokens that weigh about 2^-x of one other, their values alike: what rounding takes from each weight adds up.
