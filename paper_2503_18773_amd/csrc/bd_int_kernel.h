@@ -378,12 +378,13 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
         }
       }
       zsum = row_sum16(zsum);
-      // the power of two that brings the head's largest into [2^29, 2^30), and back (all zero: any)
-      float top = fmaxf(fabsf(t[0]), fabsf(t[1]));
+      // the power of two that brings the head's largest into [2^29, 2^30), and back (all zero: any; an integer holds no NaN
+      // and no infinity, which the way back hands to all of the head's scores)
+      float top = fabsf(t[0]);
 #pragma unroll
-      for (int i = 2; i < 8; i += 2) top = fmaxf(top, fmaxf(fabsf(t[i]), fabsf(t[i + 1])));
-      const uint32_t e = max(row_max16_u(__float_as_uint(top)) & 0x7F800000u, 30u << 23);
-      const float up = __uint_as_float((283u << 23) - e), down = __uint_as_float(e - (29u << 23));
+      for (int i = 1; i < 8; ++i) top = __builtin_elementwise_maximum(top, fabsf(t[i]));   // (NaN if one is)
+      const uint32_t most = row_max16_u(__float_as_uint(top)), e = max(most & 0x7F800000u, 30u << 23);
+      const float up = __uint_as_float((283u << 23) - e), down = __builtin_fmaf(__uint_as_float(most), 0.0f, __uint_as_float(e - (29u << 23)));
       const int h = lane >> 4;
       auto put_bytes = [&](const int (&n)[8], int level) {
         uint32_t x[8], d0[4], d1[4];

@@ -436,6 +436,34 @@ def test_a_large_product_takes_no_bits_from_the_others(fmt, gq, nb, ns):
 
 
 @pytest.mark.parametrize("fmt", ["int4", "int2", "int4_kt", "int2_kt"])
+@pytest.mark.parametrize("gq", [1, 4, 5])
+@pytest.mark.parametrize("ns", [1, 2])
+def test_infinities_show(fmt, gq, ns):
+    """A packed key of plus or minus infinity (its scale is a NaN then) gives every head of its KV head a row of zeros, as a
+    sum of weights that is no number does, an infinite query that head's; whatever arithmetic the size of the group takes, and
+    no other row is touched."""
+    import torch
+    rng = np.random.default_rng(gq)
+    K, V = (rng.standard_normal((1, 3, 640, 128)).astype(np.float16) for _ in range(2))
+    q = rng.standard_normal((1, 3 * gq, 128)).astype(np.float16)
+    q[:, :, 9] = np.arange(3 * gq) % 2   # (0: the channel's product is 0 x its scale)
+    scale = W.softmax_scale(W.CONFIGS["cfg1"])
+    ref = O.decode_attn(_caches_of(K, V, fmt, gq)[0], q, scale)
+    K[0, 0, 133, 9], K[0, 1, 7, 9] = np.inf, -np.inf
+    q[0, 2 * gq, 50] = -np.inf
+    gc = B.KVCache(1, 3 * gq, 3, fmt, 768)
+    gc.quant_pack_kv(to_dev(K, "fp16"), to_dev(V, "fp16"))
+    gc.desc.out_type = B.BD_OUT_F32
+    out = torch.full((1, 3 * gq, 128), 7.0, dtype=torch.float32, device="cuda:0")
+    gc.decode_attn(to_dev(q, "fp16"), scale, out, num_splits=ns)
+    torch.cuda.synchronize()
+    got = out_to_f64(out)
+    assert np.all(got[0, :2 * gq + 1] == 0.0)
+    if gq > 1:
+        assert attn_errors(got[0, 2 * gq + 1:], ref[0, 2 * gq + 1:])[1] <= (1e-5 if gq <= 4 else 1e-3)
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int2", "int4_kt", "int2_kt"])
 @pytest.mark.parametrize("x", [8, 13, 18, 23.5])
 def test_a_long_tail_behind_one_dominating_token_is_kept(fmt, x):
     """6144 tokens that weigh about 2^-x of one other, their values alike: what rounding takes from each weight adds up.
