@@ -305,8 +305,7 @@ bd_status bd_paged_decode_attn(const bd_paged_cache* c, const void* q, float sof
  * and files it (integer formats: the workgroup that reads the block a step fills quantizes it
  * first; MXFP4: the workgroup that reads the token's block quantizes the token), and the merge,
  * the last kernel, raises the lengths.  Larger query groups: three -- append, attention, merge.
- * (With num_splits == 1 there is no merge, and the attention launch raises the lengths itself; it
- * counts its workgroups in `workspace`, whatever that holds, so steps that may overlap need one each.)  A sequence
+ * (With num_splits == 1 there is no merge and a small kernel raises the lengths; the workspace is not touched.)  A sequence
  * whose token is dropped for want of a valid page (bit 1 of *status) attends the tokens it had. */
 bd_status bd_paged_decode_step(const bd_paged_cache* c, const void* k_new, const void* v_new,
                                const void* q, float softmax_scale, int32_t num_splits,
@@ -321,6 +320,24 @@ bd_status bd_paged_decode_step(const bd_paged_cache* c, const void* k_new, const
 bd_status bd_paged_decode_step_lazy(const bd_paged_cache* c, const void* k_new, const void* v_new,
                                     const void* q, float softmax_scale, int32_t num_splits,
                                     void* workspace, void* out, void* stream);
+
+/* A paged cache with counters of its own: device, BD_STEP_COUNTER_BYTES, 16-byte aligned, zeros before the first
+ * step.  Nothing but this cache's steps uses them, and every step leaves them as zeros. */
+#define BD_STEP_COUNTER_BYTES 1088
+typedef struct bd_paged_counted {
+  bd_paged_cache cache;
+  void* counters;
+} bd_paged_counted;
+
+/* The same two steps, same results, for such a cache: with num_splits == 1 the attention launch counts its
+ * workgroups and raises the lengths itself, a launch less (otherwise the counters are left alone).  As the
+ * lengths do, the counters forbid that two steps of a cache overlap. */
+bd_status bd_paged_counted_step(const bd_paged_counted* c, const void* k_new, const void* v_new,
+                                const void* q, float softmax_scale, int32_t num_splits,
+                                void* workspace, void* out, void* stream);
+bd_status bd_paged_counted_step_lazy(const bd_paged_counted* c, const void* k_new, const void* v_new,
+                                     const void* q, float softmax_scale, int32_t num_splits,
+                                     void* workspace, void* out, void* stream);
 
 /* Text for a status code (static storage). */
 const char* bd_strerror(bd_status s);

@@ -20,6 +20,7 @@ FORMATS = {"int4": BD_FMT_INT4, "int2": BD_FMT_INT2, "mxfp4": BD_FMT_MXFP4, "int
 BLOCK = 128
 BD_OUT_HALF, BD_OUT_F32 = 0, 1
 BD_STATIC_SCRATCH_BYTES = 4 << 20   # include/bitdecode.h
+BD_STEP_COUNTER_BYTES = 1088
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libbitdecode.so")
 _lib = None
@@ -48,6 +49,10 @@ class bd_paged_cache(ctypes.Structure):
         ("block_table", ctypes.c_void_p), ("seq_lens", ctypes.c_void_p), ("status", ctypes.c_void_p),
         ("out_type", ctypes.c_int32),
     ]
+
+
+class bd_paged_counted(bd_paged_cache):
+    _fields_ = [("counters", ctypes.c_void_p)]
 
 
 class BitDecodeError(RuntimeError):
@@ -88,6 +93,9 @@ def lib() -> ctypes.CDLL:
         L.bd_paged_decode_attn.restype, L.bd_paged_decode_attn.argtypes = ctypes.c_int, [PP, V, F, I, V, V, V]
         L.bd_paged_decode_step.restype, L.bd_paged_decode_step.argtypes = ctypes.c_int, [PP, V, V, V, F, I, V, V, V]
         L.bd_paged_decode_step_lazy.restype, L.bd_paged_decode_step_lazy.argtypes = ctypes.c_int, [PP, V, V, V, F, I, V, V, V]
+        PC = ctypes.POINTER(bd_paged_counted)
+        L.bd_paged_counted_step.restype, L.bd_paged_counted_step.argtypes = ctypes.c_int, [PC, V, V, V, F, I, V, V, V]
+        L.bd_paged_counted_step_lazy.restype, L.bd_paged_counted_step_lazy.argtypes = ctypes.c_int, [PC, V, V, V, F, I, V, V, V]
         L.bd_strerror.restype, L.bd_strerror.argtypes = ctypes.c_char_p, [ctypes.c_int]
         L.bd_last_hip_error.restype, L.bd_last_hip_error.argtypes = ctypes.c_int, []
         _entry.update((name, ctypes.cast(getattr(L, name), V).value) for name in EXPORTS)
@@ -98,7 +106,8 @@ def lib() -> ctypes.CDLL:
 EXPORTS = ["bd_cache_bytes", "bd_choose_splits", "bd_step_splits", "bd_workspace_bytes", "bd_quant_pack_kv", "bd_append_kv",
            "bd_decode_attn", "bd_decode_attn_static", "bd_probe_stream_read", "bd_decode_step", "bd_decode_step_lazy", "bd_splitk_combine", "bd_strerror", "bd_last_hip_error",
            "bd_paged_cache_bytes", "bd_paged_workspace_bytes", "bd_paged_quant_pack_kv", "bd_paged_append_kv",
-           "bd_paged_decode_attn", "bd_paged_decode_step", "bd_paged_decode_step_lazy"]
+           "bd_paged_decode_attn", "bd_paged_decode_step", "bd_paged_decode_step_lazy", "bd_paged_counted_step",
+           "bd_paged_counted_step_lazy"]
 
 
 def _ptr(t):
@@ -393,7 +402,7 @@ class PagedKVCache:
         self.fmt = fmt
         max_pages = int(block_table.shape[1])
         assert block_table.shape[0] == batch
-        self.desc = bd_paged_cache(batch, n_q_heads, n_kv_heads, 128, FORMATS[fmt], num_pages, max_pages)
+        self.desc = bd_paged_counted(batch, n_q_heads, n_kv_heads, 128, FORMATS[fmt], num_pages, max_pages)
         self.sizes = [bd_paged_cache_bytes(self.desc, i) for i in range(8)]
         if self.sizes[0] == 0:
             raise BitDecodeError(-1, "bd_paged_cache_bytes")
@@ -401,11 +410,13 @@ class PagedKVCache:
         self.block_table = torch.as_tensor(block_table, dtype=torch.int32).contiguous().to(device)
         self.seq_lens = torch.zeros(batch, dtype=torch.int32, device=device)
         self.status = torch.zeros(1, dtype=torch.int32, device=device)
+        self.counters = torch.zeros(BD_STEP_COUNTER_BYTES, dtype=torch.uint8, device=device)
         for name, buf in zip(["k_codes", "v_codes", "k_params", "v_params", "k_res", "v_res"], self.buffers):
             setattr(self.desc, name, buf.data_ptr())
         self.desc.block_table = self.block_table.data_ptr()
         self.desc.seq_lens = self.seq_lens.data_ptr()
         self.desc.status = self.status.data_ptr()
+        self.desc.counters = self.counters.data_ptr()
         self.device = device
         self._ws = None
         self._ws_rows = 0
@@ -439,7 +450,8 @@ class PagedKVCache:
 
     def decode_step(self, k_new, v_new, q, softmax_scale: float, out, num_splits: int, stream=None, lazy: bool = False):
         name = "bd_paged_decode_step_lazy" if lazy else "bd_paged_decode_step"
-        _check(_call.paged_step(_address(name), self.desc, k_new, v_new, q, softmax_scale, num_splits, self.workspace(num_splits), out,
+        entry = "bd_paged_counted_step_lazy" if lazy else "bd_paged_counted_step"   # the same in a launch less, with num_splits 1
+        _check(_call.paged_step(_address(entry), self.desc, k_new, v_new, q, softmax_scale, num_splits, self.workspace(num_splits), out,
                                 _stream(stream)), name)
         return out
 

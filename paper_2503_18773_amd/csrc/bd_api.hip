@@ -480,20 +480,22 @@ bd_status bd_paged_append_kv(const bd_paged_cache* c, const void* k_new, const v
 // (main integer kernel only), is appended by the attention launch itself.
 static bd_status paged_attention(const bd_paged_cache* c, const void* q, float softmax_scale, int32_t num_splits,
                                  void* workspace, void* out, bool step, hipStream_t st,
-                                 const void* k_new = nullptr, const void* v_new = nullptr, bool lazy = false) {
+                                 const void* k_new = nullptr, const void* v_new = nullptr, bool lazy = false,
+                                 void* counters = nullptr) {
   const bd_cache shape = shape_of(c);
   float* part_o = ws_part_o(workspace);
   float* part_ml = ws_part_ml(&shape, workspace, num_splits);
-  // one split: the attention kernel writes `out` itself and no merge runs (of a fused step it raises the lengths as well)
+  // one split: the attention kernel writes `out` itself and no merge runs (of a fused step it raises the lengths as well, with
+  // `counters`, or a launch behind it does)
   void* direct = num_splits == 1 ? out : nullptr;
   bd_status s = hip_status(c->format == BD_FMT_MXFP4
                                ? launch_decode_mx_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
-                                                        direct, st)
+                                                        direct, st, counters)
                            : fmt_group(c->format) != kBlock
                                ? launch_decode_grp_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
-                                                         direct, st, lazy)
+                                                         direct, st, lazy, counters)
                                : launch_decode_paged(c, q, softmax_scale, num_splits, part_o, part_ml, step, k_new, v_new,
-                                                     direct, st, lazy));
+                                                     direct, st, lazy, counters));
   if (s != BD_OK) return s;
   if (direct) return BD_OK;
   return hip_status(launch_combine(&shape, part_o, part_ml, num_splits, out, st, step ? c : nullptr));
@@ -509,8 +511,9 @@ bd_status bd_paged_decode_attn(const bd_paged_cache* c, const void* q, float sof
   return paged_attention(c, q, softmax_scale, num_splits, workspace, out, false, (hipStream_t)stream);
 }
 
-bd_status bd_paged_decode_step(const bd_paged_cache* c, const void* k_new, const void* v_new, const void* q,
-                               float softmax_scale, int32_t num_splits, void* workspace, void* out, void* stream) {
+// counters: those of a bd_paged_counted, nullptr: none
+static bd_status paged_step(const bd_paged_cache* c, const void* k_new, const void* v_new, const void* q, float softmax_scale,
+                            int32_t num_splits, void* workspace, void* out, void* stream, void* counters) {
   bd_status s = check_paged_shape(c);
   if (s != BD_OK) return s;
   if ((s = check_paged_buffers(c)) != BD_OK) return s;
@@ -524,26 +527,55 @@ bd_status bd_paged_decode_step(const bd_paged_cache* c, const void* k_new, const
   // that reads the token's block quantizes the token into it), and the merge raises the lengths.
   // (the kernel of the group-64/32 formats takes 8 heads per workgroup, the others 16)
   if (c->n_q_heads / c->n_kv_heads <= (fmt_is_int(c->format) && fmt_group(c->format) != kBlock ? 8 : 16))
-    return paged_attention(c, q, softmax_scale, num_splits, workspace, out, true, st, k_new, v_new);
+    return paged_attention(c, q, softmax_scale, num_splits, workspace, out, true, st, k_new, v_new, false, counters);
   // otherwise three launches instead of four: the append leaves the lengths alone, the attention
   // kernel counts the new token in, and the merge, last in line, raises the lengths
   if ((s = hip_status(launch_paged_append(c, k_new, v_new, false, st))) != BD_OK) return s;
-  return paged_attention(c, q, softmax_scale, num_splits, workspace, out, true, st);
+  return paged_attention(c, q, softmax_scale, num_splits, workspace, out, true, st, nullptr, nullptr, false, counters);
 }
 
-bd_status bd_paged_decode_step_lazy(const bd_paged_cache* c, const void* k_new, const void* v_new, const void* q,
-                                    float softmax_scale, int32_t num_splits, void* workspace, void* out, void* stream) {
+static bd_status paged_step_lazy(const bd_paged_cache* c, const void* k_new, const void* v_new, const void* q, float softmax_scale,
+                                 int32_t num_splits, void* workspace, void* out, void* stream, void* counters) {
   bd_status s = check_paged_shape(c);
   if (s != BD_OK) return s;
   if (c->format == BD_FMT_MXFP4)   // no residual: nothing to flush lazily
-    return bd_paged_decode_step(c, k_new, v_new, q, softmax_scale, num_splits, workspace, out, stream);
+    return paged_step(c, k_new, v_new, q, softmax_scale, num_splits, workspace, out, stream, counters);
   if ((s = check_paged_buffers(c)) != BD_OK) return s;
   if (!k_new || !v_new || !q || !workspace || !out || num_splits < 1 || num_splits > 65533) return BD_ERR_INVALID_ARG;
   if (!aligned16(k_new) || !aligned16(v_new) || !aligned16(q) || !aligned16(workspace) || !aligned16(out))
     return BD_ERR_ALIGNMENT;
   // Two launches for every query group size: no workgroup has to read the block a sequence fills, so the extra
   // workgroup per (sequence, KV head) packs it while the others attend the 128 fp16 rows.
-  return paged_attention(c, q, softmax_scale, num_splits, workspace, out, true, (hipStream_t)stream, k_new, v_new, true);
+  return paged_attention(c, q, softmax_scale, num_splits, workspace, out, true, (hipStream_t)stream, k_new, v_new, true, counters);
+}
+
+bd_status bd_paged_decode_step(const bd_paged_cache* c, const void* k_new, const void* v_new, const void* q,
+                               float softmax_scale, int32_t num_splits, void* workspace, void* out, void* stream) {
+  return paged_step(c, k_new, v_new, q, softmax_scale, num_splits, workspace, out, stream, nullptr);
+}
+
+bd_status bd_paged_decode_step_lazy(const bd_paged_cache* c, const void* k_new, const void* v_new, const void* q,
+                                    float softmax_scale, int32_t num_splits, void* workspace, void* out, void* stream) {
+  return paged_step_lazy(c, k_new, v_new, q, softmax_scale, num_splits, workspace, out, stream, nullptr);
+}
+
+static bd_status check_counters(const bd_paged_counted* c) {
+  if (!c || !c->counters) return BD_ERR_INVALID_ARG;
+  return aligned16(c->counters) ? BD_OK : BD_ERR_ALIGNMENT;
+}
+
+bd_status bd_paged_counted_step(const bd_paged_counted* c, const void* k_new, const void* v_new, const void* q,
+                                float softmax_scale, int32_t num_splits, void* workspace, void* out, void* stream) {
+  const bd_status s = check_counters(c);
+  if (s != BD_OK) return s;
+  return paged_step(&c->cache, k_new, v_new, q, softmax_scale, num_splits, workspace, out, stream, c->counters);
+}
+
+bd_status bd_paged_counted_step_lazy(const bd_paged_counted* c, const void* k_new, const void* v_new, const void* q,
+                                     float softmax_scale, int32_t num_splits, void* workspace, void* out, void* stream) {
+  const bd_status s = check_counters(c);
+  if (s != BD_OK) return s;
+  return paged_step_lazy(&c->cache, k_new, v_new, q, softmax_scale, num_splits, workspace, out, stream, c->counters);
 }
 
 const char* bd_strerror(bd_status s) {

@@ -79,7 +79,7 @@ static PyObject* step(PyObject* self, PyObject* const* a, Py_ssize_t n) {
 }
 
 /* paged_step(fn, cache, k_new, v_new, q, scale, num_splits, workspace, out, stream) -> status
- *   (bd_paged_decode_step, bd_paged_decode_step_lazy) */
+ *   (bd_paged_decode_step, bd_paged_counted_step and their lazy forms) */
 static PyObject* paged_step(PyObject* self, PyObject* const* a, Py_ssize_t n) {
   void *fn, *k, *v, *q, *ws, *out, *stream;
   int32_t ns;

@@ -22,7 +22,7 @@ typedef int i8_t __attribute__((ext_vector_type(8)));
 
 // A step's attention launch that raises the lengths itself (LengthRaise): its counters, nullptr: it does not.
 struct RaiseArgs {
-  unsigned long long* words;
+  uint32_t* words;
   int per_seq;   // workgroups of a sequence
 };
 
@@ -61,7 +61,7 @@ hipError_t launch_paged_prefill(const bd_paged_cache* c, int seq, const void* k,
                                 hipStream_t st);
 hipError_t launch_paged_append(const bd_paged_cache* c, const void* k_new, const void* v_new, bool bump,
                                hipStream_t st);
-// (the launches of a paged step in one split raise the lengths too, or have launch_paged_bump do it)
+// (the launches of a paged step in one split raise the lengths too, with `counters`, or have launch_paged_bump do it)
 // `out` (all decode launchers): with num_splits == 1 and out != nullptr the kernel writes the final output
 // rows itself and no merge is needed; otherwise it writes the split partials.
 // raises the length of every sequence whose step's token was appended (launch_paged_append with bump = false)
@@ -70,7 +70,7 @@ hipError_t launch_paged_bump(const bd_paged_cache* c, hipStream_t st);
 // before it; query groups of up to 16 heads only
 hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
-                               void* out, hipStream_t st, bool lazy = false);
+                               void* out, hipStream_t st, bool lazy, void* counters);
 
 // k_new / v_new non-null: fused step -- residual token res_len-1 is read from k_new / v_new
 // ([B][Hkv][128]) and also stored into the residual buffers by the kernel.
@@ -88,12 +88,12 @@ hipError_t launch_decode_grp(const bd_cache* c, const void* q, int packed_len, i
 // (k_new / v_new as in launch_decode_paged; query groups of up to 8 heads only)
 hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                    float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
-                                   void* out, hipStream_t st, bool lazy = false);
+                                   void* out, hipStream_t st, bool lazy, void* counters);
 // k_new / v_new non-null: the launch quantizes the step's token into the cache itself (contiguous: at index
 // `length`, and attends length + 1 tokens; paged: with `step`); query groups of up to 16 heads only
 hipError_t launch_decode_mx_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                   float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
-                                  void* out, hipStream_t st);
+                                  void* out, hipStream_t st, void* counters);
 hipError_t launch_decode_mx(const bd_cache* c, const void* q, int length, float softmax_scale,
                             int num_splits, float* part_o, float* part_ml, const void* k_new, const void* v_new,
                             void* out, hipStream_t st);

@@ -358,7 +358,7 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
 
 hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
-                               void* out, hipStream_t st, bool lazy) {
+                               void* out, hipStream_t st, bool lazy, void* counters) {
   DecodeArgs a;
   a.step = step ? 1 : 0;
   a.out = num_splits == 1 ? out : nullptr;
@@ -393,7 +393,7 @@ hipError_t launch_decode_paged(const bd_paged_cache* c, const void* q, float sof
   a.max_pages = c->max_pages_per_seq;
   a.num_pages = c->num_pages;
   dim3 grid(num_splits, c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);   // (paged_grid)
-  a.raise = raise_args(c, step && a.out, (long)grid.y * (lazy ? 2 : 1), part_o);
+  a.raise = raise_args(c, step && a.out, (long)grid.y * (lazy ? 2 : 1), counters);
   launch_instance(c->format, a.gq, kManyBlocks, true, a, grid, block, st);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess && step && a.out && !a.raise.words ? launch_paged_bump(c, st) : e;

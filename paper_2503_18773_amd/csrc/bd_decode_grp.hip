@@ -195,7 +195,7 @@ hipError_t launch_decode_grp(const bd_cache* c, const void* q, int packed_len, i
 
 hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                    float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
-                                   void* out, hipStream_t st, bool lazy) {
+                                   void* out, hipStream_t st, bool lazy, void* counters) {
   GrpArgs a;
   a.k_new = (const uint16_t*)k_new;   // non-null: the step's token, which this launch appends itself
   a.v_new = (const uint16_t*)v_new;
@@ -227,7 +227,7 @@ hipError_t launch_decode_grp_paged(const bd_paged_cache* c, const void* q, float
   a.step = step ? 1 : 0;
   a.flush_mode = lazy ? kFlushAfter : kFlushNone;   // (as in launch_decode_paged)
   a.flush_blk = 0;
-  a.raise = raise_args(c, step && a.out, (long)a.n_kv_heads * ((a.gq + kGrpHeads - 1) / kGrpHeads) * (lazy ? 2 : 1), part_o);
+  a.raise = raise_args(c, step && a.out, (long)a.n_kv_heads * ((a.gq + kGrpHeads - 1) / kGrpHeads) * (lazy ? 2 : 1), counters);
   const hipError_t e = launch_format(c->format, a, true, c->batch, st);
   return e == hipSuccess && step && a.out && !a.raise.words ? launch_paged_bump(c, st) : e;
 }

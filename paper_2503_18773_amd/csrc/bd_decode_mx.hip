@@ -222,7 +222,7 @@ hipError_t launch_decode_mx(const bd_cache* c, const void* q, int length, float 
 
 hipError_t launch_decode_mx_paged(const bd_paged_cache* c, const void* q, float softmax_scale, int num_splits,
                                   float* part_o, float* part_ml, bool step, const void* k_new, const void* v_new,
-                                  void* out, hipStream_t st) {
+                                  void* out, hipStream_t st, void* counters) {
   MxArgs a{};
   a.k_new = (const uint16_t*)k_new;
   a.v_new = (const uint16_t*)v_new;
@@ -247,7 +247,7 @@ hipError_t launch_decode_mx_paged(const bd_paged_cache* c, const void* q, float 
   a.status = c->status;
   a.max_pages = c->max_pages_per_seq;
   a.num_pages = c->num_pages;
-  a.raise = raise_args(c, step && a.out, (long)a.n_kv_heads * ((a.gq + 15) / 16), part_o);
+  a.raise = raise_args(c, step && a.out, (long)a.n_kv_heads * ((a.gq + 15) / 16), counters);
   const hipError_t e = launch_mx<true>(a, c->batch, st);
   return e == hipSuccess && step && a.out && !a.raise.words ? launch_paged_bump(c, st) : e;
 }

@@ -286,25 +286,18 @@ __device__ __forceinline__ int paged_sequence(const int32_t* __restrict__ seq_le
 // those raises.  The atomics are relaxed and at device scope (no cache to write back: the counters are all that is exchanged).
 // A step against a launch of its own for the lengths, one by one: 40 sequences of 1K to 3.1K tokens, 2 bits, 8 heads per KV
 // head 23.4 -> 22.0 us; 58 of 0.5K to 1.5K, 2 bits, 5 heads 21.1 -> 19.5; 9 of up to 26 tokens, 4 bits 9.3 -> 6.5; MXFP4 9 of up
-// to 242 9.2 -> 6.9.
-// A counter is kRaiseMark | count.  The workspace comes as it is: a word without the mark is not a counter yet, and whoever
-// counts there first makes it one (44 bits; the partials that other calls leave there hold no such bits, a NaN).  The last to count leaves it at zero, for the next launch.
-constexpr unsigned long long kRaiseMark = 0x7FB5A3C19E5ull << kRaiseCountBits;
+// to 242 9.2 -> 6.9.  In a graph: groups of 32, 32 of up to 1000 17.7 -> 16.7; groups of 64, 2 bits, 8 heads, 33 of up to 3000
+// 30.6 -> 29.3.
+// The counters are zero between launches: the last to count leaves each so.
 struct LengthRaise {
-  unsigned long long seen;   // the shard's counter as it was
+  uint32_t seen;   // the shard's counter as it was
 
-  __device__ __forceinline__ static unsigned long long* word(const RaiseArgs& r, int i) { return r.words + kRaiseStride * i; }
-  __device__ __forceinline__ static unsigned long long add(unsigned long long* w) {
-    return __hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __device__ __forceinline__ static uint32_t* word(const RaiseArgs& r, int i) { return r.words + kRaiseStride * i; }
+  __device__ __forceinline__ static uint32_t add(uint32_t* w) {
+    return __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  // add(w) gave `old`: how many had counted before.
-  __device__ __forceinline__ static int counted(unsigned long long* w, unsigned long long old) {
-    if ((old >> kRaiseCountBits) == (kRaiseMark >> kRaiseCountBits)) return (int)(old & ((1u << kRaiseCountBits) - 1));
-    unsigned long long cur = old + 1, next;   // (an exchange fails only where another workgroup has counted)
-    do {
-      next = (cur >> kRaiseCountBits) == (kRaiseMark >> kRaiseCountBits) ? cur + 1 : kRaiseMark + 1;
-    } while (!__hip_atomic_compare_exchange_strong(w, &cur, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    return (int)((next - 1) & ((1u << kRaiseCountBits) - 1));
+  __device__ __forceinline__ static void clear(uint32_t* w) {
+    __hip_atomic_store(w, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   // The whole workgroup, which has read all lengths that it needs; `b` its sequence.
   __device__ __forceinline__ void arrive(const RaiseArgs& r, int b, int batch) {
@@ -320,10 +313,10 @@ struct LengthRaise {
     if (threadIdx.x < blockDim.x - 64) return;
     const int shards = raise_shards(batch), s = b % shards;
     bool last = false;
-    if (threadIdx.x == blockDim.x - 64 && counted(word(r, 1 + s), seen) + 1 == (int)raise_arrivals(s, r.per_seq, batch)) {
-      __hip_atomic_store(word(r, 1 + s), kRaiseMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (counted(word(r, 0), add(word(r, 0))) + 1 == shards) {
-        __hip_atomic_store(word(r, 0), kRaiseMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == blockDim.x - 64 && seen + 1 == (uint32_t)raise_arrivals(s, r.per_seq, batch)) {
+      clear(word(r, 1 + s));
+      if (add(word(r, 0)) + 1 == (uint32_t)shards) {
+        clear(word(r, 0));
         last = true;
       }
     }
@@ -333,11 +326,10 @@ struct LengthRaise {
   }
 };
 
-// For the attention launch of a call in one split: `per_seq` workgroups of a sequence; `workspace` is free but for the counters.
-static inline RaiseArgs raise_args(const bd_paged_cache* c, bool wanted, long per_seq, void* workspace) {
-  const long bytes = (long)c->batch * c->n_q_heads * (kD + 2) * (long)sizeof(float);   // (bd_workspace_bytes of one split)
-  if (!wanted || !raises_in_launch(per_seq, c->batch, bytes)) return {nullptr, 0};
-  return {reinterpret_cast<unsigned long long*>(workspace), (int)per_seq};
+// For the attention launch of a step in one split: `per_seq` workgroups of a sequence.
+static inline RaiseArgs raise_args(const bd_paged_cache* c, bool wanted, long per_seq, void* counters) {
+  if (!wanted || !counters || !raises_in_launch(per_seq, c->batch, BD_STEP_COUNTER_BYTES)) return {nullptr, 0};
+  return {reinterpret_cast<uint32_t*>(counters), (int)per_seq};
 }
 
 // Of an integer format's workgroup: its sequence, the sequence's length, and whether it only packs (split -1).  False: it has

@@ -95,19 +95,19 @@ inline PagedGrid paged_grid(int splits, int groups, int batch, bool lazy, int ma
   }
   return g;
 }
-// One split and no merge behind it: the attention launch of a step raises the lengths itself (LengthRaise, bd_device.h), with
-// the workgroups counted in the workspace that the split's partials leave unused.
+// One split and no merge behind it: the attention launch of a step raises the lengths itself (LengthRaise, bd_device.h) if the
+// cache has counters for its workgroups.
 constexpr int kRaiseShards = 16;        // counters that share out the workgroups, by sequence: at most (a counter takes some 10 ns a workgroup)
-constexpr int kRaiseStride = 8;         // words of 8 bytes from one to the next: a cache line each
+constexpr int kRaiseStride = 16;        // words from one to the next: a line of 64 bytes each
 constexpr int kRaiseCountBits = 20;
 constexpr int raise_shards(int batch) { return batch < kRaiseShards ? batch : kRaiseShards; }
-constexpr long raise_bytes(int batch) { return 8L * kRaiseStride * (raise_shards(batch) + 1); }
+constexpr long raise_bytes(int batch) { return 4L * kRaiseStride * (raise_shards(batch) + 1); }
 // workgroups that count in at shard s, `per_seq` of every sequence
 constexpr long raise_arrivals(int s, long per_seq, int batch) { return per_seq * ((batch - s + raise_shards(batch) - 1) / raise_shards(batch)); }
 // Whether a launch can, or the lengths are left to a launch of their own.  (More workgroups of a sequence than a counter counts:
 // not in use.)
-constexpr bool raises_in_launch(long per_seq, int batch, long workspace_bytes) {
-  return raise_arrivals(0, per_seq, batch) < 1L << kRaiseCountBits && raise_bytes(batch) <= workspace_bytes;
+constexpr bool raises_in_launch(long per_seq, int batch, long counter_bytes) {
+  return raise_arrivals(0, per_seq, batch) < 1L << kRaiseCountBits && raise_bytes(batch) <= counter_bytes;
 }
 
 // The sequence of the packing workgroup at (x, z) of such a grid; `batch` and more: none.

@@ -722,6 +722,41 @@ def test_a_step_in_one_split_raises_the_lengths_in_any_workspace(fmt, hq, batch,
         assert torch.equal(a.buffers[i], twin.buffers[i]), i
 
 
+@pytest.mark.parametrize("fmt,hq,batch", [("int4", 8, 3), ("int2_kt", 16, 40), ("int4", 34, 17), ("int4_g32", 8, 16), ("mxfp4", 8, 70), ("mxfp4", 40, 5)])
+@pytest.mark.parametrize("lazy", [False, True])
+def test_a_step_in_one_split_leaves_the_workspace_alone(fmt, hq, batch, lazy):
+    """The library's paged steps (the cache class counts in memory of its own): caches whose steps overlap may share a workspace
+    while they run one split.  Step by step the rows, the lengths and the cache of the class's steps, whose counters are zeros
+    after each."""
+    import torch
+    mx, H, P = fmt == "mxfp4", 2, 2
+    dt = torch.bfloat16 if mx else torch.float16
+    rng = np.random.default_rng(batch)
+    lens = rng.integers(1, 250, batch)
+    lens[-1] = 126
+    table = torch.as_tensor(rng.permutation(batch * P).reshape(batch, P).astype(np.int32))
+    gen = torch.Generator(device="cuda:0").manual_seed(batch)
+    rows = lambda *shape: torch.randn(shape, device="cuda:0", generator=gen).to(dt)
+    a, twin = (B.PagedKVCache(batch, hq, H, fmt, batch * P, table) for _ in range(2))
+    for s in range(batch):
+        k, v = rows(H, int(lens[s]), 128), rows(H, int(lens[s]), 128)
+        a.quant_pack_kv(s, k, v)
+        twin.quant_pack_kv(s, k, v)
+    out, ref = (torch.full((batch, hq, 128), x, dtype=dt, device="cuda:0") for x in (7.0, 9.0))
+    ws = torch.randint(0, 256, (B.bd_paged_workspace_bytes(a.desc, 1),), device="cuda:0", generator=gen, dtype=torch.uint8)
+    before = ws.clone()
+    for i in range(3):
+        kn, vn, q = rows(batch, H, 128), rows(batch, H, 128), rows(batch, hq, 128)
+        (B.bd_paged_decode_step_lazy if lazy else B.bd_paged_decode_step)(a.desc, kn, vn, q, 0.088, 1, ws, out)
+        twin.decode_step(kn, vn, q, 0.088, ref, 1, lazy=lazy)
+        torch.cuda.synchronize()
+        assert torch.equal(ws, before), i
+        assert a.seq_lens.tolist() == twin.seq_lens.tolist() == [int(n) + i + 1 for n in lens]
+        assert torch.equal(out, ref) and not twin.counters.any()
+    for i in range(4 if mx else 6):
+        assert torch.equal(a.buffers[i], twin.buffers[i]), i
+
+
 @pytest.mark.parametrize("fmt,gq", [("int4", 1), ("int4", 4), ("int2", 3), ("int4_kt", 4)])
 @pytest.mark.parametrize("nb,ns", [(4, 1), (5, 1), (8, 1), (9, 1), (9, 2), (16, 2), (33, 8), (64, 8)])
 def test_workgroups_of_eight_waves(fmt, gq, nb, ns):

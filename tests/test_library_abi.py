@@ -220,6 +220,27 @@ def test_the_count_of_a_step():
     assert B.bd_step_splits(_desc(), 0) == B.bd_step_splits(_desc(), -5) == B.bd_step_splits(_desc(head_dim=64), 999) == 1
 
 
+@needs_lib
+def test_counters_of_a_paged_step():
+    """Where the C structure has them (behind a bd_paged_cache that other calls take as it is), room for the counters of any
+    batch, and what a step without them says."""
+    assert B.bd_paged_counted.counters.offset == ctypes.sizeof(B.bd_paged_cache) == 14 * 8
+    assert B.BD_STEP_COUNTER_BYTES == 64 * 17
+    assert f"#define BD_STEP_COUNTER_BYTES {B.BD_STEP_COUNTER_BYTES}\n" in open(os.path.join(ROOT, "include", "bitdecode.h")).read()
+    dummy = 4096   # (never read: every call is refused before a launch)
+    c = B.bd_paged_counted(1, 8, 2, 128, B.BD_FMT_INT4, 4, 4, *[dummy] * 9)
+    L = B.lib()
+    for step in (L.bd_paged_counted_step, L.bd_paged_counted_step_lazy):
+        call = lambda: step(ctypes.byref(c), dummy, dummy, dummy, 0.1, 0, dummy, dummy, None)   # 0 splits
+        c.counters = None
+        assert call() == -1
+        c.counters = dummy + 8
+        assert call() == -3
+        c.counters = dummy
+        assert call() == -1
+        assert step(None, dummy, dummy, dummy, 0.1, 1, dummy, dummy, None) == -1
+
+
 ECHO = """
 #include <stdint.h>
 #include <string.h>
