@@ -350,8 +350,7 @@ hipError_t launch_decode_int(const bd_cache* c, const void* q, int packed_len, i
   a.max_pages = a.num_pages = 0;
   a.step = 0;
   dim3 grid(num_splits + (flush == 2 ? 1 : 0), c->n_kv_heads * ((a.gq + 15) / 16), c->batch), block(256);
-  const long wgs = (long)num_splits * grid.y * grid.z;
-  const int blocks = wide_instance(a.nb, num_splits, fmt_bits(c->format), a.gq, fmt_kt(c->format), wgs) ? kOneBlockWide : one_block_instance(a.nb, num_splits, res_len, wgs);
+  const int blocks = contiguous_form(a.nb, num_splits, res_len, fmt_bits(c->format), a.gq, fmt_kt(c->format), (long)grid.y * grid.z, flush == 2);
   launch_instance(c->format, a.gq, blocks, false, a, grid, block, st);
   return hipGetLastError();
 }

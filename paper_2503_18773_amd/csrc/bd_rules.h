@@ -43,6 +43,14 @@ inline bool wide_instance(int nb, int splits, int bits, int gq, bool kt, long wg
   return gq <= 4 && !kt && nb > 4 * splits && nb <= (bits == 4 && splits > 1 ? 6 : 8) * splits && wgs <= 256;
 }
 
+// The form of a contiguous call: `splits` workgroups for each of `units`, and one more where the call packs a block behind its
+// attention (of which those of eight waves fill a compute unit each, too: 256 attending and 256 packing ones of them are two
+// rounds, a step of 32 sequences of 767 tokens, 8 KV heads, 4 bits 19.9 us, in four waves 16.4; 2 bits, 895 tokens 19.4 / 15.3).
+inline int contiguous_form(int nb, int splits, int res_len, int bits, int gq, bool kt, long units, bool packs) {
+  const long wgs = splits * units;
+  return wide_instance(nb, splits, bits, gq, kt, wgs + (packs ? units : 0)) ? kOneBlockWide : one_block_instance(nb, splits, res_len, wgs);
+}
+
 // Paged cache: how many sequences of a batch are to be sorted by length (0: left as they are), and how many of them are in
 // the second layer, from bit 10 (paged_sequence has the rule and its reasons).  per_seq: workgroups of a sequence; waves: per
 // SIMD, of the instance that the launch takes.

@@ -1,6 +1,7 @@
 // Answers questions about the launch rules (bd_rules.h), one per argument group, one line each:
 //   grp BITS GROUP GQP KT | mx GQP PAGED | int GQP BLOCKS   waves per SIMD that the launch counts on
-//   blocks NB SPLITS RES_LEN WGS             the form of the integer kernel that a contiguous call takes
+//   blocks NB SPLITS RES_LEN WGS             the form of the integer kernel that a contiguous call takes in workgroups of four waves
+//   form NB SPLITS RES_LEN BITS GQ KT UNITS PACKS   the form that it takes
 //   lazy SPLITS GROUPS BATCH MAX_PAGES        grid x, y, z of a lazy step, its order and flush mode; then the sequence of every
 //                                            (x, z) whose workgroups pack
 //   raise PER_SEQ BATCH WORKSPACE             the count that each shard of a step in one split reaches, or "no"
@@ -26,6 +27,9 @@ int main(int argc, char** argv) {
     } else if (!strcmp(argv[i], "blocks")) {
       printf("%d\n", bd::one_block_instance(arg(i + 1), arg(i + 2), arg(i + 3), arg(i + 4)));
       i += 5;
+    } else if (!strcmp(argv[i], "form")) {
+      printf("%d\n", bd::contiguous_form(arg(i + 1), arg(i + 2), arg(i + 3), arg(i + 4), arg(i + 5), arg(i + 6) != 0, arg(i + 7), arg(i + 8) != 0));
+      i += 9;
     } else if (!strcmp(argv[i], "raise")) {
       const int batch = arg(i + 2);
       if (!bd::raises_in_launch(arg(i + 1), batch, arg(i + 3))) printf("no");

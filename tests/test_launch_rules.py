@@ -121,6 +121,26 @@ def test_forms_of_the_integer_kernel(rules, splits):
         assert ask(4 * splits, 30 * splits + 1, 256) == MANY_BLOCKS and ask(4 * splits, 30 * splits + 1, 257) == ONE_BLOCK_SLICE
 
 
+ONE_BLOCK_WIDE = 3
+
+
+@needs_gxx
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("gq", [1, 4, 5])
+@pytest.mark.parametrize("kt", [0, 1])
+def test_workgroups_of_eight_waves_are_one_round(rules, bits, gq, kt):
+    """A call takes them where four waves would have two blocks each, none more than one with eight, and all of them, the
+    packing ones included, have a compute unit of their own; else the form that it takes in four waves."""
+    asked = [(nb, splits, res, bits, gq, kt, units, packs) for splits in (1, 2, 5) for nb in (4 * splits, 4 * splits + 1, 6 * splits, 6 * splits + 1, 8 * splits, 8 * splits + 1)
+             for res in (0, 128) for units in (1, 128 // splits, 128 // splits + 1, 256 // splits, 256 // splits + 1) for packs in (0, 1)]
+    forms = [int(x) for x in rules(*(y for a in asked for y in ("form", *a)))]
+    four = [int(x) for x in rules(*(y for a in asked for y in ("blocks", *a[:3], a[1] * a[6])))]
+    for a, form, other in zip(asked, forms, four):
+        nb, splits, _, _, _, _, units, packs = a
+        wide = gq <= 4 and not kt and 4 * splits < nb <= (6 if bits == 4 and splits > 1 else 8) * splits and units * (splits + packs) <= 256
+        assert form == (ONE_BLOCK_WIDE if wide else other), a
+
+
 FLUSH_AFTER, FLUSH_LAST = 2, 3
 
 
