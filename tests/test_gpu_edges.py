@@ -781,3 +781,33 @@ def test_workgroups_of_eight_waves(fmt, gq, nb, ns):
         torch.cuda.synchronize()
         _, rl = attn_errors(out_to_f64(out), ref)
         assert rl <= 1e-5, f"{fmt} {nb} blocks and {r} tokens, {ns} splits: rel-L2 {rl:.2e}"
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int2"])
+@pytest.mark.parametrize("gq,nb,ns", [(1, 5, 1), (4, 8, 1), (3, 11, 2), (4, 12, 2)])
+def test_lazy_steps_in_workgroups_of_eight_waves(fmt, gq, nb, ns):
+    """The lazy step that fills the residual, its packing workgroup of eight waves too: the oracle's lazy mode, and the cache
+    that the eager step leaves, whose attending workgroup packs."""
+    import torch
+    from tests.test_gpu_parity import _assert_int_cache_equal
+    w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=2 * gq, n_kv_heads=2, context=128 * nb + 126, fmt=fmt, seed=nb)
+    K, V, oc, lazy = _int_cache_pair(w, 128 * (nb + 2))
+    eager = B.KVCache(1, 2 * gq, 2, fmt, 128 * (nb + 2))
+    eager.quant_pack_kv(to_dev(K, "fp16"), to_dev(V, "fp16"))
+    for c in (lazy, eager):
+        c.desc.out_type = B.BD_OUT_F32
+    for step in range(3):
+        kn, vn, q = *W.make_new_kv(w, step), W.make_q(w, step)
+        outs = [torch.full((1, 2 * gq, 128), x, dtype=torch.float32, device="cuda:0") for x in (7.0, 5.0)]
+        for c, out in zip((lazy, eager), outs):
+            c.decode_step(*(to_dev(x, "fp16") for x in (kn, vn, q)), W.softmax_scale(w), out, ns, lazy=c is lazy)
+        torch.cuda.synchronize()
+        oc.append_kv(kn, vn, flush=False)
+        ref = O.decode_attn(oc, q, W.softmax_scale(w))
+        fills = oc.res_len == 128
+        oc.flush_if_full()
+        assert attn_errors(out_to_f64(outs[0]), ref)[1] <= 1e-5
+        assert fills or torch.equal(*outs)
+        assert lazy.packed_len == eager.packed_len == oc.packed_len
+        assert all(np.array_equal(lazy.host_buffer(i), eager.host_buffer(i)) for i in range(6))
+        _assert_int_cache_equal(oc, lazy)

@@ -54,9 +54,9 @@ def test_kernels_are_as_many_on_a_unit_as_their_launch_counts_on(rules, resident
     """Where two of an instance's workgroups share a compute unit, the order of a ragged batch puts them in layers."""
     seen = 0
     for name, held in resident.items():
-        mx = re.search(r"decode_mxg?_kernelI(?:Li(\d+)E)?Lb([01])E", name)
-        grp = re.search(r"decode_grp_kernelILi(\d)ELi(\d+)ELi(\d+)ELb[01]ELb([01])E", name)
-        integer = re.search(r"decode_int_kernelILi\d+ELi(\d+)ELi(\d)E", name)
+        mx = re.search(r"(?:decode|step)_mxg?_kernelI(?:Li(\d+)E)?Lb([01])E", name)
+        grp = re.search(r"(?:decode|step)_grp_kernelILi(\d)ELi(\d+)ELi(\d+)ELb[01]ELb([01])E", name)
+        integer = re.search(r"(?:decode|step)_int_kernelILi\d+ELi(\d+)ELi(\d)E", name)
         most = 2
         if mx:
             said, = rules("mx", mx.group(1) or 4, mx.group(2))
@@ -70,8 +70,11 @@ def test_kernels_are_as_many_on_a_unit_as_their_launch_counts_on(rules, resident
         seen += 1
         assert int(said) == min(held, most), f"{name}: {held} on a compute unit, launched as {said}"
     # 6 of MXFP4; 2 bits x 2 groups x 2 head counts x 2 K modes x paged or not of the groups; 2 bits x 3 head counts x 2 K
-    # modes x paged and the three forms
-    assert seen == 6 + 32 + 48
+    # modes x paged and the three forms; and the paged ones once more that raise the lengths
+    assert seen == 6 + 32 + 48 + 3 + 16 + 12
+    # workgroups of 512 threads: one, which is what their rule counts on
+    wide = [held for name, held in resident.items() if "wide_int_kernel" in name]
+    assert [held // 2 for held in wide] == [1, 1]
 
 
 @needs_gxx
@@ -139,6 +142,18 @@ def test_workgroups_of_eight_waves_are_one_round(rules, bits, gq, kt):
         nb, splits, _, _, _, _, units, packs = a
         wide = gq <= 4 and not kt and 4 * splits < nb <= (6 if bits == 4 and splits > 1 else 8) * splits and units * (splits + packs) <= 256
         assert form == (ONE_BLOCK_WIDE if wide else other), a
+
+
+def test_waves_that_do_not_quantize_wait_at_every_barrier_of_those_that_do():
+    """quant_block_barriers is what a workgroup of eight waves counts on: one barrier too few or too many never ends."""
+    text = open(os.path.join(CSRC, "bd_quant_block.h")).read()
+    text = re.sub(r"//.*", "", text)
+    body = text[text.index("void quant_block_at("):text.index("void quant_block(")]
+    k, v = body[:body.index("if constexpr ((PART & kPartV) != 0) {")], body[body.index("if constexpr ((PART & kPartV) != 0) {"):]
+    by_channel = k[k.index("uint32_t mn["):]
+    barrier = re.compile(r"__syncthreads|barrier|workgroup_global_sync")
+    assert len(barrier.findall(by_channel)) == len(barrier.findall(k)) == len(barrier.findall(v)) == 1
+    assert re.search(r"quant_block_barriers\(bool kt\) \{ return kt \? 1 : 2; \}", text)
 
 
 FLUSH_AFTER, FLUSH_LAST = 2, 3
