@@ -47,8 +47,11 @@ def build(verbose: bool = False, jobs: int = 6) -> str:
 
 
 def _build_call() -> None:
-    """The Python side's calling module (csrc/bd_call.c).  Without a C compiler or Python's headers binding.py does its work."""
+    """The Python side's calling module (csrc/bd_call.c).  Without a C compiler or Python's headers binding.py does its work; a
+    module of an earlier build, whose calls may be other ones, does not stay behind."""
     out = os.path.join(HERE, "_bdcall" + sysconfig.get_config_var("EXT_SUFFIX"))
+    if os.path.exists(out):
+        os.remove(out)
     cmd = [os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
            os.path.join(HERE, "csrc", "bd_call.c"), "-o", out]
     try:

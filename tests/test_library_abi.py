@@ -5,6 +5,7 @@ import os
 import re
 import shutil
 import subprocess
+import sysconfig
 
 import pytest
 
@@ -260,10 +261,16 @@ int quant(const int32_t* c, void* k, void* v, int32_t n, int32_t* p, int32_t* r,
 
 
 @pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
-@pytest.mark.parametrize("call", [B._CtypesCall, B._call])
+@pytest.mark.parametrize("call", ["ctypes", "module"])
 def test_calls_pass_every_argument_and_give_back_what_comes(call, tmp_path):
     """Both ways that the cache classes call the library, against functions that record what they are given: tensors, None,
     addresses beyond 32 bits, negative integers."""
+    if call == "module":
+        if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+            pytest.skip("the calling module needs Python's headers")
+        from paper_2503_18773_amd import _bdcall
+        assert B._call is _bdcall
+    call = B._call if call == "module" else B._CtypesCall
     (tmp_path / "echo.c").write_text(ECHO)
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", str(tmp_path / "echo.c"), "-o", str(tmp_path / "echo.so")], check=True)
     L = ctypes.CDLL(str(tmp_path / "echo.so"))
@@ -286,3 +293,14 @@ def test_calls_pass_every_argument_and_give_back_what_comes(call, tmp_path):
     assert seen(9) == [12, 0x7F0012345670, 0, 2 ** 40, half, 9, 48, 64, 0]
     assert call.paged_quant(at("paged_quant"), p, 6, k, v, 1333, 80) == 0 and seen(6) == [12, 6, 0x7F0012345670, 16, 1333, 80]
     assert call.quant(at("quant"), c, k, v, 133, 0) == (2, 128, 5) and seen(5) == [11, 0x7F0012345670, 16, 133, 0]
+
+
+@pytest.mark.parametrize("compiler", ["/bin/false", "/no/such/compiler", "cp"])
+def test_a_calling_module_that_does_not_build_is_gone(compiler, tmp_path, monkeypatch, capsys):
+    """One of an earlier build would be imported, with the library's calls of then."""
+    from paper_2503_18773_amd import build
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setenv("CC", compiler)
+    (tmp_path / ("_bdcall" + sysconfig.get_config_var("EXT_SUFFIX"))).write_bytes(b"old")
+    build._build_call()
+    assert list(tmp_path.iterdir()) == [] and "not built" in capsys.readouterr().err
