@@ -34,12 +34,13 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
   constexpr int COPIES = 16 / GQP;           // column groups
   constexpr int OWN = 4 / COPIES;            // k-steps owned by a column group
   constexpr int HP = GQP / 4;                // passes over the heads where 16 lanes work on one head
-  constexpr bool kF8 = GQP == 4;             // both products on f8f6f4 instructions (see the top of the file)
+  constexpr bool kF8 = GQP == 4;             // QK on i8 instructions, PV on f8f6f4 (see the top of bd_decode.hip)
   using E = FmtF8<BITS>;
   using I = FmtI8<BITS>;
   // The next block's keys are requested as soon as this block's are consumed, not at the block's end, where the
   // arithmetic is short or the blocks are (8 x 32K tokens, 2 bits: 32.5 -> 29.3 us, with 8 heads 39.0 -> 37.7; 128K
-  // tokens, 4 bits: 26.3 -> 25.8, but with 8 heads 26.8 -> 28.2; up to 4 heads measured with Q' in four pieces).
+  // tokens, 4 bits: 26.3 -> 25.8, but with 8 heads 26.8 -> 28.2; up to 4 heads measured with QK on f8f6f4 instructions, Q' in four e4m3
+  // pieces).
   constexpr bool kEarly = kF8 || (BITS == 2 && GQP == 8);
 
   __shared__ __attribute__((aligned(16))) unsigned char smem_raw[cmax(sizeof(ML), kWaves * sizeof(WL))];
@@ -810,7 +811,7 @@ __global__ __launch_bounds__(64 * BD_WAVES, 2) void BD_KERNEL(int)(BD_HOT_PARAMS
             sc[jj][0][r] = (half == 0 || cg == 1) ? lo : sc[jj][0][r];
             sc[jj][1][r] = (half == 0 || cg == 1) ? hi : sc[jj][1][r];
           }
-      } else {                              // column group cg keeps tile cg of each half: the sum of the four pieces' products
+      } else {                              // column group cg keeps tile cg of each half: the sum of the four bytes' products
         reduce_scatter(s, sc[0][half]);
       }
     }

@@ -106,11 +106,12 @@ def test_prompt_tails_go_to_the_residual(fmt, L):
 @pytest.mark.parametrize("fmt", ["int4", "int2", "int4_kt", "int2_kt"])
 @pytest.mark.parametrize("gq", [1, 2, 3, 4])
 def test_small_query_groups_hold_the_precision_of_their_pieces(fmt, gq):
-    """Query groups of up to 4 heads run both products on 8-bit matrix operands, queries and weights as sums of
-    e4m3 pieces whose products add up exactly: one block, fewer blocks than waves, several rounds of blocks, and
-    enough rounds (17 a wave) to fold the centre sum.  Weights hold 19 bits, a relative error of 2^-20 each, and
-    queries all of theirs; the scores' fp32 roundings (about eight of 2^-23) are of a sum of magnitudes of at most some
-    tens in log2 units, up to 1e-5 in the exponent."""
+    """Query groups of up to 4 heads run both products on 8-bit matrix operands, queries as integers in four bytes and
+    weights as sums of e4m3 pieces, whose products add up exactly: one block, fewer blocks than waves, several rounds of
+    blocks, and enough rounds (17 a wave) to fold the centre sum.  Weights hold 19 bits, a relative error of 2^-20 each, and
+    queries all that shows here (2^-30 of a block's largest product, which is of the scores' size); the scores' fp32
+    roundings (about eight of 2^-23) are of a sum of magnitudes of at most some tens in log2 units, up to 1e-5 in the
+    exponent."""
     bar = 2.0 ** -20 + 1e-5
     for L, ns in [(128, 1), (128 * 3 + 1, 1), (128 * 5, 2), (128 * 4 * 17 + 130, 1)]:
         w = W.scaled(W.CONFIGS["cfg1"], batch=1, n_q_heads=2 * gq, n_kv_heads=2, context=L, fmt=fmt, seed=700 + L + gq)
