@@ -123,9 +123,9 @@ def compute_dtype(w):
     codes = "u4" if w.fmt.startswith("int4") else "u2"
     if w.n_q_heads // w.n_kv_heads > 4 or "_g" in w.fmt:
         return codes + "->f16 mfma, f32 accumulate"
-    # queries are fixed-point numbers of 30 bits from a head's largest down (the codes bytes), weights sums of e4m3 numbers that
-    # hold 19 bits: both more than fp16
-    return (codes + "->i8 x (q * scale, 30-bit fixed point in bytes) mfma, exact; " + codes + "->" + ("e4m3" if codes == "u4" else "e2m1") +
+    # queries are fixed-point numbers of 30 bits, 60 where those would show, from a head's largest of a block down (the codes
+    # bytes), weights sums of e4m3 numbers that hold 19 bits
+    return (codes + "->i8 x (q * scale, 30- or 60-bit fixed point in bytes) mfma, exact; " + codes + "->" + ("e4m3" if codes == "u4" else "e2m1") +
             " x (weights 19 bits, in e4m3 pieces) mfma, f32 accumulate")
 
 

@@ -37,8 +37,8 @@
 // f8f6f4 instructions of 32 cycles a tile; the pieces' conversions take 8 cycles each, 52 a block) / bytes: 2048 tokens of
 // normal keys 8.7e-7 / 8.6e-7, 2 bits 7.9e-7 / 4.4e-7; one key a block of 10^3 .. 6 * 10^4 with a query of -30 there 8.2e-7 /
 // 7.7e-7, 2 bits 7.5e-7 / 6.0e-7 (without the second four 3e-6 .. 2e-4, 2 bits 2e-5 .. 1e-3); an outlier channel in q that is
-// not K's, x 30 .. x 1000, 9e-7 .. 2e-6 either way.  A step, seven pieces / bytes: 4
-// bits, 1K tokens 7.9 / 7.2 us, 32K 11.6 / 11.2, 128K 28.0 / 27.2; 2 bits, 8 x 32K 31.4 / 29.8.
+// not K's, x 30 .. x 1000, 9e-7 .. 2e-6 either way.  A step, seven pieces / bytes (the eight waves of wide_int_kernel and the
+// present merge included): 4 bits, 1K tokens 7.9 / 7.2 us, 32K 11.65 / 11.3, 128K 27.8 / 27.0; 2 bits, 8 x 32K 31.1 / 29.2.
 // fp32 outputs are 4e-7 .. 5e-7 off at 4096 tokens, with fp16 weights 1.8e-4 .. 2.2e-4.
 // Groups of 5 .. 16 heads have no columns to spare for the pieces and stay on fp16.
 //
