@@ -450,7 +450,9 @@ class PagedKVCache:
 
     def decode_step(self, k_new, v_new, q, softmax_scale: float, out, num_splits: int, stream=None, lazy: bool = False):
         name = "bd_paged_decode_step_lazy" if lazy else "bd_paged_decode_step"
-        entry = "bd_paged_counted_step_lazy" if lazy else "bd_paged_counted_step"   # the same in a launch less, with num_splits 1
+        entry = name
+        if isinstance(self.desc, bd_paged_counted):   # (not one of the caller's own) the same in a launch less, with num_splits 1
+            entry = "bd_paged_counted_step_lazy" if lazy else "bd_paged_counted_step"
         _check(_call.paged_step(_address(entry), self.desc, k_new, v_new, q, softmax_scale, num_splits, self.workspace(num_splits), out,
                                 _stream(stream)), name)
         return out

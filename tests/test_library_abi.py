@@ -242,6 +242,19 @@ def test_counters_of_a_paged_step():
         assert step(None, dummy, dummy, dummy, 0.1, 1, dummy, dummy, None) == -1
 
 
+@pytest.mark.parametrize("lazy", [False, True])
+def test_a_description_without_counters_takes_the_step_without_them(lazy, monkeypatch):
+    """One that a caller has put in the place of the cache class's own ends where the counters would be."""
+    cache, taken = object.__new__(B.PagedKVCache), []
+    monkeypatch.setattr(B, "_address", lambda name: name)
+    monkeypatch.setattr(B, "_stream", lambda stream: 0)
+    monkeypatch.setattr(B, "_call", type("", (), {"paged_step": staticmethod(lambda entry, desc, *rest: taken.append(entry) or 0)}))
+    monkeypatch.setattr(cache, "workspace", lambda num_splits: None, raising=False)
+    for cache.desc in (B.bd_paged_counted(), B.bd_paged_cache()):
+        cache.decode_step(None, None, None, 0.1, None, 1, lazy=lazy)
+    assert taken == ["bd_paged_counted_step" + "_lazy" * lazy, "bd_paged_decode_step" + "_lazy" * lazy]
+
+
 ECHO = """
 #include <stdint.h>
 #include <string.h>
